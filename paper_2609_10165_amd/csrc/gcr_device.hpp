@@ -60,7 +60,8 @@ struct Inst {
   int scheme;          // kCGC, kCGC_ES, kHGC
   int layer2;          // 1: a second ghost layer (Sec. 7.1)
   int l2r[3];          // its candidate box half-widths in cells per axis
-  int pad_;
+  int l2tight;         // 1: candidates lie within the walk below of their foot points
+  double l2walk;       // (1.5 + sqrt(d) / 2) w_max
   int64_t cell_off;    // offset of this instance in the concatenated tag array
   int64_t chunk_off;   // first classification chunk of this instance
   int64_t nchunk;

@@ -506,11 +506,84 @@ extern "C" gcr_status gcr_plan_fresh_cells(const gcr_plan* a, const gcr_plan* b,
 // candidate mark 0x20.  Every cell with psi <= 1.5 delta n is among them: a
 // walk from it through its foot point reaches a fluid centre within that
 // box (delta n <= w_max, psi 1-Lipschitz), and the last solid cell before it
-// is a solid interface cell.  One workgroup per chunk
-// of the interface chunk list (the grid covers every chunk; the rest exit):
-// the chunk's solid interface cells go to an LDS list, then the workgroup
-// walks the (cell, box offset) pairs, eight loads in flight per thread
-// before any mark is set.
+// is a solid interface cell.
+//
+// Around a sphere that lies inside the grid with that walk's room to spare
+// (l2tight, set on the host) the walk needs less than the box: beyond the
+// foot point it stays outside the ball, so its end, D = (1.5 + sqrt(d)/2) w
+// from the candidate's centre, is fluid, w the largest width of the cells
+// it can meet.  Those lie within R of the interface cell x it crosses, so w
+// is taken over that range instead of the grid, and along each axis the
+// candidate's centre is within D of x's own interval.  l2_reach finds that
+// interval of indices (a few face reads); with R = 7 (widths 2.6 : 1) it is
+// 5 cells an axis at the body instead of 15, with R = 3 it is 5 instead of
+// 7.  Bodies of other kinds, and spheres the grid cuts, keep the box.
+//
+// kL2Split workgroups per chunk of the interface chunk list (striding over it):
+// each lists the chunk's solid interface cells in LDS, in index order, and
+// takes every kL2Split-th batch of kL2Batch of them (at a sphere's poles a
+// chunk holds over a thousand, a dozen times the mean, and one workgroup took
+// them in 114 us).  A thread finds one cell's reach, then the workgroup walks
+// the (cell, row of its box) items, a row's tags read eight at a time (any
+// alignment) and kFly rows in flight per thread before any mark is set.
+// Bound by the rows' loads: they overlap heavily and hit in cache.  190^3
+// stretched by 1.01 a cell: 1459 -> 49 us; 256^3: 89 -> 21 us (one load per
+// box cell before, the box for every body, one workgroup a chunk).
+constexpr double kL2Slack = 1.0 + 1e-9;   // dwarfs the rounding of the reach
+constexpr int kL2Batch = 64, kL2Split = 8, kL2Grid = 2048;
+
+// faces i - kL2Win .. i + 1 + kL2Win of a stretched axis, read together (a
+// loop that stops at a face would pay a round trip a step)
+constexpr int kL2Win = 8;
+__device__ __forceinline__ void l2_faces(const double* f, int n, int i,
+                                         double w[2 * kL2Win + 2]) {
+#pragma unroll
+  for (int q = 0; q < 2 * kL2Win + 2; ++q) w[q] = f[min(max(i - kL2Win + q, 0), n)];
+}
+
+// largest width along axis a of the cells at most R from cell i
+__device__ __forceinline__ double l2_width(const GridD& g, int a, int i, int R) {
+  if (!g.face[a]) return g.h[a];
+  double f[2 * kL2Win + 2], w = 0.0;
+  l2_faces(g.face[a], g.n[a], i, f);
+#pragma unroll
+  for (int q = 0; q <= 2 * kL2Win; ++q)   // (cells off the grid: zero width)
+    if (abs(q - kL2Win) <= R) w = fmax(w, f[q + 1] - f[q]);
+  for (int q = kL2Win + 1; q <= R; ++q) {
+    if (i - q >= 0) w = fmax(w, width(g, a, i - q));
+    if (i + q < g.n[a]) w = fmax(w, width(g, a, i + q));
+  }
+  return w;
+}
+
+// [lo, hi]: indices along axis a whose cell centres lie within D of cell
+// i's own interval, at most R cells away and inside the grid
+__device__ __forceinline__ void l2_reach(const GridD& g, int a, int i, int R, double D, int& lo,
+                                         int& hi) {
+  const int n = g.n[a];
+  if (!g.face[a]) {
+    const int r = min(R, (int)floor(D / g.h[a] + 0.5));
+    lo = max(i - r, 0);
+    hi = min(i + r, n - 1);
+    return;
+  }
+  double f[2 * kL2Win + 2];
+  l2_faces(g.face[a], n, i, f);
+  const double f0 = f[kL2Win], f1 = f[kL2Win + 1];
+  int dn = 0, up = 0;   // centres move away monotonically: the reach is a run
+#pragma unroll
+  for (int q = 1; q <= kL2Win; ++q) {
+    if (q <= R && i - q >= 0 && f0 - 0.5 * (f[kL2Win - q] + f[kL2Win - q + 1]) <= D) dn = q;
+    if (q <= R && i + q < n && 0.5 * (f[kL2Win + q] + f[kL2Win + q + 1]) - f1 <= D) up = q;
+  }
+  if (dn == kL2Win)
+    while (dn < R && i - dn - 1 >= 0 && f0 - centre(g, a, i - dn - 1) <= D) ++dn;
+  if (up == kL2Win)
+    while (up < R && i + up + 1 < n && centre(g, a, i + up + 1) - f1 <= D) ++up;
+  lo = i - dn;
+  hi = i + up;
+}
+
 __global__ __launch_bounds__(256) void k_l2_mark(const Inst* __restrict__ insts, int ninst,
                                                  const int64_t* __restrict__ chunk_start,
                                                  const int32_t* __restrict__ chunk_list,
@@ -519,67 +592,123 @@ __global__ __launch_bounds__(256) void k_l2_mark(const Inst* __restrict__ insts,
                                                  int32_t* __restrict__ dirty,
                                                  int32_t* __restrict__ dlist,
                                                  int32_t* __restrict__ ndirty) {
-  __shared__ int s_cell[kChunk];
-  __shared__ int s_n;
-  if ((int)blockIdx.x >= nlist[0]) return;
-  const int64_t chunk = chunk_list[blockIdx.x];
-  const int ii = find_inst(chunk_start, ninst, chunk);
-  const Inst& I = insts[ii];
-  if (!I.layer2) return;
-  const GridD g = I.g;
-  const int8_t* T = tags + I.cell_off;
-  if (threadIdx.x == 0) s_n = 0;
-  __syncthreads();
-  const int64_t base = (chunk - I.chunk_off) * kChunk;
-  for (int t = threadIdx.x; t < kChunk; t += 256) {
-    const int64_t c = base + t;
-    if (c < g.ncell && (T[c] & 0x41) == 0x41) s_cell[atomicAdd(&s_n, 1)] = (int)c;
-  }
-  __syncthreads();
-  const int R[3] = {I.l2r[0], I.l2r[1], I.l2r[2]};   // 0 beyond the grid's dimension
-  const int W[3] = {2 * R[0] + 1, 2 * R[1] + 1, 2 * R[2] + 1};
-  const int box = W[0] * W[1] * W[2];
-  const int64_t items = (int64_t)s_n * box;
-  constexpr int kFly = 8;
-  for (int64_t i0 = threadIdx.x; i0 < items; i0 += 256 * kFly) {
-    int64_t at[kFly];
-    int8_t v[kFly];
+  __shared__ uint16_t s_cell[kChunk];       // cells within the chunk
+  __shared__ int s_at[kL2Batch];            // first cell of the box of each cell of the batch
+  __shared__ uint8_t s_len[3][kL2Batch];    // its size along each axis
+  __shared__ int s_w[3];
+  __shared__ int64_t sh[5];
+  for (int it = blockIdx.x; it < nlist[0]; it += gridDim.x) {
+    const int64_t chunk = chunk_list[it];
+    const int ii = find_inst(chunk_start, ninst, chunk);
+    const Inst& I = insts[ii];
+    if (!I.layer2) continue;
+    const GridD g = I.g;
+    const int8_t* T = tags + I.cell_off;
+    const int64_t base = (chunk - I.chunk_off) * kChunk;
+    int n;
+    {
+      // 16 cells a thread, one 16-byte load
+      const int t0 = (int)threadIdx.x * kSeg;
+      uint32_t mask = 0;
+      if (base + t0 + kSeg <= g.ncell) {
+        const uint4 w = *reinterpret_cast<const uint4*>(T + base + t0);
+        const uint32_t q[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-    for (int u = 0; u < kFly; ++u) {
-      const int64_t it = i0 + (int64_t)u * 256;
-      at[u] = -1;
-      v[u] = 0;
-      if (it < items) {
-        const int c = s_cell[it / box];
-        int o = (int)(it % box);
-        const int di = o % W[0] - R[0];
-        o /= W[0];
-        const int dj = o % W[1] - R[1];
-        const int dk = o / W[1] - R[2];
-        int i, j, k;
-        unlinear(g, c, i, j, k);
-        i += di;
-        j += dj;
-        k += dk;
-        if (i >= 0 && i < g.n[0] && j >= 0 && j < g.n[1] && k >= 0 && k < g.n[2]) {
-          at[u] = I.cell_off + linear(g, i, j, k);
-          v[u] = tags[at[u]];
+        for (int b = 0; b < kSeg; ++b)
+          if (((q[b >> 2] >> (8 * (b & 3))) & 0x41u) == 0x41u) mask |= 1u << b;
+      } else {
+        for (int b = 0; b < kSeg; ++b)
+          if (base + t0 + b < g.ncell && (T[base + t0 + b] & 0x41) == 0x41) mask |= 1u << b;
+      }
+      // in index order, the same list in every workgroup of the chunk (a mark
+      // of another one leaves these two bits as they are)
+      int64_t tot;
+      int at = (int)block_excl_scan<256>(__popc(mask), &tot, sh);
+      n = (int)tot;
+      for (; mask; mask &= mask - 1) s_cell[at++] = (uint16_t)(t0 + __ffs(mask) - 1);
+    }
+    const int R[3] = {I.l2r[0], I.l2r[1], I.l2r[2]};   // 0 beyond the grid's dimension
+    const bool tight = I.l2tight != 0;
+    const double len = 1.5 + 0.5 * sqrt((double)g.dim);
+    for (int b0 = (int)blockIdx.y * kL2Batch; b0 < n; b0 += (int)gridDim.y * kL2Batch) {
+      __syncthreads();   // the list is whole; the previous batch's boxes are done
+      const int nb = min(kL2Batch, n - b0);
+      if (threadIdx.x < 3) s_w[threadIdx.x] = 1;
+      __syncthreads();
+      if ((int)threadIdx.x < nb) {
+        int ijk[3], lo[3], hi[3];
+        unlinear(g, (int)(base + s_cell[b0 + threadIdx.x]), ijk[0], ijk[1], ijk[2]);
+        double D = 0.0;
+        if (tight) {
+          double w = 0.0;
+#pragma unroll
+          for (int a = 0; a < 3; ++a)
+            if (a < g.dim) w = fmax(w, l2_width(g, a, ijk[a], R[a]));
+          D = len * w * kL2Slack;
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          lo[a] = max(ijk[a] - R[a], 0);
+          hi[a] = min(ijk[a] + R[a], g.n[a] - 1);
+          if (tight && a < g.dim) l2_reach(g, a, ijk[a], R[a], D, lo[a], hi[a]);
+          s_len[a][threadIdx.x] = (uint8_t)(hi[a] - lo[a] + 1);   // <= 2 * 64 + 1
+          atomicMax(&s_w[a], hi[a] - lo[a] + 1);
+        }
+        s_at[threadIdx.x] = linear(g, lo[0], lo[1], lo[2]);
+      }
+      __syncthreads();
+      const int P = (s_w[0] + 7) / 8, rows = s_w[1] * s_w[2];   // pieces of a row, rows of a box
+      const int per = P * rows, items = nb * per;
+      constexpr int kFly = 4;
+      for (int i0 = threadIdx.x; i0 < items; i0 += 256 * kFly) {
+        int at[kFly];
+        unsigned long long m[kFly];
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+          const int it = i0 + u * 256;
+          at[u] = 0;
+          m[u] = 0ull;
+          if (it >= items) continue;
+          const int c = it / per;
+          int o = it - c * per;
+          const int p = o % P;
+          o /= P;
+          const int dj = o % s_w[1], dk = o / s_w[1];
+          const int nx = (int)s_len[0][c] - 8 * p;
+          if (nx <= 0 || dj >= s_len[1][c] || dk >= s_len[2][c]) continue;
+          at[u] = s_at[c] + 8 * p + g.n[0] * (dj + g.n[1] * dk);
+          unsigned long long v = 0ull;
+          if ((int64_t)at[u] + 8 <= g.ncell) {
+            __builtin_memcpy(&v, T + at[u], 8);
+          } else {   // the grid's last cells
+            for (int q = 0; q < min(nx, 8); ++q)
+              v |= (unsigned long long)(uint8_t)T[at[u] + q] << (8 * q);
+          }
+          // bytes equal to 1 (plain solid, not yet marked) among the row's
+          const unsigned long long x = v ^ 0x0101010101010101ull, l7 = 0x7f7f7f7f7f7f7f7full;
+          m[u] = ~(((x & l7) + l7) | x | l7);
+          if (nx < 8) m[u] &= (1ull << (8 * nx)) - 1ull;
+        }
+        // a byte store, as every writer of a cell here stores the same value
+        // (1 -> 0x21) and no other kernel runs
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+          if (!m[u]) continue;
+          if (dirty) {
+            // a re-plan counts marks in the listed chunks only: list those of
+            // the first and last cell marked (this workgroup's own is listed)
+            const int c0 = at[u] + (__ffsll((long long)m[u]) - 1) / 8;
+            const int c1 = at[u] + (63 - __clzll((long long)m[u])) / 8;
+            for (int64_t ch = I.chunk_off + c0 / kChunk; ch <= I.chunk_off + c1 / kChunk; ++ch)
+              if (ch != chunk && dirty[ch] == 0 && atomicExch(&dirty[ch], 1) == 0)
+                dlist[atomicAdd(ndirty, 1)] = (int32_t)ch;
+          }
+          for (; m[u]; m[u] &= m[u] - 1ull)
+            tags[I.cell_off + at[u] + (__ffsll((long long)m[u]) - 1) / 8] = 0x21;
         }
       }
     }
-    // plain solid, not yet marked: a byte store, as every writer of a cell
-    // here stores the same value (1 -> 0x21) and no other kernel runs
-#pragma unroll
-    for (int u = 0; u < kFly; ++u)
-      if (at[u] >= 0 && v[u] == 1) {
-        tags[at[u]] = 0x21;
-        if (dirty) {
-          // a re-plan counts marks in the listed chunks only: list this one
-          const int64_t ch = I.chunk_off + (at[u] - I.cell_off) / kChunk;
-          if (dirty[ch] == 0 && atomicExch(&dirty[ch], 1) == 0)
-            dlist[atomicAdd(ndirty, 1)] = (int32_t)ch;
-        }
-      }
+    __syncthreads();   // the list is reused by the next chunk
   }
 }
 
@@ -1171,6 +1300,7 @@ static double factorial(int n) {
 constexpr int kMaxL2Radius = 64;   // second-layer candidate box half-width, cells
 
 static gcr_status make_shape(const gcr_shape& gs, int dim, ShapeD* out);
+static void set_l2tight(Inst* I);
 
 static gcr_status make_inst(const gcr_grid& gg, const gcr_shape& gs, int scheme, Inst* I) {
   std::memset(I, 0, sizeof(Inst));
@@ -1233,8 +1363,25 @@ static gcr_status make_inst(const gcr_grid& gg, const gcr_shape& gs, int scheme,
       if (!(r <= (double)kMaxL2Radius)) return GCR_E_UNSUPPORTED;
       I->l2r[a] = (int)r;
     }
+    I->l2walk = (1.5 + 0.5 * std::sqrt((double)gg.dim)) * wmax;
   }
-  return make_shape(gs, gg.dim, &I->s);
+  const gcr_status st = make_shape(gs, gg.dim, &I->s);
+  set_l2tight(I);
+  return st;
+}
+
+// Whether the second layer's candidates lie within the walk of their foot
+// points (k_l2_mark): a sphere inside the grid with the walk's length to
+// spare on every side, so that no walk meets the grid's edge.
+static void set_l2tight(Inst* I) {
+  I->l2tight = 0;
+  if (!I->layer2 || I->s.kind != kSphere) return;
+  for (int a = 0; a < I->g.dim; ++a) {
+    const double need = I->s.r0 + 2.0 * I->l2walk;
+    const double lo = I->g.lo[a], hi = lo + I->g.h[a] * (double)I->g.n[a];
+    if (!(I->s.c[a] - need > lo) || !(I->s.c[a] + need < hi)) return;
+  }
+  I->l2tight = 1;
 }
 
 // The device description of body gs in dim dimensions (Sec. 7: the bodies
@@ -1453,6 +1600,7 @@ gcr_status build_update(BatchData& prev, const ShapeD& shape, bool incremental, 
   B->inst.resize(1);
   Inst I = prev.inst[0];
   I.s = shape;
+  set_l2tight(&I);
   // the stretched faces: device copies of the previous plan's
   for (int a = 0; a < 3; ++a) {
     if (!I.g.face[a]) continue;
@@ -1592,7 +1740,7 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
     // with a chunk list, marks outside it extend it, and the count covers
     // the list; else every chunk is counted
     const bool listed = prev || !W.every_chunk;
-    k_l2_mark<<<(unsigned)chunks, 256, 0, st>>>(
+    k_l2_mark<<<dim3((unsigned)std::min<int64_t>(chunks, kL2Grid), kL2Split), 256, 0, st>>>(
         D.d_inst, ninst, D.d_chunk_start, D.d_chunk_list, D.d_nchunk_list, D.d_tags,
         listed ? D.d_dirty : nullptr, D.d_dirty_list, D.d_ndirty);
     k_count_marks<<<(unsigned)(listed ? std::min<int64_t>(chunks, kListGrid) : chunks), 256, 0,
