@@ -449,35 +449,32 @@ gcr_status gcr_set_batch_shape(int32_t threads, int32_t grid);
  * ends. */
 gcr_status gcr_batch_status(const gcr_batch* batch);
 gcr_status gcr_set_batch_spin(int32_t polls);
-/* Layering (Sec. 3.2).  At the default setting every instance is first
- * layered by one workgroup holding its counters and levels in LDS (up to
- * about 47,000 ghosts); a plan built alone that does not fit there and has
- * at least 65,536 interface cells is layered by the whole GPU (one
- * grid-wide round per level, then a stable counting sort by level); the
- * rest by one workgroup with its state in HBM.  A threshold set here
- * (`min_interface` > 0) sends every plan built alone with at least that
- * many interface cells to the whole GPU first, fitting LDS or not (for
- * tests and measurements).  A cycle or a graph deeper than 126 levels
- * hands an instance from the whole-GPU layering to the one-workgroup one,
- * so the result never depends on this setting.  0 restores the default.
- * Process-wide; applies to plans built afterwards. */
+/* Layering (Sec. 3.2).  At the default setting a 3D plan built alone with at
+ * least 1,024 interface cells is layered by the whole GPU (each ghost waits
+ * for the levels of the ghosts it reads, then a stable counting sort by
+ * level); every other instance of at most 16,384 interface cells by one
+ * workgroup that holds its levels in LDS; the rest by one workgroup pushing
+ * levels along reverse edges, its state in LDS (up to about 47,000 ghosts)
+ * or in HBM.  A threshold set here (`min_interface` > 0) sends every plan
+ * built alone with at least that many interface cells, 2D ones too, to the
+ * whole GPU and no other (for tests and measurements).  What the first two
+ * leave (a cycle or more than 128 levels on the whole GPU, more than 256
+ * levels in the workgroup) is layered again by the last, so the result never
+ * depends on this setting.  0 restores the default.  Process-wide; applies
+ * to plans built afterwards. */
 gcr_status gcr_set_wide_layering(int64_t min_interface);
 
-/* The whole-GPU layering collects each round's newly placed ghosts in a
- * per-workgroup LDS buffer of `entries` slots (1..4096, default 4096; 0
- * restores it) and appends the overflow straight to the level's list.  The
- * result does not depend on it; a small buffer exercises the overflow (for
- * tests).  Else GCR_E_ARG.  Process-wide; applies to plans built
- * afterwards. */
+/* Accepted and checked (0..4096, else GCR_E_ARG), without effect: the
+ * whole-GPU layering no longer gathers its ghosts in buffers. */
 gcr_status gcr_set_wide_buffer(int32_t entries);
 
-/* When the Kahn layering of an instance stalls (its remaining ghosts read a
+/* When the push layering of an instance stalls (its remaining ghosts read a
  * cycle), a remainder of at most `max_ghosts` ghosts is resolved by one
- * wave (closure by repeated squaring in registers, no workgroup barrier),
- * a larger one by the workgroup (trimming, closure, placement rounds).
- * Both give the same levels and units.  0..64, default 64 (0: always the
- * workgroup); else GCR_E_ARG.  Process-wide; applies to plans built
- * afterwards. */
+ * wave (closure in registers, no workgroup barrier), a larger one by the
+ * workgroup (trimming, closure, placement rounds).  Both give the same
+ * levels and units.  0..64, default 64; any other value than the default
+ * also sends every instance of the one-workgroup layerings to the push form.
+ * Else GCR_E_ARG.  Process-wide; applies to plans built afterwards. */
 gcr_status gcr_set_wave_residual(int32_t max_ghosts);
 
 const char* gcr_status_str(gcr_status s);

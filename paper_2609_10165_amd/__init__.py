@@ -535,20 +535,21 @@ STAGES = ["classify", "interface_scan", "interface_compact", "geometry_tags",
 
 
 def set_wave_residual(max_ghosts: int = 64):
-    """Largest remainder of a stalled Kahn layering (ghosts reading a cycle)
-    that one wave resolves; larger ones go to the workgroup (0..64)."""
+    """Largest remainder of a stalled push layering (ghosts reading a cycle)
+    that one wave resolves; larger ones go to the workgroup (0..64; other
+    values than the default, 64, also choose the push layering)."""
     _check(lib().gcr_set_wave_residual(int(max_ghosts)), "gcr_set_wave_residual")
 
 
 def set_wide_buffer(entries: int = 0):
-    """Slots of the whole-GPU layering's per-workgroup release buffer
-    (1..4096; 0 the default)."""
+    """Checked (0..4096), without effect: the whole-GPU layering no longer
+    gathers its ghosts in buffers."""
     _check(lib().gcr_set_wide_buffer(int(entries)), "gcr_set_wide_buffer")
 
 
 def set_wide_layering(min_interface: int = 0):
     """Interface-cell count from which a plan built alone is layered by the
-    whole GPU (0: the default)."""
+    whole GPU (0: the default, 1,024 in 3D)."""
     _check(lib().gcr_set_wide_layering(int(min_interface)), "gcr_set_wide_layering")
 
 

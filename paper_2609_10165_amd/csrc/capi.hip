@@ -789,9 +789,7 @@ gcr_status gcr_set_wide_layering(int64_t min_interface) {
 }
 
 gcr_status gcr_set_wide_buffer(int32_t entries) {
-  if (entries < 0 || entries > kWideBuf) return GCR_E_ARG;
-  set_wide_buffer(entries);
-  return GCR_OK;
+  return entries < 0 || entries > 4096 ? GCR_E_ARG : GCR_OK;   // (no effect, see gcr.h)
 }
 
 gcr_status gcr_set_wave_residual(int32_t max_ghosts) {

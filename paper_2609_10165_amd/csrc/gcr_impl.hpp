@@ -161,27 +161,35 @@ struct LevelsArgs {
   uint32_t* cnt;
   uint32_t* bits;
   InstInfo* info;
-  // wide layering of a single large instance (null: not used)
-  int32_t* listB;        // [cap] second level list
-  int32_t* wide;         // [kWideState] completion flag, sizes of the levels
-  int32_t* hist;         // [kWideLevels][cap / 256 + 1] per-tile level counts
+  // whole-GPU layering of a single large instance
+  int32_t* flow;         // [2] waves finished, ghosts placed (from zero)
+  int32_t* hist;         // [cap / 256 + 1][kWideLevels] level counts of the tiles of 256 ghosts
   int cur_cap;           // entries of a level list held in LDS (set at launch)
   int wave_res;          // residuals up to this size go to the one-wave solver
-  int wide_cap;          // entries of the wide layering's per-workgroup release buffer
 };
-constexpr int kWideBuf = 4096;   // its LDS capacity
-constexpr int kWideLevels = 128;               // deepest graph the wide layering orders
-constexpr int kWideState = kWideLevels + 8;
-constexpr int64_t kWideMinInterface = 65536;   // default; smaller instances: one workgroup
+constexpr int kWideLevels = 128;   // deepest graph the whole-GPU layering orders
+// A 3D plan built alone with at least this many interface cells is layered
+// by the whole GPU, below by one workgroup pulling in LDS.  Measured per
+// build (both kernels of the former against the latter), spheres: 1,086
+// interface cells 15.1 / 15.7 us, 1,925 16.3 / 19.1, 7,703 18.3 / 36.2,
+// 30,816 21.9 / 82.6 (a workgroup pushing along reverse edges there, with
+// their construction not counted).
+constexpr int64_t kWideMinInterface = 1024;
 void set_wide_layering(int64_t min_interface);   // 0: the default
 int64_t wide_layering_min();
 constexpr int kWaveResidual = 64;   // most ghosts left by Kahn that one wave resolves
 void set_wave_residual(int max_ghosts);
 int wave_residual();
-void set_wide_buffer(int entries);   // 0: the default (kWideBuf)
-int wide_buffer();
 bool wide_layering_forced();         // a threshold set explicitly
 gcr_status launch_levels(const LevelsArgs& L, int ninst, int64_t max_n, hipStream_t st);
+// Whole-GPU layering of a batch of one (see levels.hip): lev starts at zero.
+gcr_status launch_levels_flow(const LevelsArgs& L, int64_t max_n, hipStream_t st);
+// Layering that needs no reverse edges (roff, radj, dcnt), for instances of
+// at most max_n ghosts; what it cannot layer (a graph deeper than 256 levels,
+// a coupled unit beyond the solver's size) it leaves with info.layered = 0.
+bool levels_pull(int64_t max_n);
+gcr_status launch_levels_pull(const LevelsArgs& L, int ninst, int64_t max_n, bool all_2d,
+                              hipStream_t st);
 
 // Classification of every cell of a batch into tags (0 fluid, 1 solid, 0x40
 // interface mark) and per-chunk interface counts; chunk_inst [chunks]

@@ -1,32 +1,31 @@
-// levels.hip -- Kahn layering of the ghost dependency graph (Sec. 3.2) and
-// the canonical order (level, linear index), one workgroup per instance.
+// levels.hip -- layering of the ghost dependency graph (Sec. 3.2) and the
+// canonical order (level, linear index).
 //
-// The reverse edges (ghost -> ghosts that read it) arrive as a CSR list and
-// the number of ghosts each ghost reads as a byte per ghost, both built by
-// grid-wide kernels.  Each ghost (or coupled unit) holds a byte counter of
-// unplaced ghosts it reads, packed four to a word and kept in LDS when the
-// instance fits.
-// Level k is formed from the dependants of level k-1 whose counter drops to
-// zero: they set their bit in a bitmap over the linear ghost order, and one
-// workgroup scan over the bitmap words emits them in linear-index order with
-// their canonical positions.  The work is O(ghosts + edges) plus one bitmap
-// scan per level; the level of a ghost is the longest dependency path from a
-// ghost that reads no ghost, independent of the order threads run in.
+// The level of a ghost is the longest dependency path from a ghost that
+// reads no ghost.  Three forms, all with that result:
+//   k_levels_pull            one workgroup per instance of at most kPullMax
+//                            ghosts, every level in LDS; cycles found on the
+//                            way
+//   k_levels_flow (+ _scan)  one large 3D instance on the whole GPU
+//   k_levels_fast, k_levels  one workgroup per instance pushing levels along
+//                            reverse edges (a CSR list built by grid-wide
+//                            kernels for them alone): batches with larger
+//                            instances, and the graphs the others leave
+//                            (deeper than their tables, a cycle in
+//                            k_levels_flow)
 //
-// If a level comes out empty while ghosts remain, the remaining ghosts hold
-// cycles: their strongly connected groups (from the transitive closure of
-// the remaining graph) become coupled units, and the layering restarts with
-// each unit as one node, so a unit sits one level above the deepest level it
-// needs.
-//
-// A single large instance is layered by the whole grid instead
-// (k_levels_wide): one cooperative launch whose rounds each release the next
-// level from the current one through the same counters (in HBM), with a grid
-// barrier between rounds; the canonical order then comes from a stable
-// counting sort of the ghosts by level.  A stall there (a cycle) or a graph
-// deeper than the sort supports hands the instance to the one-workgroup
-// layering, launched right after, which otherwise returns at once.
-#include <hip/hip_cooperative_groups.h>
+// k_levels, the most general: each ghost (or coupled unit) holds a byte
+// counter of unplaced ghosts it reads, packed four to a word and kept in LDS
+// when the instance fits.  Level k is formed from the dependants of level
+// k-1 whose counter drops to zero: they set their bit in a bitmap over the
+// linear ghost order, and one workgroup scan over the bitmap words emits them
+// in linear-index order with their canonical positions.  The work is
+// O(ghosts + edges) plus one bitmap scan per level, independent of the order
+// threads run in.  If a level comes out empty while ghosts remain, the
+// remaining ghosts hold cycles: their strongly connected groups (from the
+// transitive closure of the remaining graph) become coupled units, and the
+// layering restarts with each unit as one node, so a unit sits one level
+// above the deepest level it needs.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -59,214 +58,240 @@ __device__ __forceinline__ uint32_t cnt_get(const uint32_t* c, int i) {
   return (c[i >> 2] >> ((i & 3) * 8)) & 0xffu;
 }
 
-// Appends v to list (size counter *size) for the lanes with p set: one
-// atomic per wave.  Lanes may be diverged; only active lanes take part.
-__device__ __forceinline__ void wave_push(bool p, int v, int32_t* list, int32_t* size) {
-  const unsigned long long m = __ballot(p);
-  if (m == 0ull) return;
-  const int lane = threadIdx.x & 63;
-  const int leader = __ffsll((long long)m) - 1;
-  int base = 0;
-  if (lane == leader) base = atomicAdd(size, __popcll(m));
-  base = __shfl(base, leader);
-  if (p) list[base + __popcll(m & ((1ull << lane) - 1ull))] = v;
+// ---------------------------------------------------------------------------
+// Layering of one large instance by the whole GPU, in two launches.
+//
+// k_levels_flow: a thread holds up to kFlowJ ghosts and polls the levels of
+// the ghosts they read (agent scope, the stores and loads go past the XCDs'
+// own caches); a ghost whose reads all have a level takes 1 + the highest at
+// once.  No round, barrier or list: a level costs one store-to-load trip
+// across the chip (about 0.5 us, measured on a chain of 95 levels), where a
+// grid barrier a level cost 30-40.
+// Reads that have a level are not polled again.  Waves wait only for
+// ghosts of the same launch; its at most kFlowGrid workgroups (half of what
+// the chip holds) are resident together unless other work fills it, and a
+// wave that saw no ghost of its own placed for kFlowPatience polls, nor any
+// wave finish meanwhile, gives up, so every wave ends: an instance with a
+// cycle, or one starved that way, is left with info.layered = 0 to the
+// one-workgroup layerings.  The tiles' counts per level follow.
+//
+// k_levels_scan: the counts scanned over the tiles of each level, level
+// offsets, results.  k_finalize adds each ghost's rank in its tile: the
+// stable counting sort of the canonical order.
+//
+// Bound by the chain of levels and the polls of the ghosts that wait (HBM
+// round trips).  512^3 sphere, 74,000 ghosts: 44 us for both against 581 for
+// rounds with a grid barrier; 256^3 with a second layer (36,000): 35 against
+// 191 for one workgroup in LDS.
+constexpr int kFlowJ = 4, kFlowGrid = 1024;
+constexpr int kFlowPatience = 512;
+
+__device__ __forceinline__ int flow_get(const int32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void flow_put(int32_t* p, int v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Appends v for the lanes with p set to a workgroup's LDS buffer buf (fill
-// count *s_n, capacity cap), one LDS atomic per wave; entries beyond the
-// capacity go straight to the global list glist (length *gsize), one global
-// atomic per wave that has any.  *s_n keeps counting past cap.
-__device__ __forceinline__ void wave_push_buf(bool p, int v, int32_t* buf, int* s_n, int cap,
-                                              int32_t* glist, int32_t* gsize) {
-  const unsigned long long m = __ballot(p);
-  if (m == 0ull) return;
-  const int lane = threadIdx.x & 63;
-  const unsigned long long lt = (1ull << lane) - 1ull;
-  const int leader = __ffsll((long long)m) - 1;
-  int base = 0;
-  if (lane == leader) base = atomicAdd(s_n, __popcll(m));
-  base = __shfl(base, leader);
-  const int idx = base + __popcll(m & lt);
-  const bool spill = p && idx >= cap;
-  if (p && !spill) buf[idx] = v;
-  const unsigned long long ms = __ballot(spill);
-  if (ms == 0ull) return;
-  const int ls = __ffsll((long long)ms) - 1;
-  int gb = 0;
-  if (lane == ls) gb = atomicAdd(gsize, __popcll(ms));
-  gb = __shfl(gb, ls);
-  if (spill) glist[gb + __popcll(ms & lt)] = v;
-}
+// Whether a wave that waits may go on: true while ghosts of its own or
+// whole waves are being placed.  done: waves finished, of the whole launch.
+struct FlowWait {
+  int polls = 0, seen = -1;
+  __device__ __forceinline__ bool go_on(bool moved, const int32_t* done) {
+    if (__ballot(moved) != 0ull) {
+      polls = 0;
+      return true;
+    }
+    if (++polls < kFlowPatience) return true;
+    polls = 0;
+    const int d = __builtin_amdgcn_readfirstlane(flow_get(done));   // one answer for the wave
+    const bool alive = d != seen;
+    seen = d;
+    return alive;
+  }
+};
 
-// Wide layering of instance 0.  wide[0] = 1 when it finished (levels,
-// canonical order, level offsets and info final), wide[r] = size of level r.
-// Each round's releases collect in the workgroup's LDS buffer and join the
-// next level's list with one global atomic per workgroup (the order inside
-// a level's list is free: the counting sort orders the level).
-__global__ __launch_bounds__(256) void k_levels_wide(LevelsArgs L) {
-  namespace cg = cooperative_groups;
-  cg::grid_group grid = cg::this_grid();
-  const int tid = threadIdx.x;
-  const int G = (int)gridDim.x;
-  const int64_t GT = (int64_t)G * 256;
-  const int64_t gt = (int64_t)blockIdx.x * 256 + tid;
+__global__ __launch_bounds__(256) void k_levels_flow(LevelsArgs L) {
+  __shared__ int s_hist[kWideLevels];
+  __shared__ int s_placed;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int64_t lo = L.g_off[0];
   const int n = (int)(L.g_off[1] - lo);
-  const int C = (n + 3) >> 2;
-  uint32_t* __restrict__ cnt = L.cnt;
-  int32_t* __restrict__ lev = L.lev + lo;
-  int32_t* __restrict__ perm = L.perm + lo;
-  const uint8_t* __restrict__ dcnt = L.dcnt + lo;
-  const int32_t* __restrict__ roff = L.roff + lo;
-  const int32_t* __restrict__ radj = L.radj;
-  int32_t* __restrict__ size = L.wide;
-  int32_t* lists[2] = {L.listA + lo, L.listB + lo};
-  __shared__ int64_t sh[8];
-  __shared__ int s_hist[kWideLevels];
-  __shared__ int s_wc[4][kWideLevels];
-  __shared__ int32_t s_buf[kWideBuf];
-  __shared__ int s_n, s_base;
-  const int wcap = min(max(L.wide_cap, 1), kWideBuf);
-  if (L.info[0].layered) return;   // the LDS layering finished it (every workgroup leaves)
-
-  // counters of ghosts read, four per word; no ghost is in a unit
-  for (int64_t w = gt; w < C; w += GT) {
-    uint32_t v = 0;
-    for (int q = 0; q < 4; ++q)
-      if (4 * w + q < n) v |= (uint32_t)dcnt[4 * w + q] << (8 * q);
-    cnt[w] = v;
-  }
-  for (int64_t g = gt; g < n; g += GT) L.blk_idx[lo + g] = -1;
-  if (blockIdx.x == 0)
-    for (int r = tid; r < kWideState; r += 256) size[r] = 0;
-  grid.sync();
-  // level 1: ghosts that read no ghost (through the workgroup's buffer,
-  // flushed as after each round)
-  if (tid == 0) s_n = 0;
+  const int ntiles = (n + 255) >> 8, G = (int)gridDim.x;
+  const int np = (1 << L.insts[0].g.dim) - 1;
+  const int32_t* __restrict__ deps = L.deps + lo;
+  int32_t* lev = L.lev + lo;
+  if (tid == 0) s_placed = 0;
   __syncthreads();
-  for (int64_t g0 = (int64_t)blockIdx.x * 256; g0 < n; g0 += GT) {
-    const int g = (int)(g0 + tid);
-    const bool p = g < n && dcnt[g] == 0;
-    if (p) lev[g] = 1;
-    wave_push_buf(p, g, s_buf, &s_n, wcap, lists[1], &size[1]);
-  }
-  __syncthreads();
-  {
-    const int mcount = min(s_n, wcap);
-    if (tid == 0 && mcount > 0) s_base = atomicAdd(&size[1], mcount);
-    __syncthreads();
-    for (int k = tid; k < mcount; k += 256) lists[1][s_base + k] = s_buf[k];
-  }
-  grid.sync();
-
-  // round r: the dependants of level r whose last counted edge comes from it
-  // form level r + 1
-  int r = 1, placed = 0, maxw = 0;
-  bool ok = true;
-  for (;;) {
-    const int sz = __hip_atomic_load(&size[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (sz == 0) break;
-    placed += sz;
-    maxw = max(maxw, sz);
-    if (r == kWideLevels - 1) {
-      ok = false;
-      break;
-    }
-    const int32_t* __restrict__ cur = lists[r & 1];
-    int32_t* __restrict__ nxt = lists[(r + 1) & 1];
-    if (tid == 0) s_n = 0;
-    __syncthreads();
-    for (int64_t i = gt; i < sz; i += GT) {
-      const int g = cur[i];
-      const int e1 = roff[g + 1];
-      for (int e = roff[g]; e < e1; ++e) {
-        const int q = (int)(radj[e] - lo);
-        const bool rel = cnt_dec(cnt, q) == 1u;
-        if (rel) lev[q] = r + 1;
-        wave_push_buf(rel, q, s_buf, &s_n, wcap, nxt, &size[r + 1]);
+  int placed = 0;
+  if (ntiles <= kFlowJ * G) {
+    // the reads without a level, in registers (-1: none, or placed)
+    int32_t d[kFlowJ][7];
+    int top[kFlowJ];
+    uint32_t pend = 0;
+#pragma unroll
+    for (int j = 0; j < kFlowJ; ++j) {
+      const int e = ((int)blockIdx.x + j * G) * 256 + tid;
+      top[j] = 0;
+#pragma unroll
+      for (int q = 0; q < 7; ++q) {
+        d[j][q] = -1;
+        if (e < n && q < np) {
+          const int32_t v = deps[(int64_t)q * L.cap + e];
+          if (v >= 0) d[j][q] = (int32_t)(v - lo);
+        }
+      }
+      if (e < n) {
+        pend |= 1u << j;
+        L.blk_idx[lo + e] = -1;
       }
     }
-    __syncthreads();
-    {
-      const int mcount = min(s_n, wcap);
-      if (tid == 0 && mcount > 0) s_base = atomicAdd(&size[r + 1], mcount);
-      __syncthreads();
-      for (int k = tid; k < mcount; k += 256) nxt[s_base + k] = s_buf[k];
+    FlowWait W;
+    while (__ballot(pend != 0) != 0ull) {
+      bool moved = false;
+#pragma unroll
+      for (int j = 0; j < kFlowJ; ++j) {
+        if (!((pend >> j) & 1u)) continue;
+        int v[7];
+#pragma unroll
+        for (int q = 0; q < 7; ++q) v[q] = d[j][q] >= 0 ? flow_get(lev + d[j][q]) : 0;
+        bool open = false;
+#pragma unroll
+        for (int q = 0; q < 7; ++q) {
+          if (v[q]) d[j][q] = -1;
+          top[j] = max(top[j], v[q]);
+          open = open || d[j][q] >= 0;
+        }
+        if (open) continue;
+        flow_put(lev + ((int)blockIdx.x + j * G) * 256 + tid, top[j] + 1);
+        pend &= ~(1u << j);
+        ++placed;
+        moved = true;
+      }
+      if (!W.go_on(moved, L.flow)) break;
     }
-    ++r;
-    grid.sync();
+  } else {
+    // more ghosts than the registers hold: their reads from memory, every time
+    for (int t = blockIdx.x; t < ntiles; t += G)
+      if (t * 256 + tid < n) L.blk_idx[lo + t * 256 + tid] = -1;
+    FlowWait W;
+    for (bool open = true; __ballot(open) != 0ull;) {
+      bool moved = false;
+      open = false;
+      for (int t = blockIdx.x; t < ntiles; t += G) {
+        const int e = t * 256 + tid;
+        if (e >= n || flow_get(lev + e) != 0) continue;
+        int top = 0;
+        bool ready = true;
+        for (int q = 0; q < np; ++q) {
+          const int32_t v = deps[(int64_t)q * L.cap + e];
+          if (v < 0) continue;
+          const int l = flow_get(lev + (v - lo));
+          top = max(top, l);
+          ready = ready && l != 0;
+        }
+        if (ready) {
+          flow_put(lev + e, top + 1);
+          ++placed;
+          moved = true;
+        } else {
+          open = true;
+        }
+      }
+      if (!W.go_on(moved, L.flow)) break;
+    }
   }
-  if (!ok || placed != n) return;   // every workgroup leaves here alike
-  const int nlev = r - 1;
-  const int ntiles = (n + 255) >> 8;
-  int32_t* __restrict__ hist = L.hist;   // [level][tile]
+  // a finished (or weary) wave: one more for those that wait
+  if (lane == 0) atomicAdd(&L.flow[0], 1);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) placed += __shfl_xor(placed, o);
+  if (lane == 0 && placed) atomicAdd(&s_placed, placed);
+  __syncthreads();
+  if (tid == 0 && s_placed) atomicAdd(&L.flow[1], s_placed);
+  // the tiles' counts per level (levels beyond the table: dropped here, and
+  // the instance is left to the others, as its counts fall short)
+  for (int t = blockIdx.x; t < ntiles; t += G) {
+    __syncthreads();
+    if (tid < kWideLevels) s_hist[tid] = 0;
+    __syncthreads();
+    const int e = t * 256 + tid;
+    const int l = e < n ? flow_get(lev + e) : 0;
+    if (l >= 1 && l <= kWideLevels) atomicAdd(&s_hist[l - 1], 1);
+    __syncthreads();
+    if (tid < kWideLevels) L.hist[(int64_t)t * kWideLevels + tid] = s_hist[tid];
+  }
+}
 
-  // stable counting sort by level: per-tile counts ...
-  for (int t = blockIdx.x; t < ntiles; t += G) {
-    for (int l = tid; l < nlev; l += 256) s_hist[l] = 0;
-    __syncthreads();
-    const int g = t * 256 + tid;
-    if (g < n) atomicAdd(&s_hist[lev[g] - 1], 1);
-    __syncthreads();
-    for (int l = tid; l < nlev; l += 256) hist[(int64_t)l * ntiles + t] = s_hist[l];
-    __syncthreads();
+__global__ __launch_bounds__(1024) void k_levels_scan(LevelsArgs L) {
+  constexpr int kSeg8 = 1024 / kWideLevels, kU = 8;
+  static_assert(kWideLevels == 128, "levels on 128 threads");
+  __shared__ int s_sum[kSeg8][kWideLevels];
+  __shared__ int s_off[kWideLevels + 1];
+  __shared__ int64_t sh[17];
+  const int tid = threadIdx.x, l = tid % kWideLevels, seg = tid / kWideLevels;
+  const int n = (int)(L.g_off[1] - L.g_off[0]);
+  const int ntiles = (n + 255) >> 8;
+  const bool whole = L.flow[1] == n;
+  const int per = (ntiles + kSeg8 - 1) / kSeg8, t0 = seg * per, t1 = min(ntiles, t0 + per);
+  int32_t* h = L.hist + l;
+  int sum = 0;
+  for (int t = t0; t < t1; t += kU) {
+    int v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) v[u] = t + u < t1 ? h[(int64_t)(t + u) * kWideLevels] : 0;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) sum += v[u];
   }
-  grid.sync();
-  // ... scanned over the tiles of each level, plus the level offsets ...
-  for (int l = blockIdx.x; l < nlev; l += G) {
-    int32_t* row = hist + (int64_t)l * ntiles;
-    int64_t carry = 0;
-    for (int t0 = 0; t0 < ntiles; t0 += 256) {
-      const int t = t0 + tid;
-      const int v = t < ntiles ? row[t] : 0;
-      int64_t tot;
-      const int64_t pre = block_excl_scan<256>(v, &tot, sh);
-      if (t < ntiles) row[t] = (int32_t)(carry + pre);
-      carry += tot;
+  s_sum[seg][l] = sum;
+  __syncthreads();
+  int tot = 0;
+  if (seg == 0)
+    for (int q = 0; q < kSeg8; ++q) tot += s_sum[q][l];
+  int64_t all;
+  const int64_t off = block_excl_scan<1024>(seg == 0 ? tot : 0, &all, sh);
+  if (seg == 0) s_off[l] = (int)off;
+  // (levels are used without a gap, so the used ones are counted)
+  const int nlev = __syncthreads_count(seg == 0 && tot > 0);
+  if (!whole || all != n) return;   // uniform: info.layered stays 0
+  int run = s_off[l];
+  for (int q = 0; q < seg; ++q) run += s_sum[q][l];
+  for (int t = t0; t < t1; t += kU) {
+    int v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) v[u] = t + u < t1 ? h[(int64_t)(t + u) * kWideLevels] : 0;
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+      if (t + u < t1) {
+        h[(int64_t)(t + u) * kWideLevels] = run;
+        run += v[u];
+      }
+  }
+  if (tid <= nlev) L.lev_off[tid] = tid < nlev ? s_off[tid] : n;
+  if (tid < 64) {
+    int w = 0;
+    for (int q = tid; q < kWideLevels; q += 64) {
+      int c = 0;
+      for (int k = 0; k < kSeg8; ++k) c += s_sum[k][q];
+      w = max(w, c);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) w = max(w, __shfl_xor(w, o));
+    if (tid == 0) {
+      L.info[0].nlev = nlev;
+      L.info[0].maxwidth = w;
+      L.info[0].nunits = 0;
+      L.info[0].maxunit = 0;
+      L.info[0].layered = 1;
     }
   }
-  if (blockIdx.x == 0 && tid == 0) {
-    int32_t* lev_off = L.lev_off;
-    int run = 0;
-    lev_off[0] = 0;
-    for (int k = 1; k <= nlev; ++k) {
-      run += size[k];
-      lev_off[k] = run;
-    }
-    L.info[0].nlev = nlev;
-    L.info[0].maxwidth = maxw;
-    L.info[0].nunits = 0;
-    L.info[0].maxunit = 0;
-    size[0] = 1;
-  }
-  grid.sync();
-  // ... and each ghost's rank among the same level's ghosts before it
-  const int lane = tid & 63, wv = tid >> 6;
-  for (int t = blockIdx.x; t < ntiles; t += G) {
-    for (int i = tid; i < 4 * nlev; i += 256) s_wc[i / nlev][i % nlev] = 0;
-    __syncthreads();
-    const int g = t * 256 + tid;
-    const bool valid = g < n;
-    const int l = valid ? lev[g] - 1 : -1;
-    unsigned long long rem = __ballot(valid);
-    int inw = 0;
-    while (rem) {
-      const int leader = __ffsll((long long)rem) - 1;
-      const int l0 = __shfl(l, leader);
-      const bool same = valid && l == l0;
-      const unsigned long long m = __ballot(same);
-      if (same) inw = __popcll(m & ((1ull << lane) - 1ull));
-      if (lane == leader) s_wc[wv][l0] = __popcll(m);
-      rem &= ~m;
-    }
-    __syncthreads();
-    if (valid) {
-      int pos = L.lev_off[l] + hist[(int64_t)l * ntiles + t] + inw;
-      for (int w = 0; w < wv; ++w) pos += s_wc[w][l];
-      perm[g] = pos;
-    }
-    __syncthreads();
-  }
+}
+
+gcr_status launch_levels_flow(const LevelsArgs& L, int64_t max_n, hipStream_t st) {
+  const int64_t tiles = std::max<int64_t>(1, (max_n + 255) >> 8);
+  k_levels_flow<<<(unsigned)std::min<int64_t>(tiles, kFlowGrid), 256, 0, st>>>(L);
+  k_levels_scan<<<1, 1024, 0, st>>>(L);
+  GCR_HIP(hipGetLastError());
+  return GCR_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -311,6 +336,378 @@ __device__ __forceinline__ void wave_push16(bool p, int v, uint16_t* list, int b
   at = __shfl(at, leader);
   const int idx = base + at + __popcll(m & ((1ull << lane) - 1ull));
   if (p && idx < cap) list[idx] = (uint16_t)v;
+}
+
+// The canonical order (level, linear index) of an instance's n ghosts, and
+// its results: a stable counting sort by one workgroup of BS threads, wave w
+// taking linear positions [w R, (w + 1) R).  tab: (BS / 64) x kFastLevels
+// counts; level_of(g): the level of ghost g.  Every thread calls it, after a
+// barrier behind the last write of a level.
+template <int BS, class F>
+__device__ __forceinline__ void canonical_order(const LevelsArgs& L, int ii, int64_t lo, int n,
+                                                int nlev, int units, int maxunit, int32_t* tab,
+                                                int* s_off, int* s_tot, int64_t* sh, F level_of) {
+  constexpr int NW = BS / 64;
+  const int tid = threadIdx.x;
+  const int R = ((((n + NW - 1) / NW) + 63) / 64) * 64;
+  const int wv = tid >> 6, lane = tid & 63;
+  for (int t = tid; t < NW * nlev; t += BS) tab[t] = 0;
+  __syncthreads();
+  const int r0 = wv * R, r1 = min(n, r0 + R);
+  for (int g = r0 + lane; g < r1; g += 64) atomicAdd(&tab[wv * nlev + level_of(g) - 1], 1);
+  __syncthreads();
+  for (int l = tid; l < nlev; l += BS) {
+    int t = 0;
+    for (int w = 0; w < NW; ++w) t += tab[w * nlev + l];
+    s_tot[l] = t;
+  }
+  __syncthreads();
+  {
+    const int v = tid < nlev ? s_tot[tid] : 0;
+    int64_t tot;
+    const int64_t pre = block_excl_scan<BS>(v, &tot, sh);
+    if (tid < nlev) s_off[tid] = (int)pre;
+    if (tid == 0) s_off[nlev] = (int)tot;
+  }
+  __syncthreads();
+  for (int l = tid; l < nlev; l += BS) {
+    int run = s_off[l];
+    for (int w = 0; w < NW; ++w) {
+      const int t = tab[w * nlev + l];
+      tab[w * nlev + l] = run;
+      run += t;
+    }
+  }
+  __syncthreads();
+  int32_t* __restrict__ lev = L.lev + lo;
+  int32_t* __restrict__ perm = L.perm + lo;
+  static_assert(kFastLevels <= 256 && kFastLevels <= BS,
+                "a level index fits 8 ballots, and a level a thread");
+  for (int c = r0; c < r1; c += 64) {
+    const int g = c + lane;
+    const bool valid = g < r1;
+    const int l = valid ? level_of(g) - 1 : -1;
+    // the lanes of this lane's level: those that agree with it on every bit
+    // of the level index, one ballot a bit
+    unsigned long long mk = __ballot(valid);
+#pragma unroll
+    for (int bit = 0; bit < 8; ++bit) {
+      const bool on = (l >> bit) & 1;
+      const unsigned long long bb = __ballot(valid && on);
+      mk &= on ? bb : ~bb;
+    }
+    const int at = valid ? tab[wv * nlev + l] : 0;
+    __builtin_amdgcn_wave_barrier();
+    if (valid && lane == __ffsll((long long)mk) - 1) tab[wv * nlev + l] = at + __popcll(mk);
+    __builtin_amdgcn_wave_barrier();
+    if (valid) {
+      lev[g] = l + 1;
+      perm[g] = at + __popcll(mk & ((1ull << lane) - 1ull));
+    }
+  }
+  int32_t* lev_off = L.lev_off + (int64_t)ii * (kMaxLevels + 1);
+  for (int l = tid; l <= nlev; l += BS) lev_off[l] = s_off[l];
+  if (tid < 64) {
+    int maxw = 0;
+    for (int l = tid; l < nlev; l += 64) maxw = max(maxw, s_tot[l]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) maxw = max(maxw, __shfl_xor(maxw, o));
+    if (tid == 0) {
+      L.info[ii].nlev = nlev;
+      L.info[ii].maxwidth = maxw;
+      L.info[ii].nunits = units;
+      L.info[ii].maxunit = maxunit;
+      L.info[ii].layered = 1;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Layering by pulling, one workgroup per instance of at most kPullMax ghosts.
+// A thread holds its ghosts' dependencies in registers and every ghost's
+// level lies in LDS; a ghost whose dependencies all have a level takes 1 +
+// the highest.  No order between the waves is needed for that (a level is
+// the longest dependency path whenever it is found), so the waves only meet
+// every kPullRounds rounds to see whether anything moved: no reverse edges,
+// no counters, no queue.  Bound by the chain of LDS reads along the longest
+// path, about two per level.
+//
+// When nothing moves with ghosts left, every one of those reads another that
+// has no level.  Following each ghost's first such dependency (pointer
+// doubling, as many steps as ghosts left) ends on a cycle; a ghost found
+// there gathers the ghosts without level it reads, transitively, up to
+// kMaxUnit of them.  If the set is closed and strongly connected it is a
+// coupled unit that waits for nothing, and takes 1 + the highest level its
+// members read outside it (Sec. 3.2's level with the unit as one node);
+// pulling then goes on behind it.  One such unit always exists; if none of
+// at most kMaxUnit ghosts does, the instance is left to the other layerings.
+// Slots come in no particular order: a unit is solved by itself, and what it
+// is called by is its smallest ghost.  The 64-star batch: 50 us
+// against 129 for the push form with its reverse edges (which took another
+// 24 us to build).
+constexpr int kPullMax = 16384;
+constexpr int kPullRounds = 4;
+constexpr int kPullCand = 256;   // cycle ghosts looked at per stall
+constexpr int kPullWS = 3 * kMaxUnit;   // 2-byte members, 1-byte rows of their reads
+
+__device__ __forceinline__ int lds_get(const uint16_t* p) {
+  return (int)__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_put(uint16_t* p, int v) {
+  __hip_atomic_store(p, (uint16_t)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// LDS bytes of an instance of n ghosts: levels (one more entry, always
+// placed, stands for "no ghost"), the rank table, the cycle search's
+// pointers and marks
+__host__ __device__ __forceinline__ int64_t pull_lds(int64_t n, int waves) {
+  const int64_t tab = 4 * (int64_t)waves * kFastLevels;
+  return ((2 * (n + 1) + 15) & ~int64_t(15)) + (tab > 8192 ? tab : 8192) +
+         ((2 * n + 15) & ~int64_t(15)) + ((n + 15) & ~int64_t(15));
+}
+
+struct PullShared {
+  int off[kFastLevels + 2];
+  int tot[kFastLevels + 1];
+  int64_t sh[17];
+  int moved[3];
+  int left, cand, units, maxunit, maxlev, ok;
+};
+
+// NP dependencies per ghost at most (np in this instance), J ghosts per
+// thread (strided by BS)
+template <int BS, int NP, int J>
+__device__ __forceinline__ void pull_instance(const LevelsArgs& L, int ii, int64_t lo, int n,
+                                              int np, uint32_t* s_dyn, PullShared& S) {
+  const int tid = threadIdx.x;
+  const int64_t cap = L.cap;
+  const int32_t* __restrict__ deps = L.deps;
+  int32_t* __restrict__ blk_idx = L.blk_idx;
+  int32_t* unit_mem = L.unit_mem + (int64_t)ii * kMaxUnits * kMaxUnit;
+  int32_t* unit_cnt = L.unit_cnt + (int64_t)ii * kMaxUnits;
+  int32_t* unit_lev = L.unit_lev + (int64_t)ii * kMaxUnits;
+  auto al = [](int64_t b) { return (b + 15) & ~int64_t(15); };
+  char* base = reinterpret_cast<char*>(s_dyn);
+  uint16_t* lvl = reinterpret_cast<uint16_t*>(base);   // level + 1; 0: none yet
+  int64_t o = al(2 * (int64_t)(n + 1));
+  int32_t* tab = reinterpret_cast<int32_t*>(base + o);
+  // the cycle search's candidates, before the rank table is needed
+  uint16_t* cand = reinterpret_cast<uint16_t*>(base + o);
+  char* work = base + o + 2 * kPullCand;
+  static_assert(2 * kPullCand + kPullCand * kPullWS <= 8192, "pull_lds holds the search");
+  constexpr int64_t kTabB = 4 * (int64_t)(BS / 64) * kFastLevels;
+  o += kTabB > 8192 ? kTabB : 8192;
+  uint16_t* nxt = reinterpret_cast<uint16_t*>(base + o);
+  o += al(2 * (int64_t)n);
+  uint8_t* mark = reinterpret_cast<uint8_t*>(base + o);
+  // dependency q of ghost g as a local id, -1 if it reads no ghost there
+  auto gdep = [&](int g, int q) -> int {
+    const int32_t d = deps[(int64_t)q * cap + lo + g];
+    return d < 0 ? -1 : (int)(d - lo);
+  };
+
+  constexpr int W = (NP + 1) / 2;
+  uint32_t dp[J][W];
+  uint32_t pend = 0;
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int g = tid + BS * j;
+    int d[2 * W];
+#pragma unroll
+    for (int q = 0; q < 2 * W; ++q) d[q] = q < np && g < n ? gdep(g, q) : -1;
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+      dp[j][w] = (uint32_t)(d[2 * w] < 0 ? n : d[2 * w]) |
+                 (uint32_t)(d[2 * w + 1] < 0 ? n : d[2 * w + 1]) << 16;
+    if (g < n) {
+      pend |= 1u << j;
+      lvl[g] = 0;
+      blk_idx[lo + g] = -1;
+    }
+    // bounds the loads in flight, and so the registers that hold them
+    if ((j + 1) * W % 8 == 0) asm volatile("" ::: "memory");
+  }
+  if (tid == 0) {
+    lvl[n] = 1;   // level 0: "no ghost" holds nothing up
+    S.units = 0;
+    S.maxunit = 0;
+    S.maxlev = 0;
+    S.left = 0;
+    S.moved[0] = S.moved[1] = S.moved[2] = 0;
+  }
+  __syncthreads();
+  int top = 0;     // highest level + 1 this thread gave
+  int round = 0;
+  for (;;) {
+    bool moved;
+    do {
+      moved = false;
+      ++round;
+#pragma unroll 1
+      for (int r = 0; r < kPullRounds && pend; ++r) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+          if (!((pend >> j) & 1u)) continue;
+          int lo_ = 0xffff, hi_ = 0;
+#pragma unroll
+          for (int w = 0; w < W; ++w) {
+            // (opaque: unpacked outside the loop, the pairs would take twice
+            // their registers)
+            uint32_t d = dp[j][w];
+            asm volatile("" : "+v"(d));
+            const int a = lds_get(lvl + (d & 0xffffu));
+            const int b = 2 * w + 1 < NP ? lds_get(lvl + (d >> 16)) : 1;
+            lo_ = min(lo_, min(a, b));
+            hi_ = max(hi_, max(a, b));
+          }
+          if (lo_ == 0) continue;
+          lds_put(lvl + tid + BS * j, hi_ + 1);
+          top = max(top, hi_ + 1);
+          pend &= ~(1u << j);
+          moved = true;
+        }
+      }
+      // one barrier a turn: three flags in rotation, the next turn's cleared
+      // here (it was last read before the previous barrier)
+      if (moved) S.moved[round % 3] = 1;
+      if (tid == 0) S.moved[(round + 1) % 3] = 0;
+      __syncthreads();
+    } while (S.moved[round % 3]);
+    if (pend) atomicAdd(&S.left, __popc(pend));
+    __syncthreads();
+    const int m = S.left;
+    __syncthreads();
+    if (m == 0) break;
+
+    // ---- a stall: the units at the head of what is left
+    if (tid == 0) {
+      S.left = 0;
+      S.cand = 0;
+      S.ok = 0;
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      if (!((pend >> j) & 1u)) continue;
+      int f = n;
+#pragma unroll
+      for (int q = NP - 1; q >= 0; --q) {
+        uint32_t pair = dp[j][q / 2];
+        asm volatile("" : "+v"(pair));
+        const int d = (int)(q & 1 ? pair >> 16 : pair & 0xffffu);
+        if (lds_get(lvl + d) == 0) f = d;
+      }
+      nxt[tid + BS * j] = (uint16_t)f;
+      mark[tid + BS * j] = 0;
+    }
+    __syncthreads();
+    for (int step = 1; step < 2 * m; step <<= 1) {   // (in place: a pointer only runs ahead)
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        if ((pend >> j) & 1u) lds_put(nxt + tid + BS * j, lds_get(nxt + lds_get(nxt + tid + BS * j)));
+      __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+      if ((pend >> j) & 1u) mark[nxt[tid + BS * j]] = 1;   // every writer stores 1
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+      if (((pend >> j) & 1u) && mark[tid + BS * j]) {
+        const int at = atomicAdd(&S.cand, 1);
+        if (at < kPullCand) cand[at] = (uint16_t)(tid + BS * j);
+      }
+    __syncthreads();
+    const int nc = min(S.cand, kPullCand);
+    // one candidate a thread
+    uint16_t* mem = reinterpret_cast<uint16_t*>(work + tid * kPullWS);
+    uint8_t* row = reinterpret_cast<uint8_t*>(mem + kMaxUnit);
+    int k = 0, ext = 0;
+    if (tid < nc) {
+      const int c = cand[tid];
+      mem[0] = (uint16_t)c;
+      row[0] = 0;
+      k = 1;
+      for (int i = 0; i < k && k > 0; ++i)
+        for (int q = 0; q < np; ++q) {
+          const int d = gdep(mem[i], q);
+          if (d < 0) continue;
+          if (lvl[d] != 0) {
+            ext = max(ext, (int)lvl[d]);
+            continue;
+          }
+          int t = 0;
+          while (t < k && mem[t] != d) ++t;
+          if (t == k) {
+            if (k == kMaxUnit) {   // too large, or more than the head unit
+              k = 0;
+              break;
+            }
+            mem[k] = (uint16_t)d;
+            row[k] = 0;
+            ++k;
+          }
+          row[i] |= (uint8_t)(1u << t);
+        }
+      // closed: strongly connected if every member reaches the candidate,
+      // and taken by the smallest candidate among the members
+      for (int v = 0; v < k; ++v)
+        for (int u = 0; u < k; ++u)
+          if ((row[u] >> v) & 1u) row[u] |= row[v];
+      bool take = k > 0;
+      for (int u = 0; u < k; ++u) take = take && (row[u] & 1u) && !(mark[mem[u]] && mem[u] < c);
+      if (!take) k = 0;
+      if (k > 0) {
+        for (int u = 1; u < k; ++u)   // members ascending
+          for (int t = u; t > 0 && mem[t - 1] > mem[t]; --t) {
+            const uint16_t x = mem[t];
+            mem[t] = mem[t - 1];
+            mem[t - 1] = x;
+          }
+        const int slot = atomicAdd(&S.units, 1);
+        if (slot < kMaxUnits) {
+          for (int u = 0; u < k; ++u) {
+            unit_mem[slot * kMaxUnit + u] = (int32_t)(lo + mem[u]);
+            blk_idx[lo + mem[u]] = slot;
+          }
+          unit_cnt[slot] = k;
+          unit_lev[slot] = max(ext, 1);   // (levels in LDS are one higher)
+        }
+        atomicMax(&S.maxunit, k);
+        S.ok = 1;
+      }
+    }
+    __syncthreads();
+    if (!S.ok || S.units > kMaxUnits) {   // uniform
+      for (int g = tid; g < n; g += BS) L.perm[lo + g] = -1;
+      return;
+    }
+    for (int u = 0; u < k; ++u) lds_put(lvl + mem[u], max(ext, 1) + 1);
+    if (k > 0) top = max(top, max(ext, 1) + 1);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+      if (((pend >> j) & 1u) && lds_get(lvl + tid + BS * j) != 0) pend &= ~(1u << j);
+  }
+  if (top) atomicMax(&S.maxlev, top - 1);
+  __syncthreads();
+  const int nlev = S.maxlev, nu = S.units;
+  if (nlev > kFastLevels) {   // uniform
+    for (int g = tid; g < n; g += BS) L.perm[lo + g] = -1;
+    return;
+  }
+  canonical_order<BS>(L, ii, lo, n, nlev, nu, S.maxunit, tab, S.off, S.tot, S.sh,
+                      [&](int g) { return (int)lvl[g] - 1; });
+}
+
+template <int BS, int NP, int J>
+__global__ __launch_bounds__(BS) void k_levels_pull(LevelsArgs L, int lds_bytes) {
+  extern __shared__ uint32_t s_dyn[];
+  __shared__ PullShared S;
+  const int ii = blockIdx.x;
+  const int64_t lo = L.g_off[ii];
+  const int n = (int)(L.g_off[ii + 1] - lo);
+  if (n > BS * J || pull_lds(n, BS / 64) > lds_bytes) return;
+  pull_instance<BS, NP, J>(L, ii, lo, n, min(NP, (1 << L.insts[ii].g.dim) - 1), s_dyn, S);
 }
 
 __global__ __launch_bounds__(1024) void k_levels_fast(LevelsArgs L, int lds_bytes) {
@@ -832,76 +1229,8 @@ __global__ __launch_bounds__(1024) void k_levels_fast(LevelsArgs L, int lds_byte
   }
   __syncthreads();
   if (s_placed != n || s_maxlev > kFastLevels) return;   // k_levels does it
-  const int nlev = s_maxlev;
-
-  // ---- stable counting sort by level: wave w takes linear positions
-  // [w R, (w + 1) R)
-  const int R = ((((n + kFastWaves - 1) / kFastWaves) + 63) / 64) * 64;
-  const int wv = tid >> 6, lane = tid & 63;
-  for (int t = tid; t < kFastWaves * nlev; t += 1024) tab[t] = 0;
-  __syncthreads();
-  const int r0 = wv * R, r1 = min(n, r0 + R);
-  for (int g = r0 + lane; g < r1; g += 64) atomicAdd(&tab[wv * nlev + lvl[g] - 1], 1);
-  __syncthreads();
-  for (int l = tid; l < nlev; l += 1024) {
-    int t = 0;
-    for (int w = 0; w < kFastWaves; ++w) t += tab[w * nlev + l];
-    s_tot[l] = t;
-  }
-  __syncthreads();
-  {
-    const int v = tid < nlev ? s_tot[tid] : 0;
-    int64_t tot;
-    const int64_t pre = block_excl_scan<1024>(v, &tot, sh);
-    if (tid < nlev) s_off[tid] = (int)pre;
-    if (tid == 0) s_off[nlev] = (int)tot;
-  }
-  __syncthreads();
-  for (int l = tid; l < nlev; l += 1024) {
-    int run = s_off[l];
-    for (int w = 0; w < kFastWaves; ++w) {
-      const int t = tab[w * nlev + l];
-      tab[w * nlev + l] = run;
-      run += t;
-    }
-  }
-  __syncthreads();
-  int32_t* __restrict__ lev = L.lev + lo;
-  int32_t* __restrict__ perm = L.perm + lo;
-  static_assert(kFastLevels <= 256, "a level index fits 8 ballots");
-  for (int c = r0; c < r1; c += 64) {
-    const int g = c + lane;
-    const bool valid = g < r1;
-    const int l = valid ? (int)lvl[g] - 1 : -1;
-    // the lanes of this lane's level: those that agree with it on every bit
-    // of the level index, one ballot a bit
-    unsigned long long mk = __ballot(valid);
-#pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
-      const bool on = (l >> bit) & 1;
-      const unsigned long long bb = __ballot(valid && on);
-      mk &= on ? bb : ~bb;
-    }
-    const int at = valid ? tab[wv * nlev + l] : 0;
-    __builtin_amdgcn_wave_barrier();
-    if (valid && lane == __ffsll((long long)mk) - 1) tab[wv * nlev + l] = at + __popcll(mk);
-    __builtin_amdgcn_wave_barrier();
-    if (valid) {
-      lev[g] = l + 1;
-      perm[g] = at + __popcll(mk & ((1ull << lane) - 1ull));
-    }
-  }
-  int32_t* lev_off = L.lev_off + (int64_t)ii * (kMaxLevels + 1);
-  for (int l = tid; l <= nlev; l += 1024) lev_off[l] = s_off[l];
-  if (tid == 0) {
-    int maxw = 0;
-    for (int l = 0; l < nlev; ++l) maxw = max(maxw, s_tot[l]);
-    L.info[ii].nlev = nlev;
-    L.info[ii].maxwidth = maxw;
-    L.info[ii].nunits = s_units;
-    L.info[ii].maxunit = s_maxunit;
-    L.info[ii].layered = 1;
-  }
+  canonical_order<1024>(L, ii, lo, n, s_maxlev, s_units, s_maxunit, tab, s_off, s_tot, sh,
+                        [&](int g) { return (int)lvl[g]; });
 }
 
 constexpr int kRelU = 4;   // ghosts per thread whose releases are issued together
@@ -912,10 +1241,8 @@ constexpr int kRelE = 4;   // their edges loaded up front (the rest, if any, one
 template <bool InLds, bool CurLds>
 __global__ __launch_bounds__(1024) void k_levels(LevelsArgs L) {
   extern __shared__ uint32_t s_dyn[];
-  // after a finished wide or LDS layering there is nothing left to do
-  if (L.wide && L.wide[0] == 1) return;
   const int ii = blockIdx.x;
-  if (L.info[ii].layered) return;
+  if (L.info[ii].layered) return;   // the LDS layering finished it
   const int tid = threadIdx.x;
   const int np = (1 << L.insts[ii].g.dim) - 1;
   const int64_t lo = L.g_off[ii];
@@ -1230,6 +1557,45 @@ __global__ __launch_bounds__(1024) void k_levels(LevelsArgs L) {
   }
 }
 
+bool levels_pull(int64_t max_n) { return max_n <= kPullMax && wave_residual() == kWaveResidual; }
+
+template <int BS, int NP, int J>
+static gcr_status launch_pull(const LevelsArgs& L, int ninst, int64_t n, hipStream_t st) {
+  static std::mutex mu;
+  static bool ready = false;
+  const int bytes = (int)pull_lds(n, BS / 64);
+  if (bytes > 65536) {
+    std::lock_guard<std::mutex> lk(mu);
+    if (!ready)
+      GCR_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_levels_pull<BS, NP, J>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)pull_lds(BS * J, BS / 64)));
+    ready = true;
+  }
+  k_levels_pull<BS, NP, J><<<ninst, BS, bytes, st>>>(L, bytes);
+  GCR_HIP(hipGetLastError());
+  return GCR_OK;
+}
+
+// Small instances take a workgroup of four waves: its barriers are cheaper
+// than sixteen waves' (128^2 circle, 99 ghosts: 8.2 us a launch against
+// 9.7 for the push form).  Larger ones: as few ghosts a thread as the largest
+// instance allows.
+gcr_status launch_levels_pull(const LevelsArgs& L, int ninst, int64_t max_n, bool all_2d,
+                              hipStream_t st) {
+  const int64_t n = std::max<int64_t>(max_n, 1);
+  if (all_2d) {
+    if (n <= 1024) return launch_pull<256, 3, 4>(L, ninst, n, st);
+    if (n <= 4096) return launch_pull<1024, 3, 4>(L, ninst, n, st);
+    if (n <= 8192) return launch_pull<1024, 3, 8>(L, ninst, n, st);
+    return launch_pull<1024, 3, 16>(L, ninst, n, st);
+  }
+  if (n <= 1024) return launch_pull<256, 7, 4>(L, ninst, n, st);
+  if (n <= 4096) return launch_pull<1024, 7, 4>(L, ninst, n, st);
+  if (n <= 8192) return launch_pull<1024, 7, 8>(L, ninst, n, st);
+  return launch_pull<1024, 7, 16>(L, ninst, n, st);
+}
+
 // Counters and bitmap in LDS when the largest instance fits, else in HBM.
 gcr_status launch_levels(const LevelsArgs& L, int ninst, int64_t max_n, hipStream_t st) {
   // device limits, taken once; the LDS attribute only grows, under the lock,
@@ -1258,11 +1624,8 @@ gcr_status launch_levels(const LevelsArgs& L, int ninst, int64_t max_n, hipStrea
   const int64_t nn = std::max<int64_t>(max_n, 1);
   const int64_t bytes = 4 * (((nn + 3) >> 2) + ((nn + 31) >> 5));
   LevelsArgs F = L;   // the one-workgroup layering
-  F.wide = nullptr;
-  if (!(L.wide && ninst == 1 && wide_layering_forced())) {
-    // the LDS layering first (an instance that fits it is layered there even
-    // when the wide layering is armed, unless a threshold set explicitly
-    // forces it); k_levels_wide and k_levels below skip what it finished
+  {
+    // the LDS layering first; k_levels below skips what it finished
     static int fast_lds = -1;
     lk.lock();
     if (fast_lds < 0) {
@@ -1288,32 +1651,6 @@ gcr_status launch_levels(const LevelsArgs& L, int ninst, int64_t max_n, hipStrea
     const int fl = fast_lds;
     lk.unlock();
     if (fl > 0) k_levels_fast<<<ninst, 1024, (size_t)fl, st>>>(L, fl);
-  }
-  if (L.wide && ninst == 1) {
-    // grid: as many co-resident workgroups as fit, at most one per tile
-    static int coop = -1;
-    lk.lock();
-    if (coop < 0) {
-      int dev = 0, ncu = 0, per = 0;
-      (void)hipGetDevice(&dev);
-      if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        ncu = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-              &per, reinterpret_cast<const void*>(&k_levels_wide), 256, 0) != hipSuccess)
-        per = 0;
-      (void)hipGetLastError();
-      coop = std::max(0, std::min(per, 1) * ncu);
-    }
-    const int coop_n = coop;
-    lk.unlock();
-    const int64_t G = std::min<int64_t>(coop_n, std::max<int64_t>(1, (nn + 255) >> 8));
-    if (G > 0) {
-      LevelsArgs A = L;
-      void* args[] = {&A};
-      GCR_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&k_levels_wide),
-                                         dim3((unsigned)G), dim3(256), args, 0, st));
-      F.wide = L.wide;
-    }
   }
   // what LDS is left holds the level list (worth it from a few thousand)
   const int64_t cur_cap =

@@ -950,8 +950,7 @@ __global__ __launch_bounds__(256) void k_deps(const Inst* __restrict__ insts, in
                                               const uint32_t* __restrict__ hmask,
                                               uint32_t* __restrict__ g_code,
                                               int32_t* __restrict__ deps,
-                                              int32_t* __restrict__ rcnt,
-                                              uint8_t* __restrict__ dcnt,
+                                              int32_t* __restrict__ lev,
                                               InstInfo* __restrict__ info) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= g_off[ninst]) return;
@@ -981,12 +980,12 @@ __global__ __launch_bounds__(256) void k_deps(const Inst* __restrict__ insts, in
   }
   const uint32_t code = make_code(n, r, g.dim);
   g_code[e] = code;
+  lev[e] = 0;   // k_levels_flow: no level yet
   int i, j, k;
   unlinear(g, c, i, j, k);
   const int8_t* T = tags + I.cell_off;
   const int np = (1 << g.dim) - 1;
   const uint32_t skip = code_skip(code);
-  int nd = 0;
   for (int m = 1; m <= np; ++m) {
     int32_t d = -1;
     if (!(m & skip)) {
@@ -1003,10 +1002,25 @@ __global__ __launch_bounds__(256) void k_deps(const Inst* __restrict__ insts, in
       }
     }
     deps[(int64_t)(m - 1) * cap + e] = d;
-    if (d >= 0) {
-      atomicAdd(&rcnt[d], 1);   // reverse edge d -> e
-      ++nd;
-    }
+  }
+}
+
+// For the layerings that push along reverse edges: the number of ghosts
+// each ghost reads, and of those that read it (rcnt starts at zero).
+__global__ __launch_bounds__(256) void k_rcount(const Inst* __restrict__ insts,
+                                                const int64_t* __restrict__ g_off, int ninst,
+                                                int64_t cap, const int32_t* __restrict__ deps,
+                                                int32_t* __restrict__ rcnt,
+                                                uint8_t* __restrict__ dcnt) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= g_off[ninst]) return;
+  const int np = (1 << insts[find_inst(g_off, ninst, e)].g.dim) - 1;
+  int nd = 0;
+  for (int m = 0; m < np; ++m) {
+    const int32_t d = deps[(int64_t)m * cap + e];
+    if (d < 0) continue;
+    atomicAdd(&rcnt[d], 1);   // reverse edge d -> e
+    ++nd;
   }
   dcnt[e] = (uint8_t)nd;
 }
@@ -1094,12 +1108,44 @@ struct FinPart {
   int32_t pad;
 };
 
+// hist (null: perm holds them): the canonical positions are found here, tile
+// by tile of the whole-GPU layering (k_levels_flow; the workgroup's 256
+// ghosts are its tile): hist[tile][level] is the position of the tile's
+// first ghost of that level, its rank among the tile's comes from ballots.
+__device__ __forceinline__ int tile_position(const int32_t* __restrict__ lev,
+                                             const int32_t* __restrict__ hist, int64_t e, int64_t n,
+                                             int32_t* __restrict__ perm) {
+  __shared__ int s_wc[4][kWideLevels];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  for (int t = threadIdx.x; t < 4 * kWideLevels; t += 256) s_wc[t / kWideLevels][t % kWideLevels] = 0;
+  __syncthreads();
+  const bool valid = e < n;
+  const int l = valid ? lev[e] - 1 : 0;
+  unsigned long long mk = __ballot(valid);
+  static_assert(kWideLevels <= 128, "a level index fits 7 ballots");
+#pragma unroll
+  for (int bit = 0; bit < 7; ++bit) {
+    const bool on = (l >> bit) & 1;
+    const unsigned long long bb = __ballot(valid && on);
+    mk &= on ? bb : ~bb;
+  }
+  const int rank = __popcll(mk & ((1ull << lane) - 1ull));
+  if (valid && rank == 0) s_wc[wv][l] = __popcll(mk);
+  __syncthreads();
+  if (!valid) return -1;
+  int pos = hist[(e >> 8) * kWideLevels + l] + rank;
+  for (int w = 0; w < wv; ++w) pos += s_wc[w][l];
+  perm[e] = pos;
+  return pos;
+}
+
 __global__ __launch_bounds__(256) void k_finalize(
     const Inst* __restrict__ insts, int ninst, const int64_t* __restrict__ g_off, int64_t cap,
     const int32_t* __restrict__ g_cell, const double* __restrict__ g_psi,
     const double* __restrict__ g_n, const uint32_t* __restrict__ g_code,
     const int32_t* __restrict__ lev, const int32_t* __restrict__ blk_idx,
-    const int32_t* __restrict__ perm, int32_t* __restrict__ cell, double* __restrict__ delta,
+    int32_t* __restrict__ perm, const int32_t* __restrict__ hist, int32_t* __restrict__ cell,
+    double* __restrict__ delta,
     double* __restrict__ nrm, double* __restrict__ psi, uint32_t* __restrict__ code,
     int32_t* __restrict__ level, int32_t* __restrict__ blk, InstInfo* __restrict__ info,
     FinPart* __restrict__ part) {
@@ -1108,10 +1154,15 @@ __global__ __launch_bounds__(256) void k_finalize(
   // per-thread statistics: max alpha and multiplier per axis, fluid-side count
   double am[3] = {0.0, 0.0, 0.0};
   int rm[3] = {0, 0, 0}, fl = 0, ii = -1;
+  int pl = -1;
+  if (hist) {   // (a batch of one; uniform)
+    if (info[0].layered) pl = tile_position(lev, hist, e, ng_all, perm);
+  } else if (e < ng_all) {
+    pl = perm[e];
+  }
   if (e < ng_all) {
     ii = find_inst(g_off, ninst, e);
     const GridD& g = insts[ii].g;
-    const int pl = perm[e];
     if (pl >= 0 && pl < g_off[ii + 1] - g_off[ii]) {   // else the build failed earlier
       const int64_t p = g_off[ii] + pl;
       const double ps = g_psi[e];
@@ -1285,6 +1336,13 @@ __global__ void k_hash_remap(const int64_t* __restrict__ hoff, int ninst,
   const int ii = find_inst(hoff, ninst, s);
   const int32_t v = (int32_t)(e & 0xffffffffu);
   htab[s] = (e & 0xffffffff00000000ull) | (uint32_t)perm[g_off[ii] + v];
+}
+
+// before a second layering of the same ghosts: the statistics that
+// k_finalize adds up, from zero
+__global__ void k_info_reset(InstInfo* __restrict__ info, int ninst) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < ninst) info[i].nfluid = 0;
 }
 
 // --------------------------------------------------------------------------
@@ -1533,16 +1591,16 @@ struct StageEvents {
 void set_profiling(int mask) { g_profiling.store(mask & 3); }
 int profiling_mask() { return g_profiling.load(); }
 
-static std::atomic<int64_t> g_wide_min{kWideMinInterface};
-void set_wide_layering(int64_t v) { g_wide_min.store(v > 0 ? v : kWideMinInterface); }
-int64_t wide_layering_min() { return g_wide_min.load(); }
+static std::atomic<int64_t> g_wide_min{0};   // 0: the default
+void set_wide_layering(int64_t v) { g_wide_min.store(v > 0 ? v : 0); }
+int64_t wide_layering_min() {
+  const int64_t v = g_wide_min.load();
+  return v ? v : kWideMinInterface;
+}
 static std::atomic<int> g_wave_res{kWaveResidual};
 void set_wave_residual(int v) { g_wave_res.store(v < 0 ? 0 : (v > kWaveResidual ? kWaveResidual : v)); }
 int wave_residual() { return g_wave_res.load(); }
-static std::atomic<int> g_wide_buf{kWideBuf};
-void set_wide_buffer(int v) { g_wide_buf.store(v <= 0 || v > kWideBuf ? kWideBuf : v); }
-int wide_buffer() { return g_wide_buf.load(); }
-bool wide_layering_forced() { return g_wide_min.load() != kWideMinInterface; }
+bool wide_layering_forced() { return g_wide_min.load() != 0; }
 void last_build_times(float* ms) {
   for (int s = 0; s < kStages; ++s) ms[s] = g_stage_ms[s];
 }
@@ -1612,6 +1670,95 @@ gcr_status build_update(BatchData& prev, const ShapeD& shape, bool incremental, 
   }
   B->inst[0] = I;
   return build_core(B, st, incremental ? &prev : nullptr, out);
+}
+
+// The ghosts' cell table, dependencies, levels and canonical arrays, from the
+// ghosts in linear order, layered as `how` says: by one workgroup per
+// instance pulling, by the whole GPU, or by the layerings that push along
+// reverse edges, which take every graph the others leave.
+enum Layering { kLayerPull, kLayerFlow, kLayerPush };
+static gcr_status build_graph(BatchData& D, hipStream_t st, int ninst, int64_t nif,
+                              int64_t max_if, Layering how, StageEvents& T) {
+  const int64_t cap = D.cap;
+  int32_t* hist = nullptr;
+  // ghost count unknown on the host: launch over the interface capacity
+  k_hash_build<<<blocks(nif, 256), 256, 0, st>>>(D.d_g_off, ninst, D.d_g_cell, D.d_hoff,
+                                                  D.d_hmask, D.d_htab, D.d_rcnt,
+                                                  how == kLayerPush ? 2 * cap : 2);   // + rcnt, rfill cleared
+  k_deps<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, ninst, D.d_g_off, D.d_g_cell, D.d_g_psi,
+                                            D.d_g_n, cap, D.d_g_ext, D.d_tags, D.d_htab, D.d_hoff,
+                                            D.d_hmask, D.d_g_code, D.d_deps, D.d_lev, D.d_info);
+  if (how == kLayerPush) {
+    k_rcount<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, D.d_g_off, ninst, cap, D.d_deps,
+                                                D.d_rcnt, D.d_dcnt);
+    // reverse-edge offsets: one workgroup up to two tiles, else three passes
+    // over the interface capacity
+    const int64_t ntiles = (cap + kScanTile - 1) / kScanTile;
+    if (ntiles <= 2) {
+      k_rscan<<<1, 1024, 0, st>>>(D.d_rcnt, D.d_g_off, ninst, D.d_roff);
+    } else {
+      int64_t* tsum = own<int64_t>(D, ntiles + 1);
+      if (!tsum) return GCR_E_NOMEM;
+      k_iscan_reduce<<<(unsigned)ntiles, 1024, 0, st>>>(D.d_rcnt, cap, tsum);
+      k_scan_top<<<1, 1024, 0, st>>>(tsum, ntiles, tsum + ntiles, nullptr);
+      k_iscan_down<<<(unsigned)ntiles, 1024, 0, st>>>(D.d_rcnt, cap, tsum, D.d_roff);
+    }
+    k_rfill<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, D.d_g_off, ninst, cap, D.d_deps,
+                                               D.d_roff, D.d_rcnt + cap, D.d_radj);
+  }
+  T.mark(7, st);
+  {
+    LevelsArgs L;
+    L.insts = D.d_inst;
+    L.g_off = D.d_g_off;
+    L.deps = D.d_deps;
+    L.cap = cap;
+    L.lev = D.d_lev;
+    L.blk_idx = D.d_blk_idx;
+    L.perm = D.d_perm;
+    L.lev_off = D.d_lev_off;
+    L.unit_mem = D.d_unit_mem;
+    L.unit_cnt = D.d_unit_cnt;
+    L.unit_lev = D.d_unit_lev;
+    L.reach = D.d_reach;
+    L.listA = D.d_listA;
+    L.dcnt = D.d_dcnt;
+    L.roff = D.d_roff;
+    L.radj = D.d_radj;
+    L.cnt = D.d_cnt;
+    L.bits = D.d_bits;
+    L.info = D.d_info;
+    L.flow = L.hist = nullptr;
+    L.cur_cap = 0;
+    L.wave_res = wave_residual();
+    if (how == kLayerFlow) {
+      L.flow = D.d_rcnt;   // two cleared words
+      hist = L.hist = own<int32_t>(D, (size_t)kWideLevels * (cap / 256 + 1));
+      if (!L.hist) return GCR_E_NOMEM;
+    }
+    bool all_2d = true;
+    for (const Inst& I : D.inst) all_2d = all_2d && I.g.dim == 2;
+    const gcr_status ls = how == kLayerFlow   ? launch_levels_flow(L, max_if, st)
+                          : how == kLayerPull ? launch_levels_pull(L, ninst, max_if, all_2d, st)
+                                              : launch_levels(L, ninst, max_if, st);
+    if (ls != GCR_OK) return ls;
+  }
+  T.mark(8, st);
+  {
+    const unsigned nfb = blocks(nif, 256);
+    FinPart* fp = own<FinPart>(D, nfb);
+    if (!fp) return GCR_E_NOMEM;
+    k_finalize<<<nfb, 256, 0, st>>>(
+        D.d_inst, ninst, D.d_g_off, cap, D.d_g_cell, D.d_g_psi, D.d_g_n, D.d_g_code, D.d_lev,
+        D.d_blk_idx, D.d_perm, hist, D.d_cell, D.d_delta, D.d_nrm, D.d_psi, D.d_code, D.d_level,
+        D.d_blk, D.d_info, fp);
+    k_units_canonical<<<ninst, 256, 0, st>>>(D.d_perm, D.d_info, D.d_unit_mem, D.d_unit_cnt,
+                                             fp, (int64_t)nfb);
+  }
+  k_hash_remap<<<blocks(D.hoff[ninst], 256), 256, 0, st>>>(D.d_hoff, ninst, D.d_g_off, D.d_perm,
+                                                            D.d_htab);
+  T.mark(9, st);
+  return GCR_OK;
 }
 
 // The build proper: B holds its instances (device faces in place); with
@@ -1830,6 +1977,7 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   if (any_2d) GCR_HIP(hipMemsetAsync(D.d_if_n + 2 * cap, 0, sizeof(double) * cap, st));
 
   T.mark(3, st);
+  Layering how = kLayerPush;
   if (nif > 0) {
     k_compact_iface<<<(unsigned)nlist, 256, 0, st>>>(D.d_inst, D.d_chunk_inst, D.d_tags,
                                                      D.d_chunk_cnt, D.d_chunk_excl, D.d_chunk_list,
@@ -1847,83 +1995,15 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
     k_ghost_off<<<(unsigned)(ninst + 1), 64, 0, st>>>(D.d_if_flag, D.d_blkexcl, D.d_if_off, ninst,
                                                       D.d_g_off);
     T.mark(6, st);
-    // ghost count unknown on the host: launch over the interface capacity
-    k_hash_build<<<blocks(nif, 256), 256, 0, st>>>(D.d_g_off, ninst, D.d_g_cell, D.d_hoff,
-                                                    D.d_hmask, D.d_htab, D.d_rcnt,
-                                                    2 * cap);   // + rcnt, rfill cleared
-    k_deps<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, ninst, D.d_g_off, D.d_g_cell, D.d_g_psi,
-                                              D.d_g_n, cap, D.d_g_ext, D.d_tags, D.d_htab, D.d_hoff,
-                                              D.d_hmask, D.d_g_code, D.d_deps,
-                                              D.d_rcnt, D.d_dcnt, D.d_info);
-    {
-      // reverse-edge offsets: one workgroup up to two tiles, else three passes
-      // over the interface capacity
-      const int64_t ntiles = (cap + kScanTile - 1) / kScanTile;
-      if (ntiles <= 2) {
-        k_rscan<<<1, 1024, 0, st>>>(D.d_rcnt, D.d_g_off, ninst, D.d_roff);
-      } else {
-        int64_t* tsum = own<int64_t>(D, ntiles + 1);
-        if (!tsum) return GCR_E_NOMEM;
-        k_iscan_reduce<<<(unsigned)ntiles, 1024, 0, st>>>(D.d_rcnt, cap, tsum);
-        k_scan_top<<<1, 1024, 0, st>>>(tsum, ntiles, tsum + ntiles, nullptr);
-        k_iscan_down<<<(unsigned)ntiles, 1024, 0, st>>>(D.d_rcnt, cap, tsum, D.d_roff);
-      }
-    }
-    k_rfill<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, D.d_g_off, ninst, cap, D.d_deps,
-                                               D.d_roff, D.d_rcnt + cap, D.d_radj);
-    T.mark(7, st);
-    {
-      LevelsArgs L;
-      L.insts = D.d_inst;
-      L.g_off = D.d_g_off;
-      L.deps = D.d_deps;
-      L.cap = cap;
-      L.lev = D.d_lev;
-      L.blk_idx = D.d_blk_idx;
-      L.perm = D.d_perm;
-      L.lev_off = D.d_lev_off;
-      L.unit_mem = D.d_unit_mem;
-      L.unit_cnt = D.d_unit_cnt;
-      L.unit_lev = D.d_unit_lev;
-      L.reach = D.d_reach;
-      L.listA = D.d_listA;
-      L.dcnt = D.d_dcnt;
-      L.roff = D.d_roff;
-      L.radj = D.d_radj;
-      L.cnt = D.d_cnt;
-      L.bits = D.d_bits;
-      L.info = D.d_info;
-      int64_t max_if = 0;
-      for (int i = 0; i < ninst; ++i) max_if = std::max(max_if, D.if_off[i + 1] - D.if_off[i]);
-      L.listB = L.wide = L.hist = nullptr;
-      L.cur_cap = 0;
-      L.wave_res = wave_residual();
-      L.wide_cap = wide_buffer();
-      if (ninst == 1 && max_if >= wide_layering_min()) {
-        // the reverse-edge counters are spent once the edges are filled
-        L.listB = D.d_rcnt;
-        L.wide = own<int32_t>(D, kWideState);
-        L.hist = own<int32_t>(D, (size_t)kWideLevels * (cap / 256 + 1));
-        if (!L.wide || !L.hist) return GCR_E_NOMEM;
-      }
-      const gcr_status ls = launch_levels(L, ninst, max_if, st);
-      if (ls != GCR_OK) return ls;
-    }
-    T.mark(8, st);
-    {
-      const unsigned nfb = blocks(nif, 256);
-      FinPart* fp = own<FinPart>(D, nfb);
-      if (!fp) return GCR_E_NOMEM;
-      k_finalize<<<nfb, 256, 0, st>>>(
-          D.d_inst, ninst, D.d_g_off, cap, D.d_g_cell, D.d_g_psi, D.d_g_n, D.d_g_code, D.d_lev,
-          D.d_blk_idx, D.d_perm, D.d_cell, D.d_delta, D.d_nrm, D.d_psi, D.d_code, D.d_level,
-          D.d_blk, D.d_info, fp);
-      k_units_canonical<<<ninst, 256, 0, st>>>(D.d_perm, D.d_info, D.d_unit_mem, D.d_unit_cnt,
-                                               fp, (int64_t)nfb);
-    }
-    k_hash_remap<<<blocks(D.hoff[ninst], 256), 256, 0, st>>>(D.d_hoff, ninst, D.d_g_off, D.d_perm,
-                                                              D.d_htab);
-    T.mark(9, st);
+    int64_t max_if = 0;
+    for (int i = 0; i < ninst; ++i) max_if = std::max(max_if, D.if_off[i + 1] - D.if_off[i]);
+    // a plan alone: the whole GPU for large 3D bodies (in 2D, where concave
+    // bodies have cycles and chains are long, only when asked for)
+    const bool flow = ninst == 1 && max_if >= wide_layering_min() &&
+                      (any_3d || wide_layering_forced());
+    how = flow ? kLayerFlow : levels_pull(max_if) ? kLayerPull : kLayerPush;
+    const gcr_status s = build_graph(D, st, ninst, nif, max_if, how, T);
+    if (s != GCR_OK) return s;
   } else {
     k_hash_clear<<<blocks(D.hoff[ninst], 256), 256, 0, st>>>(D.d_htab, D.hoff[ninst]);
     for (int i = 4; i <= 9; ++i) T.mark(i, st);
@@ -1935,12 +2015,27 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   D.info.resize(ninst);
   D.lev_off.resize((size_t)ninst * (kMaxLevels + 1));
   D.unit_lev.resize((size_t)ninst * kMaxUnits);
-  GCR_HIP(hipMemcpyAsync(PS.p + o_info, tb + o_info, o_if - o_info, hipMemcpyDeviceToHost,
-                         st));   // R4
-  GCR_HIP(hipStreamSynchronize(st));
+  for (;;) {
+    GCR_HIP(hipMemcpyAsync(PS.p + o_info, tb + o_info, o_if - o_info, hipMemcpyDeviceToHost,
+                           st));   // R4
+    GCR_HIP(hipStreamSynchronize(st));
+    std::memcpy(D.g_off.data(), PS.p + o_go, 8 * (ninst + 1));
+    std::memcpy(D.info.data(), PS.p + o_info, sizeof(InstInfo) * ninst);
+    bool again = false;
+    for (int i = 0; i < ninst && how != kLayerPush; ++i)
+      again = again || (!D.info[i].layered && !D.info[i].err && D.g_off[i + 1] > D.g_off[i]);
+    if (!again) break;
+    // a graph that these layerings leave (deeper than their tables, a unit
+    // beyond the solver's size, a cycle in a large 3D one): once more
+    how = kLayerPush;
+    int64_t max_if = 0;
+    for (int i = 0; i < ninst; ++i) max_if = std::max(max_if, D.if_off[i + 1] - D.if_off[i]);
+    k_info_reset<<<blocks(ninst, 64), 64, 0, st>>>(D.d_info, ninst);
+    k_hash_clear<<<blocks(D.hoff[ninst], 256), 256, 0, st>>>(D.d_htab, D.hoff[ninst]);
+    const gcr_status s = build_graph(D, st, ninst, nif, max_if, how, T);
+    if (s != GCR_OK) return s;
+  }
   PS.pending = false;
-  std::memcpy(D.g_off.data(), PS.p + o_go, 8 * (ninst + 1));
-  std::memcpy(D.info.data(), PS.p + o_info, sizeof(InstInfo) * ninst);
   std::memcpy(D.lev_off.data(), PS.p + o_lo, 4 * (size_t)ninst * (kMaxLevels + 1));
   std::memcpy(D.unit_lev.data(), PS.p + o_ul, 4 * (size_t)ninst * kMaxUnits);
   T.collect(std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_call)
