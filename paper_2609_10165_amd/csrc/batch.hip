@@ -186,168 +186,13 @@ __device__ __forceinline__ void surface_item(const BStatic& S, const BCall& C, i
   __syncthreads();
 }
 
-// The levels of a 2D item, swept in LDS.  A prologue takes every ghost of
-// the item at once: its weights (as fill_single computes them), the term of
-// its boundary value, and per stencil corner either the product of weight
-// and fluid value or, for a corner that is a ghost, the weight and that
-// ghost's position, into a record of kRecWords doubles (bit 63 of the last
-// word marks a member of a coupled unit).  The levels then read only LDS,
-// the first word of each record becoming the ghost's value once computed;
-// the terms are added in corner order, as fill_single adds them, and each
-// level's coupled units are solved as fill_unit_field solves them, so the
-// values are the same bits.  An epilogue stores the values into the field.
-constexpr int kRecWords = 5;
-
-// A load through a global-address-space pointer (the plan's and the
-// field's arrays are device memory): a flat load would also count against
-// the LDS wait counter that every LDS access of the sweep waits on.
-template <class T>
-__device__ __forceinline__ T gload(const T* p) {
-  return *(const __attribute__((address_space(1))) T*)p;
-}
-constexpr int kRecUnitWS = 8;   // unit workspaces after the records
-constexpr uint32_t kRecFluid = 0xffffu, kRecSkip = 0xfffeu;
-constexpr uint64_t kRecMember = 1ull << 63;
-
-// Coupled unit u of an LDS sweep: (I - W_int) phi = W_ext phi_ext + w0 b,
-// assembled from the members' records in fill_unit_field's order.
-__device__ __forceinline__ void unit_lds2(const PlanD& P, int u, double* rec, UnitWS& ws) {
-  const int k = P.unit_cnt[u];
-  for (int i = 0; i < k; ++i) ws.mem[i] = P.unit_mem[u * kMaxUnit + i];
-  for (int i = 0; i < k; ++i) {
-    const double* r = rec + (int64_t)kRecWords * ws.mem[i];
-    const uint64_t pk = (uint64_t)__double_as_longlong(r[4]);
-    for (int t = 0; t < k; ++t) ws.M[i * k + t] = (t == i) ? 1.0 : 0.0;
-    double rr = r[0];
-    for (int c = 1; c < 4; ++c) {
-      const uint32_t id = (uint32_t)(pk >> (16 * (c - 1))) & 0xffffu;
-      if (id == kRecSkip) continue;
-      if (id == kRecFluid) {
-        rr += r[c];
-        continue;
-      }
-      int t = -1;
-      for (int s = 0; s < k; ++s)
-        if (ws.mem[s] == (int)id) t = s;
-      if (t >= 0) ws.M[i * k + t] -= r[c];
-      else rr += r[c] * rec[(int64_t)kRecWords * id];
-    }
-    ws.rhs[i] = rr;
-  }
-  ws_solve(ws, k);
-  for (int i = 0; i < k; ++i) rec[(int64_t)kRecWords * ws.mem[i]] = ws.rhs[i];
-}
-__device__ __forceinline__ void sweep_lds2(const PlanD& P, const int32_t* __restrict__ lev_off,
-                                           int nl, double* __restrict__ F,
-                                           const double* __restrict__ b,
-                                           const uint8_t* __restrict__ bt, int kind,
-                                           double* rec, int rec_cap) {
-  const int T = blockDim.x, tid = threadIdx.x;
-  const int ng = P.ng;
-  for (int p = tid; p < ng; p += T) {
-    const int c = gload(P.cell + p);
-    const uint32_t code = gload(P.code + p);
-    double dl[3] = {gload(P.dl[0] + p), gload(P.dl[1] + p), 0.0},
-           nn[3] = {gload(P.nn[0] + p), gload(P.nn[1] + p), 0.0}, w[8];
-    const bool member = gload(P.blk + p) >= 0;
-    const int bc = kind == 2 ? (int)gload(bt + p) : kind;
-    const double bv = gload(b + p);
-    int gi[4];
-#pragma unroll
-    for (int k = 1; k < 4; ++k) gi[k] = gload(P.cgi + (int64_t)(k - 1) * ng + p);
-    double X[3];
-    stencil_span(P.g, code, c, X);
-    ghost_weights<2>(dl, nn, X, bc, w);
-    double* r = rec + (int64_t)kRecWords * p;
-    r[0] = w[0] * bv;
-    uint64_t pk = member ? kRecMember : 0ull;
-#pragma unroll
-    for (int k = 1; k < 4; ++k) {
-      uint64_t id = kRecSkip;
-      double t = 0.0;
-      if (gi[k] >= 0) {
-        id = (uint64_t)gi[k];
-        t = w[k];
-      } else if (gi[k] == -1) {
-        id = kRecFluid;
-        t = w[k] * gload(F + c + corner_offset(P.g, code, k));
-      }
-      r[k] = t;
-      pk |= id << (16 * (k - 1));
-    }
-    r[4] = __longlong_as_double((long long)pk);
-  }
-  __syncthreads();
-  // (read once: after a barrier every level would load it again)
-  const int nunits = P.nunits;
-  int unext = 0x7fffffff;
-  if (tid < kRecUnitWS)
-    for (int s = tid; s < nunits; s += kRecUnitWS) unext = min(unext, gload(P.unit_lev + s));
-  // level offsets 64 at a time, lane j holding lev_off[base + j]: a level
-  // reads its bounds from registers instead of memory
-  const int lane = tid & 63;
-  int vlev = 0, vnext = 0;
-  for (int l = 0; l < nl; ++l) {
-    if ((l & 63) == 0) {
-      vlev = l + lane <= nl ? gload(lev_off + l + lane) : 0;
-      vnext = l + 64 <= nl ? gload(lev_off + l + 64) : 0;
-    }
-    const int lo = __builtin_amdgcn_readlane(vlev, l & 63);
-    const int hi = (l & 63) == 63 ? __builtin_amdgcn_readfirstlane(vnext)
-                                  : __builtin_amdgcn_readlane(vlev, (l & 63) + 1);
-    for (int p = lo + tid; p < hi; p += T) {
-      // the record's words, then the three corners' ghost values, each
-      // group read at once; the terms are added in corner order as before
-      double* r = rec + (int64_t)kRecWords * p;
-      double w[kRecWords];
-#pragma unroll
-      for (int k = 0; k < kRecWords; ++k) w[k] = r[k];
-      const uint64_t pk = (uint64_t)__double_as_longlong(w[4]);
-      if (pk & kRecMember) continue;   // solved with its unit below
-      uint32_t id[3];
-      double gv[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        id[k] = (uint32_t)(pk >> (16 * k)) & 0xffffu;
-        gv[k] = rec[(int64_t)kRecWords * (id[k] < kRecSkip ? (int)id[k] : p)];
-      }
-      double v = w[0];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const double t = id[k] == kRecFluid ? w[k + 1] : w[k + 1] * gv[k];
-        v = id[k] == kRecSkip ? v : v + t;
-      }
-      r[0] = v;
-    }
-    __syncthreads();
-    if (nunits) {
-      // thread s < kRecUnitWS takes units s, s + kRecUnitWS, ...; unext is
-      // the lowest level among those not solved yet
-      if (unext == l + 1) {
-        UnitWS* ws = reinterpret_cast<UnitWS*>(rec + (int64_t)kRecWords * rec_cap);
-        unext = 0x7fffffff;
-        for (int s = tid; s < nunits; s += kRecUnitWS) {
-          const int ul = gload(P.unit_lev + s);
-          if (ul == l + 1) unit_lds2(P, s, rec, ws[tid]);
-          else if (ul > l + 1) unext = min(unext, ul);
-        }
-      }
-      __syncthreads();
-    }
-  }
-  for (int p = tid; p < ng; p += T)
-    *(__attribute__((address_space(1))) double*)(F + gload(P.cell + p)) = rec[(int64_t)kRecWords * p];
-  __syncthreads();
-}
-
 // (LDS, dynamic: the surface part's reduction rows, the coupled units'
-// workspaces and the 2D sweep records share it; the records of an item are
-// dead before the rows are used, and the sweep's unit workspaces follow the
-// records.  rec_cap: the largest item, in ghosts, the records may hold.)
+// workspaces and the 2D fill's records share it; an item's records are dead before the rows are used.  lds_fill: bytes there are for the
+// latter, 0 if no item takes that form.)
 template <int D>
 __global__ __launch_bounds__(1024) void k_batch_forward(BStatic S, BCall C, double* __restrict__ part,
                                                         int* __restrict__ counter,
-                                                        double* __restrict__ Fout, int rec_cap) {
+                                                        double* __restrict__ Fout, int lds_fill) {
   extern __shared__ double s_lds[];
   double(*red)[3] = reinterpret_cast<double(*)[3]>(s_lds);
   UnitWS* ws = reinterpret_cast<UnitWS*>(s_lds);
@@ -362,8 +207,8 @@ __global__ __launch_bounds__(1024) void k_batch_forward(BStatic S, BCall C, doub
     const int kind = C.kind[f];
     const int32_t* lo_ = S.lev_off[i];
     const int nl = (C.tile_flag && C.tile_flag[0] == 0) ? 0 : S.nlev[i];
-    if (D == 2 && nl > 0 && P.ng <= rec_cap && P.cgi) {
-      sweep_lds2(P, lo_, nl, F, b, bt, kind, s_lds, rec_cap);
+    if (D == 2 && nl > 0 && fill_lds_ok(P) && fill_lds_bytes(P.ng, P.nunits) <= lds_fill) {
+      fill_lds2(P, lo_, nl, F, b, bt, kind, s_lds);
       surface_item<D>(S, C, w, red, part, counter, Fout);
       continue;
     }
@@ -816,8 +661,7 @@ struct BatchFwdState {
   // are released only once the last one has run, on whatever stream
   hipEvent_t ev_done = nullptr;
   int threads = 0, grid_mul = 0;   // tuned
-  int rec_ng = 0;                  // ghosts of the largest 2D instance
-  int32_t* d_cgi = nullptr;        // corners' ghosts of the 2D plans (PlanD::cgi)
+  size_t fill_lds = 0;             // most LDS an instance filled there takes
   // tiled fill: 0 not set up yet, 1 set up, -1 not used for this batch
   int tiled = 0;
   int calls = 0;                   // forward calls so far
@@ -864,26 +708,6 @@ std::mutex g_bfs_mu;
 // the device pool they return memory to may already be gone by then
 auto& g_bfs = *new std::vector<std::pair<const gcr_batch*, std::unique_ptr<BatchFwdState>>>();
 
-// The corners' ghosts of the batch's 2D plans, once per batch: one thread
-// per ghost (flattened over the plans, off[i] the first of plan i), corner
-// k + 1 of ghost p at cgi[3 off[i] + k ng + p]: the ghost's position from
-// the lookup table, -1 for a fluid corner, -2 for a skipped one.
-__global__ __launch_bounds__(256) void k_corner_ghosts(const PlanD* __restrict__ plans,
-                                                       const int64_t* __restrict__ off, int n,
-                                                       int32_t* __restrict__ cgi) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= off[n]) return;
-  const int i = find_inst(off, n, e);
-  const PlanD& P = plans[i];
-  const int p = (int)(e - off[i]);
-  const int c = P.cell[p];
-  const uint32_t code = P.code[p];
-  const uint32_t skip = code_skip(code);
-  int32_t* out = cgi + 3 * off[i];
-  for (int k = 1; k < 4; ++k)
-    out[(int64_t)(k - 1) * P.ng + p] = (k & skip) ? -2 : ghost_at(P, c + corner_offset(P.g, code, k));
-}
-
 BatchFwdState* state_of(gcr_batch* b, hipStream_t st, gcr_status* err) {
   std::lock_guard<std::mutex> lk(g_bfs_mu);
   for (auto& e : g_bfs)
@@ -893,23 +717,12 @@ BatchFwdState* state_of(gcr_batch* b, hipStream_t st, gcr_status* err) {
   std::vector<PlanD> pv(n);
   std::vector<int32_t*> lp(n);
   std::vector<int32_t> nl(n);
-  std::vector<int64_t> coff(n + 1, 0);   // ghosts of the 2D plans before plan i
   for (int i = 0; i < n; ++i) {
     pv[i] = plan_view(b->plans[i].get());
     lp[i] = b->plans[i]->d_lev_off;
     nl[i] = b->plans[i]->nlev;
-    if (pv[i].g.dim == 2) S->rec_ng = std::max(S->rec_ng, pv[i].ng);
-    coff[i + 1] = coff[i] + (pv[i].g.dim == 2 ? pv[i].ng : 0);
-  }
-  if (coff[n] > 0) {
-    S->d_cgi = static_cast<int32_t*>(pool_alloc(sizeof(int32_t) * 3 * coff[n]));
-    if (!S->d_cgi) {
-      *err = GCR_E_NOMEM;
-      return nullptr;
-    }
-    S->owned.push_back(S->d_cgi);
-    for (int i = 0; i < n; ++i)
-      if (pv[i].g.dim == 2) pv[i].cgi = S->d_cgi + 3 * coff[i];
+    if (fill_lds_ok(pv[i]) && fill_lds_bytes(pv[i].ng, pv[i].nunits) <= 160 * 1024)
+      S->fill_lds = std::max(S->fill_lds, fill_lds_bytes(pv[i].ng, pv[i].nunits));
   }
   // one upload from pinned staging: plans | level-offset pointers | level
   // counts | force counters and two sets of level counters (zero), each
@@ -918,8 +731,7 @@ BatchFwdState* state_of(gcr_batch* b, hipStream_t st, gcr_status* err) {
   const size_t o_lp = al(sizeof(PlanD) * n), o_nl = o_lp + al(sizeof(int32_t*) * n);
   const size_t o_ct = o_nl + al(sizeof(int32_t) * n), o_bar = o_ct + al(sizeof(int) * n);
   const size_t o_fault = o_bar + al(sizeof(int) * 2 * n);
-  const size_t o_coff = o_fault + al(sizeof(int));
-  const size_t bytes = o_coff + al(sizeof(int64_t) * (n + 1));
+  const size_t bytes = o_fault + al(sizeof(int));
   char* d = static_cast<char*>(pool_alloc(bytes));
   if (d) S->owned.push_back(d);
   S->h_static = static_cast<char*>(pinned_alloc(bytes));
@@ -937,15 +749,11 @@ BatchFwdState* state_of(gcr_batch* b, hipStream_t st, gcr_status* err) {
   std::memcpy(S->h_static, pv.data(), sizeof(PlanD) * n);
   std::memcpy(S->h_static + o_lp, lp.data(), sizeof(int32_t*) * n);
   std::memcpy(S->h_static + o_nl, nl.data(), sizeof(int32_t) * n);
-  std::memcpy(S->h_static + o_coff, coff.data(), sizeof(int64_t) * (n + 1));
   S->ev_static = event_take();
   if (!S->ev_static || hipMemcpyAsync(d, S->h_static, bytes, hipMemcpyHostToDevice, st)) {
     *err = GCR_E_HIP;
     return nullptr;
   }
-  if (coff[n] > 0)
-    k_corner_ghosts<<<(unsigned)((coff[n] + 255) / 256), 256, 0, st>>>(
-        S->d_plans, reinterpret_cast<const int64_t*>(d + o_coff), n, S->d_cgi);
   if (hipGetLastError() != hipSuccess || hipEventRecord(S->ev_static, st)) {
     *err = GCR_E_HIP;
     return nullptr;
@@ -1230,10 +1038,9 @@ static int split_capacity(int dim, int threads) {
   return c;
 }
 
-// Ghosts a workgroup's LDS can hold as sweep records (k_batch_forward), from
-// the device's largest dynamic LDS, which the forward kernels are allowed
-// once; 0 where that fails.
-static int forward_rec_cap() {
+// Dynamic LDS the forward kernels may use, set once to the device's largest;
+// 0 where that fails.
+static int forward_lds() {
   static std::mutex mu;
   static int cap = -1;
   std::lock_guard<std::mutex> lk(mu);
@@ -1243,14 +1050,12 @@ static int forward_rec_cap() {
   if (hipDeviceGetAttribute(&a, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) a = 0;
   if (hipDeviceGetAttribute(&o, hipDeviceAttributeSharedMemPerBlockOptin, dev) != hipSuccess) o = 0;
   const int v = std::max(a, o) & ~255;
-  bool ok = v > (int)(kRecUnitWS * sizeof(UnitWS));
+  bool ok = v > 0;
   for (const void* k : {reinterpret_cast<const void*>(&k_batch_forward<2>),
                         reinterpret_cast<const void*>(&k_batch_forward<3>)})
     ok = ok && hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess;
   (void)hipGetLastError();
-  cap = ok ? std::min<int>((v - (int)(kRecUnitWS * sizeof(UnitWS))) / (kRecWords * (int)sizeof(double)),
-                           (int)kRecSkip - 1)
-           : 0;
+  cap = ok ? v : 0;
   return cap;
 }
 
@@ -1287,21 +1092,26 @@ static gcr_status launch_batch(BatchFwdState* S, const BCall& C, int dim, int th
                                        st));
   } else {
     const int grid = std::min(C.nitems, 256 * gm);
-    // LDS: the reduction rows, the unit workspaces, or (2D) the sweep records
-    // of the largest item that takes them, whichever is largest
-    const int rcap = forward_rec_cap();
-    const int rec = dim == 2 && S->rec_ng <= rcap ? S->rec_ng : 0;
-    const size_t lds =
-        std::max({(size_t)threads * 3 * sizeof(double), 64 * sizeof(UnitWS),
-                  rec ? (size_t)rec * kRecWords * sizeof(double) + kRecUnitWS * sizeof(UnitWS) : 0});
-    if (rcap == 0 && lds > 64 * 1024) return GCR_E_UNSUPPORTED;
+    // LDS: the reduction rows, the unit workspaces, or (2D) the values of the
+    // largest item filled in LDS, whichever is largest
+    const int lmax = forward_lds();
+    const int fill = dim == 2 && S->fill_lds <= (size_t)lmax ? (int)S->fill_lds : 0;
+    const size_t lds = std::max({(size_t)threads * 3 * sizeof(double), 64 * sizeof(UnitWS),
+                                 (size_t)fill});
+    if (lmax == 0 && lds > 64 * 1024) return GCR_E_UNSUPPORTED;
     if (dim == 2)
-      k_batch_forward<2><<<grid, threads, lds, st>>>(bs, C, S->d_part, S->d_counter, F, rec);
+      k_batch_forward<2><<<grid, threads, lds, st>>>(bs, C, S->d_part, S->d_counter, F, fill);
     else
-      k_batch_forward<3><<<grid, threads, lds, st>>>(bs, C, S->d_part, S->d_counter, F, rec);
+      k_batch_forward<3><<<grid, threads, lds, st>>>(bs, C, S->d_part, S->d_counter, F, fill);
   }
   GCR_HIP(hipGetLastError());
   return GCR_OK;
+}
+
+int gcr::fill_polls() {
+  // (its default: a wait of about half a second)
+  const int v = g_split_spin.load();
+  return v == kSpinMax ? 1 << 20 : v;
 }
 
 extern "C" gcr_status gcr_set_batch_spin(int32_t polls) {

@@ -156,14 +156,13 @@ PlanD plan_view(const gcr_plan* p) {
   P.blk = p->blk;
   P.unit_mem = p->unit_mem;
   P.unit_cnt = p->unit_cnt;
-  P.sorted_cell = p->sorted_cell;
-  P.sorted_pos = p->sorted_pos;
-  for (int a = 0; a < 3; ++a) P.rmax[a] = a < p->dim ? std::max(1, p->info.rmax[a]) : 0;
   P.htab = p->htab;
   P.hmask = p->hmask;
   P.nunits = p->info.nunits;
   P.unit_lev = p->unit_lev;
-  P.cgi = nullptr;
+  P.cgi = p->cgi;
+  P.cgi_stride = p->stride;
+  P.fill_fault = p->fill_fault;
   return P;
 }
 
@@ -598,6 +597,13 @@ gcr_status gcr_fill(const gcr_plan* plan, int32_t nf, double* const* fields,
   if (plan->ng == 0) return GCR_OK;
   gcr_plan* p = const_cast<gcr_plan*>(plan);
   hipStream_t st = (hipStream_t)stream;
+  if (p->schedule == kSchedAuto) {
+    // one launch in LDS where the plan fits, else every ghost waiting for
+    // its corners; plans with coupled units beyond the former: the tuner
+    if (fill_lds_fits(A.P)) return launch_fill_lds(A, p->d_lev_off, p->nlev, st);
+    if (p->info.nunits == 0)
+      return launch_fill_flow(A, p->lev_off[1], p->d_lev_off, p->nlev, fill_polls(), st);
+  }
   s = plan_weights(p, A.nf, A.kind, A.w, st);
   if (s != GCR_OK) return s;
   {

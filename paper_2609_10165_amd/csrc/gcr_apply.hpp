@@ -20,16 +20,15 @@ struct PlanD {
   const int32_t* blk;       // coupled-unit slot or -1
   const int32_t* unit_mem;  // [slot][kMaxUnit] canonical positions
   const int32_t* unit_cnt;
-  const int32_t* sorted_cell;  // ghost cells in linear-index order
-  const int32_t* sorted_pos;   // their canonical positions
-  int rmax[3];                 // largest stencil multiplier per axis
   const unsigned long long* htab;  // open-addressing table cell -> canonical position
   unsigned hmask;
   int nunits;                  // coupled units
   const int32_t* unit_lev;     // their levels (1-based)
-  // batched forward, 2D: [3][ng] the position of corner k + 1's ghost, -1 for
-  // a fluid corner, -2 for a skipped one (null elsewhere)
+  // 2D: the position of corner k + 1's ghost at cgi[k cgi_stride + p], -1 for
+  // a fluid corner, -2 for a skipped one (null where the build made none)
   const int32_t* cgi;
+  int64_t cgi_stride;
+  int32_t* fill_fault;         // set by a fill whose wait gave up (k_fill_flow)
 };
 
 constexpr unsigned long long kHashEmpty = ~0ull;
@@ -121,6 +120,13 @@ struct ForceArgs {
 };
 
 PlanD plan_view(const gcr_plan* p);
+
+// The fill in LDS, one workgroup per field (2D plans that fit), or by every
+// ghost waiting for its corners (plans without coupled units); see fill.hip.
+bool fill_lds_fits(const PlanD& P);
+gcr_status launch_fill_lds(const FillArgs& A, const int32_t* d_lev_off, int nlev, hipStream_t st);
+gcr_status launch_fill_flow(const FillArgs& A, int n1, const int32_t* d_lev_off, int nlev,
+                            int polls, hipStream_t st);
 
 void launch_fill_range(const FillArgs& A, int lo, int hi, hipStream_t st);
 void launch_weights(const PlanD& P, int bc, double* w, uint8_t* kinds, hipStream_t st);

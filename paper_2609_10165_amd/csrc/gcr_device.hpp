@@ -197,7 +197,8 @@ __device__ __forceinline__ int linear(const GridD& g, int i, int j, int k) {
 // --------------------------------------------------------------------------
 // stencil code of a ghost: sign of each normal component (sgn 0 = +1),
 // axes whose normal component is exactly zero (their displaced points carry
-// zero weight and are never read), and the multipliers r_i (<= 15).
+// zero weight and are never read), the multipliers r_i (<= 15), and from bit
+// 20 on which corners k (bit 20 + k) are ghosts.
 // --------------------------------------------------------------------------
 
 __device__ __forceinline__ uint32_t make_code(const double n[3], const int r[3], int dim) {
@@ -233,6 +234,7 @@ __device__ __forceinline__ void stencil_span(const GridD& g, uint32_t code, int 
   }
 }
 __device__ __forceinline__ uint32_t code_skip(uint32_t code) { return (code >> 3) & 7u; }
+__device__ __forceinline__ uint32_t code_ghosts(uint32_t code) { return (code >> 20) & 0xffu; }
 
 // Linear offset of stencil corner `k` (bit i set: displaced by e_i r_i along
 // axis i) from the ghost's cell.

@@ -27,6 +27,7 @@ struct InstInfo {
   int32_t nfluid;
   int32_t rmax[3];      // largest stencil multiplier per axis
   int32_t layered;      // set when the LDS layering finished the instance
+  int32_t fill_fault;   // set on the device by a fill whose wait gave up
   unsigned long long max_alpha_bits[3];
 };
 
@@ -64,6 +65,7 @@ T* palloc(size_t n) {
 struct BatchData {
   int ninst = 0;
   int64_t ncells_total = 0, nchunks = 0, nif = 0, cap = 0, ng_total = 0;
+  bool flow_order = false;           // canonical order from the whole-GPU layering
   int64_t nband = 0;                 // row segments tested by the band pass
   std::vector<Inst> inst;            // host copies
   std::vector<int64_t> if_off, g_off;  // host [ninst+1]
@@ -116,6 +118,7 @@ struct BatchData {
   uint32_t* d_code = nullptr;
   int32_t* d_level = nullptr;
   int32_t* d_blk = nullptr;
+  int32_t* d_cgi = nullptr;          // [3][cap] corner ghosts of 2D plans (null: not made)
   int32_t* d_unit_mem = nullptr;     // [ninst][kMaxUnits][kMaxUnit]
   int32_t* d_unit_cnt = nullptr;     // [ninst][kMaxUnits]
   int32_t* d_unit_lev = nullptr;     // [ninst][kMaxUnits] level of each unit
@@ -262,10 +265,10 @@ struct gcr_plan {
   uint32_t* code = nullptr;
   int32_t* level = nullptr;
   int32_t* blk = nullptr;
+  const int32_t* cgi = nullptr;     // 2D: positions of the corners' ghosts (stride `stride`)
+  int32_t* fill_fault = nullptr;
   int32_t* unit_mem = nullptr;
   int32_t* unit_cnt = nullptr;
-  int32_t* sorted_cell = nullptr;   // ghost cells in linear-index order
-  int32_t* sorted_pos = nullptr;    // their canonical positions
   int32_t* d_lev_off = nullptr;
   int32_t* unit_lev = nullptr;      // device [nunits]
   std::vector<int32_t> unit_lev_host;
@@ -331,6 +334,8 @@ void launch_scan(const int32_t* cnt, int64_t n, int64_t* excl, int32_t* list,
 // default), 2 from its first (process-wide).
 void set_batch_tiling(int mode);
 int batch_tiling();
+// Polls of a waiting fill before it gives up (gcr_set_batch_spin).
+int fill_polls();
 void set_batch_shape(int threads, int grid);
 void* plan_scratch(gcr_plan* p, int slot, size_t bytes);
 void last_build_times(float* ms);

@@ -979,7 +979,7 @@ __global__ __launch_bounds__(256) void k_deps(const Inst* __restrict__ insts, in
     }
   }
   const uint32_t code = make_code(n, r, g.dim);
-  g_code[e] = code;
+  uint32_t ghosts = 0;   // corners that are ghosts
   lev[e] = 0;   // k_levels_flow: no level yet
   int i, j, k;
   unlinear(g, c, i, j, k);
@@ -1002,7 +1002,9 @@ __global__ __launch_bounds__(256) void k_deps(const Inst* __restrict__ insts, in
       }
     }
     deps[(int64_t)(m - 1) * cap + e] = d;
+    if (d >= 0) ghosts |= 1u << m;
   }
+  g_code[e] = code | ghosts << 20;
 }
 
 // For the layerings that push along reverse edges: the number of ghosts
@@ -1143,6 +1145,7 @@ __global__ __launch_bounds__(256) void k_finalize(
     const Inst* __restrict__ insts, int ninst, const int64_t* __restrict__ g_off, int64_t cap,
     const int32_t* __restrict__ g_cell, const double* __restrict__ g_psi,
     const double* __restrict__ g_n, const uint32_t* __restrict__ g_code,
+    const int32_t* __restrict__ deps, int32_t* __restrict__ cgi,
     const int32_t* __restrict__ lev, const int32_t* __restrict__ blk_idx,
     int32_t* __restrict__ perm, const int32_t* __restrict__ hist, int32_t* __restrict__ cell,
     double* __restrict__ delta,
@@ -1185,6 +1188,14 @@ __global__ __launch_bounds__(256) void k_finalize(
         }
       }
       fl = ps < 0.0 ? 1 : 0;
+      if (cgi && g.dim == 2) {
+        // the corners' ghosts, by position (the graph's edges in this order)
+#pragma unroll
+        for (int k = 1; k < 4; ++k) {
+          const int32_t d = deps[(int64_t)(k - 1) * cap + e];
+          cgi[(int64_t)(k - 1) * cap + p] = (k & code_skip(cd)) ? -2 : d < 0 ? -1 : perm[d];
+        }
+      }
     }
   }
   // one instance in the whole workgroup: reduce there, one atomic per value
@@ -1749,7 +1760,8 @@ static gcr_status build_graph(BatchData& D, hipStream_t st, int ninst, int64_t n
     FinPart* fp = own<FinPart>(D, nfb);
     if (!fp) return GCR_E_NOMEM;
     k_finalize<<<nfb, 256, 0, st>>>(
-        D.d_inst, ninst, D.d_g_off, cap, D.d_g_cell, D.d_g_psi, D.d_g_n, D.d_g_code, D.d_lev,
+        D.d_inst, ninst, D.d_g_off, cap, D.d_g_cell, D.d_g_psi, D.d_g_n, D.d_g_code, D.d_deps,
+        hist ? nullptr : D.d_cgi, D.d_lev,
         D.d_blk_idx, D.d_perm, hist, D.d_cell, D.d_delta, D.d_nrm, D.d_psi, D.d_code, D.d_level,
         D.d_blk, D.d_info, fp);
     k_units_canonical<<<ninst, 256, 0, st>>>(D.d_perm, D.d_info, D.d_unit_mem, D.d_unit_cnt,
@@ -1959,6 +1971,7 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   D.d_code = own<uint32_t>(D, cap);
   D.d_level = own<int32_t>(D, cap);
   D.d_blk = own<int32_t>(D, cap);
+  if (any_2d) D.d_cgi = own<int32_t>(D, 3 * cap);
   D.d_listA = own<int32_t>(D, cap);
   D.d_rcnt = own<int32_t>(D, 2 * cap);   // counts, then fill pointers
   D.d_roff = own<int32_t>(D, cap + 1);
@@ -1971,7 +1984,7 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   if (!D.d_if_cell || !D.d_if_psi || !D.d_if_n || !D.d_if_flag || !D.d_blkcnt || !D.d_blkexcl ||
       !D.d_g_cell || !D.d_g_ext || !D.d_g_psi || !D.d_g_n || !D.d_g_code || !D.d_deps || !D.d_lev ||
       !D.d_blk_idx || !D.d_perm || !D.d_cell || !D.d_delta || !D.d_nrm || !D.d_psi ||
-      !D.d_code || !D.d_level || !D.d_blk)
+      !D.d_code || !D.d_level || !D.d_blk || (any_2d && !D.d_cgi))
     return GCR_E_NOMEM;
   // the third normal component of 2D ghosts stays zero
   if (any_2d) GCR_HIP(hipMemsetAsync(D.d_if_n + 2 * cap, 0, sizeof(double) * cap, st));
@@ -2040,6 +2053,7 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   std::memcpy(D.unit_lev.data(), PS.p + o_ul, 4 * (size_t)ninst * kMaxUnits);
   T.collect(std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_call)
                 .count());
+  D.flow_order = how == kLayerFlow;
   D.ng_total = D.g_off[ninst];
   for (int i = 0; i < ninst; ++i) {
     gcr_status s = status_from_err(D.info[i].err);
@@ -2078,9 +2092,10 @@ void make_plan_view(const std::shared_ptr<BatchData>& B, int i, gcr_plan* p) {
     p->code = D.d_code + o;
     p->level = D.d_level + o;
     p->blk = D.d_blk + o;
-    p->sorted_cell = D.d_g_cell + o;
-    p->sorted_pos = D.d_perm + o;
+    // (the whole-GPU layering finds the positions too late for the table)
+    p->cgi = p->dim == 2 && !D.flow_order && D.d_cgi ? D.d_cgi + o : nullptr;
   }
+  p->fill_fault = &D.d_info[i].fill_fault;
   p->unit_mem = D.d_unit_mem + (int64_t)i * kMaxUnits * kMaxUnit;
   p->unit_cnt = D.d_unit_cnt + (int64_t)i * kMaxUnits;
   p->d_lev_off = D.d_lev_off + (int64_t)i * (kMaxLevels + 1);
