@@ -135,26 +135,57 @@ def _check(code: int, what: str):
         raise GcrError(code, what)
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+# The raw handle of the current stream, as torch.cuda.current_stream() gives it
+# but without its Python stream object (1.3 us a call): PyTorch's own accessor
+# where it has one.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+def _stream(stream) -> Optional[int]:
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+        return _raw_stream(_raw_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _dptr(t: Optional[torch.Tensor], dtype=torch.float64) -> Optional[int]:
     if t is None:
         return None
-    if not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
+    if not t.is_cuda or t.dtype is not dtype or not t.is_contiguous():
         raise ValueError(f"expected a contiguous {dtype} CUDA tensor, got {t.dtype} "
                          f"on {t.device} (contiguous={t.is_contiguous()})")
     return t.data_ptr()
 
 
+# array types by length, made once (ctypes caches them too, behind a lookup)
+_PTRS = [ctypes.c_void_p * n for n in range(9)]
+_INTS = [ctypes.c_int32 * n for n in range(9)]
+
+
 def _ptr_array(ts, dtype=torch.float64):
-    arr = (ctypes.c_void_p * len(ts))()
-    for i, t in enumerate(ts):
-        arr[i] = _dptr(t, dtype)
-    return arr
+    n = len(ts)
+    return (_PTRS[n] if n < 9 else ctypes.c_void_p * n)(*[_dptr(t, dtype) for t in ts])
+
+
+def _int_array(ks):
+    n = len(ks)
+    return (_INTS[n] if n < 9 else ctypes.c_int32 * n)(*map(int, ks))
+
+
+def _kinds(bc_kind, nf):
+    a = _int_array(bc_kind)
+    if len(a) > nf:
+        raise IndexError("more boundary-condition kinds than fields")
+    return a if len(a) == nf else (ctypes.c_int32 * nf)(*a)
+
+
+def _opt_array(ts, nf, dtype):
+    """Pointers of nf tensors, None entries and missing ones null."""
+    if len(ts) > nf:
+        raise IndexError("more entries than fields")
+    return (_PTRS[nf] if nf < 9 else ctypes.c_void_p * nf)(*[_dptr(t, dtype) for t in ts])
 
 
 def make_grid(grid) -> _Grid:
@@ -299,12 +330,8 @@ class Plan:
     def fill(self, fields: Sequence[torch.Tensor], bc_kind: Sequence[int],
              bc_val: Sequence[torch.Tensor], bc_type: Optional[Sequence] = None, stream=None):
         nf = len(fields)
-        kinds = (ctypes.c_int32 * nf)(*[int(k) for k in bc_kind])
-        bt = None
-        if bc_type is not None:
-            bt = (ctypes.c_void_p * nf)()
-            for i, t in enumerate(bc_type):
-                bt[i] = _dptr(t, torch.uint8) if t is not None else None
+        kinds = _kinds(bc_kind, nf)
+        bt = None if bc_type is None else _opt_array(bc_type, nf, torch.uint8)
         _check(lib().gcr_fill(self._h, nf, _ptr_array(fields), kinds, bt, _ptr_array(bc_val),
                               _stream(stream)), "gcr_fill")
 
@@ -324,8 +351,8 @@ class Plan:
         val = torch.empty((nf, nq), dtype=torch.float64, device=dev)
         grad = torch.empty((nf, self.dim, nq), dtype=torch.float64, device=dev)
         anchor = torch.empty(nq, dtype=torch.int32, device=dev)
-        _check(lib().gcr_surface(self._h, nq, _dptr(xq), nf, _ptr_array(fields), _dptr(val),
-                                 _dptr(grad), _dptr(anchor, torch.int32), _stream(stream)),
+        _check(lib().gcr_surface(self._h, nq, _dptr(xq), nf, _ptr_array(fields), val.data_ptr(),
+                                 grad.data_ptr(), anchor.data_ptr(), _stream(stream)),
                "gcr_surface")
         return val, grad, anchor
 
@@ -351,12 +378,8 @@ class Plan:
     def fill_adjoint(self, lam: Sequence[torch.Tensor], bc_kind: Sequence[int],
                      lam_bc: Sequence[torch.Tensor], bc_type=None, stream=None):
         nf = len(lam)
-        kinds = (ctypes.c_int32 * nf)(*[int(k) for k in bc_kind])
-        bt = None
-        if bc_type is not None:
-            bt = (ctypes.c_void_p * nf)()
-            for i, t in enumerate(bc_type):
-                bt[i] = _dptr(t, torch.uint8) if t is not None else None
+        kinds = _kinds(bc_kind, nf)
+        bt = None if bc_type is None else _opt_array(bc_type, nf, torch.uint8)
         _check(lib().gcr_fill_adjoint(self._h, nf, _ptr_array(lam), kinds, bt,
                                       _ptr_array(lam_bc), _stream(stream)), "gcr_fill_adjoint")
 

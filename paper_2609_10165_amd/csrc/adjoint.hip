@@ -651,6 +651,7 @@ gcr_status gcr_forces_adjoint(const gcr_plan* plan, int64_t nq, const double* xq
 gcr_status gcr_fill_adjoint(const gcr_plan* plan, int32_t nf, double* const* lam,
                             const int32_t* bc_kind, const uint8_t* const* bc_type,
                             double* const* lam_bc, void* stream) {
+  gcr::touch_thread_storage();   // (autograd calls this from a thread of its own)
   if (!plan_ok(plan) || !nonnull(nf, (const void* const*)lam) || !bc_kind ||
       !nonnull(nf, (const void* const*)lam_bc))
     return GCR_E_ARG;

@@ -18,8 +18,6 @@
 
 namespace gcr {
 
-thread_local hipError_t g_last_hip_error = hipSuccess;
-
 // --------------------------------------------------------------------------
 // device memory pool
 // --------------------------------------------------------------------------

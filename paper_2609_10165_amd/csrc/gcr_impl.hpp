@@ -324,6 +324,7 @@ gcr_status build_update(BatchData& prev, const ShapeD& shape, bool incremental, 
                         std::shared_ptr<BatchData>* out);
 void make_plan_view(const std::shared_ptr<BatchData>& B, int i, gcr_plan* p);
 void set_profiling(int mask);
+void touch_thread_storage();   // see plan.hip; once per thread that calls the library
 int profiling_mask();   // bit 0 build stages, bit 1 batched forward
 // Exclusive scan of n counts into excl[n + 1] (total last); where list is
 // set, the indices with a nonzero count go there in order and their number
@@ -341,8 +342,6 @@ void* plan_scratch(gcr_plan* p, int slot, size_t bytes);
 void last_build_times(float* ms);
 gcr_status status_from_err(uint32_t err);
 
-extern thread_local hipError_t g_last_hip_error;
-
 }  // namespace gcr
 
 // drops the batched-forward tables of a batch (defined with the batched kernel)
@@ -350,9 +349,5 @@ void gcr_batch_release_state(const gcr_batch* b);
 
 #define GCR_HIP(x)                                  \
   do {                                              \
-    hipError_t e_ = (x);                            \
-    if (e_ != hipSuccess) {                         \
-      gcr::g_last_hip_error = e_;                   \
-      return GCR_E_HIP;                             \
-    }                                               \
+    if ((x) != hipSuccess) return GCR_E_HIP;        \
   } while (0)
