@@ -1,7 +1,8 @@
 // adjoint.hip -- adjoints of the fill, the surface evaluation and the forces.
 //
 // The fill is affine: phi_G = ws b_G + sum_k w_k phi_{P_k}.  Its adjoint runs
-// the levels in reverse.  Every value is produced by exactly one thread and
+// the levels in reverse, each ghost waiting for its readers' adjoints unless a
+// schedule is forced.  Every value is produced by exactly one thread and
 // every sum is taken in a fixed order, so results are bitwise reproducible.
 // Both adjoints pull through the transposed stencil ("support"), built on
 // the first adjoint call of a plan and kept with it: every cell that some
@@ -10,15 +11,16 @@
 //   * a ghost pulls w * lambda from the ghosts that read it (higher levels);
 //   * a non-ghost cell sums all its readers once, in its own slot;
 //   * a coupled unit solves its transposed system;
-//   * the surface adjoint groups caller points by anchor ghost (sorted
-//     buckets), forms per-corner seeds, and each slot sums the seeds of the
-//     anchors whose box holds it.
+//   * the surface adjoint groups caller points by anchor ghost, forms
+//     per-corner seeds in ascending point order, and each slot sums the seeds
+//     of the anchors whose box holds it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstring>
 
 #include "gcr_apply.hpp"
+#include "gcr_fill.hpp"
 #include "gcr_impl.hpp"
 
 namespace gcr {
@@ -225,6 +227,15 @@ static gcr_status plan_support(gcr_plan* p, hipStream_t st, SupView* out) {
   return GCR_OK;
 }
 
+// Fields that a thread takes together; one at a time where a caller passes
+// one array for several fields, whose sums then follow each other.
+static int field_group(int nf, double* const* lam) {
+  for (int f = 0; f < nf; ++f)
+    for (int g = 0; g < f; ++g)
+      if (lam[f] == lam[g]) return 1;
+  return std::min(nf, 4);
+}
+
 struct AdjArgs {
   PlanD P;
   int nf;
@@ -254,106 +265,105 @@ __device__ __forceinline__ int field_bc(const AdjArgs& A, int f, int g) {
   return A.kind[f] == 2 ? (int)A.bt[f][g] : A.kind[f];
 }
 
-// w[corner] * Lam of each fill reader of slot s, summed in entry order into
-// acc[f]; readers inside unit `skip_unit` (>= 0) are left out.
-template <int D>
-__device__ __forceinline__ void pull_readers(const AdjArgs& A, int s, int skip_unit,
-                                             double acc[kMaxFields]) {
+// the weight of corner m in reader r's relation for field f
+__device__ __forceinline__ double reader_weight(const AdjArgs& A, int f, int r, int m) {
+  return (field_bc(A, f, r) == 0 ? A.w[0] : A.w[1])[(int64_t)m * A.P.ng + r];
+}
+
+// acc + w[corner] * Lam of each fill reader of slot s in field f, in entry
+// order; readers inside unit `skip_unit` (>= 0) are left out.  With
+// `left` given, each reader's value is waited for: false once *left polls
+// have passed.
+__device__ __forceinline__ bool pull_readers(const AdjArgs& A, int s, int skip_unit, int f,
+                                             double& acc, int* left = nullptr) {
   const PlanD& P = A.P;
   const int b = A.S.off[s], e = A.S.off[s + 1];
+  const double* const L = A.Lam + (int64_t)f * P.ng;
   for (int t = b; t < e; ++t) {
     const int en = A.S.ent[t];
     if (!(en & 1)) continue;
     const int r = en >> 4, m = (en >> 1) & 7;
     if (skip_unit >= 0 && P.blk[r] == skip_unit) continue;
-    const double* const W0 = A.w[0];
-    const double* const W1 = A.w[1];
-#pragma unroll
-    for (int f = 0; f < kMaxFields; ++f) {
-      if (f >= A.nf) break;
-      const double wm = (field_bc(A, f, r) == 0 ? W0 : W1)[(int64_t)m * P.ng + r];
-      acc[f] += wm * A.Lam[(int64_t)f * P.ng + r];
+    double v;
+    if (left) {
+      unsigned long long x;
+      while ((x = poll_value(L + r)) == kFillOpen)
+        if ((*left)-- <= 0) return false;
+      v = __longlong_as_double((long long)x);
+    } else {
+      v = L[r];
     }
+    acc += reader_weight(A, f, r, m) * v;
   }
+  return true;
 }
 
-// Adjoint of coupled unit u: (I - W_int)^T mu = lam + external pulls,
-// solved in an LDS workspace (one unit per thread).
+// Adjoint of coupled unit u in field f: (I - W_int)^T mu = lam + external
+// pulls, solved in an LDS workspace (one unit per thread); false where a wait
+// gave up.
 template <int D>
-__device__ __forceinline__ void adj_unit(const AdjArgs& A, int u, UnitWS& ws) {
+__device__ __forceinline__ bool adj_unit(const AdjArgs& A, int u, int f, UnitWS& ws,
+                                         int* left = nullptr) {
   const PlanD& P = A.P;
   const int k = P.unit_cnt[u];
   for (int i = 0; i < k; ++i) {
     ws.mem[i] = P.unit_mem[u * kMaxUnit + i];
     ws.cel[i] = P.cell[ws.mem[i]];
   }
-  for (int f = 0; f < A.nf; ++f) {
-    // transposed matrix directly: M[t][i] = delta - w(i reads t)
-    for (int i = 0; i < k * k; ++i) ws.M[i] = 0.0;
-    for (int i = 0; i < k; ++i) {
-      ws.M[i * k + i] = 1.0;
-      double acc[kMaxFields];
-#pragma unroll
-      for (int g = 0; g < kMaxFields; ++g) acc[g] = 0.0;
-      pull_readers<D>(A, A.S.gslot[ws.mem[i]], u, acc);
-      double a = A.lam[f][ws.cel[i]];
-#pragma unroll
-      for (int g = 0; g < kMaxFields; ++g)
-        if (g == f) a += acc[g];
-      ws.rhs[i] = a;
-    }
-    for (int i = 0; i < k; ++i) {
-      double w[8];
-      weights_of<D>(P, ws.mem[i], field_bc(A, f, ws.mem[i]), w);
-      const uint32_t code = P.code[ws.mem[i]];
-      for (int c = 1; c < (1 << D); ++c) {
-        if (c & code_skip(code)) continue;
-        const int q = ws.cel[i] + corner_offset(P.g, code, c);
-        for (int t = 0; t < k; ++t)
-          if (ws.cel[t] == q) ws.M[t * k + i] -= w[c];
-      }
-    }
-    ws_solve(ws, k);
-    for (int i = 0; i < k; ++i) A.Lam[(int64_t)f * P.ng + ws.mem[i]] = ws.rhs[i];
+  // transposed matrix directly: M[t][i] = delta - w(i reads t)
+  for (int i = 0; i < k * k; ++i) ws.M[i] = 0.0;
+  for (int i = 0; i < k; ++i) {
+    ws.M[i * k + i] = 1.0;
+    double acc = 0.0;
+    if (!pull_readers(A, A.S.gslot[ws.mem[i]], u, f, acc, left)) return false;
+    ws.rhs[i] = A.lam[f][ws.cel[i]] + acc;
   }
+  for (int i = 0; i < k; ++i) {
+    double w[8];
+    weights_of<D>(P, ws.mem[i], field_bc(A, f, ws.mem[i]), w);
+    const uint32_t code = P.code[ws.mem[i]];
+    for (int c = 1; c < (1 << D); ++c) {
+      if (c & code_skip(code)) continue;
+      const int q = ws.cel[i] + corner_offset(P.g, code, c);
+      for (int t = 0; t < k; ++t)
+        if (ws.cel[t] == q) ws.M[t * k + i] -= w[c];
+    }
+  }
+  ws_solve(ws, k);
+  for (int i = 0; i < k; ++i) post_value(A.Lam + (int64_t)f * P.ng + ws.mem[i], ws.rhs[i]);
+  return true;
 }
 
 template <int D>
 __device__ __forceinline__ void adj_units_of_level(const AdjArgs& A, int level, UnitWS* ws,
                                                    int tid, int nthreads) {
   for (int s = tid; s < A.P.nunits; s += nthreads)
-    if (A.P.unit_lev[s] == level) adj_unit<D>(A, s, ws[tid]);
+    if (A.P.unit_lev[s] == level)
+      for (int f = 0; f < A.nf; ++f) adj_unit<D>(A, s, f, ws[tid]);
 }
 
-template <int D>
-__device__ __forceinline__ void adj_ghost(const AdjArgs& A, int p) {
+__device__ __forceinline__ void adj_ghost(const AdjArgs& A, int p, int f) {
   const PlanD& P = A.P;
-  const int blk = P.blk[p];
-  const int c = P.cell[p];
-  const int s = A.S.gslot[p];
-  if (blk >= 0) return;   // coupled units: adj_units_of_level
-  double acc[kMaxFields];
-#pragma unroll
-  for (int f = 0; f < kMaxFields; ++f) acc[f] = f < A.nf ? A.lam[f][c] : 0.0;
-  pull_readers<D>(A, s, -1, acc);
-#pragma unroll
-  for (int f = 0; f < kMaxFields; ++f)
-    if (f < A.nf) A.Lam[(int64_t)f * P.ng + p] = acc[f];
+  if (P.blk[p] >= 0) return;   // coupled units: adj_units_of_level
+  double acc = A.lam[f][P.cell[p]];
+  pull_readers(A, A.S.gslot[p], -1, f, acc);
+  A.Lam[(int64_t)f * P.ng + p] = fill_result(acc);
 }
 
-template <int D>
 __global__ __launch_bounds__(256) void k_adj_range(AdjArgs A, int lo, int hi) {
   const int p = lo + blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < hi) adj_ghost<D>(A, p);
+  if (p < hi) adj_ghost(A, p, blockIdx.y);
 }
 
+// The whole sweep by one workgroup; with `fault` given, only where it is set.
 template <int D>
 __global__ __launch_bounds__(256) void k_adj_wg(AdjArgs A, const int32_t* __restrict__ lev_off,
-                                                 int nlev) {
+                                                int nlev, const int32_t* __restrict__ fault) {
   __shared__ UnitWS ws[64];
+  if (fault && fault[0] == 0) return;   // uniform
   for (int l = nlev - 1; l >= 0; --l) {
-    for (int p = lev_off[l] + (int)threadIdx.x; p < lev_off[l + 1]; p += blockDim.x)
-      adj_ghost<D>(A, p);
+    const int lo = lev_off[l], n = (lev_off[l + 1] - lo) * A.nf;
+    for (int e = (int)threadIdx.x; e < n; e += blockDim.x) adj_ghost(A, lo + e / A.nf, e % A.nf);
     __syncthreads();
     if (A.P.nunits) {
       if (threadIdx.x < 64) adj_units_of_level<D>(A, l + 1, ws, threadIdx.x, 64);
@@ -368,9 +378,110 @@ __global__ __launch_bounds__(64) void k_adj_units(AdjArgs A, int level) {
   adj_units_of_level<D>(A, level, ws, threadIdx.x, 64);
 }
 
+// --------------------------------------------------------------------------
+// The sweep by waiting, as the fill's (k_fill_flow): k_adj_open marks every
+// ghost's adjoint open, then one thread per ghost and field, the last level
+// first, polls the adjoints of the ghosts that read it and stores its own.
+// Readers lie in later levels, so workgroups wait for earlier ones; their
+// entries and weights are gathered eight at a time before the first poll, and
+// summed in entry order.  A coupled unit is one thread's, four to a workgroup,
+// and those workgroups lead the grid: they wait for later ones, but fill a
+// corner of the chip at most.  Waits are bounded as the fill's are, and
+// k_adj_wg sweeps again after one that gave up.
+// Bound by the chain of levels.  160^3 spherical-harmonic body, four fields,
+// ten levels: 24 us for the three launches against 90 for ten.
+// --------------------------------------------------------------------------
+constexpr int kAdjUnitsPerBlock = 4;
+
+__global__ __launch_bounds__(256) void k_adj_open(double* __restrict__ Lam, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) Lam[i] = __longlong_as_double((long long)kFillOpen);
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void k_adj_flow(AdjArgs A, int unit_blocks, int polls) {
+  __shared__ UnitWS ws[kAdjUnitsPerBlock];
+  const PlanD& P = A.P;
+  const int f = blockIdx.y;
+  if ((int)blockIdx.x < unit_blocks) {
+    const int wave = threadIdx.x >> 6, u = blockIdx.x * kAdjUnitsPerBlock + wave;
+    int left = polls;
+    if ((threadIdx.x & 63) == 0 && u < P.nunits && !adj_unit<D>(A, u, f, ws[wave], &left))
+      atomicOr(P.fill_fault, 1);
+    return;
+  }
+  // (past the first ghost: that one again)
+  const int p = max(P.ng - 1 - (int)((blockIdx.x - unit_blocks) * 256 + threadIdx.x), 0);
+  double* const L = A.Lam + (int64_t)f * P.ng;
+  const int s = A.S.gslot[p];
+  bool done = P.blk[p] >= 0;
+  double acc = A.lam[f][P.cell[p]];
+  int t = A.S.off[s];
+  const int e = A.S.off[s + 1];
+  double w[8], val[8];
+  int r[8];
+  uint32_t use = 0, open = 0;
+  bool fetch = true;
+  for (int left = polls;; --left) {
+    if (!done) {
+      if (fetch) {
+        use = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int en = t + j < e ? A.S.ent[t + j] : 0;
+          r[j] = en >> 4;
+          use |= (uint32_t)(en & 1) << j;
+          // (an entry that is not read: any weight of ghost r)
+          w[j] = reader_weight(A, f, r[j], (en >> 1) & ((1 << D) - 1));
+        }
+        open = use;
+        fetch = false;
+      }
+      unsigned long long x[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[j] = (open >> j) & 1u ? poll_value(L + r[j]) : kFillOpen;
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (x[j] != kFillOpen) {
+          val[j] = __longlong_as_double((long long)x[j]);
+          open &= ~(1u << j);
+        }
+      if (!open) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if ((use >> j) & 1u) acc += w[j] * val[j];
+        t += 8;
+        fetch = true;
+        if (t >= e) {
+          post_value(L + p, acc);
+          done = true;
+        }
+      }
+    }
+    if (__ballot(!done) == 0ull) return;
+    if (left <= 0) {
+      if (!done) atomicOr(P.fill_fault, 1);
+      return;
+    }
+  }
+}
+
+template <int D>
+static void adj_flow(const AdjArgs& A, const int32_t* d_lev_off, int nlev, hipStream_t st) {
+  const int64_t n = (int64_t)A.nf * A.P.ng;
+  const int ub = (A.P.nunits + kAdjUnitsPerBlock - 1) / kAdjUnitsPerBlock;
+  k_adj_open<<<nblk(n, 256), 256, 0, st>>>(A.Lam, n);
+  k_adj_flow<D><<<dim3((unsigned)ub + nblk(A.P.ng, 256), (unsigned)A.nf), 256, 0, st>>>(
+      A, ub, fill_polls());
+  k_adj_wg<D><<<1, 256, 0, st>>>(A, d_lev_off, nlev, A.P.fill_fault);
+}
+
 // Per slot: a ghost's own cell gives its boundary-data sensitivity and is
 // zeroed (the fill overwrites it); a non-ghost cell sums its readers once.
-template <int D>
+// Eight entries are read at a time and NF fields together (field_group); bound
+// by the scattered cells it reads and writes (160^3, four fields, 25,000
+// slots: 18 us, 100,000 cells of distinct lines).
+template <int D, int NF>
 __global__ __launch_bounds__(256) void k_adj_support(AdjArgs A) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= A.S.bound || s >= A.S.nslot[0]) return;
@@ -378,23 +489,71 @@ __global__ __launch_bounds__(256) void k_adj_support(AdjArgs A) {
   const int q = A.S.cell[s];
   const int p = A.S.ghost[s];
   if (p >= 0) {
-    for (int f = 0; f < A.nf; ++f) {
-      const double w0 = (field_bc(A, f, p) == 0 ? A.w[0] : A.w[1])[p];
-      A.lam_bc[f][p] = w0 * A.Lam[(int64_t)f * P.ng + p];
-      A.lam[f][q] = 0.0;
+    for (int f0 = 0; f0 < A.nf; f0 += NF) {
+      double v[NF];
+#pragma unroll
+      for (int g = 0; g < NF; ++g) {
+        const int f = min(f0 + g, A.nf - 1);
+        v[g] = reader_weight(A, f, p, 0) * A.Lam[(int64_t)f * P.ng + p];
+      }
+#pragma unroll
+      for (int g = 0; g < NF; ++g)
+        if (f0 + g < A.nf) {
+          A.lam_bc[f0 + g][p] = v[g];
+          A.lam[f0 + g][q] = 0.0;
+        }
     }
     return;
   }
-  bool any = false;
-  for (int t = A.S.off[s]; t < A.S.off[s + 1]; ++t) any |= (A.S.ent[t] & 1) != 0;
-  if (!any) return;
-  double acc[kMaxFields];
+  const int b = A.S.off[s], e = A.S.off[s + 1];
+  for (int f0 = 0; f0 < A.nf; f0 += NF) {
+    double acc[NF], was[NF];
 #pragma unroll
-  for (int f = 0; f < kMaxFields; ++f) acc[f] = 0.0;
-  pull_readers<D>(A, (int)s, -1, acc);
+    for (int g = 0; g < NF; ++g) {
+      acc[g] = 0.0;
+      was[g] = A.lam[min(f0 + g, A.nf - 1)][q];
+    }
+    bool any = false;
+    for (int t = b; t < e; t += 8) {
+      int r[8], m[8];
+      uint32_t use = 0;
 #pragma unroll
-  for (int f = 0; f < kMaxFields; ++f)
-    if (f < A.nf) A.lam[f][q] += acc[f];
+      for (int j = 0; j < 8; ++j) {
+        const int en = t + j < e ? A.S.ent[t + j] : 0;
+        r[j] = en >> 4;
+        m[j] = (en >> 1) & ((1 << D) - 1);
+        use |= (uint32_t)(en & 1) << j;
+      }
+      any |= use != 0;
+#pragma unroll
+      for (int g = 0; g < NF; ++g) {
+        const int f = min(f0 + g, A.nf - 1);
+        double w[8], v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          w[j] = reader_weight(A, f, r[j], m[j]);
+          v[j] = A.Lam[(int64_t)f * P.ng + r[j]];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if ((use >> j) & 1u) acc[g] += w[j] * v[j];
+      }
+    }
+    if (!any) return;
+#pragma unroll
+    for (int g = 0; g < NF; ++g)
+      if (f0 + g < A.nf) A.lam[f0 + g][q] = was[g] + acc[g];
+  }
+}
+
+template <int D>
+static void adj_support(const AdjArgs& A, hipStream_t st) {
+  const unsigned nb = nblk(A.S.bound, 256);
+  const int n = field_group(A.nf, A.lam);
+  if (n == 1) k_adj_support<D, 1><<<nb, 256, 0, st>>>(A);
+  else if (n == 2) k_adj_support<D, 2><<<nb, 256, 0, st>>>(A);
+  else if (n == 3) k_adj_support<D, 3><<<nb, 256, 0, st>>>(A);
+  else k_adj_support<D, 4><<<nb, 256, 0, st>>>(A);
 }
 
 // --------------------------------------------------------------------------
@@ -409,10 +568,12 @@ struct SurfAdjArgs {
   const double* gval;    // [nf][nq] or null
   const double* ggrad;   // [nf][dim][nq] or null
   double* lam[kMaxFields];
+  const double *nrm, *wq, *gF;   // the force's instead of gval, ggrad, or null
+  double mu;
   int32_t* anchor;       // [nq]
-  int32_t* cnt;          // [ng+1]
-  int32_t* off;          // [ng+1]
-  int32_t* fillc;        // [ng]
+  int32_t* rank;         // [nq] place of the point among its anchor's
+  int32_t* cnt;          // [ng + 1] points per anchor; [ng]: places given out
+  int32_t* off;          // [ng] first place of an anchor's points
   int32_t* bucket;       // [nq]
   double* seed;          // [nf][8][ng]
   SupView Sp;
@@ -421,11 +582,6 @@ struct SurfAdjArgs {
 __global__ void k_zero_i32(int32_t* __restrict__ a, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) a[i] = 0;
-}
-
-__global__ void k_zero_f64(double* __restrict__ a, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) a[i] = 0.0;
 }
 
 template <int D>
@@ -441,10 +597,28 @@ __global__ __launch_bounds__(256) void k_sadj_anchor(SurfAdjArgs S) {
   const int g = find_anchor_group<D, NL>(S.P, x, sub, active);
   if (!active || sub != 0) return;
   S.anchor[q] = g;
-  if (g >= 0) atomicAdd(&S.cnt[g], 1);
+  if (g >= 0) S.rank[q] = atomicAdd(&S.cnt[g], 1);
 }
 
-// exclusive scan of the per-ghost counts (one workgroup)
+// Places for each anchor's points.  Which anchor's come first does not matter,
+// so a wave takes its ghosts' total from one counter; a scan over all ghosts
+// by one workgroup took 9 us at 7,000.
+__global__ __launch_bounds__(256) void k_sadj_place(SurfAdjArgs S) {
+  const int g = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63;
+  const int c = g < S.P.ng ? S.cnt[g] : 0;
+  int sum = c;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(sum, d);
+    if (lane >= d) sum += o;
+  }
+  int base = 0;
+  if (lane == 63 && sum) base = atomicAdd(&S.cnt[S.P.ng], sum);
+  base = __shfl(base, 63);
+  if (g < S.P.ng) S.off[g] = base + sum - c;
+}
+
+// exclusive scan of n counts (one workgroup)
 __global__ __launch_bounds__(1024) void k_sadj_scan(const int32_t* __restrict__ cnt, int n,
                                                     int32_t* __restrict__ off) {
   __shared__ int64_t sh[17];
@@ -455,150 +629,188 @@ __global__ __launch_bounds__(256) void k_sadj_bucket(SurfAdjArgs S) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= S.nq) return;
   const int g = S.anchor[q];
-  if (g >= 0) S.bucket[S.off[g] + atomicAdd(&S.fillc[g], 1)] = (int32_t)q;
+  if (g >= 0) S.bucket[S.off[g] + S.rank[q]] = (int32_t)q;
 }
 
-// per anchor: sort its bucket (ascending point index), then the seeds
-// seed[f][corner][g] = sum_q coef(corner, x_q) . (gval, ggrad)
-template <int D>
+// Cotangents of field f's value and gradient at point q: the caller's, or
+// those of J = gF . F, where per point d J / d p = -w (gF . n) and
+// d J / d (d u_i / d x_j) = mu w (gF_i n_j + gF_j n_i); p is field 0.
+template <int D, bool FORCE>
+__device__ __forceinline__ void cotangents(const SurfAdjArgs& S, int f, int64_t q, double& gv,
+                                           double gg[3]) {
+  gv = 0.0;
+  gg[0] = gg[1] = gg[2] = 0.0;
+  if (!FORCE) {
+    if (S.gval) gv = S.gval[(int64_t)f * S.nq + q];
+    if (S.ggrad)
+#pragma unroll
+      for (int a = 0; a < D; ++a) gg[a] = S.ggrad[((int64_t)f * D + a) * S.nq + q];
+    return;
+  }
+  double n[3], g[3];
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    n[a] = S.nrm[a * S.nq + q];
+    g[a] = S.gF[a];
+  }
+  const double w = S.wq[q];
+  if (f == 0) {
+    double gn = 0.0;
+#pragma unroll
+    for (int a = 0; a < D; ++a) gn += g[a] * n[a];
+    gv = -w * gn;
+    return;
+  }
+  double gi = g[0], ni = n[0];
+#pragma unroll
+  for (int a = 1; a < D; ++a)
+    if (f == 1 + a) {
+      gi = g[a];
+      ni = n[a];
+    }
+#pragma unroll
+  for (int j = 0; j < D; ++j) gg[j] = S.mu * w * (gi * n[j] + g[j] * ni);
+}
+
+// per anchor and field, over its points in ascending index: the seeds
+// seed[f][corner][g] = sum_q coef(corner, x_q) . (gval, ggrad).  The next
+// index is searched among the anchor's few points; nothing is moved, so the
+// fields' threads share the bucket.
+template <int D, bool FORCE>
 __global__ __launch_bounds__(256) void k_sadj_seed(SurfAdjArgs S) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
+  const int g = blockIdx.x * blockDim.x + threadIdx.x, f = blockIdx.y;
   const PlanD& P = S.P;
   if (g >= P.ng) return;
-  const int b = S.off[g], e = S.off[g + 1];
-  if (b == e) return;
-  for (int i = b + 1; i < e; ++i) {
-    int v = S.bucket[i], j = i - 1;
-    while (j >= b && S.bucket[j] > v) {
-      S.bucket[j + 1] = S.bucket[j];
-      --j;
-    }
-    S.bucket[j + 1] = v;
-  }
+  const int n = S.cnt[g];
+  if (n == 0) return;
+  const int32_t* const bucket = S.bucket + S.off[g];
   const uint32_t code = P.code[g];
   int i, j, k;
   unlinear(P.g, P.cell[g], i, j, k);
   const int ijk[3] = {i, j, k};
   double X[3];
   stencil_span(P.g, code, P.cell[g], X);
-  // one field at a time keeps the 2^D corner sums in registers
-  for (int f = 0; f < S.nf; ++f) {
-    double acc[8];
+  double acc[8];
 #pragma unroll
-    for (int m = 0; m < 8; ++m) acc[m] = 0.0;
-    for (int t = b; t < e; ++t) {
-      const int64_t q = S.bucket[t];
-      double rel[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-      for (int a = 0; a < D; ++a) rel[a] = S.xq[a * S.nq + q] - centre(P.g, a, ijk[a]);
-      const double gv = S.gval ? S.gval[(int64_t)f * S.nq + q] : 0.0;
-      double gg[3] = {0.0, 0.0, 0.0};
-      if (S.ggrad)
-#pragma unroll
-        for (int a = 0; a < D; ++a) gg[a] = S.ggrad[((int64_t)f * D + a) * S.nq + q];
-#pragma unroll
-      for (int m = 0; m < (1 << D); ++m) {
-        double cv, cg[3];
-        box_coeffs<D>(rel, X, m, cv, cg);
-        double s = cv * gv;
-#pragma unroll
-        for (int a = 0; a < D; ++a) s += cg[a] * gg[a];
-        acc[m] += s;
-      }
+  for (int m = 0; m < 8; ++m) acc[m] = 0.0;
+  int32_t last = -1;
+  for (int t = 0; t < n; ++t) {
+    int32_t q = 0x7fffffff;
+    for (int u = 0; u < n; ++u) {
+      const int32_t c = bucket[u];
+      if (c > last && c < q) q = c;
     }
+    last = q;
+    double rel[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-    for (int m = 0; m < (1 << D); ++m) S.seed[((int64_t)f * 8 + m) * P.ng + g] = acc[m];
+    for (int a = 0; a < D; ++a) rel[a] = S.xq[a * S.nq + q] - centre(P.g, a, ijk[a]);
+    double gv, gg[3];
+    cotangents<D, FORCE>(S, f, q, gv, gg);
+#pragma unroll
+    for (int m = 0; m < (1 << D); ++m) {
+      double cv, cg[3];
+      box_coeffs<D>(rel, X, m, cv, cg);
+      double s = cv * gv;
+#pragma unroll
+      for (int a = 0; a < D; ++a) s += cg[a] * gg[a];
+      acc[m] += s;
+    }
   }
+#pragma unroll
+  for (int m = 0; m < (1 << D); ++m) S.seed[((int64_t)f * 8 + m) * P.ng + g] = acc[m];
 }
 
 // each slot: the seeds of every anchor whose box holds its cell, in entry
-// order (ghosts that anchor no point have no seeds)
+// order (ghosts that anchor no point have no seeds).  Bound by the chain
+// entry -> count -> seed: eight entries at a time, NF fields together
+// (field_group).  160^3, four fields, 2,048 points: 9.4 us, entry by entry 17.
+template <int NF>
 __global__ __launch_bounds__(256) void k_sadj_pull(SurfAdjArgs S) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= S.Sp.bound || s >= S.Sp.nslot[0]) return;
-  const int ng = S.P.ng;
-  double acc[kMaxFields];
-#pragma unroll
-  for (int f = 0; f < kMaxFields; ++f) acc[f] = 0.0;
-  bool any = false;
-  for (int t = S.Sp.off[s]; t < S.Sp.off[s + 1]; ++t) {
-    const int en = S.Sp.ent[t];
-    const int r = en >> 4, m = (en >> 1) & 7;
-    if (S.off[r] == S.off[r + 1]) continue;
-    any = true;
-#pragma unroll
-    for (int f = 0; f < kMaxFields; ++f)
-      if (f < S.nf) acc[f] += S.seed[((int64_t)f * 8 + m) * ng + r];
-  }
-  if (!any) return;
+  const int64_t ng = S.P.ng;
+  const int b = S.Sp.off[s], e = S.Sp.off[s + 1];
   const int q = S.Sp.cell[s];
+  for (int f0 = 0; f0 < S.nf; f0 += NF) {
+    double acc[NF], was[NF];
 #pragma unroll
-  for (int f = 0; f < kMaxFields; ++f)
-    if (f < S.nf) S.lam[f][q] += acc[f];
-}
-
-// forces adjoint: J = gF . F gives, per point, d J / d p = -w (gF . n) and
-// d J / d (d u_i / d x_j) = mu w (gF_i n_j + gF_j n_i)
-__global__ void k_forces_seed(int64_t nq, int dim, const double* __restrict__ nrm,
-                              const double* __restrict__ wq, double mu,
-                              const double* __restrict__ gF, double* __restrict__ gval,
-                              double* __restrict__ ggrad) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nq) return;
-  double n[3] = {0.0, 0.0, 0.0}, g[3] = {0.0, 0.0, 0.0};
-  for (int a = 0; a < dim; ++a) {
-    n[a] = nrm[a * nq + q];
-    g[a] = gF[a];
+    for (int g = 0; g < NF; ++g) {
+      acc[g] = 0.0;
+      was[g] = S.lam[min(f0 + g, S.nf - 1)][q];
+    }
+    bool any = false;
+    for (int t = b; t < e; t += 8) {
+      int r[8], m[8], c[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int en = t + j < e ? S.Sp.ent[t + j] : -1;
+        r[j] = max(en >> 4, 0);
+        m[j] = (en >> 1) & 7;
+        c[j] = en < 0 ? -1 : 0;
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) c[j] = c[j] < 0 ? 0 : S.cnt[r[j]];
+#pragma unroll
+      for (int g = 0; g < NF; ++g) {
+        const int f = min(f0 + g, S.nf - 1);
+        double v[8];   // (of no meaning where an anchor has no points)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = S.seed[((int64_t)f * 8 + m[j]) * ng + r[j]];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (c[j] != 0) {
+            any = true;
+            acc[g] += v[j];
+          }
+      }
+    }
+    if (!any) return;
+#pragma unroll
+    for (int g = 0; g < NF; ++g)
+      if (f0 + g < S.nf) S.lam[f0 + g][q] = was[g] + acc[g];
   }
-  const double w = wq[q];
-  double gn = 0.0;
-  for (int a = 0; a < dim; ++a) gn += g[a] * n[a];
-  gval[q] = -w * gn;
-  for (int i = 0; i < dim; ++i) gval[(int64_t)(1 + i) * nq + q] = 0.0;
-  for (int j = 0; j < dim; ++j) ggrad[(int64_t)j * nq + q] = 0.0;
-  for (int i = 0; i < dim; ++i)
-    for (int j = 0; j < dim; ++j)
-      ggrad[((int64_t)(1 + i) * dim + j) * nq + q] = mu * w * (g[i] * n[j] + g[j] * n[i]);
 }
 
-static gcr_status surface_adjoint_impl(gcr_plan* p, int64_t nq, const double* xq, int nf,
-                                       const double* gval, const double* ggrad,
-                                       double* const* lam, hipStream_t st) {
-  const int64_t ng = p->ng;
+// S: fields, points and cotangents set
+static gcr_status surface_adjoint_impl(gcr_plan* p, SurfAdjArgs S, double* const* lam,
+                                       hipStream_t st) {
+  const int64_t ng = p->ng, nq = S.nq;
   if (nq == 0 || ng == 0) return GCR_OK;
-  SurfAdjArgs S;
-  std::memset(&S, 0, sizeof(S));
   S.P = plan_view(p);
-  S.nf = nf;
-  S.nq = nq;
-  S.xq = xq;
-  S.gval = gval;
-  S.ggrad = ggrad;
-  for (int f = 0; f < nf; ++f) S.lam[f] = lam[f];
+  for (int f = 0; f < S.nf; ++f) S.lam[f] = lam[f];
   {
     const gcr_status ss = plan_support(p, st, &S.Sp);
     if (ss != GCR_OK) return ss;
   }
-  char* ib = (char*)plan_scratch(p, 1, sizeof(int32_t) * (2 * nq + 3 * (ng + 1)));
-  double* sb = (double*)plan_scratch(p, 2, sizeof(double) * (size_t)nf * 8 * ng);
-  if (!ib || !sb) return GCR_E_NOMEM;
-  S.anchor = (int32_t*)ib;
-  S.bucket = S.anchor + nq;
+  int32_t* ib = (int32_t*)plan_scratch(p, 1, sizeof(int32_t) * (3 * nq + 2 * (ng + 1)));
+  S.seed = (double*)plan_scratch(p, 2, sizeof(double) * (size_t)S.nf * 8 * ng);
+  if (!ib || !S.seed) return GCR_E_NOMEM;
+  S.anchor = ib;
+  S.rank = S.anchor + nq;
+  S.bucket = S.rank + nq;
   S.cnt = S.bucket + nq;
   S.off = S.cnt + (ng + 1);
-  S.fillc = S.off + (ng + 1);
-  S.seed = sb;
   k_zero_i32<<<nblk(ng + 1, 256), 256, 0, st>>>(S.cnt, ng + 1);
-  k_zero_i32<<<nblk(ng + 1, 256), 256, 0, st>>>(S.fillc, ng + 1);
   const int D = p->dim;
   const unsigned nba = (unsigned)force_blocks(D, nq);
   if (D == 2) k_sadj_anchor<2><<<nba, 256, 0, st>>>(S);
   else k_sadj_anchor<3><<<nba, 256, 0, st>>>(S);
-  k_sadj_scan<<<1, 1024, 0, st>>>(S.cnt, (int)ng, S.off);
+  k_sadj_place<<<nblk(ng, 256), 256, 0, st>>>(S);
   k_sadj_bucket<<<nblk(nq, 256), 256, 0, st>>>(S);
-  if (D == 2) k_sadj_seed<2><<<nblk(ng, 256), 256, 0, st>>>(S);
-  else k_sadj_seed<3><<<nblk(ng, 256), 256, 0, st>>>(S);
-  k_sadj_pull<<<nblk(S.Sp.bound, 256), 256, 0, st>>>(S);
+  const dim3 gs(nblk(ng, 256), (unsigned)S.nf);
+  if (D == 2) {
+    if (S.gF) k_sadj_seed<2, true><<<gs, 256, 0, st>>>(S);
+    else k_sadj_seed<2, false><<<gs, 256, 0, st>>>(S);
+  } else {
+    if (S.gF) k_sadj_seed<3, true><<<gs, 256, 0, st>>>(S);
+    else k_sadj_seed<3, false><<<gs, 256, 0, st>>>(S);
+  }
+  const unsigned nbp = nblk(S.Sp.bound, 256);
+  const int n = field_group(S.nf, S.lam);
+  if (n == 1) k_sadj_pull<1><<<nbp, 256, 0, st>>>(S);
+  else if (n == 2) k_sadj_pull<2><<<nbp, 256, 0, st>>>(S);
+  else if (n == 3) k_sadj_pull<3><<<nbp, 256, 0, st>>>(S);
+  else k_sadj_pull<4><<<nbp, 256, 0, st>>>(S);
   GCR_HIP(hipGetLastError());
   return GCR_OK;
 }
@@ -622,8 +834,14 @@ gcr_status gcr_surface_adjoint(const gcr_plan* plan, int64_t nq, const double* x
   if (!plan_ok(plan) || nq < 0 || (nq > 0 && !xq) || !nonnull(nf, (const void* const*)lam))
     return GCR_E_ARG;
   if (nq >= (int64_t(1) << 31)) return GCR_E_UNSUPPORTED;
-  return surface_adjoint_impl(const_cast<gcr_plan*>(plan), nq, xq, nf, gval, ggrad, lam,
-                              (hipStream_t)stream);
+  SurfAdjArgs S;
+  std::memset(&S, 0, sizeof(S));
+  S.nf = nf;
+  S.nq = nq;
+  S.xq = xq;
+  S.gval = gval;
+  S.ggrad = ggrad;
+  return surface_adjoint_impl(const_cast<gcr_plan*>(plan), S, lam, (hipStream_t)stream);
 }
 
 gcr_status gcr_forces_adjoint(const gcr_plan* plan, int64_t nq, const double* xq,
@@ -637,15 +855,17 @@ gcr_status gcr_forces_adjoint(const gcr_plan* plan, int64_t nq, const double* xq
   if (nq == 0) return GCR_OK;
   if (nq >= (int64_t(1) << 31)) return GCR_E_UNSUPPORTED;
   gcr_plan* p = const_cast<gcr_plan*>(plan);
-  hipStream_t st = (hipStream_t)stream;
-  double* buf = (double*)plan_scratch(p, 3, sizeof(double) * (size_t)nq * (1 + d) * (1 + d));
-  if (!buf) return GCR_E_NOMEM;
-  double* gval = buf;
-  double* ggrad = buf + (size_t)(1 + d) * nq;
-  k_forces_seed<<<nblk(nq, 256), 256, 0, st>>>(nq, d, nrm, wq, mu, gF, gval, ggrad);
-  GCR_HIP(hipGetLastError());
+  SurfAdjArgs S;
+  std::memset(&S, 0, sizeof(S));
+  S.nf = 1 + d;
+  S.nq = nq;
+  S.xq = xq;
+  S.nrm = nrm;
+  S.wq = wq;
+  S.gF = gF;
+  S.mu = mu;
   double* lam[4] = {lam_p, lam_u[0], lam_u[1], d == 3 ? lam_u[2] : nullptr};
-  return surface_adjoint_impl(p, nq, xq, 1 + d, gval, ggrad, lam, st);
+  return surface_adjoint_impl(p, S, lam, (hipStream_t)stream);
 }
 
 gcr_status gcr_fill_adjoint(const gcr_plan* plan, int32_t nf, double* const* lam,
@@ -681,17 +901,18 @@ gcr_status gcr_fill_adjoint(const gcr_plan* plan, int32_t nf, double* const* lam
     const gcr_status ss = plan_support(p, st, &A.S);
     if (ss != GCR_OK) return ss;
   }
-  // the same schedule family as the fill: one workgroup, or one launch per level
-  const bool wg = (p->schedule == kSchedWorkgroup) ||
-                  (p->schedule == kSchedAuto && p->tuned == kSchedWorkgroup);
-  if (wg) {
-    if (p->dim == 2) k_adj_wg<2><<<1, 256, 0, st>>>(A, p->d_lev_off, p->nlev);
-    else k_adj_wg<3><<<1, 256, 0, st>>>(A, p->d_lev_off, p->nlev);
+  // as the fill: by waiting, or a forced schedule's one workgroup or launch
+  // per level
+  if (p->schedule == kSchedAuto) {
+    if (p->dim == 2) adj_flow<2>(A, p->d_lev_off, p->nlev, st);
+    else adj_flow<3>(A, p->d_lev_off, p->nlev, st);
+  } else if (p->schedule == kSchedWorkgroup) {
+    if (p->dim == 2) k_adj_wg<2><<<1, 256, 0, st>>>(A, p->d_lev_off, p->nlev, nullptr);
+    else k_adj_wg<3><<<1, 256, 0, st>>>(A, p->d_lev_off, p->nlev, nullptr);
   } else {
     for (int l = p->nlev - 1; l >= 0; --l) {
       const int lo = p->lev_off[l], hi = p->lev_off[l + 1];
-      if (p->dim == 2) k_adj_range<2><<<nblk(hi - lo, 256), 256, 0, st>>>(A, lo, hi);
-      else k_adj_range<3><<<nblk(hi - lo, 256), 256, 0, st>>>(A, lo, hi);
+      k_adj_range<<<dim3(nblk(hi - lo, 256), (unsigned)nf), 256, 0, st>>>(A, lo, hi);
       for (int32_t ul : p->unit_lev_host)
         if (ul == l + 1) {
           if (p->dim == 2) k_adj_units<2><<<1, 64, 0, st>>>(A, l + 1);
@@ -700,8 +921,8 @@ gcr_status gcr_fill_adjoint(const gcr_plan* plan, int32_t nf, double* const* lam
         }
     }
   }
-  if (p->dim == 2) k_adj_support<2><<<nblk(A.S.bound, 256), 256, 0, st>>>(A);
-  else k_adj_support<3><<<nblk(A.S.bound, 256), 256, 0, st>>>(A);
+  if (p->dim == 2) adj_support<2>(A, st);
+  else adj_support<3>(A, st);
   GCR_HIP(hipGetLastError());
   return GCR_OK;
 }

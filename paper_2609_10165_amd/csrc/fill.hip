@@ -98,11 +98,7 @@ __global__ __launch_bounds__(256) void k_fill_flow(FillArgs A, int n1, int polls
       unsigned long long x[8];
 #pragma unroll
       for (int k = 1; k < (1 << D); ++k)
-        x[k] = (open >> k) & 1u
-                   ? __hip_atomic_load(reinterpret_cast<const unsigned long long*>(
-                                           F + c + corner_offset(P.g, code, k)),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                   : kFillOpen;
+        x[k] = (open >> k) & 1u ? poll_value(F + c + corner_offset(P.g, code, k)) : kFillOpen;
 #pragma unroll
       for (int k = 1; k < (1 << D); ++k)
         if (x[k] != kFillOpen) {
@@ -114,9 +110,7 @@ __global__ __launch_bounds__(256) void k_fill_flow(FillArgs A, int n1, int polls
 #pragma unroll
         for (int k = 1; k < (1 << D); ++k)
           if (!(k & skip)) v += w[k] * val[k];
-        __hip_atomic_store(reinterpret_cast<unsigned long long*>(F + c),
-                           (unsigned long long)__double_as_longlong(fill_result(v)),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        post_value(F + c, v);
         done = true;
       }
     }

@@ -209,6 +209,17 @@ __device__ __forceinline__ double fill_result(double v) {
                                                          : v;
 }
 
+// a value that another workgroup may be about to post, and its posting
+__device__ __forceinline__ unsigned long long poll_value(const double* p) {
+  return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void post_value(double* p, double v) {
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p),
+                     (unsigned long long)__double_as_longlong(fill_result(v)), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // --------------------------------------------------------------------------
 // The fill of one field of a 2D plan by one workgroup, in LDS.
 //
