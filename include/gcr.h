@@ -387,7 +387,7 @@ gcr_status gcr_set_profiling(int32_t mask);
 gcr_status gcr_last_build_times(float* ms);
 /* With bit 1 set, each gcr_batch_forward records HIP events around
  * its two kernels (the surface-point anchor search and the persistent fill
- * + force launch).  This call waits for the recorded work, writes the mean
+ * + force launch; the waiting fill's anchors count with its launches).  This call waits for the recorded work, writes the mean
  * ms of each over the calls since the last query to out[0] and out[1] and
  * their number to out[2] (-1, -1, 0 if none), and clears the record. */
 gcr_status gcr_forward_times(float* out);
@@ -400,14 +400,17 @@ gcr_status gcr_forward_times(float* out);
  * the tiles' closures costs about as much as one sweep, so:
  *   mode 0  always the level-by-level sweep;
  *   mode 1  tiles from a batch's second forward call on (the default: a
- *           batch forwarded once never pays for them);
+ *           batch forwarded once never pays for them); a 3D batch without
+ *           coupled units instead fills by ghosts waiting for their corners,
+ *           from the first call, with the same values;
  *   mode 2  tiles from the first call.
  * Batches with coupled units, graphs deeper than 128 levels or an instance
  * of more than about 980,000 ghosts, and any batch whose tile closures would
  * not fit, take the sweep.  Applies to batches not yet set up. */
 gcr_status gcr_set_batch_tiling(int32_t mode);
 /* Which fill a batch's forward calls use: *state = -1 the level-by-level
- * sweep, 0 not decided yet (no forward call so far), 1 the tiled fill,
+ * sweep (or, 3D at the default mode, the waiting fill), 0 not decided yet
+ * (no forward call so far), 1 the tiled fill,
  * 2 the sweep after the tile closures did not fit.  Synchronises the
  * device (a diagnostic, not for the hot path). */
 gcr_status gcr_batch_tiled(const gcr_batch* batch, int32_t* state);
@@ -416,7 +419,7 @@ gcr_status gcr_batch_tiled(const gcr_batch* batch, int32_t* state);
  * *threads per workgroup and *grid, > 0 one workgroup per (instance, field)
  * item times grid (k_batch_forward), < 0 the split sweep with -grid
  * workgroups per instance (k_batch_split); both 0 before the first forward
- * call.  Host only, no synchronisation. */
+ * call and for the waiting fill, which has no shape to pick.  Host only, no synchronisation. */
 gcr_status gcr_batch_shape(const gcr_batch* batch, int32_t* threads, int32_t* grid);
 
 /* Launch shape of the batched forward's level sweep (Sec. 3.2 fill, one

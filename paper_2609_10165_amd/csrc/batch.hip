@@ -55,7 +55,30 @@ struct BCall {
   double* const* sval;           // [ninst*nf] surface values [nq_i] (null: none)
   double* const* sgrad;          // [ninst*nf] surface gradients [dim][nq_i] (null: none)
   const int32_t* tile_flag;      // tiled fill ran when set and zero: items skip the levels
+  const int32_t* soff;           // [ninst + 1] first chunk of kSurfChunk points of each instance
 };
+
+// Fill by waiting over a whole batch: first workgroup of each instance in the
+// launch that opens its ghosts and in the one that waits, one field's worth.
+struct FlowTab {
+  const int32_t* open;   // [ninst + 1]
+  const int32_t* wait;   // [ninst + 1]
+  int nopen, nwait;
+};
+constexpr int kSurfChunk = 256;
+
+// The instance of workgroup b: the last whose first workgroup is not past it
+// (a wave compares 64 entries at once).
+__device__ __forceinline__ int inst_of_block(const int32_t* __restrict__ off, int n, int b) {
+  const int lane = threadIdx.x & 63;
+  int i = 0;
+  for (int k = 0; k < n; k += 64) {
+    const int m = __popcll(__ballot(k + lane < n && off[k + lane + 1] <= b));
+    i += m;
+    if (m < 64) break;
+  }
+  return __builtin_amdgcn_readfirstlane(i);
+}
 
 // Anchor ghost of every surface point of every instance, one group of lanes
 // per point (the search is geometry only, so the fields' items share it).
@@ -94,6 +117,61 @@ __global__ __launch_bounds__(256) void k_batch_anchor(BStatic S, BCall C, int64_
   if (active && sub == 0) anchor[gq] = g;
 }
 
+// Field f of instance i at surface point q: its value and gradient, written
+// where asked for, and its share of the force, added to t.
+template <int D>
+__device__ __forceinline__ void surface_point(const PlanD& P, const BCall& C, int i, int f,
+                                              int64_t q, double t[3]) {
+  const int w = i * C.nf + f, vc = f - C.u_first;
+  const bool isp = f == C.p_field, isu = vc >= 0 && vc < D;
+  double* const sv = C.sval ? C.sval[w] : nullptr;
+  double* const sg = C.sgrad ? C.sgrad[w] : nullptr;
+  if (!(isp || isu || sv || sg)) return;
+  const double* F = C.fields[w];
+  const int64_t nq = C.nq[i];
+  const double* xq = C.xq[i];
+  const double* nr = C.nrm[i];
+  const double* wq = C.wq[i];
+  double x[3] = {0.0, 0.0, 0.0}, n[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    x[a] = xq[a * nq + q];
+    n[a] = nr[a * nq + q];
+  }
+  const int g = C.anchor[C.aoff[i] + q];
+  double val, gr[3];
+  if (g < 0) {
+    val = __longlong_as_double(0x7ff8000000000000LL);
+    gr[0] = gr[1] = gr[2] = val;
+  } else {
+    int ii, jj, kk;
+    unlinear(P.g, P.cell[g], ii, jj, kk);
+    const int ijk[3] = {ii, jj, kk};
+    double rel[3] = {0.0, 0.0, 0.0}, v[8];
+#pragma unroll
+    for (int a = 0; a < D; ++a) rel[a] = x[a] - centre(P.g, a, ijk[a]);
+    corner_values<D>(P, g, F, v);
+    double X[3];
+    stencil_span(P.g, P.code[g], P.cell[g], X);
+    box_eval<D>(rel, X, v, val, gr);
+  }
+  if (sv) sv[q] = val;
+  if (sg)
+#pragma unroll
+    for (int a = 0; a < D; ++a) sg[a * nq + q] = gr[a];
+  const double wt = wq[q];
+  if (isp) {
+#pragma unroll
+    for (int a = 0; a < D; ++a) t[a] += -wt * val * n[a];
+  } else if (isu) {
+    double gn = 0.0;
+#pragma unroll
+    for (int a = 0; a < D; ++a) gn += gr[a] * n[a];
+#pragma unroll
+    for (int a = 0; a < D; ++a) t[a] += C.mu * wt * ((a == vc ? gn : 0.0) + n[vc] * gr[a]);
+  }
+}
+
 // The surface part of item w = (instance, field), by a whole workgroup: the
 // field's value and gradient at the instance's points (one box-polynomial
 // evaluation serves both) and its share of the force, reduced over the
@@ -107,60 +185,9 @@ __device__ __forceinline__ void surface_item(const BStatic& S, const BCall& C, i
   const int T = blockDim.x;
   const int i = w / C.nf, f = w % C.nf;
   const PlanD& P = S.plans[i];
-  const double* F = C.fields[w];
-  // share of the force, and the field's value and gradient at the points
-  // (one box-polynomial evaluation serves both)
-  const int vc = f - C.u_first;
-  const bool isp = f == C.p_field, isu = vc >= 0 && vc < D;
-  double* const sv = C.sval ? C.sval[w] : nullptr;
-  double* const sg = C.sgrad ? C.sgrad[w] : nullptr;
   double t[3] = {0.0, 0.0, 0.0};
-  if (C.nq && (isp || isu || sv || sg)) {
-    const int64_t nq = C.nq[i];
-    const double* xq = C.xq[i];
-    const double* nr = C.nrm[i];
-    const double* wq = C.wq[i];
-    for (int64_t q = threadIdx.x; q < nq; q += T) {
-      double x[3] = {0.0, 0.0, 0.0}, n[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-      for (int a = 0; a < D; ++a) {
-        x[a] = xq[a * nq + q];
-        n[a] = nr[a * nq + q];
-      }
-      const int g = C.anchor[C.aoff[i] + q];
-      double val, gr[3];
-      if (g < 0) {
-        val = __longlong_as_double(0x7ff8000000000000LL);
-        gr[0] = gr[1] = gr[2] = val;
-      } else {
-        int ii, jj, kk;
-        unlinear(P.g, P.cell[g], ii, jj, kk);
-        const int ijk[3] = {ii, jj, kk};
-        double rel[3] = {0.0, 0.0, 0.0}, v[8];
-#pragma unroll
-        for (int a = 0; a < D; ++a) rel[a] = x[a] - centre(P.g, a, ijk[a]);
-        corner_values<D>(P, g, F, v);
-        double X[3];
-        stencil_span(P.g, P.code[g], P.cell[g], X);
-        box_eval<D>(rel, X, v, val, gr);
-      }
-      if (sv) sv[q] = val;
-      if (sg)
-#pragma unroll
-        for (int a = 0; a < D; ++a) sg[a * nq + q] = gr[a];
-      const double wt = wq[q];
-      if (isp) {
-#pragma unroll
-        for (int a = 0; a < D; ++a) t[a] += -wt * val * n[a];
-      } else if (isu) {
-        double gn = 0.0;
-#pragma unroll
-        for (int a = 0; a < D; ++a) gn += gr[a] * n[a];
-#pragma unroll
-        for (int a = 0; a < D; ++a) t[a] += C.mu * wt * ((a == vc ? gn : 0.0) + n[vc] * gr[a]);
-      }
-    }
-  }
+  if (C.nq)
+    for (int64_t q = threadIdx.x; q < C.nq[i]; q += T) surface_point<D>(P, C, i, f, q, t);
   for (int a = 0; a < 3; ++a) red[threadIdx.x][a] = t[a];
   __syncthreads();
   for (int s = T / 2; s > 0; s >>= 1) {
@@ -304,6 +331,137 @@ __global__ __launch_bounds__(1024) void k_batch_split(BStatic S, BCall C, int G,
     }
   }
   for (int f = s; f < nf; f += G) surface_item<D>(S, C, i * nf + f, red, part, counter, Fout);
+}
+
+// ---------------------------------------------------------------------------
+// Fill by waiting (k_fill_open, k_fill_flow, k_fill_rest) of every instance of
+// a 3D batch at once, and the surface part by chunks of points.
+//
+// The anchors of the points depend on the geometry only, so their search
+// rides in the waiting launch, behind its fill workgroups.  Workgroups wait
+// for earlier ones of the same instance and field only; the waits are bounded,
+// and k_batch_rest sweeps an instance whose plan's fault word is set.
+// Bound by the chain of levels beside the anchors, then by the chain anchor ->
+// corner -> sum of the surface part, which a workgroup per (instance, field)
+// ran in eight rounds on 28 of the CUs.  Seven spheres of 60^3 to 200^3, four
+// fields, 2,048 points each: 65 us a call, with tiles 130; the anchors by 16
+// lanes a point 70, in the launch before 74.
+// ---------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(256) void k_batch_open(BStatic S, BCall C, FlowTab T) {
+  const int f = (int)blockIdx.x / T.nopen, r = (int)blockIdx.x % T.nopen;
+  const int i = inst_of_block(T.open, C.ninst, r);
+  const PlanD& P = S.plans[i];
+  const int p = (r - T.open[i]) * 256 + (int)threadIdx.x, w = i * C.nf + f;
+  if (p >= P.ng) return;
+  double* const F = C.fields[w];
+  if (p < S.lev_off[i][1])
+    fill_single<D>(P, p, F, C.bcv[w], C.bct ? C.bct[w] : nullptr, C.kind[f]);
+  else
+    F[P.cell[p]] = __longlong_as_double((long long)kFillOpen);
+}
+
+// (workgroups past the fill's nfill: the anchors)
+constexpr int kFlowLanes = anchor_lanes<3>(), kFlowPoints = 256 / kFlowLanes;
+
+template <int D>
+__global__ __launch_bounds__(256) void k_batch_flow(BStatic S, BCall C, FlowTab T, int nfill,
+                                                    int32_t* __restrict__ anchor, int polls) {
+  if ((int)blockIdx.x >= nfill) {
+    constexpr int kPerChunk = kSurfChunk / kFlowPoints;
+    const int b = (int)blockIdx.x - nfill, chunk = b / kPerChunk;
+    const int i = inst_of_block(C.soff, C.ninst, chunk);
+    const int sub = (int)threadIdx.x % kFlowLanes;
+    const int64_t nq = C.nq[i], q0 = (int64_t)(chunk - C.soff[i]) * kSurfChunk +
+                                     (b % kPerChunk) * kFlowPoints;
+    if (q0 >= nq) return;   // uniform
+    const int64_t q = q0 + (int)threadIdx.x / kFlowLanes;
+    const bool active = q < nq;
+    double x[3] = {0.0, 0.0, 0.0};
+    if (active)
+#pragma unroll
+      for (int a = 0; a < D; ++a) x[a] = C.xq[i][a * nq + q];
+    const int g = find_anchor_group<D, kFlowLanes>(S.plans[i], x, sub, active);
+    if (active && sub == 0) anchor[C.aoff[i] + q] = g;
+    return;
+  }
+  const int f = (int)blockIdx.x / T.nwait, r = (int)blockIdx.x % T.nwait;
+  const int i = inst_of_block(T.wait, C.ninst, r);
+  const PlanD& P = S.plans[i];
+  const int w = i * C.nf + f;
+  // (past the last ghost: that one again)
+  const int p = min(S.lev_off[i][1] + (r - T.wait[i]) * 256 + (int)threadIdx.x, P.ng - 1);
+  fill_wait<D>(P, p, C.fields[w], C.bcv[w], C.bct ? C.bct[w] : nullptr, C.kind[f], polls);
+}
+
+template <int D>
+__global__ __launch_bounds__(1024) void k_batch_rest(BStatic S, BCall C) {
+  const int w = blockIdx.x, i = w / C.nf, f = w % C.nf;
+  const PlanD& P = S.plans[i];
+  if (P.ng == 0 || P.fill_fault[0] == 0) return;   // uniform
+  const int32_t* const lo = S.lev_off[i];
+  const int nl = S.nlev[i];
+  for (int l = 0; l < nl; ++l) {
+    for (int p = lo[l] + (int)threadIdx.x; p < lo[l + 1]; p += blockDim.x)
+      fill_single<D>(P, p, C.fields[w], C.bcv[w], C.bct ? C.bct[w] : nullptr, C.kind[f]);
+    __syncthreads();
+  }
+}
+
+// sum over the workgroup in lane, then wave order; thread 0 holds it
+__device__ __forceinline__ void block_sum3(double t[3], double (*sh)[3]) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) t[a] += __shfl_down(t[a], o);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0)
+    for (int a = 0; a < 3; ++a) sh[threadIdx.x >> 6][a] = t[a];
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int a = 0; a < 3; ++a) {
+      double s = 0.0;
+      for (int v = 0; v < kSurfChunk / 64; ++v) s += sh[v][a];
+      t[a] = s;
+    }
+}
+
+// One chunk of an instance's points and one field per workgroup.  The last
+// workgroup of an instance to finish (device-scope counter, reset after use)
+// adds the parts in a fixed order, so the force does not depend on timing.
+template <int D>
+__global__ __launch_bounds__(kSurfChunk) void k_batch_surface(BStatic S, BCall C,
+                                                              double* __restrict__ part,
+                                                              int* __restrict__ counter,
+                                                              double* __restrict__ Fout) {
+  __shared__ double sh[kSurfChunk / 64][3];
+  __shared__ int s_last;
+  const int i = inst_of_block(C.soff, C.ninst, (int)blockIdx.x), f = (int)blockIdx.y;
+  const int first = C.soff[i], parts = (C.soff[i + 1] - first) * C.nf;
+  const int64_t q = (int64_t)((int)blockIdx.x - first) * kSurfChunk + threadIdx.x;
+  double t[3] = {0.0, 0.0, 0.0};
+  if (q < C.nq[i]) surface_point<D>(S.plans[i], C, i, f, q, t);
+  block_sum3(t, sh);
+  double* const mine = part + (int64_t)first * C.nf * 3;
+  if (threadIdx.x == 0) {
+    const int at = ((int)blockIdx.x - first) * C.nf + f;
+    for (int a = 0; a < 3; ++a) mine[(int64_t)at * 3 + a] = t[a];
+    __threadfence();
+    s_last = atomicAdd(&counter[i], 1) == parts - 1;
+  }
+  __syncthreads();
+  if (!s_last) return;   // uniform
+  __threadfence();
+  double u[3] = {0.0, 0.0, 0.0};
+  for (int k = threadIdx.x; k < parts; k += kSurfChunk)
+    for (int a = 0; a < 3; ++a)
+      u[a] += __hip_atomic_load(&mine[(int64_t)k * 3 + a], __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_AGENT);
+  block_sum3(u, sh);
+  if (threadIdx.x == 0) {
+    for (int a = 0; a < 3; ++a) Fout[(int64_t)i * 3 + a] = u[a];
+    atomicExch(&counter[i], 0);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -662,6 +820,8 @@ struct BatchFwdState {
   hipEvent_t ev_done = nullptr;
   int threads = 0, grid_mul = 0;   // tuned
   size_t fill_lds = 0;             // most LDS an instance filled there takes
+  bool flow = false;               // 3D without coupled units: fill by waiting
+  FlowTab ft{};
   // tiled fill: 0 not set up yet, 1 set up, -1 not used for this batch
   int tiled = 0;
   int calls = 0;                   // forward calls so far
@@ -731,7 +891,22 @@ BatchFwdState* state_of(gcr_batch* b, hipStream_t st, gcr_status* err) {
   const size_t o_lp = al(sizeof(PlanD) * n), o_nl = o_lp + al(sizeof(int32_t*) * n);
   const size_t o_ct = o_nl + al(sizeof(int32_t) * n), o_bar = o_ct + al(sizeof(int) * n);
   const size_t o_fault = o_bar + al(sizeof(int) * 2 * n);
-  const size_t bytes = o_fault + al(sizeof(int));
+  const size_t o_open = o_fault + al(sizeof(int)), o_wait = o_open + al(sizeof(int32_t) * (n + 1));
+  const size_t bytes = o_wait + al(sizeof(int32_t) * (n + 1));
+  std::vector<int32_t> fopen(n + 1, 0), fwait(n + 1, 0);
+  int64_t nopen = 0, nwait = 0;
+  bool flow = true;
+  for (int i = 0; i < n; ++i) {
+    const gcr_plan* p = b->plans[i].get();
+    flow = flow && p->dim == 3 && p->info.nunits == 0;
+    const int64_t n1 = p->nlev > 0 ? p->lev_off[1] : 0;
+    nopen += (p->ng + 255) / 256;
+    nwait += (p->ng - n1 + 255) / 256;
+    fopen[i + 1] = (int32_t)nopen;
+    fwait[i + 1] = (int32_t)nwait;
+  }
+  // (a launch's workgroups, fields and points counted, stay in 31 bits)
+  S->flow = flow && nopen < (int64_t(1) << 26);
   char* d = static_cast<char*>(pool_alloc(bytes));
   if (d) S->owned.push_back(d);
   S->h_static = static_cast<char*>(pinned_alloc(bytes));
@@ -749,6 +924,10 @@ BatchFwdState* state_of(gcr_batch* b, hipStream_t st, gcr_status* err) {
   std::memcpy(S->h_static, pv.data(), sizeof(PlanD) * n);
   std::memcpy(S->h_static + o_lp, lp.data(), sizeof(int32_t*) * n);
   std::memcpy(S->h_static + o_nl, nl.data(), sizeof(int32_t) * n);
+  std::memcpy(S->h_static + o_open, fopen.data(), sizeof(int32_t) * (n + 1));
+  std::memcpy(S->h_static + o_wait, fwait.data(), sizeof(int32_t) * (n + 1));
+  S->ft = FlowTab{reinterpret_cast<int32_t*>(d + o_open), reinterpret_cast<int32_t*>(d + o_wait),
+                  (int)nopen, (int)nwait};
   S->ev_static = event_take();
   if (!S->ev_static || hipMemcpyAsync(d, S->h_static, bytes, hipMemcpyHostToDevice, st)) {
     *err = GCR_E_HIP;
@@ -1108,6 +1287,26 @@ static gcr_status launch_batch(BatchFwdState* S, const BCall& C, int dim, int th
   return GCR_OK;
 }
 
+// The launches of a batch that fills by waiting; nchunk: chunks of points (0
+// without forces).
+static gcr_status launch_flow(BatchFwdState* S, const BCall& C, int nchunk, double* F,
+                              hipStream_t st) {
+  const BStatic bs{S->d_plans, S->d_levp, S->d_nlev};
+  const unsigned nf = (unsigned)C.nf;
+  const int nfill = S->ft.nwait * C.nf;
+  const int na = nchunk * (kSurfChunk / kFlowPoints);
+  if (S->ft.nopen) k_batch_open<3><<<S->ft.nopen * nf, 256, 0, st>>>(bs, C, S->ft);
+  if (nfill + na > 0)
+    k_batch_flow<3><<<(unsigned)(nfill + na), 256, 0, st>>>(bs, C, S->ft, nfill, S->d_anchor,
+                                                            fill_polls());
+  if (nfill) k_batch_rest<3><<<(unsigned)C.nitems, 1024, 0, st>>>(bs, C);
+  if (C.nq)
+    k_batch_surface<3><<<dim3((unsigned)nchunk, nf), kSurfChunk, 0, st>>>(bs, C, S->d_part,
+                                                                         S->d_counter, F);
+  GCR_HIP(hipGetLastError());
+  return GCR_OK;
+}
+
 int gcr::fill_polls() {
   // (its default: a wait of about half a second)
   const int v = g_split_spin.load();
@@ -1183,9 +1382,12 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   // tiles from the second forward call of a batch (mode 1: a batch used once
   // does not pay for the closures), or from the first (mode 2)
   ++S->calls;
+  // 3D without coupled units fills by waiting unless a form is asked for: no
+  // closures to find, no shape to time
+  const bool flow = S->flow && batch_tiling() == 1 && S->tiled <= 0 && !g_force_shape.load();
   if (S->tiled == 0) {
     const int mode = batch_tiling();
-    if (mode == 0) {
+    if (mode == 0 || flow) {
       S->tiled = -1;
     } else if (mode == 2 || S->calls >= 2) {
       S->tiled = tile_setup(S, batch, dim, st, &err) ? 1 : -1;
@@ -1220,7 +1422,7 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   // call table: one upload
   const size_t np = (size_t)nitems;
   const size_t bytes = sizeof(void*) * (5 * np + 3 * n) + sizeof(int64_t) * (2 * n + 1) +
-                       sizeof(int32_t) * np + 64;
+                       sizeof(int32_t) * (np + n + 1) + 64;
   std::vector<char> host(bytes, 0);
   char* h = host.data();
   size_t o = 0;
@@ -1238,8 +1440,9 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   const size_t o_bct = put(bt.data(), sizeof(void*) * np);
   const size_t o_sval = sval ? put(sval, sizeof(void*) * np) : 0;
   const size_t o_sgrad = sgrad ? put(sgrad, sizeof(void*) * np) : 0;
-  size_t o_nq = 0, o_xq = 0, o_nrm = 0, o_wq = 0, o_aoff = 0;
+  size_t o_nq = 0, o_xq = 0, o_nrm = 0, o_wq = 0, o_aoff = 0, o_soff = 0;
   std::vector<int64_t> aoff(n + 1, 0);
+  std::vector<int32_t> soff(n + 1, 0);
   if (nq) {
     for (int i = 0; i < n; ++i) aoff[i + 1] = aoff[i] + nq[i];
     o_nq = put(nq, sizeof(int64_t) * n);
@@ -1247,6 +1450,10 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
     o_nrm = put(nrm, sizeof(void*) * n);
     o_wq = put(wq, sizeof(void*) * n);
     o_aoff = put(aoff.data(), sizeof(int64_t) * (n + 1));
+    // (an instance without points has one empty chunk: its force is zero)
+    for (int i = 0; i < n; ++i)
+      soff[i + 1] = soff[i] + (int32_t)std::max<int64_t>(1, (nq[i] + kSurfChunk - 1) / kSurfChunk);
+    o_soff = put(soff.data(), sizeof(int32_t) * (n + 1));
   }
   const int64_t npts = aoff[n];
   if (npts > 0 && S->anchor_cap < (size_t)npts) {
@@ -1262,10 +1469,11 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
     S->call_cap = S->d_call ? o : 0;
     if (!S->d_call) return GCR_E_NOMEM;
   }
-  if (S->part_cap < np * 3) {
+  const size_t parts = 3 * std::max(np, (size_t)nf * (size_t)soff[n]);
+  if (S->part_cap < parts) {
     if (!retire(S->d_part)) return GCR_E_HIP;
-    S->d_part = static_cast<double*>(pool_alloc(sizeof(double) * np * 3));
-    S->part_cap = S->d_part ? np * 3 : 0;
+    S->d_part = static_cast<double*>(pool_alloc(sizeof(double) * parts));
+    S->part_cap = S->d_part ? parts : 0;
     if (!S->d_part) return GCR_E_NOMEM;
   }
   {
@@ -1306,6 +1514,7 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   C.wq = nq ? reinterpret_cast<const double* const*>(d + o_wq) : nullptr;
   C.order = reinterpret_cast<const int32_t*>(d + o_order);
   C.aoff = nq ? reinterpret_cast<const int64_t*>(d + o_aoff) : nullptr;
+  C.soff = nq ? reinterpret_cast<const int32_t*>(d + o_soff) : nullptr;
   C.anchor = S->d_anchor;
   C.tile_flag = S->tiled == 1 ? S->T.flag : nullptr;
   C.sval = sval ? reinterpret_cast<double* const*>(d + o_sval) : nullptr;
@@ -1313,6 +1522,20 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   std::array<hipEvent_t, 3> ev{};
   bool timed = (profiling_mask() & 2) != 0 && take_fwd_events(&ev);
   if (timed) (void)hipEventRecord(ev[0], st);
+  auto end_call = [&](gcr_status rs) -> gcr_status {
+    if (!S->ev_done && !(S->ev_done = event_take())) return GCR_E_HIP;
+    GCR_HIP(hipEventRecord(S->ev_done, st));
+    if (timed) {
+      (void)hipEventRecord(ev[2], st);
+      std::lock_guard<std::mutex> lk(g_fwd_ev_mu);
+      g_fwd_ev.push_back(ev);
+    }
+    return rs;
+  };
+  if (flow) {
+    if (timed) (void)hipEventRecord(ev[1], st);   // (the anchors ride in the fill)
+    return end_call(launch_flow(S, C, soff[n], F, st));
+  }
   if (npts > 0) {
     BStatic bs{S->d_plans, S->d_levp, S->d_nlev};
     // a row of workgroups per instance, unless the rows' lengths are so
@@ -1406,12 +1629,5 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
     gm = (int)(int8_t)(fs & 0xff);
   }
   const gcr_status rs = launch_batch(S, C, dim, th, gm, Fo, st);
-  if (!S->ev_done && !(S->ev_done = event_take())) return GCR_E_HIP;
-  GCR_HIP(hipEventRecord(S->ev_done, st));
-  if (timed) {
-    (void)hipEventRecord(ev[2], st);
-    std::lock_guard<std::mutex> lk(g_fwd_ev_mu);
-    g_fwd_ev.push_back(ev);
-  }
-  return rs;
+  return end_call(rs);
 }

@@ -72,54 +72,7 @@ template <int D>
 __global__ __launch_bounds__(256) void k_fill_flow(FillArgs A, int n1, int polls) {
   const int f = blockIdx.y;
   const int p = min(n1 + (int)(blockIdx.x * 256 + threadIdx.x), A.P.ng - 1);   // (the last: again)
-  const PlanD& P = A.P;
-  double* F = A.f[f];
-  const int c = P.cell[p];
-  const uint32_t code = P.code[p];
-  double dl[3], nn[3], w[8], val[8];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    dl[a] = a < D ? P.dl[a][p] : 0.0;
-    nn[a] = a < D ? P.nn[a][p] : 0.0;
-  }
-  const int bc = A.kind[f] == 2 ? (int)A.bt[f][p] : A.kind[f];
-  const double bv = A.b[f][p];
-  const uint32_t skip = code_skip(code);
-  uint32_t open = code_ghosts(code);
-#pragma unroll
-  for (int k = 1; k < (1 << D); ++k)
-    val[k] = (k & skip) || ((open >> k) & 1u) ? 0.0 : F[c + corner_offset(P.g, code, k)];
-  double X[3];
-  stencil_span(P.g, code, c, X);
-  ghost_weights<D>(dl, nn, X, bc, w);
-  bool done = false;
-  for (int left = polls;; --left) {
-    if (!done) {
-      unsigned long long x[8];
-#pragma unroll
-      for (int k = 1; k < (1 << D); ++k)
-        x[k] = (open >> k) & 1u ? poll_value(F + c + corner_offset(P.g, code, k)) : kFillOpen;
-#pragma unroll
-      for (int k = 1; k < (1 << D); ++k)
-        if (x[k] != kFillOpen) {
-          val[k] = __longlong_as_double((long long)x[k]);
-          open &= ~(1u << k);
-        }
-      if (!open) {
-        double v = w[0] * bv;
-#pragma unroll
-        for (int k = 1; k < (1 << D); ++k)
-          if (!(k & skip)) v += w[k] * val[k];
-        post_value(F + c, v);
-        done = true;
-      }
-    }
-    if (__ballot(!done) == 0ull) return;
-    if (left <= 0) {
-      if (!done) atomicOr(P.fill_fault, 1);
-      return;
-    }
-  }
+  fill_wait<D>(A.P, p, A.f[f], A.b[f], A.bt[f], A.kind[f], polls);
 }
 
 template <int D>

@@ -212,30 +212,52 @@ __device__ __forceinline__ int find_anchor_group(const PlanD& P, const double x[
   for (int a = 0; a < D; ++a) qi[a] = cell_of(P.g, a, x[a]);
   double bd = 1e300;
   int bc = 0x7fffffff, bg = -1;
-  if (active) {
-    for (int t = sub; t < NC; t += NL) {
-      const int ix = qi[0] - 2 + t % 5;
-      const int jy = qi[1] - 2 + (t / 5) % 5;
-      const int kz = D == 3 ? qi[2] - 2 + t / 25 : 0;
-      if (ix < 0 || ix >= P.g.n[0] || jy < 0 || jy >= P.g.n[1]) continue;
-      if (D == 3 && (kz < 0 || kz >= P.g.n[2])) continue;
-      const int c = linear(P.g, ix, jy, kz);
-      const int8_t tg = P.tags[c];
-      if (tg != 2 && tg != -2) continue;
-      const int g = ghost_at(P, c);
-      if (g < 0) continue;
-      const int q[3] = {ix, jy, kz};
-      double d2 = 0.0;
+  // a lane's cells side by side: the wait is the chain tag -> table -> foot
+  // point, once instead of once per cell
+  constexpr int M = (NC + NL - 1) / NL;
+  int c[M], g[M], ix[M], jy[M], kz[M];
+  int8_t tg[M];
 #pragma unroll
-      for (int a = 0; a < D; ++a) {
-        double s = centre(P.g, a, q[a]) + P.dl[a][g];
-        d2 += (x[a] - s) * (x[a] - s);
-      }
-      if (d2 < bd || (d2 == bd && c < bc)) {
-        bd = d2;
-        bc = c;
-        bg = g;
-      }
+  for (int m = 0; m < M; ++m) {
+    const int t = sub + m * NL;
+    ix[m] = qi[0] - 2 + t % 5;
+    jy[m] = qi[1] - 2 + (t / 5) % 5;
+    kz[m] = D == 3 ? qi[2] - 2 + t / 25 : 0;
+    const bool in = active && t < NC && ix[m] >= 0 && ix[m] < P.g.n[0] && jy[m] >= 0 &&
+                    jy[m] < P.g.n[1] && (D == 2 || (kz[m] >= 0 && kz[m] < P.g.n[2]));
+    c[m] = in ? linear(P.g, ix[m], jy[m], kz[m]) : -1;
+    tg[m] = 0;
+    if (in) tg[m] = P.tags[c[m]];
+  }
+  unsigned long long en[M];
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    en[m] = kHashEmpty;
+    if (tg[m] == 2 || tg[m] == -2) en[m] = P.htab[cell_hash(c[m]) & P.hmask];
+  }
+  double d[M][3];
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    g[m] = -1;
+    if (en[m] != kHashEmpty)
+      g[m] = (int)(en[m] >> 32) == c[m] ? (int)(en[m] & 0xffffffffu) : ghost_at(P, c[m]);
+#pragma unroll
+    for (int a = 0; a < D; ++a) d[m][a] = g[m] >= 0 ? P.dl[a][g[m]] : 0.0;
+  }
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    if (g[m] < 0) continue;
+    const int q[3] = {ix[m], jy[m], kz[m]};
+    double d2 = 0.0;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      const double s = centre(P.g, a, q[a]) + d[m][a];
+      d2 += (x[a] - s) * (x[a] - s);
+    }
+    if (d2 < bd || (d2 == bd && c[m] < bc)) {
+      bd = d2;
+      bc = c[m];
+      bg = g[m];
     }
   }
 #pragma unroll

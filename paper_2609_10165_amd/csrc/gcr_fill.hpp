@@ -220,6 +220,62 @@ __device__ __forceinline__ void post_value(double* p, double v) {
                      __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Ghost p of a level above the first, whose wave's lanes each hold such a
+// ghost: its fluid corners and weights are gathered, the slots of its ghost
+// corners (the code's mask) polled until each holds a value, its own stored.
+// A wait that passes `polls` sets the plan's fault word.
+template <int D>
+__device__ __forceinline__ void fill_wait(const PlanD& P, int p, double* F,
+                                          const double* __restrict__ b,
+                                          const uint8_t* __restrict__ bt, int kind, int polls) {
+  const int c = P.cell[p];
+  const uint32_t code = P.code[p];
+  double dl[3], nn[3], w[8], val[8];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    dl[a] = a < D ? P.dl[a][p] : 0.0;
+    nn[a] = a < D ? P.nn[a][p] : 0.0;
+  }
+  const int bc = kind == 2 ? (int)bt[p] : kind;
+  const double bv = b[p];
+  const uint32_t skip = code_skip(code);
+  uint32_t open = code_ghosts(code);
+#pragma unroll
+  for (int k = 1; k < (1 << D); ++k)
+    val[k] = (k & skip) || ((open >> k) & 1u) ? 0.0 : F[c + corner_offset(P.g, code, k)];
+  double X[3];
+  stencil_span(P.g, code, c, X);
+  ghost_weights<D>(dl, nn, X, bc, w);
+  bool done = false;
+  for (int left = polls;; --left) {
+    if (!done) {
+      unsigned long long x[8];
+#pragma unroll
+      for (int k = 1; k < (1 << D); ++k)
+        x[k] = (open >> k) & 1u ? poll_value(F + c + corner_offset(P.g, code, k)) : kFillOpen;
+#pragma unroll
+      for (int k = 1; k < (1 << D); ++k)
+        if (x[k] != kFillOpen) {
+          val[k] = __longlong_as_double((long long)x[k]);
+          open &= ~(1u << k);
+        }
+      if (!open) {
+        double v = w[0] * bv;
+#pragma unroll
+        for (int k = 1; k < (1 << D); ++k)
+          if (!(k & skip)) v += w[k] * val[k];
+        post_value(F + c, v);
+        done = true;
+      }
+    }
+    if (__ballot(!done) == 0ull) return;
+    if (left <= 0) {
+      if (!done) atomicOr(P.fill_fault, 1);
+      return;
+    }
+  }
+}
+
 // --------------------------------------------------------------------------
 // The fill of one field of a 2D plan by one workgroup, in LDS.
 //

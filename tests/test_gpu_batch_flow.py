@@ -1,0 +1,94 @@
+"""The forward of a 3D batch (Sec. 3.2 fill, Sec. 6 surface values and
+forces) by ghosts waiting for their corners and by chunks of points: one
+point, a chunk's edge, none; one to eight fields; instances of one workgroup
+and many; and after a wait that gave up.  Fields and surface values are those
+of each plan's own calls with one launch per level, bit for bit; the force
+differs from theirs by the order of its sum."""
+import numpy as np
+import pytest
+
+import synth
+from synth import CGC, CGC_ES, HGC, LAYER2, DIRICHLET, NEUMANN
+from test_gpu_parity import gcr  # noqa: F401  (the fixture)
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+MIXED = 2
+
+
+def rand(*shape, seed):
+    return torch.randn(*shape, dtype=torch.float64, device="cuda",
+                       generator=torch.Generator(device="cuda").manual_seed(seed))
+
+
+def agree(gcr, ns, schemes, kinds, nqs, forces=True):
+    insts = [synth.sphere256(seed=k, n=n) for k, n in enumerate(ns)]
+    B = gcr.Batch([i.grid for i in insts], [i.shape for i in insts], schemes)
+    nf = len(kinds)
+    clean = [rand(p.n_cells, seed=10 + f) for p in B.plans for f in range(nf)]
+    bcv = [rand(p.n_ghost, seed=50 + f) for p in B.plans for f in range(nf)]
+    bct = [(rand(p.n_ghost, seed=90 + f) < 0).to(torch.uint8) for p in B.plans for f in range(nf)]
+    S = [p.foot_points()[0] for p in B.plans]
+    x = [s[:, torch.arange(q, device="cuda") * 7 % s.shape[1]].contiguous() for s, q in zip(S, nqs)]
+    n = [rand(3, q, seed=3) for q in nqs]
+    w = [rand(q, seed=4).abs() for q in nqs]
+    mu, u = 0.7, [c.clone() for c in clean]
+    F = torch.full((len(ns), 3), 7.0, dtype=torch.float64, device="cuda")
+    val = [torch.empty(q, dtype=torch.float64, device="cuda") for q in nqs for _ in range(nf)]
+    grad = [torch.empty((3, q), dtype=torch.float64, device="cuda") for q in nqs for _ in range(nf)]
+    for _ in range(2):   # every value again from the clean fields
+        for a, c in zip(u, clean):
+            a.copy_(c)
+        if forces:
+            B.forward(nf, u, kinds, bcv, bct, nq=nqs, xq=x, nrm=n, wq=w, p_field=nf - 1, u_first=0,
+                      mu=mu, F=F, sval=val, sgrad=grad)
+        else:
+            B.forward(nf, u, kinds, bcv, bct)
+    B.status()
+    for i, p in enumerate(B.plans):
+        s = slice(i * nf, (i + 1) * nf)
+        want = [c.clone() for c in clean[s]]
+        p.set_schedule(1)
+        p.fill(want, kinds, bcv[s], bct[s])
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(u[s], want)), i
+        if not forces:
+            continue
+        if nqs[i] == 0:
+            assert (F[i] == 0).all()
+            continue
+        v, g, _ = p.surface(x[i], want)
+        assert all(torch.equal(a, b) for a, b in zip(val[s], v)), i
+        assert all(torch.equal(a, b) for a, b in zip(grad[s], g)), i
+        # each point's share, in the terms of the sum; 40 roundings on a term
+        # and the sum's own bound the difference
+        if nf >= 4:
+            G = g[:3]
+            t = -w[i] * v[nf - 1] * n[i] + mu * w[i] * (torch.einsum("caq,aq->cq", G, n[i])
+                                                         + torch.einsum("caq,cq->aq", G, n[i]))
+            mag = (w[i] * v[nf - 1] * n[i]).abs() + mu * w[i] * (
+                torch.einsum("caq,aq->cq", G.abs(), n[i].abs()) + torch.einsum("caq,cq->aq", G.abs(), n[i].abs()))
+            assert ((F[i] - t.sum(1)).abs() <= (40 + nqs[i]) * 2.0 ** -53 * mag.sum(1)).all(), i
+
+
+@pytest.mark.parametrize("kinds", [[DIRICHLET], [NEUMANN, DIRICHLET, MIXED, DIRICHLET], [MIXED] * 8])
+def test_batch_waiting_fill(gcr, kinds):  # noqa: F811
+    agree(gcr, [16, 64, 33, 90], [HGC, CGC_ES, CGC, HGC | LAYER2], kinds, [1, 256, 257, 0])
+
+
+def test_batch_waiting_fill_one_instance(gcr):  # noqa: F811
+    agree(gcr, [120], [HGC], [DIRICHLET, NEUMANN, DIRICHLET, MIXED], [1000])
+    agree(gcr, [120], [HGC], [DIRICHLET, NEUMANN], [0], forces=False)
+
+
+def test_batch_waiting_fill_many_instances(gcr):  # noqa: F811
+    ns = [int(n) for n in np.random.default_rng(3).integers(16, 40, 70)]
+    agree(gcr, ns, [HGC] * 70, [DIRICHLET] * 4, [k % 5 * 64 for k in range(70)])
+
+
+def test_batch_wait_that_gives_up_is_swept_again(gcr):  # noqa: F811
+    gcr.set_batch_spin(1)   # no polls: every wait gives up at once
+    try:
+        agree(gcr, [64, 33], [HGC, CGC], [DIRICHLET, MIXED, NEUMANN, DIRICHLET], [300, 5])
+    finally:
+        gcr.set_batch_spin(0)
