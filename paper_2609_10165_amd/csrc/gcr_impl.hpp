@@ -71,7 +71,8 @@ struct BatchData {
   std::vector<int64_t> if_off, g_off;  // host [ninst+1]
   std::vector<int64_t> iface_off;      // host [ninst+1] interface cells alone
   std::vector<InstInfo> info;        // host [ninst]
-  std::vector<int32_t> lev_off;      // host [ninst][kMaxLevels+1]
+  std::vector<int32_t> lev_off;      // host, of instance i from lev_at[i]: [nlev + 1]
+  std::vector<size_t> lev_at, unit_at;
   // device
   Inst* d_inst = nullptr;
   int8_t* d_tags = nullptr;
@@ -95,17 +96,13 @@ struct BatchData {
   int32_t* d_lev_off = nullptr;      // [ninst][kMaxLevels+1]
   // interface cells
   int32_t* d_if_cell = nullptr;
-  double* d_if_psi = nullptr;
-  double* d_if_n = nullptr;          // [3][cap]
-  uint8_t* d_if_flag = nullptr;
-  int32_t* d_blkcnt = nullptr;
-  int64_t* d_blkexcl = nullptr;
   // ghosts, linear-index order
   int32_t* d_g_cell = nullptr;
   uint8_t* d_g_ext = nullptr;        // ghost on the extended stencil (second layer)
   double* d_g_psi = nullptr;
   double* d_g_n = nullptr;           // [3][cap]
   uint32_t* d_g_code = nullptr;
+  uint32_t* d_g_slot = nullptr;      // slot of the ghost's cell in its instance's table
   int32_t* d_deps = nullptr;         // [7][cap]
   int32_t* d_lev = nullptr;
   int32_t* d_blk_idx = nullptr;
@@ -130,7 +127,7 @@ struct BatchData {
   uint8_t* d_dcnt = nullptr;         // [cap] ghost dependencies per ghost
   uint32_t* d_cnt = nullptr;         // byte counters in HBM (instances beyond LDS)
   uint32_t* d_bits = nullptr;        // level bitmaps in HBM (instances beyond LDS)
-  std::vector<int32_t> unit_lev;     // host copy
+  std::vector<int32_t> unit_lev;     // host, of instance i from unit_at[i]: [nunits]
   // cell -> ghost hash tables, concatenated per instance
   unsigned long long* d_htab = nullptr;
   int64_t* d_hoff = nullptr;

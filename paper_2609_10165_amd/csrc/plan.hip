@@ -776,11 +776,13 @@ __global__ __launch_bounds__(256) void k_compact_iface(const Inst* __restrict__ 
                                                        const int32_t* __restrict__ chunk_list,
                                                        int32_t* __restrict__ if_cell,
                                                        unsigned long long* __restrict__ htab,
-                                                       int64_t nhash) {
-  // the cell -> ghost tables, emptied here for k_hash_build
-  for (int64_t z = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; z < nhash;
-       z += (int64_t)gridDim.x * blockDim.x)
-    htab[z] = ~0ull;
+                                                       int64_t nhash,
+                                                       unsigned long long* __restrict__ posted,
+                                                       int64_t nposted) {
+  // for k_geometry: the cell -> ghost tables emptied, its counts cleared
+  const int64_t z0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t z = z0; z < nhash; z += (int64_t)gridDim.x * blockDim.x) htab[z] = ~0ull;
+  for (int64_t z = z0; z < nposted; z += (int64_t)gridDim.x * blockDim.x) posted[z] = 0ull;
   const int64_t chunk = chunk_list[blockIdx.x];   // chunks holding listed cells
   __shared__ int64_t sh[5];
   const int ii = chunk_inst[chunk];
@@ -816,128 +818,184 @@ __global__ __launch_bounds__(256) void k_compact_iface(const Inst* __restrict__ 
 // 3. geometry and ghost tags
 // --------------------------------------------------------------------------
 
-__global__ __launch_bounds__(256) void k_geometry(const Inst* __restrict__ insts, int ninst,
-                                                  const int64_t* __restrict__ if_off,
-                                                  const int32_t* __restrict__ if_cell,
-                                                  int8_t* __restrict__ tags,
-                                                  double* __restrict__ if_psi,
-                                                  double* __restrict__ if_n, int64_t cap,
-                                                  uint8_t* __restrict__ if_flag,
-                                                  InstInfo* __restrict__ info) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= if_off[ninst]) return;
-  const int ii = find_inst(if_off, ninst, e);
-  const Inst& I = insts[ii];
-  const GridD& g = I.g;
-  const int c = if_cell[e];
-  int8_t* tp = tags + I.cell_off + c;
-  const int8_t t0 = *tp;
-  const bool solid = (t0 & 1) != 0;
-  const bool iface = (t0 & 0x40) != 0;   // else a second-layer candidate
-  int i, j, k;
-  unlinear(g, c, i, j, k);
-  double x[3] = {centre(g, 0, i), centre(g, 1, j), g.dim == 3 ? centre(g, 2, k) : 0.0};
-  double n[3] = {0.0, 0.0, 0.0}, psi = 0.0;
-  bool ok = project(I.s, g.dim, x, solid, n, psi);
-  if (!ok) atomicOr(&info[ii].err, kErrGeometry);
-  // Eq. delta_n with the cell's own widths
-  const int ijk[3] = {i, j, k};
-  double sum = 0.0;
-  for (int a = 0; a < g.dim; ++a) {
-    const double w = width(g, a, ijk[a]);
-    sum += (n[a] / w) * (n[a] / w);
+// The instance of element x of a batch, for lanes whose elements ascend from
+// the wave's first, x0: a wave compares 64 offsets at once (find_inst's chain
+// of loads once instead of log2 times), then each lane steps on.
+__device__ __forceinline__ int find_inst_wave(const int64_t* __restrict__ off, int ninst, int64_t x0,
+                                              int64_t x) {
+  const int lane = threadIdx.x & 63;
+  int i = 0;
+  for (int k = 0; k < ninst - 1; k += 64) {
+    const int m = __popcll(__ballot(k + lane < ninst - 1 && off[k + lane + 1] <= x0));
+    i += m;
+    if (m < 64) break;
   }
-  double dn = 1.0 / sqrt(sum);
-  bool ghost = false;
-  if (iface) {
-    if (I.scheme == kHGC) ghost = solid ? (psi <= dn / 2.0) : (-psi < dn / 2.0);
-    else ghost = solid;
-  }
-  // Sec. 7.1: a second layer adds the solid cells with psi <= 1.5 delta n,
-  // reconstructed on the extended stencil
-  const bool ext = I.layer2 && solid && !ghost && psi <= 1.5 * dn;
-  ghost = ghost || ext;
-  *tp = ghost ? (solid ? 2 : -2) : (solid ? 1 : 0);
-  if_psi[e] = psi;
-  for (int a = 0; a < 3; ++a) if_n[a * cap + e] = n[a];
-  if_flag[e] = ghost ? (ext ? 3 : 1) : 0;   // bit 0 ghost, bit 1 extended stencil
+  while (i < ninst - 1 && off[i + 1] <= x) ++i;
+  return i;
 }
 
-// per 1024-entry block counts of flags
-__global__ __launch_bounds__(256) void k_count_flags(const uint8_t* __restrict__ flag, int64_t n,
-                                                     int32_t* __restrict__ cnt) {
-  __shared__ int s;
-  if (threadIdx.x == 0) s = 0;
-  __syncthreads();
-  int c = 0;
-  for (int t = 0; t < 4; ++t) {
-    int64_t e = (int64_t)blockIdx.x * 1024 + t * 256 + threadIdx.x;
-    if (e < n) c += flag[e] & 1;
-  }
-  if (c) atomicAdd(&s, c);
-  __syncthreads();
-  if (threadIdx.x == 0) cnt[blockIdx.x] = s;
+__device__ __forceinline__ uint32_t table_slot(int c, uint32_t mask) {
+  const uint32_t h = (uint32_t)c * 2654435761u;
+  return (h ^ (h >> 15)) & mask;
 }
 
-__global__ __launch_bounds__(256) void k_scatter_ghosts(
-    const uint8_t* __restrict__ flag, int64_t n, const int64_t* __restrict__ blk_excl,
-    const int32_t* __restrict__ if_cell, const double* __restrict__ if_psi,
-    const double* __restrict__ if_n, int64_t cap, int32_t* __restrict__ g_cell,
-    double* __restrict__ g_psi, double* __restrict__ g_n, uint8_t* __restrict__ g_ext) {
-  __shared__ int64_t sh[5];
-  int64_t run = blk_excl[blockIdx.x];
-  for (int t = 0; t < 4; ++t) {
-    int64_t e = (int64_t)blockIdx.x * 1024 + t * 256 + threadIdx.x;
-    const int fl = (e < n) ? flag[e] : 0;
-    const int f = fl & 1;
-    int64_t tot;
-    int64_t pos = run + block_excl_scan<256>(f, &tot, sh);
-    if (f) {
-      g_ext[pos] = (uint8_t)(fl >> 1);
-      g_cell[pos] = if_cell[e];
-      g_psi[pos] = if_psi[e];
-      for (int a = 0; a < 3; ++a) g_n[a * cap + pos] = if_n[a * cap + e];
-    }
-    run += tot;
-  }
+// enters (cell c, value v); the table is at most half full
+__device__ __forceinline__ uint32_t table_insert(unsigned long long* t, uint32_t mask, int c,
+                                                 uint32_t v) {
+  const unsigned long long entry = ((unsigned long long)(uint32_t)c << 32) | v;
+  uint32_t h = table_slot(c, mask);
+  while (atomicCAS(&t[h], ~0ull, entry) != ~0ull) h = (h + 1) & mask;
+  return h;
 }
 
-// ghost offsets of the instances: ghosts before interface entry if_off[i]
-// one wave per offset i = 0..ninst: the ghosts before interface cell
-// if_off[i] are those of the whole 1024-flag blocks before it plus the
-// flags of its own block up to it
-__global__ __launch_bounds__(64) void k_ghost_off(const uint8_t* __restrict__ flag,
-                                                  const int64_t* __restrict__ blk_excl,
-                                                  const int64_t* __restrict__ if_off, int ninst,
-                                                  int64_t* __restrict__ g_off) {
-  const int i = blockIdx.x;
-  if (i > ninst) return;
-  const int64_t e = if_off[i];
-  const int64_t b = e / 1024;
-  int c = 0;
-  for (int64_t q = b * 1024 + threadIdx.x; q < e; q += 64) c += flag[q] & 1;
+// Elements before workgroup b's own `tot`, for workgroups numbered in the
+// order they started: each posts its count, sums those posted before it, 256
+// at a time, back to the nearest that has posted its sum, and posts its own
+// sum.  Workgroups wait only for ones that started earlier and post their
+// counts without waiting, so every wait ends.  (Called by all 256 threads.)
+constexpr unsigned long long kPostCount = 1ull << 62, kPostSum = 2ull << 62;
+__device__ __forceinline__ int64_t posted_before(unsigned long long* __restrict__ posted, int b,
+                                                 int64_t tot) {
+  __shared__ int64_t s_sum[4];
+  __shared__ int s_end[4];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  if (tid == 0)
+    __hip_atomic_store(&posted[b], (b == 0 ? kPostSum : kPostCount) | (unsigned long long)tot,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int64_t before = 0;
+  for (int top = b; top > 0; top -= 256) {
+    const int j = top - 1 - tid;
+    unsigned long long v = kPostSum;   // (before the first: nothing)
+    if (j >= 0)
+      while ((v = __hip_atomic_load(&posted[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
+      }
+    const unsigned long long sums = __ballot((v & kPostSum) != 0);
+    const int end = sums ? __ffsll(sums) - 1 : 64;
+    int64_t x = lane <= end ? (int64_t)(v & (kPostCount - 1)) : 0;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o);
-  if (threadIdx.x == 0) g_off[i] = blk_excl[b] + c;
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+    if (lane == 0) {
+      s_sum[wv] = x;
+      s_end[wv] = end;
+    }
+    __syncthreads();
+    bool found = false;
+    for (int w = 0; w < 4 && !found; ++w) {
+      before += s_sum[w];
+      found = s_end[w] < 64;
+    }
+    __syncthreads();
+    if (found) break;
+  }
+  if (tid == 0 && b > 0)
+    __hip_atomic_store(&posted[b], kPostSum | (unsigned long long)(before + tot), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  return before;
+}
+
+// Distance, normal and ghost decision of every interface cell, and the ghosts
+// in linear order at once: their positions from the counts that the
+// workgroups post to each other (posted: [workgroups], then the number
+// started), so that one launch does what four did (the cells' arrays written,
+// counted, scanned, read back) and the ghosts enter the cell table too.
+// Bound by the latency of the projection and of the insertion.  With the
+// statistics folded and the results stored by k_finalize, a build went from 14
+// launches and a copy after the compaction to 4: 128^2 circle 174 -> 117 us
+// for the whole build, fill and read-out, 64 stars 483 -> 375, 512^3 sphere
+// 349 -> 316.
+__global__ __launch_bounds__(256) void k_geometry(
+    const Inst* __restrict__ insts, int ninst, const int64_t* __restrict__ if_off,
+    const int32_t* __restrict__ if_cell, int8_t* __restrict__ tags, int64_t cap,
+    unsigned long long* __restrict__ posted, const int64_t* __restrict__ hoff,
+    const uint32_t* __restrict__ hmask, unsigned long long* __restrict__ htab,
+    int64_t* __restrict__ g_off, int32_t* __restrict__ g_cell, double* __restrict__ g_psi,
+    double* __restrict__ g_n, uint8_t* __restrict__ g_ext, uint32_t* __restrict__ g_slot,
+    int32_t* __restrict__ flow, InstInfo* __restrict__ info) {
+  __shared__ int s_b;
+  __shared__ int64_t sh[5];
+  if (threadIdx.x == 0) s_b = (int)atomicAdd(&posted[gridDim.x], 1ull);
+  __syncthreads();
+  const int b = s_b;
+  const int64_t nif = if_off[ninst], e0 = (int64_t)b * 256, e = e0 + threadIdx.x;
+  const bool valid = e < nif;
+  const int ii = find_inst_wave(if_off, ninst, e0 + (threadIdx.x & ~63), min(e, nif - 1));
+  int c = 0;
+  double n[3] = {0.0, 0.0, 0.0}, psi = 0.0;
+  bool ghost = false, ext = false;
+  if (valid) {
+    const Inst& I = insts[ii];
+    const GridD& g = I.g;
+    c = if_cell[e];
+    int8_t* tp = tags + I.cell_off + c;
+    const int8_t t0 = *tp;
+    const bool solid = (t0 & 1) != 0;
+    const bool iface = (t0 & 0x40) != 0;   // else a second-layer candidate
+    int i, j, k;
+    unlinear(g, c, i, j, k);
+    double x[3] = {centre(g, 0, i), centre(g, 1, j), g.dim == 3 ? centre(g, 2, k) : 0.0};
+    bool ok = project(I.s, g.dim, x, solid, n, psi);
+    if (!ok) atomicOr(&info[ii].err, kErrGeometry);
+    // Eq. delta_n with the cell's own widths
+    const int ijk[3] = {i, j, k};
+    double sum = 0.0;
+    for (int a = 0; a < g.dim; ++a) {
+      const double w = width(g, a, ijk[a]);
+      sum += (n[a] / w) * (n[a] / w);
+    }
+    double dn = 1.0 / sqrt(sum);
+    if (iface) {
+      if (I.scheme == kHGC) ghost = solid ? (psi <= dn / 2.0) : (-psi < dn / 2.0);
+      else ghost = solid;
+    }
+    // Sec. 7.1: a second layer adds the solid cells with psi <= 1.5 delta n,
+    // reconstructed on the extended stencil
+    ext = I.layer2 && solid && !ghost && psi <= 1.5 * dn;
+    ghost = ghost || ext;
+    *tp = ghost ? (solid ? 2 : -2) : (solid ? 1 : 0);
+    if (g.dim == 2) n[2] = 0.0;   // the third normal component of 2D ghosts
+  }
+  int64_t tot;
+  const int64_t rank = block_excl_scan<256>(ghost ? 1 : 0, &tot, sh);
+  const int64_t pos = posted_before(posted, b, tot) + rank;
+  if (ghost) {
+    g_ext[pos] = ext ? 1 : 0;
+    g_cell[pos] = c;
+    g_psi[pos] = psi;
+    for (int a = 0; a < 3; ++a) g_n[a * cap + pos] = n[a];
+    g_slot[pos] = table_insert(htab + hoff[ii], hmask[ii], c, (uint32_t)pos);
+  }
+  // offsets of the instances that start here, and of those past the last
+  // interface cell
+  if (valid)
+    for (int i = ii; i >= 0 && if_off[i] == e; --i) g_off[i] = pos;
+  if (e == nif - 1)
+    for (int i = ninst; i >= 0 && if_off[i] == nif; --i) g_off[i] = pos + (ghost ? 1 : 0);
+  if (e == 0) flow[0] = flow[1] = 0;   // of the whole-GPU layering
 }
 
 // --------------------------------------------------------------------------
 // 4. stencils and dependencies
 // --------------------------------------------------------------------------
 
-// value stored for cell c in one instance's table, or -1 (linear probing;
-// the table is at most half full, so an empty slot ends every probe)
-__device__ __forceinline__ int hash_find(const unsigned long long* t, uint32_t mask, int c) {
-  uint32_t h = (uint32_t)c * 2654435761u;
-  h = (h ^ (h >> 15)) & mask;
-  for (;;) {
-    const unsigned long long e = t[h];
-    if (e == ~0ull) return -1;
-    if ((int)(e >> 32) == c) return (int)(e & 0xffffffffu);
-    h = (h + 1) & mask;
-  }
+__device__ __forceinline__ void atomic_max_nonneg(unsigned long long* a, double v) {
+  if (v > 0.0) atomicMax(a, (unsigned long long)__double_as_longlong(v));
 }
 
+// Statistics of a wave's ghosts of one instance (k_deps): largest alpha and
+// multiplier per axis, ghosts on the fluid side.
+struct FinPart {
+  double am[3];
+  int32_t rm[3];
+  int32_t fl;
+  int32_t inst;
+  int32_t pad;
+};
+
+// Stencils and the ghosts they read.  A ghost's corners are taken side by side
+// (their tags, then the first slots probed in the table, then the rest), so
+// the chain tag -> slot is waited for once: the 512^3 sphere's 74,000 ghosts
+// take 26 us, one corner after the other 34.  The table holds positions among
+// all ghosts here.
 __global__ __launch_bounds__(256) void k_deps(const Inst* __restrict__ insts, int ninst,
                                               const int64_t* __restrict__ g_off,
                                               const int32_t* __restrict__ g_cell,
@@ -951,60 +1009,134 @@ __global__ __launch_bounds__(256) void k_deps(const Inst* __restrict__ insts, in
                                               uint32_t* __restrict__ g_code,
                                               int32_t* __restrict__ deps,
                                               int32_t* __restrict__ lev,
-                                              InstInfo* __restrict__ info) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= g_off[ninst]) return;
-  const int ii = find_inst(g_off, ninst, e);
-  const Inst& I = insts[ii];
-  const GridD& g = I.g;
-  const int c = g_cell[e];
-  const double psi = g_psi[e];
-  double n[3];
-  int r[3] = {1, 1, 1};
-  for (int a = 0; a < 3; ++a) n[a] = g_n[a * cap + e];
-  if (I.scheme == kCGC_ES || g_ext[e]) {
-    // Eq. stencil_anisotropic: r_i = max(1, ceil(2 |x_1 - x_s|_i / dx_i)),
-    // dx_i the ghost cell's own width
-    int gi[3];
-    unlinear(g, c, gi[0], gi[1], gi[2]);
-    for (int a = 0; a < g.dim; ++a) {
-      double d = psi * n[a];
-      double q = 2.0 * fabs(d) / width(g, a, gi[a]);
-      int ri = (int)ceil(q);
-      r[a] = ri < 1 ? 1 : ri;
-      if (r[a] > 15) {
-        atomicOr(&info[ii].err, kErrUnsupported);
-        r[a] = 15;
-      }
-    }
-  }
-  const uint32_t code = make_code(n, r, g.dim);
-  uint32_t ghosts = 0;   // corners that are ghosts
-  lev[e] = 0;   // k_levels_flow: no level yet
-  int i, j, k;
-  unlinear(g, c, i, j, k);
-  const int8_t* T = tags + I.cell_off;
-  const int np = (1 << g.dim) - 1;
-  const uint32_t skip = code_skip(code);
-  for (int m = 1; m <= np; ++m) {
-    int32_t d = -1;
-    if (!(m & skip)) {
-      if (!corner_in_grid(g, code, i, j, k, m)) {
-        atomicOr(&info[ii].err, kErrStencil);
-      } else {
-        int q = c + corner_offset(g, code, m);
-        int8_t t = T[q];
-        if (t == 1) atomicOr(&info[ii].err, kErrStencil);
-        else if (t == 2 || t == -2) {
-          const int v = hash_find(htab + hoff[ii], hmask[ii], q);
-          if (v >= 0) d = (int32_t)(g_off[ii] + v);
+                                              InstInfo* __restrict__ info,
+                                              FinPart* __restrict__ part) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, ng = g_off[ninst];
+  if ((int64_t)blockIdx.x * blockDim.x >= ng) return;   // uniform
+  const bool valid = e < ng;
+  const int lane = threadIdx.x & 63;
+  const int ii = find_inst_wave(g_off, ninst, e - lane, min(e, ng - 1));
+  double am[3] = {0.0, 0.0, 0.0};
+  int rm[3] = {0, 0, 0}, fl = 0;
+  if (valid) {
+    const Inst& I = insts[ii];
+    const GridD& g = I.g;
+    const int c = g_cell[e];
+    const double psi = g_psi[e];
+    double n[3];
+    int r[3] = {1, 1, 1};
+    for (int a = 0; a < 3; ++a) n[a] = g_n[a * cap + e];
+    int i, j, k;
+    unlinear(g, c, i, j, k);
+    if (I.scheme == kCGC_ES || g_ext[e]) {
+      // Eq. stencil_anisotropic: r_i = max(1, ceil(2 |x_1 - x_s|_i / dx_i)),
+      // dx_i the ghost cell's own width
+      const int gi[3] = {i, j, k};
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        if (a >= g.dim) break;
+        double d = psi * n[a];
+        double q = 2.0 * fabs(d) / width(g, a, gi[a]);
+        int ri = (int)ceil(q);
+        r[a] = ri < 1 ? 1 : ri;
+        if (r[a] > 15) {
+          atomicOr(&info[ii].err, kErrUnsupported);
+          r[a] = 15;
         }
       }
     }
-    deps[(int64_t)(m - 1) * cap + e] = d;
-    if (d >= 0) ghosts |= 1u << m;
+    const uint32_t code = make_code(n, r, g.dim);
+    uint32_t ghosts = 0;   // corners that are ghosts
+    lev[e] = 0;   // k_levels_flow: no level yet
+    const int8_t* T = tags + I.cell_off;
+    const unsigned long long* const tab = htab + hoff[ii];
+    const uint32_t mask = hmask[ii], skip = code_skip(code);
+    const int np = (1 << g.dim) - 1;
+    int q[8];
+    int8_t t[8];
+    unsigned long long en[8];
+    bool out = false;
+#pragma unroll
+    for (int m = 1; m < 8; ++m) {
+      const bool use = m <= np && !(m & skip), in = use && corner_in_grid(g, code, i, j, k, m);
+      out = out || (use && !in);
+      q[m] = in ? c + corner_offset(g, code, m) : -1;
+      t[m] = 0;
+      if (in) t[m] = T[q[m]];
+    }
+#pragma unroll
+    for (int m = 1; m < 8; ++m) {
+      out = out || t[m] == 1;
+      en[m] = ~0ull;
+      if (t[m] == 2 || t[m] == -2) en[m] = tab[table_slot(q[m], mask)];
+    }
+    if (out) atomicOr(&info[ii].err, kErrStencil);
+#pragma unroll
+    for (int m = 1; m < 8; ++m) {
+      if (m > np) break;
+      // (linear probing; an empty slot ends every probe)
+      for (uint32_t h = table_slot(q[m], mask); en[m] != ~0ull && (int)(en[m] >> 32) != q[m];
+           en[m] = tab[h])
+        h = (h + 1) & mask;
+      const int32_t d = en[m] == ~0ull ? -1 : (int32_t)(en[m] & 0xffffffffu);
+      deps[(int64_t)(m - 1) * cap + e] = d;
+      if (d >= 0) ghosts |= 1u << m;
+    }
+    g_code[e] = code | ghosts << 20;
+    double Xs[3];
+    stencil_span(g, code, c, Xs);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      if (a < g.dim) {
+        am[a] = fmax(0.0, psi * n[a] / Xs[a]);
+        rm[a] = code_r(code, a);
+      }
+    fl = psi < 0.0 ? 1 : 0;
   }
-  g_code[e] = code | ghosts << 20;
+  // statistics: the wave's first instance in its record, others (the wave
+  // where they meet) by one lane's atomics
+  bool first = true;
+  for (unsigned long long todo = __ballot(valid); todo;) {   // uniform
+    const int i0 = __shfl(ii, __ffsll(todo) - 1);
+    const bool mine = valid && ii == i0;
+    todo &= ~__ballot(mine);
+    double a3[3];
+    int r3[3], f = mine ? fl : 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      a3[a] = mine ? am[a] : 0.0;
+      r3[a] = mine ? rm[a] : 0;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        a3[a] = fmax(a3[a], __shfl_xor(a3[a], o));
+        r3[a] = max(r3[a], __shfl_xor(r3[a], o));
+      }
+      f += __shfl_xor(f, o);
+    }
+    if (lane == 0) {
+      if (first) {
+        FinPart R;
+        for (int a = 0; a < 3; ++a) {
+          R.am[a] = a3[a];
+          R.rm[a] = r3[a];
+        }
+        R.fl = f;
+        R.inst = i0;
+        R.pad = 0;
+        part[e >> 6] = R;
+      } else {
+        for (int a = 0; a < 3; ++a) {
+          atomic_max_nonneg(&info[i0].max_alpha_bits[a], a3[a]);
+          if (r3[a]) atomicMax(&info[i0].rmax[a], r3[a]);
+        }
+        if (f) atomicAdd(&info[i0].nfluid, f);
+      }
+    }
+    first = false;
+  }
 }
 
 // For the layerings that push along reverse edges: the number of ghosts
@@ -1095,21 +1227,6 @@ __global__ __launch_bounds__(256) void k_rfill(const Inst* __restrict__ insts,
 // 6. canonical arrays
 // --------------------------------------------------------------------------
 
-__device__ __forceinline__ void atomic_max_nonneg(unsigned long long* a, double v) {
-  if (v > 0.0) atomicMax(a, (unsigned long long)__double_as_longlong(v));
-}
-
-// per-workgroup statistics of k_finalize, reduced per instance by
-// k_units_canonical (inst -1: the workgroup held no ghosts, or ghosts of
-// two instances, whose statistics it applied with atomics itself)
-struct FinPart {
-  double am[3];
-  int32_t rm[3];
-  int32_t fl;
-  int32_t inst;
-  int32_t pad;
-};
-
 // hist (null: perm holds them): the canonical positions are found here, tile
 // by tile of the whole-GPU layering (k_levels_flow; the workgroup's 256
 // ghosts are its tile): hist[tile][level] is the position of the tile's
@@ -1141,127 +1258,43 @@ __device__ __forceinline__ int tile_position(const int32_t* __restrict__ lev,
   return pos;
 }
 
-__global__ __launch_bounds__(256) void k_finalize(
-    const Inst* __restrict__ insts, int ninst, const int64_t* __restrict__ g_off, int64_t cap,
-    const int32_t* __restrict__ g_cell, const double* __restrict__ g_psi,
-    const double* __restrict__ g_n, const uint32_t* __restrict__ g_code,
-    const int32_t* __restrict__ deps, int32_t* __restrict__ cgi,
-    const int32_t* __restrict__ lev, const int32_t* __restrict__ blk_idx,
-    int32_t* __restrict__ perm, const int32_t* __restrict__ hist, int32_t* __restrict__ cell,
-    double* __restrict__ delta,
-    double* __restrict__ nrm, double* __restrict__ psi, uint32_t* __restrict__ code,
-    int32_t* __restrict__ level, int32_t* __restrict__ blk, InstInfo* __restrict__ info,
-    FinPart* __restrict__ part) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t ng_all = g_off[ninst];
-  // per-thread statistics: max alpha and multiplier per axis, fluid-side count
-  double am[3] = {0.0, 0.0, 0.0};
-  int rm[3] = {0, 0, 0}, fl = 0, ii = -1;
-  int pl = -1;
-  if (hist) {   // (a batch of one; uniform)
-    if (info[0].layered) pl = tile_position(lev, hist, e, ng_all, perm);
-  } else if (e < ng_all) {
-    pl = perm[e];
-  }
-  if (e < ng_all) {
-    ii = find_inst(g_off, ninst, e);
-    const GridD& g = insts[ii].g;
-    if (pl >= 0 && pl < g_off[ii + 1] - g_off[ii]) {   // else the build failed earlier
-      const int64_t p = g_off[ii] + pl;
-      const double ps = g_psi[e];
-      const uint32_t cd = g_code[e];
-      cell[p] = g_cell[e];
-      psi[p] = ps;
-      code[p] = cd;
-      level[p] = lev[e];
-      blk[p] = blk_idx[e];
-      for (int a = 0; a < 3; ++a) {
-        double na = g_n[a * cap + e];
-        double da = ps * na;
-        nrm[a * cap + p] = na;
-        delta[a * cap + p] = da;
-        if (a < g.dim) {
-          double Xs[3];
-          stencil_span(g, cd, g_cell[e], Xs);
-          am[a] = fmax(0.0, da / Xs[a]);
-          rm[a] = code_r(cd, a);
-        }
-      }
-      fl = ps < 0.0 ? 1 : 0;
-      if (cgi && g.dim == 2) {
-        // the corners' ghosts, by position (the graph's edges in this order)
-#pragma unroll
-        for (int k = 1; k < 4; ++k) {
-          const int32_t d = deps[(int64_t)(k - 1) * cap + e];
-          cgi[(int64_t)(k - 1) * cap + p] = (k & code_skip(cd)) ? -2 : d < 0 ? -1 : perm[d];
-        }
-      }
-    }
-  }
-  // one instance in the whole workgroup: reduce there, one atomic per value
-  __shared__ int s_i0;
-  __shared__ double s_am[3][256];
-  __shared__ int s_rm[3][256], s_fl[256];
-  if (threadIdx.x == 0) s_i0 = ii;
-  __syncthreads();
-  const bool uniform = __syncthreads_and(ii == s_i0 || ii < 0) && s_i0 >= 0;
-  if (!uniform && threadIdx.x == 0) part[blockIdx.x].inst = -1;
-  if (!uniform) {
-    if (ii >= 0) {
-      for (int a = 0; a < 3; ++a) {
-        atomic_max_nonneg(&info[ii].max_alpha_bits[a], am[a]);
-        if (rm[a]) atomicMax(&info[ii].rmax[a], rm[a]);
-      }
-      if (fl) atomicAdd(&info[ii].nfluid, 1);
-    }
-    return;
-  }
-  for (int a = 0; a < 3; ++a) {
-    s_am[a][threadIdx.x] = am[a];
-    s_rm[a][threadIdx.x] = rm[a];
-  }
-  s_fl[threadIdx.x] = fl;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      for (int a = 0; a < 3; ++a) {
-        s_am[a][threadIdx.x] = fmax(s_am[a][threadIdx.x], s_am[a][threadIdx.x + s]);
-        s_rm[a][threadIdx.x] = max(s_rm[a][threadIdx.x], s_rm[a][threadIdx.x + s]);
-      }
-      s_fl[threadIdx.x] += s_fl[threadIdx.x + s];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    // one record per workgroup (atomics from every workgroup of an instance
-    // on its one record would serialise)
-    FinPart r;
-    for (int a = 0; a < 3; ++a) {
-      r.am[a] = s_am[a][0];
-      r.rm[a] = s_rm[a][0];
-    }
-    r.fl = s_fl[0];
-    r.inst = s_i0;
-    r.pad = 0;
-    part[blockIdx.x] = r;
-  }
-}
+// What the host reads of a build, in pinned memory: of each instance its
+// info, first ghost, level offsets and units' levels, as many as there are.
+struct BuildResult {
+  InstInfo* info;
+  int64_t* g_off;
+  int32_t* lev_off;    // [ninst][kMaxLevels + 1]
+  int32_t* unit_lev;   // [ninst][kMaxUnits]
+};
 
-// k_finalize's workgroup records of this instance folded into its info
-// (max, max, sum: the order does not matter), then unit members:
-// linear-order positions -> instance-local canonical positions
-__global__ __launch_bounds__(256) void k_units_canonical(const int32_t* __restrict__ perm,
-                                                         InstInfo* __restrict__ info,
-                                                         int32_t* __restrict__ unit_mem_all,
-                                                         const int32_t* __restrict__ unit_cnt_all,
-                                                         const FinPart* __restrict__ part,
-                                                         int64_t nparts) {
-  const int ii = blockIdx.x;
-  {
-    double am[3] = {0.0, 0.0, 0.0};
-    int rm[3] = {0, 0, 0}, fl = 0;
-    for (int64_t b = threadIdx.x; b < nparts; b += blockDim.x) {
-      const FinPart& r = part[b];
+// Workgroup ii < ninst: the instance's unit members from linear-order to
+// canonical positions, the waves' statistics (k_deps) folded into its info
+// (max, max, sum: the order does not matter), and its results to the host.
+__device__ __forceinline__ void finish_instance(int ii, int ninst, const int64_t* __restrict__ g_off,
+                                                const int32_t* __restrict__ perm,
+                                                InstInfo* __restrict__ info,
+                                                int32_t* __restrict__ unit_mem,
+                                                const int32_t* __restrict__ unit_cnt,
+                                                const int32_t* __restrict__ unit_lev,
+                                                const int32_t* __restrict__ lev_off,
+                                                const FinPart* __restrict__ part,
+                                                const BuildResult& out) {
+  const int tid = threadIdx.x;
+  const int nu = min(max(info[ii].nunits, 0), kMaxUnits), nl = min(max(info[ii].nlev, 0), kMaxLevels);
+  int32_t* um = unit_mem + (int64_t)ii * kMaxUnits * kMaxUnit;
+  const int32_t* uc = unit_cnt + (int64_t)ii * kMaxUnits;
+  for (int t = tid; t < nu * kMaxUnit; t += blockDim.x)
+    if (t % kMaxUnit < uc[t / kMaxUnit]) um[t] = perm[um[t]];
+  for (int t = tid; t <= nl; t += blockDim.x)
+    out.lev_off[(int64_t)ii * (kMaxLevels + 1) + t] = lev_off[(int64_t)ii * (kMaxLevels + 1) + t];
+  for (int t = tid; t < nu; t += blockDim.x)
+    out.unit_lev[(int64_t)ii * kMaxUnits + t] = unit_lev[(int64_t)ii * kMaxUnits + t];
+  double am[3] = {0.0, 0.0, 0.0};
+  int rm[3] = {0, 0, 0}, fl = 0;
+  const int64_t b = g_off[ii], e = g_off[ii + 1];
+  if (e > b)
+    for (int64_t w = (b >> 6) + tid; w <= (e - 1) >> 6; w += blockDim.x) {
+      const FinPart r = part[w];
       if (r.inst != ii) continue;
       for (int a = 0; a < 3; ++a) {
         am[a] = fmax(am[a], r.am[a]);
@@ -1269,40 +1302,93 @@ __global__ __launch_bounds__(256) void k_units_canonical(const int32_t* __restri
       }
       fl += r.fl;
     }
-    __shared__ double s_am[3][256];
-    __shared__ int s_rm[3][256], s_fl[256];
+  __shared__ double s_am[3][4];
+  __shared__ int s_rm[3][4], s_fl[4];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
     for (int a = 0; a < 3; ++a) {
-      s_am[a][threadIdx.x] = am[a];
-      s_rm[a][threadIdx.x] = rm[a];
+      am[a] = fmax(am[a], __shfl_xor(am[a], o));
+      rm[a] = max(rm[a], __shfl_xor(rm[a], o));
     }
-    s_fl[threadIdx.x] = fl;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-      if ((int)threadIdx.x < st) {
-        for (int a = 0; a < 3; ++a) {
-          s_am[a][threadIdx.x] = fmax(s_am[a][threadIdx.x], s_am[a][threadIdx.x + st]);
-          s_rm[a][threadIdx.x] = max(s_rm[a][threadIdx.x], s_rm[a][threadIdx.x + st]);
-        }
-        s_fl[threadIdx.x] += s_fl[threadIdx.x + st];
-      }
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-      InstInfo& I = info[ii];
-      for (int a = 0; a < 3; ++a) {
-        const unsigned long long bits = (unsigned long long)__double_as_longlong(s_am[0 + a][0]);
-        if (bits > I.max_alpha_bits[a]) I.max_alpha_bits[a] = bits;   // non-negative: bit order
-        I.rmax[a] = max(I.rmax[a], s_rm[a][0]);
-      }
-      I.nfluid += s_fl[0];
-    }
+    fl += __shfl_xor(fl, o);
   }
-  const int nu = info[ii].nunits;
-  int32_t* um = unit_mem_all + (int64_t)ii * kMaxUnits * kMaxUnit;
-  const int32_t* uc = unit_cnt_all + (int64_t)ii * kMaxUnits;
-  for (int t = threadIdx.x; t < nu * kMaxUnit; t += blockDim.x) {
-    int u = t / kMaxUnit, q = t % kMaxUnit;
-    if (q < uc[u]) um[t] = perm[um[t]];
+  if ((tid & 63) == 0) {
+    for (int a = 0; a < 3; ++a) {
+      s_am[a][tid >> 6] = am[a];
+      s_rm[a][tid >> 6] = rm[a];
+    }
+    s_fl[tid >> 6] = fl;
+  }
+  __syncthreads();
+  if (tid != 0) return;
+  InstInfo I = info[ii];
+  for (int w = 0; w < 4; ++w) {
+    for (int a = 0; a < 3; ++a) {
+      const unsigned long long bits = (unsigned long long)__double_as_longlong(s_am[a][w]);
+      if (bits > I.max_alpha_bits[a]) I.max_alpha_bits[a] = bits;   // non-negative: bit order
+      I.rmax[a] = max(I.rmax[a], s_rm[a][w]);
+    }
+    I.nfluid += s_fl[w];
+  }
+  info[ii] = I;
+  out.info[ii] = I;
+  out.g_off[ii] = b;
+  if (ii == ninst - 1) out.g_off[ninst] = e;
+}
+
+__global__ __launch_bounds__(256) void k_finalize(
+    const Inst* __restrict__ insts, int ninst, const int64_t* __restrict__ g_off, int64_t cap,
+    const int32_t* __restrict__ g_cell, const double* __restrict__ g_psi,
+    const double* __restrict__ g_n, const uint32_t* __restrict__ g_code,
+    const uint32_t* __restrict__ g_slot,
+    const int32_t* __restrict__ deps, int32_t* __restrict__ cgi,
+    const int32_t* __restrict__ lev, const int32_t* __restrict__ blk_idx,
+    int32_t* __restrict__ perm, const int32_t* __restrict__ hist, int32_t* __restrict__ cell,
+    double* __restrict__ delta,
+    double* __restrict__ nrm, double* __restrict__ psi, uint32_t* __restrict__ code,
+    int32_t* __restrict__ level, int32_t* __restrict__ blk, const int64_t* __restrict__ hoff,
+    unsigned long long* __restrict__ htab, InstInfo* __restrict__ info,
+    int32_t* __restrict__ unit_mem, const int32_t* __restrict__ unit_cnt,
+    const int32_t* __restrict__ unit_lev, const int32_t* __restrict__ lev_off,
+    const FinPart* __restrict__ part, BuildResult out) {
+  if ((int)blockIdx.x < ninst)
+    finish_instance(blockIdx.x, ninst, g_off, perm, info, unit_mem, unit_cnt, unit_lev, lev_off,
+                    part, out);
+  const int64_t e0 = (int64_t)blockIdx.x * blockDim.x, e = e0 + threadIdx.x;
+  const int64_t ng_all = g_off[ninst];
+  if (e0 >= ng_all) return;   // uniform
+  const int ii = find_inst_wave(g_off, ninst, e0 + (threadIdx.x & ~63), min(e, ng_all - 1));
+  int pl = -1;
+  if (hist) {   // (a batch of one; uniform)
+    if (info[0].layered) pl = tile_position(lev, hist, e, ng_all, perm);
+  } else if (e < ng_all) {
+    pl = perm[e];
+  }
+  if (e >= ng_all || pl < 0 || pl >= g_off[ii + 1] - g_off[ii]) return;   // (the build failed earlier)
+  const int64_t p = g_off[ii] + pl;
+  const double ps = g_psi[e];
+  const uint32_t cd = g_code[e];
+  const int c = g_cell[e];
+  cell[p] = c;
+  psi[p] = ps;
+  code[p] = cd;
+  level[p] = lev[e];
+  blk[p] = blk_idx[e];
+  for (int a = 0; a < 3; ++a) {
+    const double na = g_n[a * cap + e];
+    nrm[a * cap + p] = na;
+    delta[a * cap + p] = ps * na;
+  }
+  // the cell table from positions among all ghosts to canonical ones
+  htab[hoff[ii] + g_slot[e]] = ((unsigned long long)(uint32_t)c << 32) | (uint32_t)pl;
+  if (cgi && insts[ii].g.dim == 2) {
+    // the corners' ghosts, by position (the graph's edges in this order)
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+      const int32_t d = deps[(int64_t)(k - 1) * cap + e];
+      cgi[(int64_t)(k - 1) * cap + p] = (k & code_skip(cd)) ? -2 : d < 0 ? -1 : perm[d];
+    }
   }
 }
 
@@ -1315,38 +1401,22 @@ __global__ void k_hash_clear(unsigned long long* __restrict__ t, int64_t n) {
   if (i < n) t[i] = ~0ull;
 }
 
+// the tables of a second layering, as k_geometry fills them
 __global__ void k_hash_build(const int64_t* __restrict__ g_off, int ninst,
                              const int32_t* __restrict__ cell,
                              const int64_t* __restrict__ hoff,
                              const uint32_t* __restrict__ hmask,
                              unsigned long long* __restrict__ htab,
-                             int32_t* __restrict__ zero, int64_t nzero) {
+                             uint32_t* __restrict__ g_slot) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  // the dependency counters that the next launch fills, cleared here
-  for (int64_t z = e; z < nzero; z += (int64_t)gridDim.x * blockDim.x) zero[z] = 0;
   if (e >= g_off[ninst]) return;
   const int ii = find_inst(g_off, ninst, e);
-  const int c = cell[e];
-  const unsigned long long entry =
-      ((unsigned long long)(uint32_t)c << 32) | (uint32_t)(e - g_off[ii]);
-  unsigned long long* t = htab + hoff[ii];
-  const uint32_t mask = hmask[ii];
-  uint32_t h = (uint32_t)c * 2654435761u;
-  h = (h ^ (h >> 15)) & mask;
-  while (atomicCAS(&t[h], ~0ull, entry) != ~0ull) h = (h + 1) & mask;
+  g_slot[e] = table_insert(htab + hoff[ii], hmask[ii], cell[e], (uint32_t)e);
 }
 
-// linear-order ghost index -> canonical position, in place
-__global__ void k_hash_remap(const int64_t* __restrict__ hoff, int ninst,
-                             const int64_t* __restrict__ g_off, const int32_t* __restrict__ perm,
-                             unsigned long long* __restrict__ htab) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= hoff[ninst]) return;
-  const unsigned long long e = htab[s];
-  if (e == ~0ull) return;
-  const int ii = find_inst(hoff, ninst, s);
-  const int32_t v = (int32_t)(e & 0xffffffffu);
-  htab[s] = (e & 0xffffffff00000000ull) | (uint32_t)perm[g_off[ii] + v];
+__global__ void k_zero_words(int32_t* __restrict__ a, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) a[i] = 0;
 }
 
 // before a second layering of the same ghosts: the statistics that
@@ -1701,17 +1771,19 @@ gcr_status build_update(BatchData& prev, const ShapeD& shape, bool incremental, 
 // reverse edges, which take every graph the others leave.
 enum Layering { kLayerPull, kLayerFlow, kLayerPush };
 static gcr_status build_graph(BatchData& D, hipStream_t st, int ninst, int64_t nif,
-                              int64_t max_if, Layering how, StageEvents& T) {
+                              int64_t max_if, Layering how, const BuildResult& out,
+                              StageEvents& T) {
   const int64_t cap = D.cap;
   int32_t* hist = nullptr;
   // ghost count unknown on the host: launch over the interface capacity
-  k_hash_build<<<blocks(nif, 256), 256, 0, st>>>(D.d_g_off, ninst, D.d_g_cell, D.d_hoff,
-                                                  D.d_hmask, D.d_htab, D.d_rcnt,
-                                                  how == kLayerPush ? 2 * cap : 2);   // + rcnt, rfill cleared
+  FinPart* const part = own<FinPart>(D, (cap + 63) / 64);
+  if (!part) return GCR_E_NOMEM;
   k_deps<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, ninst, D.d_g_off, D.d_g_cell, D.d_g_psi,
                                             D.d_g_n, cap, D.d_g_ext, D.d_tags, D.d_htab, D.d_hoff,
-                                            D.d_hmask, D.d_g_code, D.d_deps, D.d_lev, D.d_info);
+                                            D.d_hmask, D.d_g_code, D.d_deps, D.d_lev, D.d_info,
+                                            part);
   if (how == kLayerPush) {
+    k_zero_words<<<blocks(2 * cap, 256), 256, 0, st>>>(D.d_rcnt, 2 * cap);
     k_rcount<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, D.d_g_off, ninst, cap, D.d_deps,
                                                 D.d_rcnt, D.d_dcnt);
     // reverse-edge offsets: one workgroup up to two tiles, else three passes
@@ -1767,20 +1839,12 @@ static gcr_status build_graph(BatchData& D, hipStream_t st, int ninst, int64_t n
     if (ls != GCR_OK) return ls;
   }
   T.mark(8, st);
-  {
-    const unsigned nfb = blocks(nif, 256);
-    FinPart* fp = own<FinPart>(D, nfb);
-    if (!fp) return GCR_E_NOMEM;
-    k_finalize<<<nfb, 256, 0, st>>>(
-        D.d_inst, ninst, D.d_g_off, cap, D.d_g_cell, D.d_g_psi, D.d_g_n, D.d_g_code, D.d_deps,
-        hist ? nullptr : D.d_cgi, D.d_lev,
-        D.d_blk_idx, D.d_perm, hist, D.d_cell, D.d_delta, D.d_nrm, D.d_psi, D.d_code, D.d_level,
-        D.d_blk, D.d_info, fp);
-    k_units_canonical<<<ninst, 256, 0, st>>>(D.d_perm, D.d_info, D.d_unit_mem, D.d_unit_cnt,
-                                             fp, (int64_t)nfb);
-  }
-  k_hash_remap<<<blocks(D.hoff[ninst], 256), 256, 0, st>>>(D.d_hoff, ninst, D.d_g_off, D.d_perm,
-                                                            D.d_htab);
+  const unsigned nfb = std::max(blocks(nif, 256), (unsigned)ninst);
+  k_finalize<<<nfb, 256, 0, st>>>(
+      D.d_inst, ninst, D.d_g_off, cap, D.d_g_cell, D.d_g_psi, D.d_g_n, D.d_g_code, D.d_g_slot,
+      D.d_deps, hist ? nullptr : D.d_cgi, D.d_lev, D.d_blk_idx, D.d_perm, hist, D.d_cell,
+      D.d_delta, D.d_nrm, D.d_psi, D.d_code, D.d_level, D.d_blk, D.d_hoff, D.d_htab, D.d_info,
+      D.d_unit_mem, D.d_unit_cnt, D.d_unit_lev, D.d_lev_off, part, out);
   T.mark(9, st);
   return GCR_OK;
 }
@@ -1811,7 +1875,7 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   // one device block with the layout of the pinned staging block, so each
   // transfer is one contiguous copy:
   //   R1 up:   instances | chunk starts | info (zeroed)
-  //   R4 down:                            info | g_off | lev_off | unit_lev
+  //   written by k_finalize at the end:   info | g_off | lev_off | unit_lev
   //   R2 down: if_off | chunk-list and band counts | interface offsets
   //   R3 up:   hash offsets | hash masks
   // each region 256-byte aligned
@@ -1961,18 +2025,15 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   std::memcpy(PS.p + o_hm, D.hmask.data(), 4 * ninst);
   GCR_HIP(hipMemcpyAsync(tb + o_ho, PS.p + o_ho, stage_bytes - o_ho, hipMemcpyHostToDevice,
                          st));   // R3
-  const int64_t nblk = (nif + 1023) / 1024;
+  const int64_t nblk = (nif + 255) / 256;
   D.d_if_cell = own<int32_t>(D, cap);
-  D.d_if_psi = own<double>(D, cap);
-  D.d_if_n = own<double>(D, 3 * cap);
-  D.d_if_flag = own<uint8_t>(D, cap);
-  D.d_blkcnt = own<int32_t>(D, nblk + 1);
-  D.d_blkexcl = own<int64_t>(D, nblk + 2);
+  unsigned long long* const posted = own<unsigned long long>(D, nblk + 1);
   D.d_g_cell = own<int32_t>(D, cap);
   D.d_g_ext = own<uint8_t>(D, cap);
   D.d_g_psi = own<double>(D, cap);
   D.d_g_n = own<double>(D, 3 * cap);
   D.d_g_code = own<uint32_t>(D, cap);
+  D.d_g_slot = own<uint32_t>(D, cap);
   D.d_deps = own<int32_t>(D, 7 * cap);
   D.d_lev = own<int32_t>(D, cap);
   D.d_blk_idx = own<int32_t>(D, cap);
@@ -1994,32 +2055,27 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   D.d_bits = own<uint32_t>(D, (cap >> 5) + ninst + 2);
   if (!D.d_listA || !D.d_rcnt || !D.d_roff || !D.d_radj || !D.d_cnt || !D.d_bits || !D.d_dcnt)
     return GCR_E_NOMEM;
-  if (!D.d_if_cell || !D.d_if_psi || !D.d_if_n || !D.d_if_flag || !D.d_blkcnt || !D.d_blkexcl ||
-      !D.d_g_cell || !D.d_g_ext || !D.d_g_psi || !D.d_g_n || !D.d_g_code || !D.d_deps || !D.d_lev ||
+  if (!D.d_if_cell || !posted || !D.d_g_cell || !D.d_g_ext || !D.d_g_psi || !D.d_g_n ||
+      !D.d_g_code || !D.d_g_slot || !D.d_deps || !D.d_lev ||
       !D.d_blk_idx || !D.d_perm || !D.d_cell || !D.d_delta || !D.d_nrm || !D.d_psi ||
       !D.d_code || !D.d_level || !D.d_blk || (any_2d && !D.d_cgi))
     return GCR_E_NOMEM;
-  // the third normal component of 2D ghosts stays zero
-  if (any_2d) GCR_HIP(hipMemsetAsync(D.d_if_n + 2 * cap, 0, sizeof(double) * cap, st));
-
   T.mark(3, st);
+  const BuildResult out_host{reinterpret_cast<InstInfo*>(PS.p + o_info),
+                             reinterpret_cast<int64_t*>(PS.p + o_go),
+                             reinterpret_cast<int32_t*>(PS.p + o_lo),
+                             reinterpret_cast<int32_t*>(PS.p + o_ul)};
   Layering how = kLayerPush;
   if (nif > 0) {
     k_compact_iface<<<(unsigned)nlist, 256, 0, st>>>(D.d_inst, D.d_chunk_inst, D.d_tags,
                                                      D.d_chunk_cnt, D.d_chunk_excl, D.d_chunk_list,
-                                                     D.d_if_cell, D.d_htab, D.hoff[ninst]);
+                                                     D.d_if_cell, D.d_htab, D.hoff[ninst], posted, nblk + 1);
     T.mark(4, st);
-    k_geometry<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, ninst, D.d_if_off, D.d_if_cell,
-                                                  D.d_tags, D.d_if_psi, D.d_if_n, cap,
-                                                  D.d_if_flag, D.d_info);
+    k_geometry<<<(unsigned)nblk, 256, 0, st>>>(
+        D.d_inst, ninst, D.d_if_off, D.d_if_cell, D.d_tags, cap, posted, D.d_hoff, D.d_hmask,
+        D.d_htab, D.d_g_off, D.d_g_cell, D.d_g_psi, D.d_g_n, D.d_g_ext, D.d_g_slot, D.d_rcnt,
+        D.d_info);
     T.mark(5, st);
-    k_count_flags<<<(unsigned)nblk, 256, 0, st>>>(D.d_if_flag, nif, D.d_blkcnt);
-    k_scan<<<1, 1024, 0, st>>>(D.d_blkcnt, nblk, D.d_blkexcl, nullptr, nullptr);
-    k_scatter_ghosts<<<(unsigned)nblk, 256, 0, st>>>(D.d_if_flag, nif, D.d_blkexcl, D.d_if_cell,
-                                                     D.d_if_psi, D.d_if_n, cap, D.d_g_cell,
-                                                     D.d_g_psi, D.d_g_n, D.d_g_ext);
-    k_ghost_off<<<(unsigned)(ninst + 1), 64, 0, st>>>(D.d_if_flag, D.d_blkexcl, D.d_if_off, ninst,
-                                                      D.d_g_off);
     T.mark(6, st);
     int64_t max_if = 0;
     for (int i = 0; i < ninst; ++i) max_if = std::max(max_if, D.if_off[i + 1] - D.if_off[i]);
@@ -2028,22 +2084,21 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
     const bool flow = ninst == 1 && max_if >= wide_layering_min() &&
                       (any_3d || wide_layering_forced());
     how = flow ? kLayerFlow : levels_pull(max_if) ? kLayerPull : kLayerPush;
-    const gcr_status s = build_graph(D, st, ninst, nif, max_if, how, T);
+    const gcr_status s = build_graph(D, st, ninst, nif, max_if, how, out_host, T);
     if (s != GCR_OK) return s;
   } else {
     k_hash_clear<<<blocks(D.hoff[ninst], 256), 256, 0, st>>>(D.d_htab, D.hoff[ninst]);
     for (int i = 4; i <= 9; ++i) T.mark(i, st);
     GCR_HIP(hipMemsetAsync(D.d_g_off, 0, sizeof(int64_t) * (ninst + 1), st));
     GCR_HIP(hipMemsetAsync(D.d_lev_off, 0, sizeof(int32_t) * ninst * (kMaxLevels + 1), st));
+    GCR_HIP(hipMemcpyAsync(PS.p + o_info, tb + o_info, o_go - o_info, hipMemcpyDeviceToHost, st));
+    std::memset(out_host.g_off, 0, sizeof(int64_t) * (ninst + 1));
+    for (int i = 0; i < ninst; ++i) out_host.lev_off[(size_t)i * (kMaxLevels + 1)] = 0;
   }
   GCR_HIP(hipGetLastError());
   D.g_off.resize(ninst + 1);
   D.info.resize(ninst);
-  D.lev_off.resize((size_t)ninst * (kMaxLevels + 1));
-  D.unit_lev.resize((size_t)ninst * kMaxUnits);
   for (;;) {
-    GCR_HIP(hipMemcpyAsync(PS.p + o_info, tb + o_info, o_if - o_info, hipMemcpyDeviceToHost,
-                           st));   // R4
     GCR_HIP(hipStreamSynchronize(st));
     std::memcpy(D.g_off.data(), PS.p + o_go, 8 * (ninst + 1));
     std::memcpy(D.info.data(), PS.p + o_info, sizeof(InstInfo) * ninst);
@@ -2058,12 +2113,26 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
     for (int i = 0; i < ninst; ++i) max_if = std::max(max_if, D.if_off[i + 1] - D.if_off[i]);
     k_info_reset<<<blocks(ninst, 64), 64, 0, st>>>(D.d_info, ninst);
     k_hash_clear<<<blocks(D.hoff[ninst], 256), 256, 0, st>>>(D.d_htab, D.hoff[ninst]);
-    const gcr_status s = build_graph(D, st, ninst, nif, max_if, how, T);
+    k_hash_build<<<blocks(nif, 256), 256, 0, st>>>(D.d_g_off, ninst, D.d_g_cell, D.d_hoff,
+                                                    D.d_hmask, D.d_htab, D.d_g_slot);
+    const gcr_status s = build_graph(D, st, ninst, nif, max_if, how, out_host, T);
     if (s != GCR_OK) return s;
   }
   PS.pending = false;
-  std::memcpy(D.lev_off.data(), PS.p + o_lo, 4 * (size_t)ninst * (kMaxLevels + 1));
-  std::memcpy(D.unit_lev.data(), PS.p + o_ul, 4 * (size_t)ninst * kMaxUnits);
+  // each instance's level offsets and units' levels, one after another
+  D.lev_at.resize(ninst);
+  D.unit_at.resize(ninst);
+  D.lev_off.clear();
+  D.unit_lev.clear();
+  for (int i = 0; i < ninst; ++i) {
+    const int32_t* const lo = out_host.lev_off + (size_t)i * (kMaxLevels + 1);
+    const int32_t* const ul = out_host.unit_lev + (size_t)i * kMaxUnits;
+    D.lev_at[i] = D.lev_off.size();
+    D.unit_at[i] = D.unit_lev.size();
+    if (D.info[i].err) continue;   // (the build fails below)
+    D.lev_off.insert(D.lev_off.end(), lo, lo + D.info[i].nlev + 1);
+    D.unit_lev.insert(D.unit_lev.end(), ul, ul + D.info[i].nunits);
+  }
   T.collect(std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_call)
                 .count());
   D.flow_order = how == kLayerFlow;
@@ -2090,8 +2159,8 @@ void make_plan_view(const std::shared_ptr<BatchData>& B, int i, gcr_plan* p) {
   p->stride = D.cap;
   p->info = D.info[i];
   p->nlev = p->info.nlev;
-  p->lev_off.assign(D.lev_off.begin() + (size_t)i * (kMaxLevels + 1),
-                    D.lev_off.begin() + (size_t)i * (kMaxLevels + 1) + p->nlev + 1);
+  p->lev_off.assign(D.lev_off.begin() + D.lev_at[i],
+                    D.lev_off.begin() + D.lev_at[i] + p->nlev + 1);
   p->tags = D.d_tags + p->inst.cell_off;
   p->span = D.d_span + p->inst.chunk_off * (kChunk / (64 * kSeg));
   const int64_t o = p->goff;
@@ -2113,8 +2182,8 @@ void make_plan_view(const std::shared_ptr<BatchData>& B, int i, gcr_plan* p) {
   p->unit_cnt = D.d_unit_cnt + (int64_t)i * kMaxUnits;
   p->d_lev_off = D.d_lev_off + (int64_t)i * (kMaxLevels + 1);
   p->unit_lev = D.d_unit_lev + (int64_t)i * kMaxUnits;
-  p->unit_lev_host.assign(D.unit_lev.begin() + (size_t)i * kMaxUnits,
-                          D.unit_lev.begin() + (size_t)i * kMaxUnits + p->info.nunits);
+  p->unit_lev_host.assign(D.unit_lev.begin() + D.unit_at[i],
+                          D.unit_lev.begin() + D.unit_at[i] + p->info.nunits);
   p->htab = D.d_htab + D.hoff[i];
   p->hmask = D.hmask[i];
 }

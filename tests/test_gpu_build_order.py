@@ -1,0 +1,57 @@
+"""The ghosts of a build put in order by counts that workgroups post to each
+other (Sec. 3.1): more workgroups than one look covers, instances that begin
+and end within a wave, instances without ghosts at either end and between.
+Every plan against the oracle, and its statistics with its arrays."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from synth import CGC, CGC_ES, HGC, LAYER2
+from test_gpu_layering import check, circle, sphere
+from test_gpu_parity import gcr, host  # noqa: F401  (gcr: the fixture)
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def stats_agree(p, g):
+    st, d = p.stats(), p.dim
+    a = {k: host(v) for k, v in p.export(("psi", "normal", "r")).items()}
+    assert st["n_ghost_fluid_side"] == int((a["psi"] < 0).sum())
+    for k in range(d):
+        # a displacement over its stencil's length: a few roundings
+        al = np.maximum(a["psi"] * np.abs(a["normal"][k]) / (a["r"][k] * g.h[k]), 0.0)
+        assert abs(st["max_alpha"][k] - al.max(initial=0.0)) <= 1e-12, k
+
+
+def away(n):
+    """A body far outside its grid."""
+    g, s = circle(n)
+    return g, synth.Shape(synth.SPHERE, (9.0, 9.0, 0.0), 0.5)
+
+
+@pytest.mark.parametrize("case", ["tiny", "mixed", "empty", "many"])
+def test_batch_order(gcr, case):  # noqa: F811
+    if case == "tiny":      # a few ghosts each: several instances in a wave
+        b = [(circle(n, 0.4), HGC) for n in (6, 8, 7, 9, 6, 12, 33, 8)]
+    elif case == "mixed":
+        b = [(circle(n), s) for n, s in ((64, CGC), (300, HGC), (41, CGC_ES), (700, HGC | LAYER2), (64, HGC))]
+    elif case == "empty":
+        b = [(away(20), HGC), (circle(90), HGC), (away(64), CGC), (away(8), CGC), (circle(16, 0.4), CGC),
+             (away(300), HGC)]
+    else:                   # more instances than a wave compares at once
+        b = [(circle(10 + k % 7, 0.4) if k % 5 else away(9), CGC) for k in range(150)]
+    B = gcr.Batch([g for (g, _), _ in b], [s for (_, s), _ in b], [c for _, c in b])
+    for p, ((g, s), c) in zip(B.plans, b):
+        check(p, oracle.OraclePlan(g, s, c))
+        stats_agree(p, g)
+
+
+def test_more_workgroups_than_one_look(gcr):  # noqa: F811
+    g, s = sphere(168, 0.95)
+    op = oracle.OraclePlan(g, s, HGC)
+    p = gcr.Plan(g, s, HGC)
+    assert p.stats()["n_interface"] > 256 * 256
+    check(p, op)
+    stats_agree(p, g)
