@@ -326,8 +326,19 @@ int profiling_mask();   // bit 0 build stages, bit 1 batched forward
 // Exclusive scan of n counts into excl[n + 1] (total last); where list is
 // set, the indices with a nonzero count go there in order and their number
 // to nlist[0].  tsum: ceil(n / 8192) + 1 int64 of scratch (plan.hip).
-void launch_scan(const int32_t* cnt, int64_t n, int64_t* excl, int32_t* list,
-                 int32_t* nlist, int64_t* tsum, hipStream_t st);
+// What a scan of chunk counts also leaves (see instance_offsets); off null:
+// nothing.
+struct ScanOffsets {
+  const int64_t* start;     // [ninst + 1] first chunk of each instance
+  int ninst;
+  int64_t *off, *host_off;  // [ninst + 1]
+  int64_t* hoff;            // [ninst + 1], or null: the offsets alone
+  uint32_t* hmask;          // [ninst]
+  const int32_t* nband;     // [kBandStripes], 16 apart
+  int32_t* host_counts;     // [2] listed chunks, band segments
+};
+void launch_scan(const int32_t* cnt, int64_t n, int64_t* excl, int32_t* list, int32_t* nlist,
+                 int64_t* tsum, hipStream_t st, const ScanOffsets* O = nullptr);
 // Tiled batched fill: 0 off, 1 from a batch's second forward call (the
 // default), 2 from its first (process-wide).
 void set_batch_tiling(int mode);

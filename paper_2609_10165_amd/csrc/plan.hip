@@ -302,11 +302,59 @@ __device__ __forceinline__ int64_t scan_tile(const int32_t* __restrict__ cnt, in
   return tot;
 }
 
-// the whole scan by one workgroup (short inputs)
+// Offsets of the instances from the scan of their chunks, and what follows
+// from them: off[i] = excl[start[i]]; with hoff, the instances' cell tables
+// too (a power of two, at least 64 and twice the interface cells: at most half
+// full).  The offsets, the listed chunks and the band segments go to the host
+// as well (pinned memory), so nothing is copied back or up between the halves
+// of a build.  By one workgroup of 1024, after its own scan or a launch.
+__device__ __forceinline__ void instance_offsets(const ScanOffsets& O, const int64_t* excl,
+                                                 const int32_t* nlist, int64_t* sh) {
+  int64_t carry = 0;
+  for (int i0 = 0; i0 <= O.ninst; i0 += 1024) {
+    const int i = i0 + (int)threadIdx.x;
+    int64_t at = 0, size = 0;
+    if (i <= O.ninst) {
+      at = excl[O.start[i]];
+      O.off[i] = at;
+      O.host_off[i] = at;
+    }
+    if (!O.hoff) continue;
+    if (i < O.ninst) {
+      const int64_t twice = 2 * (excl[O.start[i + 1]] - at);
+      size = 64;
+      while (size < twice) size <<= 1;
+      O.hmask[i] = (uint32_t)(size - 1);
+    }
+    int64_t tot;
+    const int64_t before = carry + block_excl_scan<1024>(size, &tot, sh);
+    if (i <= O.ninst) O.hoff[i] = before;
+    carry += tot;
+  }
+  if (!O.hoff) return;
+  if (threadIdx.x < 64) {
+    int v = 0;
+    for (int q = threadIdx.x; q < kBandStripes; q += 64) v += O.nband[q * 16];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
+    if (threadIdx.x == 0) {
+      O.host_counts[0] = nlist[0];
+      O.host_counts[1] = v;
+    }
+  }
+}
+
+__global__ __launch_bounds__(1024) void k_offsets(const int64_t* __restrict__ excl,
+                                                  const int32_t* __restrict__ nlist,
+                                                  ScanOffsets O) {
+  __shared__ int64_t sh[17];
+  instance_offsets(O, excl, nlist, sh);
+}
+
+// the whole scan by one workgroup (short inputs), and the offsets if asked for
 __global__ __launch_bounds__(1024) void k_scan(const int32_t* __restrict__ cnt, int64_t n,
-                                               int64_t* __restrict__ excl,
-                                               int32_t* __restrict__ list,
-                                               int32_t* __restrict__ nlist) {
+                                               int64_t* excl, int32_t* __restrict__ list,
+                                               int32_t* nlist, ScanOffsets O) {
   __shared__ int64_t sh[17];
   int64_t carry = 0;
   for (int64_t t0 = 0; t0 < n; t0 += kScanTile) carry += scan_tile(cnt, n, t0, carry, excl, list, sh);
@@ -314,6 +362,9 @@ __global__ __launch_bounds__(1024) void k_scan(const int32_t* __restrict__ cnt, 
     excl[n] = carry & (kScanHi - 1);
     if (nlist) nlist[0] = (int32_t)(carry >> 40);
   }
+  if (!O.off) return;
+  __syncthreads();   // the scan's values, before they are read back
+  instance_offsets(O, excl, nlist, sh);
 }
 
 // long inputs: packed total of each tile, one workgroup per tile ...
@@ -362,15 +413,16 @@ __global__ __launch_bounds__(1024) void k_scan_down(const int32_t* __restrict__ 
 // One workgroup up to two tiles, else the three-pass form (tsum: ntiles
 // int64 of scratch).
 void launch_scan(const int32_t* cnt, int64_t n, int64_t* excl, int32_t* list,
-                 int32_t* nlist, int64_t* tsum, hipStream_t st) {
+                 int32_t* nlist, int64_t* tsum, hipStream_t st, const ScanOffsets* O) {
   const int64_t ntiles = (n + kScanTile - 1) / kScanTile;
   if (ntiles <= 2 || !tsum) {
-    k_scan<<<1, 1024, 0, st>>>(cnt, n, excl, list, nlist);
+    k_scan<<<1, 1024, 0, st>>>(cnt, n, excl, list, nlist, O ? *O : ScanOffsets{});
     return;
   }
   k_scan_reduce<<<(unsigned)ntiles, 1024, 0, st>>>(cnt, n, tsum);
   k_scan_top<<<1, 1024, 0, st>>>(tsum, ntiles, excl + n, nlist);
   k_scan_down<<<(unsigned)ntiles, 1024, 0, st>>>(cnt, n, tsum, excl, list);
+  if (O) k_offsets<<<1, 1024, 0, st>>>(excl, nlist, *O);
 }
 
 // Fresh cells of a moved body (Sec. 7.1: a moving boundary exposes fresh
@@ -759,13 +811,6 @@ __global__ __launch_bounds__(256) void k_count_marks(const Inst* __restrict__ in
     count_marks_chunk(list[it], insts, ninst, chunk_start, tags, chunk_cnt);
     __syncthreads();   // s is reused by the next chunk
   }
-}
-
-// off[i] = excl[start[i]] for the instance boundaries
-__global__ void k_gather_off(const int64_t* __restrict__ excl, const int64_t* __restrict__ start,
-                             int n, int64_t* __restrict__ off) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i <= n) off[i] = excl[start[i]];
 }
 
 __global__ __launch_bounds__(256) void k_compact_iface(const Inst* __restrict__ insts,
@@ -1875,9 +1920,9 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   // one device block with the layout of the pinned staging block, so each
   // transfer is one contiguous copy:
   //   R1 up:   instances | chunk starts | info (zeroed)
-  //   written by k_finalize at the end:   info | g_off | lev_off | unit_lev
-  //   R2 down: if_off | chunk-list and band counts | interface offsets
-  //   R3 up:   hash offsets | hash masks
+  //   stored by k_finalize at the end:    info | g_off | lev_off | unit_lev
+  //   stored by the scans halfway: if_off | chunk-list and band counts | interface offsets
+  //   device only: hash offsets | hash masks
   // each region 256-byte aligned
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   const size_t o_inst = 0, o_cs = o_inst + al(sizeof(Inst) * ninst);
@@ -1966,13 +2011,17 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
                   D.d_chunk_cnt, D.d_band, D.d_nband, T.event(10), T.event(11), st, W,
                   prev ? &U : nullptr);
   T.mark(1, st);
-  launch_scan(D.d_chunk_cnt, chunks, D.d_chunk_excl, D.d_chunk_list, D.d_nchunk_list,
-              D.d_scan_tmp, st);
+  ScanOffsets O{};
+  O.start = D.d_chunk_start;
+  O.ninst = ninst;
+  O.nband = D.d_nband;
   if (any_layer2) {
     // interface counts of the instances, then the second-layer candidates
     // join the list: mark, recount every chunk, scan again
-    k_gather_off<<<blocks(ninst + 1, 64), 64, 0, st>>>(D.d_chunk_excl, D.d_chunk_start, ninst,
-                                                       D.d_iface_off);
+    O.off = D.d_iface_off;
+    O.host_off = reinterpret_cast<int64_t*>(PS.p + o_io);
+    launch_scan(D.d_chunk_cnt, chunks, D.d_chunk_excl, D.d_chunk_list, D.d_nchunk_list,
+                D.d_scan_tmp, st, &O);
     // with a chunk list, marks outside it extend it, and the count covers
     // the list; else every chunk is counted
     const bool listed = prev || !W.every_chunk;
@@ -1982,35 +2031,29 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
     k_count_marks<<<(unsigned)(listed ? std::min<int64_t>(chunks, kListGrid) : chunks), 256, 0,
                     st>>>(D.d_inst, ninst, D.d_chunk_start, D.d_tags, D.d_chunk_cnt,
                           listed ? D.d_dirty_list : nullptr, D.d_ndirty);
-    launch_scan(D.d_chunk_cnt, chunks, D.d_chunk_excl, D.d_chunk_list, D.d_nchunk_list,
-                D.d_scan_tmp, st);
   }
-  k_gather_off<<<blocks(ninst + 1, 64), 64, 0, st>>>(D.d_chunk_excl, D.d_chunk_start, ninst,
-                                                     D.d_if_off);
+  O.off = D.d_if_off;
+  O.host_off = reinterpret_cast<int64_t*>(PS.p + o_if);
+  O.hoff = D.d_hoff;
+  O.hmask = D.d_hmask;
+  O.host_counts = reinterpret_cast<int32_t*>(PS.p + o_nl);
+  launch_scan(D.d_chunk_cnt, chunks, D.d_chunk_excl, D.d_chunk_list, D.d_nchunk_list,
+              D.d_scan_tmp, st, &O);
   T.mark(2, st);
   GCR_HIP(hipGetLastError());
-  D.if_off.resize(ninst + 1);
-  // R2 (the interface offsets only mean something with a second layer)
-  GCR_HIP(hipMemcpyAsync(PS.p + o_if, tb + o_if, o_ho - o_if, hipMemcpyDeviceToHost, st));
   GCR_HIP(hipStreamSynchronize(st));
-  std::memcpy(D.if_off.data(), PS.p + o_if, 8 * (ninst + 1));
+  D.if_off.assign(O.host_off, O.host_off + ninst + 1);
   D.iface_off = D.if_off;   // interface cells alone (second-layer candidates excluded)
   if (any_layer2) std::memcpy(D.iface_off.data(), PS.p + o_io, 8 * (ninst + 1));
-  int32_t nlist = 0, nband = 0;
-  std::memcpy(&nlist, PS.p + o_nl, sizeof(int32_t));
-  for (int q = 0; q < kBandStripes; ++q) {
-    int32_t v = 0;
-    std::memcpy(&v, PS.p + o_nl + 64 + 64 * q, sizeof(int32_t));
-    nband += v;
-  }
-  D.nband = nband;
+  const int32_t nlist = O.host_counts[0];
+  D.nband = O.host_counts[1];
   const int64_t nif = D.if_off[ninst];
   const int64_t cap = std::max<int64_t>(nif, 1);
   D.nif = nif;
   D.cap = cap;
   // cell -> ghost tables: at most half full (ghosts <= interface cells);
   // keyed to linear-order ghost indices while the plan is built, remapped
-  // to canonical positions once those are known
+  // to canonical positions once those are known (instance_offsets' sizes)
   D.hoff.assign(ninst + 1, 0);
   D.hmask.assign(ninst, 0);
   for (int i = 0; i < ninst; ++i) {
@@ -2021,10 +2064,6 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   }
   D.d_htab = own<unsigned long long>(D, D.hoff[ninst]);
   if (!D.d_htab) return GCR_E_NOMEM;
-  std::memcpy(PS.p + o_ho, D.hoff.data(), 8 * (ninst + 1));
-  std::memcpy(PS.p + o_hm, D.hmask.data(), 4 * ninst);
-  GCR_HIP(hipMemcpyAsync(tb + o_ho, PS.p + o_ho, stage_bytes - o_ho, hipMemcpyHostToDevice,
-                         st));   // R3
   const int64_t nblk = (nif + 255) / 256;
   D.d_if_cell = own<int32_t>(D, cap);
   unsigned long long* const posted = own<unsigned long long>(D, nblk + 1);

@@ -55,3 +55,13 @@ def test_more_workgroups_than_one_look(gcr):  # noqa: F811
     assert p.stats()["n_interface"] > 256 * 256
     check(p, op)
     stats_agree(p, g)
+
+
+def test_more_instances_than_a_workgroup(gcr):  # noqa: F811
+    """Offsets of more instances than the workgroup that finds them has
+    threads, the last ones beyond it among several sizes."""
+    b = [circle(6 + k % 3, 0.4) if k % 11 else away(9) for k in range(1030)]
+    B = gcr.Batch([g for g, _ in b], [s for _, s in b], [CGC] * len(b))
+    for k in list(range(5)) + list(range(1015, 1030)):
+        check(B.plans[k], oracle.OraclePlan(*b[k], CGC))
+    assert [p.n_ghost for p in B.plans[:990:33]] == [B.plans[0].n_ghost] * 30
