@@ -1083,11 +1083,11 @@ static bool tile_setup(BatchFwdState* S, gcr_batch* b, int dim, hipStream_t st,
   const size_t o_sb = al(sizeof(int32_t) * 4 * n);
   const size_t o_cnt = o_sb + al(sizeof(int64_t) * (n + 1));
   const size_t o_fill = o_cnt + al(sizeof(int32_t) * slots);
-  const size_t o_off = o_fill + al(sizeof(int32_t) * slots);
+  const size_t o_post = o_fill + al(sizeof(int32_t) * slots);
+  const size_t o_off = o_post + al(sizeof(unsigned long long) * scan_words(slots));
   const size_t o_list = o_off + al(sizeof(int64_t) * (slots + 1));
   const size_t o_nlist = o_list + al(sizeof(int32_t) * slots);
-  const size_t o_tsum = o_nlist + al(sizeof(int32_t) * 4);
-  const size_t o_bucket = o_tsum + al(sizeof(int64_t) * ((slots + 8191) / 8192 + 2));
+  const size_t o_bucket = o_nlist + al(sizeof(int32_t) * 4);
   const size_t o_mem = o_bucket + al(sizeof(int32_t) * ng_total);
   const size_t o_ref = o_mem + al(sizeof(int32_t) * mcap);
   const size_t o_mbase = o_ref + al(sizeof(int16_t) * 7 * mcap);
@@ -1140,12 +1140,13 @@ static bool tile_setup(BatchFwdState* S, gcr_batch* b, int dim, hipStream_t st,
   T.mcap = mcap;
   S->tmax = tmax;
   auto nb = [](int64_t v) { return (unsigned)((v + 255) / 256); };
-  const int64_t nz = (int64_t)(o_off - o_cnt) / 4;   // count and fillc (with padding)
+  const int64_t nz = (int64_t)(o_off - o_cnt) / 4;   // count, fillc and the scan's posts (with padding)
   k_tile_zero<<<nb(nz), 256, 0, st>>>(T.count, nz);
   k_tile_zero<<<1, 256, 0, st>>>(T.mtotal, 2);
   BStatic bs{S->d_plans, S->d_levp, S->d_nlev};
   k_tile_count<<<nb(ng_total), 256, 0, st>>>(bs, T, 0);
-  launch_scan(T.count, slots, off, list, nlist, reinterpret_cast<int64_t*>(d + o_tsum), st);
+  launch_scan(T.count, slots, off, list, nlist, 
+              reinterpret_cast<unsigned long long*>(d + o_post), st);
   k_tile_count<<<nb(ng_total), 256, 0, st>>>(bs, T, 1);
   const void* kc = dim == 2 ? reinterpret_cast<const void*>(&k_tile_closure<2>)
                             : reinterpret_cast<const void*>(&k_tile_closure<3>);

@@ -123,7 +123,9 @@ __global__ __launch_bounds__(256) void k_spans(const Inst* __restrict__ insts, i
                                                int32_t* __restrict__ chunk_cnt,
                                                uint64_t* __restrict__ bandmask,
                                                int8_t* __restrict__ tags,
-                                               int32_t* __restrict__ nband) {
+                                               int32_t* __restrict__ nband,
+                                               unsigned long long* __restrict__ posted,
+                                               int64_t nposted) {
   constexpr int kSpan = 64 * kSeg, kPer = kChunk / kSpan, kSpans = kSpanChunks * kPer;
   static_assert(kSpans <= 64, "one wave tests the workgroup's spans");
   __shared__ int8_t s_flag[kSpans];
@@ -131,6 +133,9 @@ __global__ __launch_bounds__(256) void k_spans(const Inst* __restrict__ insts, i
   const int tid = (int)threadIdx.x;
   const int64_t c0 = (int64_t)blockIdx.x * kSpanChunks;
   if (blockIdx.x == 0 && tid < kBandStripes) nband[tid * 16] = 0;   // k_band_iface counts from zero
+  // (what the long scans post, from zero)
+  for (int64_t q = (int64_t)blockIdx.x * 256 + tid; q < nposted; q += (int64_t)gridDim.x * 256)
+    posted[q] = 0ull;
   if (tid < kSpans) {
     const int64_t chunk = c0 + tid / kPer;
     int8_t r = -1;
@@ -514,7 +519,7 @@ void launch_classify(const Inst* insts, int ninst, const int64_t* chunk_start, i
   const bool every = !U && W.every_chunk;
   k_spans<<<(unsigned)((chunks + kSpanChunks - 1) / kSpanChunks), 256, 0, st>>>(
       insts, ninst, chunk_start, chunks, span, chunk_inst, W.flag, chunk_cnt, mask,
-      U || every ? nullptr : tags, nband);
+      U || every ? nullptr : tags, nband, W.scan_tmp, W.scan_words);
   if (ev_prepass) (void)hipEventRecord(ev_prepass, st);
   if (every) {
     k_classify<0><<<(unsigned)chunks, 256, 0, st>>>(insts, chunk_inst, span, tags, chunk_cnt, mask,

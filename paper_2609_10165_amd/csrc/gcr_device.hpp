@@ -184,10 +184,10 @@ __device__ __forceinline__ int cell_of(const GridD& g, int ax, double x) {
 }
 
 __device__ __forceinline__ void unlinear(const GridD& g, int c, int& i, int& j, int& k) {
-  i = c % g.n[0];
-  int t = c / g.n[0];
-  j = t % g.n[1];
-  k = t / g.n[1];
+  const int t = c / g.n[0];
+  i = c - t * g.n[0];
+  k = g.dim == 2 ? 0 : t / g.n[1];
+  j = t - k * g.n[1];
 }
 
 __device__ __forceinline__ int linear(const GridD& g, int i, int j, int k) {

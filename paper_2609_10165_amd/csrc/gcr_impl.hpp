@@ -87,7 +87,7 @@ struct BatchData {
   int32_t* d_dirty = nullptr;        // chunks the store pass classifies (flags, then list)
   int32_t* d_dirty_list = nullptr;
   int32_t* d_ndirty = nullptr;
-  int64_t* d_scan_tmp = nullptr;     // tile totals of the long chunk scan
+  unsigned long long* d_scan_tmp = nullptr;   // what the long scans' workgroups post
   int64_t* d_iface_off = nullptr;    // interface cells per instance (second layer)
   int64_t* d_chunk_excl = nullptr;
   int64_t* d_if_off = nullptr;       // [ninst+1]
@@ -208,7 +208,8 @@ struct ClassifyWork {
   int32_t* list;               // [chunks]
   int32_t* nlist;              // [1]
   int64_t* scan_excl;          // [chunks + 1] scan scratch
-  int64_t* scan_tmp;           // scan tile totals
+  unsigned long long* scan_tmp;   // zeroed by the span pass: the list's scan_words(chunks), ...
+  int64_t scan_words;          // ... and what follows for later scans
   bool every_chunk;            // full build: the store pass takes every chunk (2D grids)
 };
 struct ClassifyUpdate {
@@ -338,7 +339,8 @@ struct ScanOffsets {
   int32_t* host_counts;     // [2] listed chunks, band segments
 };
 void launch_scan(const int32_t* cnt, int64_t n, int64_t* excl, int32_t* list, int32_t* nlist,
-                 int64_t* tsum, hipStream_t st, const ScanOffsets* O = nullptr);
+                 unsigned long long* posted, hipStream_t st, const ScanOffsets* O = nullptr);
+int64_t scan_words(int64_t n);   // of `posted`, zeroed before each scan
 // Tiled batched fill: 0 off, 1 from a batch's second forward call (the
 // default), 2 from its first (process-wide).
 void set_batch_tiling(int mode);

@@ -255,13 +255,17 @@ __device__ bool project(const ShapeD& s, int dim, const double x[3], bool solid,
 // 2. scans and compactions
 // --------------------------------------------------------------------------
 
+__global__ void k_zero_words(int32_t* __restrict__ a, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) a[i] = 0;
+}
+
 // excl[i] = sum cnt[0..i), excl[n] = total.  If list is given, the indices
 // i with cnt[i] > 0 are written to it in ascending order and their number
-// to nlist[0]: each count carries a flag in bits 40 and up, so one scan
-// yields both (counts stay below 2^40).  Tiles of 8 values per thread of a
-// 1024-thread workgroup.
-constexpr int kScanT = 8, kScanTile = 1024 * kScanT;
-constexpr int64_t kScanHi = int64_t(1) << 40;
+// to nlist[0]: each count carries a flag in bits 31 and up, so one scan
+// yields both (their sum stays below 2^31).  Tiles of 8 values per thread.
+constexpr int kScanT = 8;
+constexpr int64_t kScanHi = int64_t(1) << 31;
 
 __device__ __forceinline__ void scan_load(const int32_t* __restrict__ cnt, int64_t n, int64_t b,
                                           int v[kScanT]) {
@@ -277,29 +281,30 @@ __device__ __forceinline__ void scan_load(const int32_t* __restrict__ cnt, int64
   }
 }
 
-// One tile from t0 with the packed prefix `carry`; returns the tile's
-// packed total.  Every thread of the workgroup calls it.
-__device__ __forceinline__ int64_t scan_tile(const int32_t* __restrict__ cnt, int64_t n,
-                                             int64_t t0, int64_t carry,
-                                             int64_t* __restrict__ excl,
-                                             int32_t* __restrict__ list, int64_t* sh) {
-  const int64_t b = t0 + (int64_t)threadIdx.x * kScanT;
-  int v[kScanT];
-  scan_load(cnt, n, b, v);
+// the packed sum of a thread's values
+__device__ __forceinline__ int64_t scan_sum(const int v[kScanT]) {
   int64_t sum = 0;
 #pragma unroll
   for (int q = 0; q < kScanT; ++q) sum += v[q] + (v[q] > 0 ? kScanHi : 0);
-  int64_t tot;
-  int64_t run = carry + block_excl_scan<1024>(sum, &tot, sh);
+  return sum;
+}
+
+// the values from b on, `run` the packed sum before them
+__device__ __forceinline__ void scan_store(const int v[kScanT], int64_t n, int64_t b, int64_t run,
+                                           int64_t* excl, int32_t* __restrict__ list) {
 #pragma unroll
   for (int q = 0; q < kScanT; ++q) {
     if (b + q < n) {
       excl[b + q] = run & (kScanHi - 1);
-      if (list && v[q] > 0) list[run >> 40] = (int32_t)(b + q);
+      if (list && v[q] > 0) list[run >> 31] = (int32_t)(b + q);
     }
     run += v[q] + (v[q] > 0 ? kScanHi : 0);
   }
-  return tot;
+}
+
+template <bool Others>
+__device__ __forceinline__ int64_t scanned(const int64_t* p) {
+  return Others ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
 }
 
 // Offsets of the instances from the scan of their chunks, and what follows
@@ -307,27 +312,29 @@ __device__ __forceinline__ int64_t scan_tile(const int32_t* __restrict__ cnt, in
 // too (a power of two, at least 64 and twice the interface cells: at most half
 // full).  The offsets, the listed chunks and the band segments go to the host
 // as well (pinned memory), so nothing is copied back or up between the halves
-// of a build.  By one workgroup of 1024, after its own scan or a launch.
+// of a build.  By the last workgroup of the scan to finish; where there are
+// others, what they stored is read past its own caches.
+template <int BS, bool Others>
 __device__ __forceinline__ void instance_offsets(const ScanOffsets& O, const int64_t* excl,
-                                                 const int32_t* nlist, int64_t* sh) {
+                                                 int32_t nlisted, int64_t* sh) {
   int64_t carry = 0;
-  for (int i0 = 0; i0 <= O.ninst; i0 += 1024) {
+  for (int i0 = 0; i0 <= O.ninst; i0 += BS) {
     const int i = i0 + (int)threadIdx.x;
     int64_t at = 0, size = 0;
     if (i <= O.ninst) {
-      at = excl[O.start[i]];
+      at = scanned<Others>(excl + O.start[i]);
       O.off[i] = at;
       O.host_off[i] = at;
     }
     if (!O.hoff) continue;
     if (i < O.ninst) {
-      const int64_t twice = 2 * (excl[O.start[i + 1]] - at);
+      const int64_t twice = 2 * (scanned<Others>(excl + O.start[i + 1]) - at);
       size = 64;
       while (size < twice) size <<= 1;
       O.hmask[i] = (uint32_t)(size - 1);
     }
     int64_t tot;
-    const int64_t before = carry + block_excl_scan<1024>(size, &tot, sh);
+    const int64_t before = carry + block_excl_scan<BS>(size, &tot, sh);
     if (i <= O.ninst) O.hoff[i] = before;
     carry += tot;
   }
@@ -338,105 +345,144 @@ __device__ __forceinline__ void instance_offsets(const ScanOffsets& O, const int
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
     if (threadIdx.x == 0) {
-      O.host_counts[0] = nlist[0];
+      O.host_counts[0] = nlisted;
       O.host_counts[1] = v;
     }
   }
 }
 
-__global__ __launch_bounds__(1024) void k_offsets(const int64_t* __restrict__ excl,
-                                                  const int32_t* __restrict__ nlist,
-                                                  ScanOffsets O) {
-  __shared__ int64_t sh[17];
-  instance_offsets(O, excl, nlist, sh);
+// Elements before workgroup b's own `tot`, for workgroups numbered in the
+// order they started: each posts its count, sums those posted before it, BS at
+// a time, back to the nearest that has posted its sum, and posts its own sum.
+// Workgroups wait only for ones that started earlier and post their counts
+// without waiting, so every wait ends.  (Called by all BS threads.)  The
+// numbers come from one counter, about 20 ns each across the chip, so where
+// there would be more than a few hundred workgroups they are larger instead.
+constexpr unsigned long long kPostCount = 1ull << 62, kPostSum = 2ull << 62;
+template <int BS>
+__device__ __forceinline__ int64_t posted_before(unsigned long long* __restrict__ posted, int b,
+                                                 int64_t tot) {
+  __shared__ int64_t s_sum[BS / 64];
+  __shared__ int s_end[BS / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  if (tid == 0)
+    __hip_atomic_store(&posted[b], (b == 0 ? kPostSum : kPostCount) | (unsigned long long)tot,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int64_t before = 0;
+  for (int top = b; top > 0; top -= BS) {
+    const int j = top - 1 - tid;
+    unsigned long long v = kPostSum;   // (before the first: nothing)
+    if (j >= 0)
+      while ((v = __hip_atomic_load(&posted[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
+      }
+    const unsigned long long sums = __ballot((v & kPostSum) != 0);
+    const int end = sums ? __ffsll(sums) - 1 : 64;
+    int64_t x = lane <= end ? (int64_t)(v & (kPostCount - 1)) : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+    if (lane == 0) {
+      s_sum[wv] = x;
+      s_end[wv] = end;
+    }
+    __syncthreads();
+    bool found = false;
+    for (int w = 0; w < BS / 64 && !found; ++w) {
+      before += s_sum[w];
+      found = s_end[w] < 64;
+    }
+    __syncthreads();
+    if (found) break;
+  }
+  if (tid == 0 && b > 0)
+    __hip_atomic_store(&posted[b], kPostSum | (unsigned long long)(before + tot), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  return before;
 }
 
-// the whole scan by one workgroup (short inputs), and the offsets if asked for
+// Short inputs: the whole scan by one workgroup, and the offsets if asked for.
 __global__ __launch_bounds__(1024) void k_scan(const int32_t* __restrict__ cnt, int64_t n,
                                                int64_t* excl, int32_t* __restrict__ list,
                                                int32_t* nlist, ScanOffsets O) {
   __shared__ int64_t sh[17];
   int64_t carry = 0;
-  for (int64_t t0 = 0; t0 < n; t0 += kScanTile) carry += scan_tile(cnt, n, t0, carry, excl, list, sh);
-  if (threadIdx.x == 0) {
-    excl[n] = carry & (kScanHi - 1);
-    if (nlist) nlist[0] = (int32_t)(carry >> 40);
-  }
-  if (!O.off) return;
-  __syncthreads();   // the scan's values, before they are read back
-  instance_offsets(O, excl, nlist, sh);
-}
-
-// long inputs: packed total of each tile, one workgroup per tile ...
-__global__ __launch_bounds__(1024) void k_scan_reduce(const int32_t* __restrict__ cnt, int64_t n,
-                                                      int64_t* __restrict__ tsum) {
-  __shared__ int64_t sh[17];
-  int v[kScanT];
-  scan_load(cnt, n, (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanT, v);
-  int64_t sum = 0;
-#pragma unroll
-  for (int q = 0; q < kScanT; ++q) sum += v[q] + (v[q] > 0 ? kScanHi : 0);
-  int64_t tot;
-  (void)block_excl_scan<1024>(sum, &tot, sh);
-  if (threadIdx.x == 0) tsum[blockIdx.x] = tot;
-}
-
-// ... their exclusive scan in place, the total and the list length ...
-__global__ __launch_bounds__(1024) void k_scan_top(int64_t* __restrict__ tsum, int64_t ntiles,
-                                                   int64_t* __restrict__ excl_n,
-                                                   int32_t* __restrict__ nlist) {
-  __shared__ int64_t sh[17];
-  int64_t carry = 0;
-  for (int64_t t0 = 0; t0 < ntiles; t0 += 1024) {
-    const int64_t t = t0 + threadIdx.x;
-    const int64_t v = t < ntiles ? tsum[t] : 0;
+  for (int64_t t0 = 0; t0 < n; t0 += 1024 * kScanT) {
+    const int64_t b = t0 + (int64_t)threadIdx.x * kScanT;
+    int v[kScanT];
+    scan_load(cnt, n, b, v);
     int64_t tot;
-    const int64_t pre = block_excl_scan<1024>(v, &tot, sh);
-    if (t < ntiles) tsum[t] = carry + pre;
+    const int64_t before = block_excl_scan<1024>(scan_sum(v), &tot, sh);
+    scan_store(v, n, b, carry + before, excl, list);
     carry += tot;
   }
   if (threadIdx.x == 0) {
-    excl_n[0] = carry & (kScanHi - 1);
-    if (nlist) nlist[0] = (int32_t)(carry >> 40);
+    excl[n] = carry & (kScanHi - 1);
+    if (nlist) nlist[0] = (int32_t)(carry >> 31);
   }
+  if (!O.off) return;
+  __syncthreads();   // the scan's values, before they are read back
+  instance_offsets<1024, false>(O, excl, (int32_t)(carry >> 31), sh);
 }
 
-// ... then every tile again from its offset
-__global__ __launch_bounds__(1024) void k_scan_down(const int32_t* __restrict__ cnt, int64_t n,
-                                                    const int64_t* __restrict__ toff,
-                                                    int64_t* __restrict__ excl,
-                                                    int32_t* __restrict__ list) {
-  __shared__ int64_t sh[17];
-  (void)scan_tile(cnt, n, (int64_t)blockIdx.x * kScanTile, toff[blockIdx.x], excl, list, sh);
+// Longer ones: a tile per workgroup, the sums before it from what the
+// workgroups post (posted: [tiles], then the numbers started and finished,
+// from zero).  32,768 chunks of a 512^3 grid: 7.1 us in one launch, in three
+// (totals, their scan, the tiles again) 15 and their gaps.
+__global__ __launch_bounds__(256) void k_scan_tiles(const int32_t* __restrict__ cnt, int64_t n,
+                                                    int64_t* excl, int32_t* __restrict__ list,
+                                                    int32_t* nlist,
+                                                    unsigned long long* __restrict__ posted,
+                                                    ScanOffsets O) {
+  __shared__ int64_t sh[5];
+  __shared__ int s_b, s_nlist;
+  if (threadIdx.x == 0) s_b = (int)atomicAdd(&posted[gridDim.x], 1ull);
+  __syncthreads();
+  const int t = s_b;
+  const int64_t b = ((int64_t)t * 256 + threadIdx.x) * kScanT;
+  int v[kScanT];
+  scan_load(cnt, n, b, v);
+  int64_t tot;
+  const int64_t rank = block_excl_scan<256>(scan_sum(v), &tot, sh);
+  const int64_t before = posted_before<256>(posted, t, tot);
+  scan_store(v, n, b, before + rank, excl, list);
+  if (t == (int)gridDim.x - 1 && threadIdx.x == 0) {
+    excl[n] = (before + tot) & (kScanHi - 1);
+    if (nlist) nlist[0] = (int32_t)((before + tot) >> 31);
+  }
+  if (!O.off) return;   // uniform
+  __threadfence();
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    s_b = atomicAdd(&posted[gridDim.x + 1], 1ull) == gridDim.x - 1;
+    __threadfence();
+    if (s_b) s_nlist = __hip_atomic_load(nlist, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (s_b) instance_offsets<256, true>(O, excl, s_nlist, sh);   // uniform
 }
 
-// One workgroup up to two tiles, else the three-pass form (tsum: ntiles
-// int64 of scratch).
-void launch_scan(const int32_t* cnt, int64_t n, int64_t* excl, int32_t* list,
-                 int32_t* nlist, int64_t* tsum, hipStream_t st, const ScanOffsets* O) {
-  const int64_t ntiles = (n + kScanTile - 1) / kScanTile;
-  if (ntiles <= 2 || !tsum) {
-    k_scan<<<1, 1024, 0, st>>>(cnt, n, excl, list, nlist, O ? *O : ScanOffsets{});
-    return;
-  }
-  k_scan_reduce<<<(unsigned)ntiles, 1024, 0, st>>>(cnt, n, tsum);
-  k_scan_top<<<1, 1024, 0, st>>>(tsum, ntiles, excl + n, nlist);
-  k_scan_down<<<(unsigned)ntiles, 1024, 0, st>>>(cnt, n, tsum, excl, list);
-  if (O) k_offsets<<<1, 1024, 0, st>>>(excl, nlist, *O);
+// One workgroup takes 8,192 values about as fast as four launched with their
+// posts (4 us); `posted`: scan_words(n) zeroed words.
+constexpr int64_t kScanAlone = 1024 * kScanT, kScanTile = 256 * kScanT;
+int64_t scan_words(int64_t n) { return n <= kScanAlone ? 0 : (n + kScanTile - 1) / kScanTile + 2; }
+void launch_scan(const int32_t* cnt, int64_t n, int64_t* excl, int32_t* list, int32_t* nlist,
+                 unsigned long long* posted, hipStream_t st, const ScanOffsets* O) {
+  const ScanOffsets o = O ? *O : ScanOffsets{};
+  if (n <= kScanAlone)
+    k_scan<<<1, 1024, 0, st>>>(cnt, n, excl, list, nlist, o);
+  else
+    k_scan_tiles<<<(unsigned)((n + kScanTile - 1) / kScanTile), 256, 0, st>>>(cnt, n, excl, list,
+                                                                             nlist, posted, o);
 }
 
 // Fresh cells of a moved body (Sec. 7.1: a moving boundary exposes fresh
 // fluid cells): cells whose centre was solid before the move (tag 1 or 2)
 // and is fluid after it (tag 0 or -2); uncovered ones were not ghosts before
-// (tag 1), so no value was ever reconstructed there.  One workgroup per
-// chunk of 4096 cells, 16 per thread (tag arrays are 256-byte aligned).  A
-// chunk whose spans both plans settled to the same class holds no fresh
-// cell (each of its cells lies on that side of both boundaries) and is
-// skipped on its span flags alone.
-__global__ void k_fresh_zero(int64_t* counts) {
-  if (threadIdx.x < 2) counts[threadIdx.x] = 0;
-}
-
+// (tag 1), so no value was ever reconstructed there.  Tags (their
+// arrays are 256-byte aligned) are not read where both plans settled their
+// span to the same class (each of its cells lies on that side of both
+// boundaries).  The workgroups post their counts to each other, so one pass
+// over the tags counts and lists: 256^3, 12 us; a pass to count, a scan and a
+// pass to list took 20 and their gaps.
 __device__ __forceinline__ uint32_t fresh_bits(const int8_t* __restrict__ a,
                                                const int8_t* __restrict__ b, int64_t base,
                                                int64_t n, int& unc) {
@@ -461,62 +507,63 @@ __device__ __forceinline__ uint32_t fresh_bits(const int8_t* __restrict__ a,
   return m;
 }
 
-__device__ __forceinline__ bool spans_agree(const int8_t* __restrict__ sa,
-                                            const int8_t* __restrict__ sb, int64_t chunk) {
-  constexpr int kPer = kChunk / (64 * kSeg);
-  bool same = true;
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    const int8_t x = sa[chunk * kPer + q];
-    same = same && x >= 0 && x == sb[chunk * kPer + q];
-  }
-  return same;
-}
-
-__global__ __launch_bounds__(256) void k_fresh_count(const int8_t* __restrict__ a,
-                                                     const int8_t* __restrict__ b,
-                                                     const int8_t* __restrict__ sa,
-                                                     const int8_t* __restrict__ sb, int64_t n,
-                                                     int32_t* __restrict__ chunk_cnt,
-                                                     int64_t* __restrict__ counts) {
-  __shared__ int s_cnt, s_unc;
-  if (spans_agree(sa, sb, blockIdx.x)) {   // uniform over the workgroup
-    if (threadIdx.x == 0) chunk_cnt[blockIdx.x] = 0;
-    return;
-  }
-  if (threadIdx.x == 0) s_cnt = s_unc = 0;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * kChunk + (int64_t)threadIdx.x * kSeg;
-  int unc = 0;
-  const uint32_t m = base < n ? fresh_bits(a, b, base, n, unc) : 0u;
-  if (m) atomicAdd(&s_cnt, __popc(m));
-  if (unc) atomicAdd(&s_unc, unc);
-  __syncthreads();
+constexpr int kFreshRuns = 4, kFreshBS = 1024;   // runs of a workgroup's cells; a wave's part is a span
+constexpr int64_t kFreshRun = (int64_t)kFreshBS * kSeg, kFreshTile = kFreshRuns * kFreshRun;
+__global__ __launch_bounds__(kFreshBS) void k_fresh(const int8_t* __restrict__ a,
+                                               const int8_t* __restrict__ b,
+                                               const int8_t* __restrict__ sa,
+                                               const int8_t* __restrict__ sb, int64_t n,
+                                               unsigned long long* __restrict__ posted,
+                                               int64_t* __restrict__ counts,
+                                               int32_t* __restrict__ list, int64_t cap) {
+  static_assert(kFreshRun < (1 << 16) && kFreshRuns <= 4, "a run's count fits 16 bits");
+  __shared__ int64_t sh[kFreshBS / 64 + 1];
+  __shared__ int s_b, s_unc;
   if (threadIdx.x == 0) {
-    chunk_cnt[blockIdx.x] = s_cnt;
-    if (s_cnt) atomicAdd(reinterpret_cast<unsigned long long*>(&counts[0]), (unsigned long long)s_cnt);
-    if (s_unc) atomicAdd(reinterpret_cast<unsigned long long*>(&counts[1]), (unsigned long long)s_unc);
+    s_b = (int)atomicAdd(&posted[gridDim.x], 1ull);
+    s_unc = 0;
   }
-}
-
-__global__ __launch_bounds__(256) void k_fresh_scatter(const int8_t* __restrict__ a,
-                                                       const int8_t* __restrict__ b,
-                                                       const int8_t* __restrict__ sa,
-                                                       const int8_t* __restrict__ sb, int64_t n,
-                                                       const int64_t* __restrict__ excl,
-                                                       int32_t* __restrict__ list, int64_t cap) {
-  __shared__ int64_t sh[5];
-  if (spans_agree(sa, sb, blockIdx.x)) return;   // no fresh cell here
-  const int64_t base = (int64_t)blockIdx.x * kChunk + (int64_t)threadIdx.x * kSeg;
-  int unc = 0;
-  uint32_t m = base < n ? fresh_bits(a, b, base, n, unc) : 0u;
-  int64_t tot;
-  int64_t pos = excl[blockIdx.x] + block_excl_scan<256>(__popc(m), &tot, sh);
-  while (m) {
-    const int q = __ffs(m) - 1;
-    m &= m - 1;
-    if (pos < cap) list[pos] = (int32_t)(base + q);
-    ++pos;
+  __syncthreads();
+  const int t = s_b;
+  const int64_t base = (int64_t)t * kFreshTile + (int64_t)threadIdx.x * kSeg;
+  uint32_t m[kFreshRuns];
+  int8_t x[kFreshRuns], y[kFreshRuns];
+#pragma unroll
+  for (int q = 0; q < kFreshRuns; ++q) {
+    const int64_t span = (base + q * kFreshRun) / (64 * kSeg);
+    const bool in = base + q * kFreshRun < n;
+    x[q] = in ? sa[span] : 0;
+    y[q] = in ? sb[span] : 0;
+  }
+  int64_t sum = 0;   // of each run, 16 bits
+  int uncovered = 0;
+#pragma unroll
+  for (int q = 0; q < kFreshRuns; ++q) {
+    m[q] = 0;
+    int unc = 0;
+    if (x[q] < 0 || x[q] != y[q]) m[q] = fresh_bits(a, b, base + q * kFreshRun, n, unc);
+    sum += (int64_t)__popc(m[q]) << (16 * q);
+    uncovered += unc;
+  }
+  if (uncovered) atomicAdd(&s_unc, uncovered);
+  int64_t packed;
+  const int64_t rank = block_excl_scan<kFreshBS>(sum, &packed, sh);   // (its barriers: s_unc too)
+  int64_t tot = 0;
+#pragma unroll
+  for (int q = 0; q < kFreshRuns; ++q) tot += (packed >> (16 * q)) & 0xffff;
+  tot |= (int64_t)s_unc << 31;
+  const int64_t before = posted_before<kFreshBS>(posted, t, tot);
+  int64_t first = before & ((int64_t(1) << 31) - 1);
+#pragma unroll
+  for (int q = 0; q < kFreshRuns; ++q) {
+    int64_t pos = first + ((rank >> (16 * q)) & 0xffff);
+    for (uint32_t w = m[q]; w; w &= w - 1, ++pos)
+      if (pos < cap) list[pos] = (int32_t)(base + q * kFreshRun + __ffs(w) - 1);
+    first += (packed >> (16 * q)) & 0xffff;
+  }
+  if (t == (int)gridDim.x - 1 && threadIdx.x == 0) {
+    counts[0] = (before + tot) & ((int64_t(1) << 31) - 1);
+    counts[1] = (before + tot) >> 31;
   }
 }
 
@@ -529,24 +576,15 @@ extern "C" gcr_status gcr_plan_fresh_cells(const gcr_plan* a, const gcr_plan* b,
         a->inst.g.h[ax] != b->inst.g.h[ax])
       return GCR_E_ARG;
   hipStream_t st = (hipStream_t)stream;
-  const int64_t n = a->ncell, nch = (n + kChunk - 1) / kChunk;
-  const int64_t ntiles = (nch + kScanTile - 1) / kScanTile;
-  auto al = [](size_t v) { return (v + 255) & ~size_t(255); };
-  const size_t o_ex = al(sizeof(int32_t) * nch), o_ts = o_ex + al(sizeof(int64_t) * (nch + 1));
-  char* scr = static_cast<char*>(
-      plan_scratch(const_cast<gcr_plan*>(b), 6, o_ts + al(sizeof(int64_t) * (ntiles + 1))));
-  if (!scr) return GCR_E_NOMEM;
-  int32_t* ccnt = reinterpret_cast<int32_t*>(scr);
-  int64_t* excl = reinterpret_cast<int64_t*>(scr + o_ex);
-  int64_t* tsum = reinterpret_cast<int64_t*>(scr + o_ts);
-  k_fresh_zero<<<1, 64, 0, st>>>(counts);
-  k_fresh_count<<<(unsigned)nch, 256, 0, st>>>(a->tags, b->tags, a->span, b->span, n, ccnt,
-                                               counts);
-  if (list && cap > 0) {
-    launch_scan(ccnt, nch, excl, nullptr, nullptr, tsum, st);
-    k_fresh_scatter<<<(unsigned)nch, 256, 0, st>>>(a->tags, b->tags, a->span, b->span, n, excl,
-                                                   list, cap);
-  }
+  const int64_t n = a->ncell, ntiles = (n + kFreshTile - 1) / kFreshTile;
+  unsigned long long* const posted = static_cast<unsigned long long*>(
+      plan_scratch(const_cast<gcr_plan*>(b), 6, sizeof(unsigned long long) * (ntiles + 1)));
+  if (!posted) return GCR_E_NOMEM;
+  const int64_t words = 2 * (ntiles + 1);
+  k_zero_words<<<(unsigned)((words + 255) / 256), 256, 0, st>>>(reinterpret_cast<int32_t*>(posted),
+                                                                words);
+  k_fresh<<<(unsigned)ntiles, kFreshBS, 0, st>>>(a->tags, b->tags, a->span, b->span, n, posted, counts,
+                                            list, list ? cap : 0);
   GCR_HIP(hipGetLastError());
   return GCR_OK;
 }
@@ -893,51 +931,6 @@ __device__ __forceinline__ uint32_t table_insert(unsigned long long* t, uint32_t
   return h;
 }
 
-// Elements before workgroup b's own `tot`, for workgroups numbered in the
-// order they started: each posts its count, sums those posted before it, 256
-// at a time, back to the nearest that has posted its sum, and posts its own
-// sum.  Workgroups wait only for ones that started earlier and post their
-// counts without waiting, so every wait ends.  (Called by all 256 threads.)
-constexpr unsigned long long kPostCount = 1ull << 62, kPostSum = 2ull << 62;
-__device__ __forceinline__ int64_t posted_before(unsigned long long* __restrict__ posted, int b,
-                                                 int64_t tot) {
-  __shared__ int64_t s_sum[4];
-  __shared__ int s_end[4];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  if (tid == 0)
-    __hip_atomic_store(&posted[b], (b == 0 ? kPostSum : kPostCount) | (unsigned long long)tot,
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  int64_t before = 0;
-  for (int top = b; top > 0; top -= 256) {
-    const int j = top - 1 - tid;
-    unsigned long long v = kPostSum;   // (before the first: nothing)
-    if (j >= 0)
-      while ((v = __hip_atomic_load(&posted[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
-      }
-    const unsigned long long sums = __ballot((v & kPostSum) != 0);
-    const int end = sums ? __ffsll(sums) - 1 : 64;
-    int64_t x = lane <= end ? (int64_t)(v & (kPostCount - 1)) : 0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    if (lane == 0) {
-      s_sum[wv] = x;
-      s_end[wv] = end;
-    }
-    __syncthreads();
-    bool found = false;
-    for (int w = 0; w < 4 && !found; ++w) {
-      before += s_sum[w];
-      found = s_end[w] < 64;
-    }
-    __syncthreads();
-    if (found) break;
-  }
-  if (tid == 0 && b > 0)
-    __hip_atomic_store(&posted[b], kPostSum | (unsigned long long)(before + tot), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-  return before;
-}
-
 // Distance, normal and ghost decision of every interface cell, and the ghosts
 // in linear order at once: their positions from the counts that the
 // workgroups post to each other (posted: [workgroups], then the number
@@ -948,7 +941,14 @@ __device__ __forceinline__ int64_t posted_before(unsigned long long* __restrict_
 // launches and a copy after the compaction to 4: 128^2 circle 174 -> 117 us
 // for the whole build, fill and read-out, 64 stars 483 -> 375, 512^3 sphere
 // 349 -> 316.
-__global__ __launch_bounds__(256) void k_geometry(
+// Workgroups of 256 up to this many interface cells, of 1024 beyond (see
+// posted_before), which wait for the slowest of more projections but are
+// numbered sooner.  Spheres, with 256 / 1024: 1,332 cells 9.6 / 11.3 us, 33,435
+// 11.8 / 13.5, 54,759 13.8 / 16.1, 85,532 16.8 / 15.2, 219,077 33.0 / 20.7.
+constexpr int64_t kGeometrySmall = 65536;
+
+template <int BS>
+__global__ __launch_bounds__(BS) void k_geometry(
     const Inst* __restrict__ insts, int ninst, const int64_t* __restrict__ if_off,
     const int32_t* __restrict__ if_cell, int8_t* __restrict__ tags, int64_t cap,
     unsigned long long* __restrict__ posted, const int64_t* __restrict__ hoff,
@@ -957,11 +957,11 @@ __global__ __launch_bounds__(256) void k_geometry(
     double* __restrict__ g_n, uint8_t* __restrict__ g_ext, uint32_t* __restrict__ g_slot,
     int32_t* __restrict__ flow, InstInfo* __restrict__ info) {
   __shared__ int s_b;
-  __shared__ int64_t sh[5];
+  __shared__ int64_t sh[BS / 64 + 1];
   if (threadIdx.x == 0) s_b = (int)atomicAdd(&posted[gridDim.x], 1ull);
   __syncthreads();
   const int b = s_b;
-  const int64_t nif = if_off[ninst], e0 = (int64_t)b * 256, e = e0 + threadIdx.x;
+  const int64_t nif = if_off[ninst], e0 = (int64_t)b * BS, e = e0 + threadIdx.x;
   const bool valid = e < nif;
   const int ii = find_inst_wave(if_off, ninst, e0 + (threadIdx.x & ~63), min(e, nif - 1));
   int c = 0;
@@ -1000,8 +1000,8 @@ __global__ __launch_bounds__(256) void k_geometry(
     if (g.dim == 2) n[2] = 0.0;   // the third normal component of 2D ghosts
   }
   int64_t tot;
-  const int64_t rank = block_excl_scan<256>(ghost ? 1 : 0, &tot, sh);
-  const int64_t pos = posted_before(posted, b, tot) + rank;
+  const int64_t rank = block_excl_scan<BS>(ghost ? 1 : 0, &tot, sh);
+  const int64_t pos = posted_before<BS>(posted, b, tot) + rank;
   if (ghost) {
     g_ext[pos] = ext ? 1 : 0;
     g_cell[pos] = c;
@@ -1205,45 +1205,26 @@ __global__ __launch_bounds__(256) void k_rcount(const Inst* __restrict__ insts,
 }
 
 // Reverse edges of the dependency graph as CSR over all ghosts (linear
-// order): off[e] = first reader of ghost e, off[ng] = number of edges.
-// One workgroup; the ghost count is read on the device.
-__global__ __launch_bounds__(1024) void k_rscan(const int32_t* __restrict__ cnt,
-                                                const int64_t* __restrict__ g_off, int ninst,
-                                                int32_t* __restrict__ off) {
-  __shared__ int64_t sh[17];
-  block_scan_i32(cnt, g_off[ninst], off, sh);
-}
-
-// The same for long inputs, in three passes (tile totals; their scan,
-// k_scan_top; tiles again from their offsets), tiles of kScanTile values.
-// The counts past the ghost count are zero, so scanning the interface
-// capacity gives the same offsets up to the ghost count.
-__global__ __launch_bounds__(1024) void k_iscan_reduce(const int32_t* __restrict__ in, int64_t n,
-                                                       int64_t* __restrict__ tsum) {
-  __shared__ int64_t sh[17];
-  const int64_t b = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanT;
-  int64_t sum = 0;
-#pragma unroll
-  for (int q = 0; q < kScanT; ++q) sum += b + q < n ? in[b + q] : 0;
-  int64_t tot;
-  (void)block_excl_scan<1024>(sum, &tot, sh);
-  if (threadIdx.x == 0) tsum[blockIdx.x] = tot;
-}
-
-__global__ __launch_bounds__(1024) void k_iscan_down(const int32_t* __restrict__ in, int64_t n,
-                                                     const int64_t* __restrict__ toff,
-                                                     int32_t* __restrict__ out) {
-  __shared__ int64_t sh[17];
-  const int64_t b = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanT;
+// order): out[e] = first reader of ghost e, out[ng] = number of edges (posted
+// as in k_scan_tiles).  The counts past the ghost count are zero, so scanning
+// the interface capacity gives the same offsets up to the ghost count.
+__global__ __launch_bounds__(256) void k_iscan(const int32_t* __restrict__ in, int64_t n,
+                                               unsigned long long* __restrict__ posted,
+                                               int32_t* __restrict__ out) {
+  __shared__ int64_t sh[5];
+  __shared__ int s_b;
+  if (threadIdx.x == 0) s_b = (int)atomicAdd(&posted[gridDim.x], 1ull);
+  __syncthreads();
+  const int t = s_b;
+  const int64_t b = ((int64_t)t * 256 + threadIdx.x) * kScanT;
   int v[kScanT];
+  scan_load(in, n, b, v);
   int64_t sum = 0;
 #pragma unroll
-  for (int q = 0; q < kScanT; ++q) {
-    v[q] = b + q < n ? in[b + q] : 0;
-    sum += v[q];
-  }
+  for (int q = 0; q < kScanT; ++q) sum += v[q];
   int64_t tot;
-  int64_t run = toff[blockIdx.x] + block_excl_scan<1024>(sum, &tot, sh);
+  const int64_t rank = block_excl_scan<256>(sum, &tot, sh);
+  int64_t run = posted_before<256>(posted, t, tot) + rank;
 #pragma unroll
   for (int q = 0; q < kScanT; ++q) {
     if (b + q < n) out[b + q] = (int32_t)run;
@@ -1457,11 +1438,6 @@ __global__ void k_hash_build(const int64_t* __restrict__ g_off, int ninst,
   if (e >= g_off[ninst]) return;
   const int ii = find_inst(g_off, ninst, e);
   g_slot[e] = table_insert(htab + hoff[ii], hmask[ii], cell[e], (uint32_t)e);
-}
-
-__global__ void k_zero_words(int32_t* __restrict__ a, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) a[i] = 0;
 }
 
 // before a second layering of the same ghosts: the statistics that
@@ -1831,18 +1807,13 @@ static gcr_status build_graph(BatchData& D, hipStream_t st, int ninst, int64_t n
     k_zero_words<<<blocks(2 * cap, 256), 256, 0, st>>>(D.d_rcnt, 2 * cap);
     k_rcount<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, D.d_g_off, ninst, cap, D.d_deps,
                                                 D.d_rcnt, D.d_dcnt);
-    // reverse-edge offsets: one workgroup up to two tiles, else three passes
-    // over the interface capacity
+    // reverse-edge offsets, over the interface capacity
     const int64_t ntiles = (cap + kScanTile - 1) / kScanTile;
-    if (ntiles <= 2) {
-      k_rscan<<<1, 1024, 0, st>>>(D.d_rcnt, D.d_g_off, ninst, D.d_roff);
-    } else {
-      int64_t* tsum = own<int64_t>(D, ntiles + 1);
-      if (!tsum) return GCR_E_NOMEM;
-      k_iscan_reduce<<<(unsigned)ntiles, 1024, 0, st>>>(D.d_rcnt, cap, tsum);
-      k_scan_top<<<1, 1024, 0, st>>>(tsum, ntiles, tsum + ntiles, nullptr);
-      k_iscan_down<<<(unsigned)ntiles, 1024, 0, st>>>(D.d_rcnt, cap, tsum, D.d_roff);
-    }
+    unsigned long long* const posted = own<unsigned long long>(D, ntiles + 1);
+    if (!posted) return GCR_E_NOMEM;
+    k_zero_words<<<blocks(2 * (ntiles + 1), 256), 256, 0, st>>>(reinterpret_cast<int32_t*>(posted),
+                                                                2 * (ntiles + 1));
+    k_iscan<<<(unsigned)ntiles, 256, 0, st>>>(D.d_rcnt, cap, posted, D.d_roff);
     k_rfill<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, D.d_g_off, ninst, cap, D.d_deps,
                                                D.d_roff, D.d_rcnt + cap, D.d_radj);
   }
@@ -1973,7 +1944,10 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   D.d_band = own<int32_t>(D, chunks * 8);   // band mask of each chunk (4 x 64 bits)
   D.d_chunk_inst = own<int32_t>(D, chunks);
   D.d_chunk_excl = own<int64_t>(D, chunks + 1);
-  D.d_scan_tmp = own<int64_t>(D, (chunks + kScanTile - 1) / kScanTile + 1);
+  // what the scans' workgroups post: of the store pass's list, of the chunk
+  // counts, and of those with the second layer's marks
+  const int64_t words = scan_words(chunks);
+  D.d_scan_tmp = own<unsigned long long>(D, 3 * words);
   D.d_unit_mem = own<int32_t>(D, (size_t)ninst * kMaxUnits * kMaxUnit);
   D.d_unit_cnt = own<int32_t>(D, (size_t)ninst * kMaxUnits);
   D.d_reach = own<uint32_t>(D, (size_t)ninst * kMaxResidual * (kMaxResidual / 32));
@@ -1999,7 +1973,7 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
 
   StageEvents T((g_profiling.load() & 1) != 0);
   T.mark(0, st);
-  ClassifyWork W{D.d_dirty, D.d_dirty_list, D.d_ndirty, D.d_chunk_excl, D.d_scan_tmp,
+  ClassifyWork W{D.d_dirty, D.d_dirty_list, D.d_ndirty, D.d_chunk_excl, D.d_scan_tmp, 3 * words,
                  !any_3d};
   ClassifyUpdate U{};
   if (prev) {
@@ -2021,7 +1995,7 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
     O.off = D.d_iface_off;
     O.host_off = reinterpret_cast<int64_t*>(PS.p + o_io);
     launch_scan(D.d_chunk_cnt, chunks, D.d_chunk_excl, D.d_chunk_list, D.d_nchunk_list,
-                D.d_scan_tmp, st, &O);
+                D.d_scan_tmp + words, st, &O);
     // with a chunk list, marks outside it extend it, and the count covers
     // the list; else every chunk is counted
     const bool listed = prev || !W.every_chunk;
@@ -2038,7 +2012,7 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   O.hmask = D.d_hmask;
   O.host_counts = reinterpret_cast<int32_t*>(PS.p + o_nl);
   launch_scan(D.d_chunk_cnt, chunks, D.d_chunk_excl, D.d_chunk_list, D.d_nchunk_list,
-              D.d_scan_tmp, st, &O);
+              D.d_scan_tmp + 2 * words, st, &O);
   T.mark(2, st);
   GCR_HIP(hipGetLastError());
   GCR_HIP(hipStreamSynchronize(st));
@@ -2110,10 +2084,14 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
                                                      D.d_chunk_cnt, D.d_chunk_excl, D.d_chunk_list,
                                                      D.d_if_cell, D.d_htab, D.hoff[ninst], posted, nblk + 1);
     T.mark(4, st);
-    k_geometry<<<(unsigned)nblk, 256, 0, st>>>(
-        D.d_inst, ninst, D.d_if_off, D.d_if_cell, D.d_tags, cap, posted, D.d_hoff, D.d_hmask,
-        D.d_htab, D.d_g_off, D.d_g_cell, D.d_g_psi, D.d_g_n, D.d_g_ext, D.d_g_slot, D.d_rcnt,
-        D.d_info);
+    auto geometry = [&](auto kernel, unsigned bs) {
+      kernel<<<blocks(nif, bs), bs, 0, st>>>(
+          D.d_inst, ninst, D.d_if_off, D.d_if_cell, D.d_tags, cap, posted, D.d_hoff, D.d_hmask,
+          D.d_htab, D.d_g_off, D.d_g_cell, D.d_g_psi, D.d_g_n, D.d_g_ext, D.d_g_slot, D.d_rcnt,
+          D.d_info);
+    };
+    if (nif <= kGeometrySmall) geometry(k_geometry<256>, 256);
+    else geometry(k_geometry<1024>, 1024);
     T.mark(5, st);
     T.mark(6, st);
     int64_t max_if = 0;
