@@ -162,7 +162,7 @@ struct LevelsArgs {
   uint32_t* bits;
   InstInfo* info;
   // whole-GPU layering of a single large instance
-  int32_t* flow;         // [2] waves finished, ghosts placed (from zero)
+  int32_t* flow;         // [2] workgroups finished, ghosts placed (from zero; 8-byte aligned)
   int32_t* hist;         // [cap / 256 + 1][kWideLevels] level counts of the tiles of 256 ghosts
   int cur_cap;           // entries of a level list held in LDS (set at launch)
   int wave_res;          // residuals up to this size go to the one-wave solver
@@ -170,10 +170,10 @@ struct LevelsArgs {
 constexpr int kWideLevels = 128;   // deepest graph the whole-GPU layering orders
 // A 3D plan built alone with at least this many interface cells is layered
 // by the whole GPU, below by one workgroup pulling in LDS.  Measured per
-// build (both kernels of the former against the latter), spheres: 1,086
-// interface cells 15.1 / 15.7 us, 1,925 16.3 / 19.1, 7,703 18.3 / 36.2,
-// 30,816 21.9 / 82.6 (a workgroup pushing along reverse edges there, with
-// their construction not counted).
+// build (both kernels of the former, to which a launch's gap adds, against the
+// latter), spheres: 481 interface cells 11.1 / 11.6 us, 1,086 13.0 / 15.8,
+// 1,925 13.7 / 15.8, 7,703 15.4 / 33.3, 30,816 18.8 / 77.6 (a workgroup
+// pushing along reverse edges there, with their construction not counted).
 constexpr int64_t kWideMinInterface = 1024;
 void set_wide_layering(int64_t min_interface);   // 0: the default
 int64_t wide_layering_min();

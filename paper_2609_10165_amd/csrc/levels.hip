@@ -71,7 +71,7 @@ __device__ __forceinline__ uint32_t cnt_get(const uint32_t* c, int i) {
 // ghosts of the same launch; its at most kFlowGrid workgroups (half of what
 // the chip holds) are resident together unless other work fills it, and a
 // wave that saw no ghost of its own placed for kFlowPatience polls, nor any
-// wave finish meanwhile, gives up, so every wave ends: an instance with a
+// workgroup finish meanwhile, gives up, so every wave ends: an instance with a
 // cycle, or one starved that way, is left with info.layered = 0 to the
 // one-workgroup layerings.  The tiles' counts per level follow.
 //
@@ -80,8 +80,8 @@ __device__ __forceinline__ uint32_t cnt_get(const uint32_t* c, int i) {
 // stable counting sort of the canonical order.
 //
 // Bound by the chain of levels and the polls of the ghosts that wait (HBM
-// round trips).  512^3 sphere, 74,000 ghosts: 44 us for both against 581 for
-// rounds with a grid barrier; 256^3 with a second layer (36,000): 35 against
+// round trips).  512^3 sphere, 74,000 ghosts: 27 us for both against 581 for
+// rounds with a grid barrier; 256^3 with a second layer (36,000): 26 against
 // 191 for one workgroup in LDS.
 constexpr int kFlowJ = 4, kFlowGrid = 1024;
 constexpr int kFlowPatience = 512;
@@ -94,7 +94,7 @@ __device__ __forceinline__ void flow_put(int32_t* p, int v) {
 }
 
 // Whether a wave that waits may go on: true while ghosts of its own or
-// whole waves are being placed.  done: waves finished, of the whole launch.
+// whole workgroups are being placed.  done: workgroups finished, of the launch.
 struct FlowWait {
   int polls = 0, seen = -1;
   __device__ __forceinline__ bool go_on(bool moved, const int32_t* done) {
@@ -201,13 +201,16 @@ __global__ __launch_bounds__(256) void k_levels_flow(LevelsArgs L) {
       if (!W.go_on(moved, L.flow)) break;
     }
   }
-  // a finished (or weary) wave: one more for those that wait
-  if (lane == 0) atomicAdd(&L.flow[0], 1);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) placed += __shfl_xor(placed, o);
   if (lane == 0 && placed) atomicAdd(&s_placed, placed);
   __syncthreads();
-  if (tid == 0 && s_placed) atomicAdd(&L.flow[1], s_placed);
+  // a finished (or weary) workgroup: one more for those that wait, and its
+  // ghosts, by one atomic (about 20 ns each; with one a wave the 512^3
+  // sphere's pass took 31 us instead of 19)
+  if (tid == 0 && s_placed)
+    atomicAdd(reinterpret_cast<unsigned long long*>(L.flow),
+              1ull | (unsigned long long)s_placed << 32);
   // the tiles' counts per level (levels beyond the table: dropped here, and
   // the instance is left to the others, as its counts fall short)
   for (int t = blockIdx.x; t < ntiles; t += G) {
@@ -223,7 +226,7 @@ __global__ __launch_bounds__(256) void k_levels_flow(LevelsArgs L) {
 }
 
 __global__ __launch_bounds__(1024) void k_levels_scan(LevelsArgs L) {
-  constexpr int kSeg8 = 1024 / kWideLevels, kU = 8;
+  constexpr int kSeg8 = 1024 / kWideLevels, kU = 20;
   static_assert(kWideLevels == 128, "levels on 128 threads");
   __shared__ int s_sum[kSeg8][kWideLevels];
   __shared__ int s_off[kWideLevels + 1];
