@@ -513,9 +513,11 @@ def roofline_of(W, m, cells):
     each launch), against its algorithmic bytes."""
     d = W.dim
     npts = sum(W.nq)
-    # the forward's kernel: the split sweep for a negative grid, else the
-    # per-item kernel
-    fwd = f"k_batch_split<{d}>" if W.shape[1] < 0 else f"k_batch_forward<{d}>"
+    # the forward's kernel: without a shape the fill in LDS (2D) or the waiting
+    # one, with the launches beside it; else the split sweep for a negative
+    # grid, the per-item kernel for another
+    fwd = f"k_batch_split<{d}>" if W.shape[1] < 0 else f"k_batch_forward<{d}>" if W.shape[0] \
+        else "k_batch_lds" if d == 2 else f"k_batch_flow<{d}>"
     cands = {
         fwd: (m["fwd_ms"], forward_bytes(d, W.nf, m["ghosts"], npts)),
         "k_spans + k_classify": (m["stage_ms"]["classify_prepass"] + m["stage_ms"]["classify_store"],

@@ -402,7 +402,10 @@ gcr_status gcr_forward_times(float* out);
  *   mode 1  tiles from a batch's second forward call on (the default: a
  *           batch forwarded once never pays for them); a 3D batch without
  *           coupled units instead fills by ghosts waiting for their corners,
- *           from the first call, with the same values;
+ *           from the first call, with the same values, and where every
+ *           instance of a 2D batch fits in LDS whole, each is one tile, with
+ *           no closure to find (a workgroup per instance and field, the same
+ *           values; with coupled units too);
  *   mode 2  tiles from the first call.
  * Batches with coupled units, graphs deeper than 128 levels or an instance
  * of more than about 980,000 ghosts, and any batch whose tile closures would

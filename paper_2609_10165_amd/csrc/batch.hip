@@ -1,5 +1,11 @@
 // batch.hip -- batched forward: many uneven instances, several fields each,
-// reconstructed in one persistent launch.
+// reconstructed by shared launches.
+//
+// As a rule a 2D batch fills in LDS (k_batch_lds), a 3D one by waiting
+// (k_batch_open, k_batch_flow), with the anchors of the surface points beside
+// the fill, and the points follow by chunks (k_batch_surface, k_batch_force).
+// The forms below serve batches these leave (2D instances beyond LDS, 3D
+// coupled units) and forced shapes and tilings.
 //
 // Work items are (instance, field) pairs, largest first.  A workgroup takes
 // items round-robin; for each it sweeps the instance's levels for that
@@ -117,11 +123,11 @@ __global__ __launch_bounds__(256) void k_batch_anchor(BStatic S, BCall C, int64_
   if (active && sub == 0) anchor[gq] = g;
 }
 
-// Field f of instance i at surface point q: its value and gradient, written
-// where asked for, and its share of the force, added to t.
+// Field f of instance i at surface point q, whose anchor is g: its value and
+// gradient, written where asked for, and its share of the force, added to t.
 template <int D>
 __device__ __forceinline__ void surface_point(const PlanD& P, const BCall& C, int i, int f,
-                                              int64_t q, double t[3]) {
+                                              int64_t q, int g, double t[3]) {
   const int w = i * C.nf + f, vc = f - C.u_first;
   const bool isp = f == C.p_field, isu = vc >= 0 && vc < D;
   double* const sv = C.sval ? C.sval[w] : nullptr;
@@ -138,7 +144,6 @@ __device__ __forceinline__ void surface_point(const PlanD& P, const BCall& C, in
     x[a] = xq[a * nq + q];
     n[a] = nr[a * nq + q];
   }
-  const int g = C.anchor[C.aoff[i] + q];
   double val, gr[3];
   if (g < 0) {
     val = __longlong_as_double(0x7ff8000000000000LL);
@@ -187,7 +192,7 @@ __device__ __forceinline__ void surface_item(const BStatic& S, const BCall& C, i
   const PlanD& P = S.plans[i];
   double t[3] = {0.0, 0.0, 0.0};
   if (C.nq)
-    for (int64_t q = threadIdx.x; q < C.nq[i]; q += T) surface_point<D>(P, C, i, f, q, t);
+    for (int64_t q = threadIdx.x; q < C.nq[i]; q += T) surface_point<D>(P, C, i, f, q, C.anchor[C.aoff[i] + q], t);
   for (int a = 0; a < 3; ++a) red[threadIdx.x][a] = t[a];
   __syncthreads();
   for (int s = T / 2; s > 0; s >>= 1) {
@@ -214,8 +219,9 @@ __device__ __forceinline__ void surface_item(const BStatic& S, const BCall& C, i
 }
 
 // (LDS, dynamic: the surface part's reduction rows, the coupled units'
-// workspaces and the 2D fill's records share it; an item's records are dead before the rows are used.  lds_fill: bytes there are for the
-// latter, 0 if no item takes that form.)
+// workspaces and the 2D fill's records share it; an item's records are dead
+// before the rows are used.  lds_fill: bytes there are for the latter, 0 if no
+// item takes that form.)
 template <int D>
 __global__ __launch_bounds__(1024) void k_batch_forward(BStatic S, BCall C, double* __restrict__ part,
                                                         int* __restrict__ counter,
@@ -344,8 +350,8 @@ __global__ __launch_bounds__(1024) void k_batch_split(BStatic S, BCall C, int G,
 // Bound by the chain of levels beside the anchors, then by the chain anchor ->
 // corner -> sum of the surface part, which a workgroup per (instance, field)
 // ran in eight rounds on 28 of the CUs.  Seven spheres of 60^3 to 200^3, four
-// fields, 2,048 points each: 65 us a call, with tiles 130; the anchors by 16
-// lanes a point 70, in the launch before 74.
+// fields, 2,048 points each: 60 us a call, with tiles 130; with the anchors by 16
+// lanes a point 5 more, in the launch before 9 more.
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) void k_batch_open(BStatic S, BCall C, FlowTab T) {
@@ -361,28 +367,35 @@ __global__ __launch_bounds__(256) void k_batch_open(BStatic S, BCall C, FlowTab 
     F[P.cell[p]] = __longlong_as_double((long long)kFillOpen);
 }
 
-// (workgroups past the fill's nfill: the anchors)
-constexpr int kFlowLanes = anchor_lanes<3>(), kFlowPoints = 256 / kFlowLanes;
+// The anchors of a part of one chunk of points, by workgroup b (of BS threads)
+// behind a launch's fill workgroups.
+template <int D, int BS>
+constexpr int kAnchorParts = kSurfChunk * anchor_lanes<D>() / BS;
+template <int D, int BS>
+__device__ __forceinline__ void chunk_anchors(const BStatic& S, const BCall& C, int b,
+                                              int32_t* __restrict__ anchor) {
+  constexpr int NL = anchor_lanes<D>(), kParts = kAnchorParts<D, BS>;
+  const int chunk = b / kParts, i = inst_of_block(C.soff, C.ninst, chunk);
+  const int sub = (int)threadIdx.x % NL;
+  const int64_t nq = C.nq[i],
+                q0 = (int64_t)(chunk - C.soff[i]) * kSurfChunk + (b % kParts) * (BS / NL);
+  if (q0 >= nq) return;   // uniform
+  const int64_t q = q0 + (int)threadIdx.x / NL;
+  const bool active = q < nq;
+  double x[3] = {0.0, 0.0, 0.0};
+  if (active)
+#pragma unroll
+    for (int a = 0; a < D; ++a) x[a] = C.xq[i][a * nq + q];
+  const int g = find_anchor_group<D, NL>(S.plans[i], x, sub, active);
+  if (active && sub == 0) anchor[C.aoff[i] + q] = g;
+}
 
+// (workgroups past the fill's nfill: the anchors)
 template <int D>
 __global__ __launch_bounds__(256) void k_batch_flow(BStatic S, BCall C, FlowTab T, int nfill,
                                                     int32_t* __restrict__ anchor, int polls) {
   if ((int)blockIdx.x >= nfill) {
-    constexpr int kPerChunk = kSurfChunk / kFlowPoints;
-    const int b = (int)blockIdx.x - nfill, chunk = b / kPerChunk;
-    const int i = inst_of_block(C.soff, C.ninst, chunk);
-    const int sub = (int)threadIdx.x % kFlowLanes;
-    const int64_t nq = C.nq[i], q0 = (int64_t)(chunk - C.soff[i]) * kSurfChunk +
-                                     (b % kPerChunk) * kFlowPoints;
-    if (q0 >= nq) return;   // uniform
-    const int64_t q = q0 + (int)threadIdx.x / kFlowLanes;
-    const bool active = q < nq;
-    double x[3] = {0.0, 0.0, 0.0};
-    if (active)
-#pragma unroll
-      for (int a = 0; a < D; ++a) x[a] = C.xq[i][a * nq + q];
-    const int g = find_anchor_group<D, kFlowLanes>(S.plans[i], x, sub, active);
-    if (active && sub == 0) anchor[C.aoff[i] + q] = g;
+    chunk_anchors<D, 256>(S, C, (int)blockIdx.x - nfill, anchor);
     return;
   }
   const int f = (int)blockIdx.x / T.nwait, r = (int)blockIdx.x % T.nwait;
@@ -408,6 +421,24 @@ __global__ __launch_bounds__(1024) void k_batch_rest(BStatic S, BCall C) {
   }
 }
 
+// 2D batches whose instances all fill in LDS: an (instance, field) item per
+// workgroup, largest first, then the anchors (each of their workgroups holds
+// the LDS of a fill, so they are large ones).  With a launch for the anchors
+// before and the surface part behind each item's fill, in its workgroup, 64
+// stars took 63 us a call, so 49; five of up to 773^2 without coupled units in
+// tiles with closures 76, so 31.
+__global__ __launch_bounds__(1024) void k_batch_lds(BStatic S, BCall C, int32_t* __restrict__ anchor) {
+  extern __shared__ double s_lds[];
+  if ((int)blockIdx.x >= C.nitems) {
+    chunk_anchors<2, 1024>(S, C, (int)blockIdx.x - C.nitems, anchor);
+    return;
+  }
+  const int w = C.order[blockIdx.x], i = w / C.nf, f = w % C.nf, nl = S.nlev[i];
+  if (nl > 0)   // uniform
+    fill_lds2(S.plans[i], S.lev_off[i], nl, C.fields[w], C.bcv[w], C.bct ? C.bct[w] : nullptr,
+              C.kind[f], s_lds);
+}
+
 // sum over the workgroup in lane, then wave order; thread 0 holds it
 __device__ __forceinline__ void block_sum3(double t[3], double (*sh)[3]) {
 #pragma unroll
@@ -426,42 +457,36 @@ __device__ __forceinline__ void block_sum3(double t[3], double (*sh)[3]) {
     }
 }
 
-// One chunk of an instance's points and one field per workgroup.  The last
-// workgroup of an instance to finish (device-scope counter, reset after use)
-// adds the parts in a fixed order, so the force does not depend on timing.
+// An instance's force from its workgroups' parts, one to a chunk and field, in
+// a fixed order.  (A launch of its own: with the last workgroup of an instance
+// adding them, each pays a fence that writes back its XCD's cache, 15 us for 224
+// of them where they take 8 now and this 3.)
+__global__ __launch_bounds__(kSurfChunk) void k_batch_force(BCall C,
+                                                            const double* __restrict__ part,
+                                                            double* __restrict__ Fout) {
+  __shared__ double sh[kSurfChunk / 64][3];
+  const int i = blockIdx.x, n = (C.soff[i + 1] - C.soff[i]) * C.nf;
+  const double* const mine = part + (int64_t)C.soff[i] * C.nf * 3;
+  double t[3] = {0.0, 0.0, 0.0};
+  for (int k = threadIdx.x; k < n; k += kSurfChunk)
+    for (int a = 0; a < 3; ++a) t[a] += mine[(int64_t)k * 3 + a];
+  block_sum3(t, sh);
+  if (threadIdx.x == 0)
+    for (int a = 0; a < 3; ++a) Fout[(int64_t)i * 3 + a] = t[a];
+}
+
+// One chunk of an instance's points and one field per workgroup.
 template <int D>
 __global__ __launch_bounds__(kSurfChunk) void k_batch_surface(BStatic S, BCall C,
-                                                              double* __restrict__ part,
-                                                              int* __restrict__ counter,
-                                                              double* __restrict__ Fout) {
+                                                              double* __restrict__ part) {
   __shared__ double sh[kSurfChunk / 64][3];
-  __shared__ int s_last;
   const int i = inst_of_block(C.soff, C.ninst, (int)blockIdx.x), f = (int)blockIdx.y;
-  const int first = C.soff[i], parts = (C.soff[i + 1] - first) * C.nf;
-  const int64_t q = (int64_t)((int)blockIdx.x - first) * kSurfChunk + threadIdx.x;
+  const int64_t q = (int64_t)((int)blockIdx.x - C.soff[i]) * kSurfChunk + threadIdx.x;
   double t[3] = {0.0, 0.0, 0.0};
-  if (q < C.nq[i]) surface_point<D>(S.plans[i], C, i, f, q, t);
+  if (q < C.nq[i]) surface_point<D>(S.plans[i], C, i, f, q, C.anchor[C.aoff[i] + q], t);
   block_sum3(t, sh);
-  double* const mine = part + (int64_t)first * C.nf * 3;
-  if (threadIdx.x == 0) {
-    const int at = ((int)blockIdx.x - first) * C.nf + f;
-    for (int a = 0; a < 3; ++a) mine[(int64_t)at * 3 + a] = t[a];
-    __threadfence();
-    s_last = atomicAdd(&counter[i], 1) == parts - 1;
-  }
-  __syncthreads();
-  if (!s_last) return;   // uniform
-  __threadfence();
-  double u[3] = {0.0, 0.0, 0.0};
-  for (int k = threadIdx.x; k < parts; k += kSurfChunk)
-    for (int a = 0; a < 3; ++a)
-      u[a] += __hip_atomic_load(&mine[(int64_t)k * 3 + a], __ATOMIC_RELAXED,
-                                __HIP_MEMORY_SCOPE_AGENT);
-  block_sum3(u, sh);
-  if (threadIdx.x == 0) {
-    for (int a = 0; a < 3; ++a) Fout[(int64_t)i * 3 + a] = u[a];
-    atomicExch(&counter[i], 0);
-  }
+  if (threadIdx.x == 0)
+    for (int a = 0; a < 3; ++a) part[((int64_t)blockIdx.x * C.nf + f) * 3 + a] = t[a];
 }
 
 // ---------------------------------------------------------------------------
@@ -820,10 +845,13 @@ struct BatchFwdState {
   hipEvent_t ev_done = nullptr;
   int threads = 0, grid_mul = 0;   // tuned
   size_t fill_lds = 0;             // most LDS an instance filled there takes
+  bool all_lds = true;             // every instance with ghosts can be filled there
+  bool units = false;              // an instance has coupled units
   bool flow = false;               // 3D without coupled units: fill by waiting
   FlowTab ft{};
   // tiled fill: 0 not set up yet, 1 set up, -1 not used for this batch
   int tiled = 0;
+  bool whole = false;              // tiles are whole instances (k_batch_lds), without tables
   int calls = 0;                   // forward calls so far
   TileArgs T{};
   int64_t tmax = 0;                // workgroups of the closure and fill launches
@@ -883,6 +911,9 @@ BatchFwdState* state_of(gcr_batch* b, hipStream_t st, gcr_status* err) {
     nl[i] = b->plans[i]->nlev;
     if (fill_lds_ok(pv[i]) && fill_lds_bytes(pv[i].ng, pv[i].nunits) <= 160 * 1024)
       S->fill_lds = std::max(S->fill_lds, fill_lds_bytes(pv[i].ng, pv[i].nunits));
+    else if (pv[i].ng > 0)
+      S->all_lds = false;
+    S->units = S->units || pv[i].nunits > 0;
   }
   // one upload from pinned staging: plans | level-offset pointers | level
   // counts | force counters and two sets of level counters (zero), each
@@ -1005,6 +1036,10 @@ extern "C" gcr_status gcr_batch_tiled(const gcr_batch* b, int32_t* state) {
   if (!S || S->tiled == 0) return GCR_OK;
   if (S->tiled < 0) {
     *state = -1;
+    return GCR_OK;
+  }
+  if (S->whole) {
+    *state = 1;
     return GCR_OK;
   }
   int32_t flag = 0;
@@ -1232,7 +1267,8 @@ static int forward_lds() {
   const int v = std::max(a, o) & ~255;
   bool ok = v > 0;
   for (const void* k : {reinterpret_cast<const void*>(&k_batch_forward<2>),
-                        reinterpret_cast<const void*>(&k_batch_forward<3>)})
+                        reinterpret_cast<const void*>(&k_batch_forward<3>),
+                        reinterpret_cast<const void*>(&k_batch_lds)})
     ok = ok && hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess;
   (void)hipGetLastError();
   cap = ok ? v : 0;
@@ -1288,24 +1324,41 @@ static gcr_status launch_batch(BatchFwdState* S, const BCall& C, int dim, int th
   return GCR_OK;
 }
 
-// The launches of a batch that fills by waiting; nchunk: chunks of points (0
-// without forces).
+// The surface part of the two below; nchunk: chunks of points (0 without
+// forces).
+template <int D>
+static gcr_status launch_surface(BatchFwdState* S, const BCall& C, int nchunk, double* F,
+                                 hipStream_t st) {
+  if (C.nq) {
+    k_batch_surface<D><<<dim3((unsigned)nchunk, (unsigned)C.nf), kSurfChunk, 0, st>>>(
+        BStatic{S->d_plans, S->d_levp, S->d_nlev}, C, S->d_part);
+    k_batch_force<<<(unsigned)C.ninst, kSurfChunk, 0, st>>>(C, S->d_part, F);
+  }
+  GCR_HIP(hipGetLastError());
+  return GCR_OK;
+}
+
+// The launches of a batch that fills by waiting.
 static gcr_status launch_flow(BatchFwdState* S, const BCall& C, int nchunk, double* F,
                               hipStream_t st) {
   const BStatic bs{S->d_plans, S->d_levp, S->d_nlev};
   const unsigned nf = (unsigned)C.nf;
   const int nfill = S->ft.nwait * C.nf;
-  const int na = nchunk * (kSurfChunk / kFlowPoints);
+  const int na = nchunk * kAnchorParts<3, 256>;
   if (S->ft.nopen) k_batch_open<3><<<S->ft.nopen * nf, 256, 0, st>>>(bs, C, S->ft);
   if (nfill + na > 0)
     k_batch_flow<3><<<(unsigned)(nfill + na), 256, 0, st>>>(bs, C, S->ft, nfill, S->d_anchor,
                                                             fill_polls());
   if (nfill) k_batch_rest<3><<<(unsigned)C.nitems, 1024, 0, st>>>(bs, C);
-  if (C.nq)
-    k_batch_surface<3><<<dim3((unsigned)nchunk, nf), kSurfChunk, 0, st>>>(bs, C, S->d_part,
-                                                                         S->d_counter, F);
-  GCR_HIP(hipGetLastError());
-  return GCR_OK;
+  return launch_surface<3>(S, C, nchunk, F, st);
+}
+
+static gcr_status launch_lds(BatchFwdState* S, const BCall& C, int nchunk, double* F,
+                             hipStream_t st) {
+  const BStatic bs{S->d_plans, S->d_levp, S->d_nlev};
+  const int na = nchunk * kAnchorParts<2, 1024>;
+  k_batch_lds<<<(unsigned)(C.nitems + na), 1024, S->fill_lds, st>>>(bs, C, S->d_anchor);
+  return launch_surface<2>(S, C, nchunk, F, st);
 }
 
 int gcr::fill_polls() {
@@ -1386,15 +1439,23 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   // 3D without coupled units fills by waiting unless a form is asked for: no
   // closures to find, no shape to time
   const bool flow = S->flow && batch_tiling() == 1 && S->tiled <= 0 && !g_force_shape.load();
+  const bool lds_whole = dim == 2 && S->all_lds && S->fill_lds <= (size_t)forward_lds();
   if (S->tiled == 0) {
     const int mode = batch_tiling();
     if (mode == 0 || flow) {
       S->tiled = -1;
+    } else if (mode == 1 && S->calls >= 2 && lds_whole && !S->units) {
+      S->tiled = 1;
+      S->whole = true;
     } else if (mode == 2 || S->calls >= 2) {
       S->tiled = tile_setup(S, batch, dim, st, &err) ? 1 : -1;
       if (err != GCR_OK) return err;
     }
   }
+  // likewise 2D where every instance fills in LDS, unless there are tiles
+  const bool lds = lds_whole && (S->tiled <= 0 || S->whole) && batch_tiling() == 1 &&
+                   !g_force_shape.load();
+  const bool tiles = S->tiled == 1 && !S->whole;
   // items, largest first: fill work ~ ghosts, latency ~ levels, surface ~ points
   const int nitems = n * nf;
   std::vector<double> cost(nitems);
@@ -1517,7 +1578,7 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   C.aoff = nq ? reinterpret_cast<const int64_t*>(d + o_aoff) : nullptr;
   C.soff = nq ? reinterpret_cast<const int32_t*>(d + o_soff) : nullptr;
   C.anchor = S->d_anchor;
-  C.tile_flag = S->tiled == 1 ? S->T.flag : nullptr;
+  C.tile_flag = tiles ? S->T.flag : nullptr;
   C.sval = sval ? reinterpret_cast<double* const*>(d + o_sval) : nullptr;
   C.sgrad = sgrad ? reinterpret_cast<double* const*>(d + o_sgrad) : nullptr;
   std::array<hipEvent_t, 3> ev{};
@@ -1536,6 +1597,10 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   if (flow) {
     if (timed) (void)hipEventRecord(ev[1], st);   // (the anchors ride in the fill)
     return end_call(launch_flow(S, C, soff[n], F, st));
+  }
+  if (lds) {
+    if (timed) (void)hipEventRecord(ev[1], st);
+    return end_call(launch_lds(S, C, soff[n], F, st));
   }
   if (npts > 0) {
     BStatic bs{S->d_plans, S->d_levp, S->d_nlev};
@@ -1574,7 +1639,7 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
     while ((int64_t(1) << b) < v) ++b;
     return b;
   };
-  const auto key = std::make_tuple(dim, nf, (nq ? 1 : 0) | (S->tiled == 1 ? 2 : 0),
+  const auto key = std::make_tuple(dim, nf, (nq ? 1 : 0) | (tiles ? 2 : 0),
                                    bucket(nitems), bucket(max_ng), bucket(max_lev));
   if (S->threads == 0) {
     std::lock_guard<std::mutex> lk(g_shape_mu);
@@ -1600,7 +1665,7 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
       for (int gm : cand_g) {
         if (gm > 1 && std::min(nitems, 256 * gm) == std::min(nitems, 256 * (gm / 4)))
           continue;   // same shape
-        if (gm < 0 && (S->tiled == 1 || (int64_t)(-gm) * n > kSplitMaxGrid)) continue;
+        if (gm < 0 && (tiles || (int64_t)(-gm) * n > kSplitMaxGrid)) continue;
         gcr_status s = launch_batch(S, C, dim, tt, gm, Fo, st);
         if (s == GCR_E_UNSUPPORTED) continue;   // workgroups not co-resident
         if (s != GCR_OK) return s;

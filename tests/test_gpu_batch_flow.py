@@ -1,7 +1,8 @@
-"""The forward of a 3D batch (Sec. 3.2 fill, Sec. 6 surface values and
-forces) by ghosts waiting for their corners and by chunks of points: one
-point, a chunk's edge, none; one to eight fields; instances of one workgroup
-and many; and after a wait that gave up.  Fields and surface values are those
+"""The forward of a batch (Sec. 3.2 fill, Sec. 6 surface values and forces) by
+ghosts waiting for their corners (3D) or in LDS (2D), and by chunks of points:
+one point, a chunk's edge, none; one to eight fields; instances of one
+workgroup and many, without ghosts, with coupled units, beyond LDS; and after a
+wait that gave up.  Fields and surface values are those
 of each plan's own calls with one launch per level, bit for bit; the force
 differs from theirs by the order of its sum."""
 import numpy as np
@@ -23,19 +24,25 @@ def rand(*shape, seed):
 
 def agree(gcr, ns, schemes, kinds, nqs, forces=True):
     insts = [synth.sphere256(seed=k, n=n) for k, n in enumerate(ns)]
-    B = gcr.Batch([i.grid for i in insts], [i.shape for i in insts], schemes)
+    return agree_on(gcr, [i.grid for i in insts], [i.shape for i in insts], schemes, kinds, nqs, forces)
+
+
+def agree_on(gcr, grids, shapes, schemes, kinds, nqs, forces=True):
+    ns, d = grids, grids[0].dim
+    B = gcr.Batch(grids, shapes, schemes)
     nf = len(kinds)
     clean = [rand(p.n_cells, seed=10 + f) for p in B.plans for f in range(nf)]
     bcv = [rand(p.n_ghost, seed=50 + f) for p in B.plans for f in range(nf)]
     bct = [(rand(p.n_ghost, seed=90 + f) < 0).to(torch.uint8) for p in B.plans for f in range(nf)]
     S = [p.foot_points()[0] for p in B.plans]
-    x = [s[:, torch.arange(q, device="cuda") * 7 % s.shape[1]].contiguous() for s, q in zip(S, nqs)]
-    n = [rand(3, q, seed=3) for q in nqs]
+    x = [s[:, torch.arange(q, device="cuda") * 7 % max(s.shape[1], 1)].contiguous()[:d] if s.shape[1] else
+         rand(d, q, seed=8) for s, q in zip(S, nqs)]
+    n = [rand(d, q, seed=3) for q in nqs]
     w = [rand(q, seed=4).abs() for q in nqs]
     mu, u = 0.7, [c.clone() for c in clean]
     F = torch.full((len(ns), 3), 7.0, dtype=torch.float64, device="cuda")
     val = [torch.empty(q, dtype=torch.float64, device="cuda") for q in nqs for _ in range(nf)]
-    grad = [torch.empty((3, q), dtype=torch.float64, device="cuda") for q in nqs for _ in range(nf)]
+    grad = [torch.empty((d, q), dtype=torch.float64, device="cuda") for q in nqs for _ in range(nf)]
     for _ in range(2):   # every value again from the clean fields
         for a, c in zip(u, clean):
             a.copy_(c)
@@ -52,23 +59,29 @@ def agree(gcr, ns, schemes, kinds, nqs, forces=True):
         p.fill(want, kinds, bcv[s], bct[s])
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(u[s], want)), i
+        p.set_schedule(0)
         if not forces:
             continue
         if nqs[i] == 0:
             assert (F[i] == 0).all()
             continue
         v, g, _ = p.surface(x[i], want)
+        if p.n_ghost == 0:
+            assert v.isnan().all() and all(a.isnan().all() for a in val[s] + grad[s])
+            continue
         assert all(torch.equal(a, b) for a, b in zip(val[s], v)), i
         assert all(torch.equal(a, b) for a, b in zip(grad[s], g)), i
         # each point's share, in the terms of the sum; 40 roundings on a term
         # and the sum's own bound the difference
-        if nf >= 4:
-            G = g[:3]
+        if nf >= d + 1:
+            G = g[:d]
             t = -w[i] * v[nf - 1] * n[i] + mu * w[i] * (torch.einsum("caq,aq->cq", G, n[i])
                                                          + torch.einsum("caq,cq->aq", G, n[i]))
             mag = (w[i] * v[nf - 1] * n[i]).abs() + mu * w[i] * (
                 torch.einsum("caq,aq->cq", G.abs(), n[i].abs()) + torch.einsum("caq,cq->aq", G.abs(), n[i].abs()))
-            assert ((F[i] - t.sum(1)).abs() <= (40 + nqs[i]) * 2.0 ** -53 * mag.sum(1)).all(), i
+            assert (F[i, d:] == 0).all()
+            assert ((F[i, :d] - t.sum(1)).abs() <= (40 + nqs[i]) * 2.0 ** -53 * mag.sum(1)).all(), i
+    return B
 
 
 @pytest.mark.parametrize("kinds", [[DIRICHLET], [NEUMANN, DIRICHLET, MIXED, DIRICHLET], [MIXED] * 8])
@@ -92,3 +105,27 @@ def test_batch_wait_that_gives_up_is_swept_again(gcr):  # noqa: F811
         agree(gcr, [64, 33], [HGC, CGC], [DIRICHLET, MIXED, NEUMANN, DIRICHLET], [300, 5])
     finally:
         gcr.set_batch_spin(0)
+
+def test_batch_in_lds(gcr):  # noqa: F811
+    from test_gpu_layering import circle
+    b = [circle(n) for n in (128, 40, 700, 330, 128)]
+    b[3] = (b[3][0], synth.Shape(synth.SPHERE, (9.0, 9.0, 0.0), 0.5))   # no ghosts
+    g, s = [x for x, _ in b], [y for _, y in b]
+    for kinds in ([DIRICHLET], [NEUMANN, MIXED, DIRICHLET], [MIXED] * 8):
+        B = agree_on(gcr, g, s, [HGC, CGC, HGC | LAYER2, CGC, CGC_ES], kinds, [1, 256, 257, 300, 0])
+        assert B.tiled() == 1 and B.shape() == (0, 0)
+    agree_on(gcr, g[:1], s[:1], [HGC], [NEUMANN, DIRICHLET], [0], forces=False)
+
+
+def test_batch_in_lds_coupled_units(gcr):  # noqa: F811
+    insts = [i for i in synth.stars64(1) if i.grid.n[0] <= 1200]
+    B = agree_on(gcr, [i.grid for i in insts], [i.shape for i in insts], [HGC] * len(insts),
+                 [MIXED, DIRICHLET, NEUMANN], [64] * len(insts))
+    assert sum(p.stats()["n_units_coupled"] for p in B.plans) and B.shape() == (0, 0)
+
+
+def test_batch_beyond_lds(gcr):  # noqa: F811
+    from test_gpu_layering import circle
+    b = [circle(2630), circle(64)]
+    B = agree_on(gcr, [g for g, _ in b], [s for _, s in b], [HGC] * 2, [MIXED, DIRICHLET, NEUMANN], [300, 5])
+    assert B.shape() != (0, 0)
