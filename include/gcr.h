@@ -452,7 +452,9 @@ gcr_status gcr_set_batch_shape(int32_t threads, int32_t grid);
  * forward calls on the same batch.  gcr_set_batch_spin sets the polls of a
  * wait before it gives up, process-wide (0: the default, 4M polls of about
  * 64 cycles); tests set 1 to make waits give up while every kernel still
- * ends. */
+ * ends.  It bounds the waits of the waiting fills and adjoints too (1M polls
+ * by default), which then compute what they waited for: their values do not
+ * depend on it. */
 gcr_status gcr_batch_status(const gcr_batch* batch);
 gcr_status gcr_set_batch_spin(int32_t polls);
 /* Layering (Sec. 3.2).  At the default setting a 3D plan built alone with at

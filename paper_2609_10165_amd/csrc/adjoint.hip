@@ -386,16 +386,44 @@ __global__ __launch_bounds__(64) void k_adj_units(AdjArgs A, int level) {
 // entries and weights are gathered eight at a time before the first poll, and
 // summed in entry order.  A coupled unit is one thread's, four to a workgroup,
 // and those workgroups lead the grid: they wait for later ones, but fill a
-// corner of the chip at most.  Waits are bounded as the fill's are, and
-// k_adj_wg sweeps again after one that gave up.
+// corner of the chip at most.  Waits are bounded as the fill's are; a thread
+// that passes the bound computes what it waits for (adj_help), or, in a plan
+// with coupled units, sets the plan's fault word, for k_adj_wg to sweep again.
 // Bound by the chain of levels.  160^3 spherical-harmonic body, four fields,
-// ten levels: 24 us for the three launches against 90 for ten.
+// ten levels: 20 us for the two launches against 90 for ten.
 // --------------------------------------------------------------------------
 constexpr int kAdjUnitsPerBlock = 4;
 
 __global__ __launch_bounds__(256) void k_adj_open(double* __restrict__ Lam, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) Lam[i] = __longlong_as_double((long long)kFillOpen);
+}
+
+// The adjoint of ghost p in field f, posted, without waiting (as fill_help:
+// down to a reader that is open, until one has all of its own).  Plans without
+// coupled units.
+__device__ __forceinline__ void adj_help(const AdjArgs& A, int p, int f) {
+  const PlanD& P = A.P;
+  double* const L = A.Lam + (int64_t)f * P.ng;
+  for (int cur = p;;) {
+    const int s = A.S.gslot[cur], e = A.S.off[s + 1];
+    double acc = A.lam[f][P.cell[cur]];
+    int open = -1;
+    for (int t = A.S.off[s]; t < e && open < 0; ++t) {
+      const int en = A.S.ent[t], r = en >> 4;
+      if (!(en & 1)) continue;
+      const unsigned long long x = poll_value(L + r);
+      if (x == kFillOpen) open = r;
+      else acc += reader_weight(A, f, r, (en >> 1) & 7) * __longlong_as_double((long long)x);
+    }
+    if (open >= 0) {
+      cur = open;
+      continue;
+    }
+    post_value(L + cur, acc);
+    if (cur == p) return;
+    cur = p;
+  }
 }
 
 template <int D>
@@ -460,7 +488,8 @@ __global__ __launch_bounds__(256) void k_adj_flow(AdjArgs A, int unit_blocks, in
     }
     if (__ballot(!done) == 0ull) return;
     if (left <= 0) {
-      if (!done) atomicOr(P.fill_fault, 1);
+      if (!done && P.nunits == 0) adj_help(A, p, f);
+      else if (!done) atomicOr(P.fill_fault, 1);
       return;
     }
   }
@@ -473,7 +502,7 @@ static void adj_flow(const AdjArgs& A, const int32_t* d_lev_off, int nlev, hipSt
   k_adj_open<<<nblk(n, 256), 256, 0, st>>>(A.Lam, n);
   k_adj_flow<D><<<dim3((unsigned)ub + nblk(A.P.ng, 256), (unsigned)A.nf), 256, 0, st>>>(
       A, ub, fill_polls());
-  k_adj_wg<D><<<1, 256, 0, st>>>(A, d_lev_off, nlev, A.P.fill_fault);
+  if (ub) k_adj_wg<D><<<1, 256, 0, st>>>(A, d_lev_off, nlev, A.P.fill_fault);
 }
 
 // Per slot: a ghost's own cell gives its boundary-data sensitivity and is

@@ -340,13 +340,13 @@ __global__ __launch_bounds__(1024) void k_batch_split(BStatic S, BCall C, int G,
 }
 
 // ---------------------------------------------------------------------------
-// Fill by waiting (k_fill_open, k_fill_flow, k_fill_rest) of every instance of
+// Fill by waiting (k_fill_open, k_fill_flow) of every instance of
 // a 3D batch at once, and the surface part by chunks of points.
 //
 // The anchors of the points depend on the geometry only, so their search
 // rides in the waiting launch, behind its fill workgroups.  Workgroups wait
-// for earlier ones of the same instance and field only; the waits are bounded,
-// and k_batch_rest sweeps an instance whose plan's fault word is set.
+// for earlier ones of the same instance and field only, and the waits are
+// bounded (fill_wait).
 // Bound by the chain of levels beside the anchors, then by the chain anchor ->
 // corner -> sum of the surface part, which a workgroup per (instance, field)
 // ran in eight rounds on 28 of the CUs.  Seven spheres of 60^3 to 200^3, four
@@ -405,20 +405,6 @@ __global__ __launch_bounds__(256) void k_batch_flow(BStatic S, BCall C, FlowTab 
   // (past the last ghost: that one again)
   const int p = min(S.lev_off[i][1] + (r - T.wait[i]) * 256 + (int)threadIdx.x, P.ng - 1);
   fill_wait<D>(P, p, C.fields[w], C.bcv[w], C.bct ? C.bct[w] : nullptr, C.kind[f], polls);
-}
-
-template <int D>
-__global__ __launch_bounds__(1024) void k_batch_rest(BStatic S, BCall C) {
-  const int w = blockIdx.x, i = w / C.nf, f = w % C.nf;
-  const PlanD& P = S.plans[i];
-  if (P.ng == 0 || P.fill_fault[0] == 0) return;   // uniform
-  const int32_t* const lo = S.lev_off[i];
-  const int nl = S.nlev[i];
-  for (int l = 0; l < nl; ++l) {
-    for (int p = lo[l] + (int)threadIdx.x; p < lo[l + 1]; p += blockDim.x)
-      fill_single<D>(P, p, C.fields[w], C.bcv[w], C.bct ? C.bct[w] : nullptr, C.kind[f]);
-    __syncthreads();
-  }
 }
 
 // 2D batches whose instances all fill in LDS: an (instance, field) item per
@@ -1349,7 +1335,6 @@ static gcr_status launch_flow(BatchFwdState* S, const BCall& C, int nchunk, doub
   if (nfill + na > 0)
     k_batch_flow<3><<<(unsigned)(nfill + na), 256, 0, st>>>(bs, C, S->ft, nfill, S->d_anchor,
                                                             fill_polls());
-  if (nfill) k_batch_rest<3><<<(unsigned)C.nitems, 1024, 0, st>>>(bs, C);
   return launch_surface<3>(S, C, nchunk, F, st);
 }
 

@@ -600,7 +600,7 @@ gcr_status gcr_fill(const gcr_plan* plan, int32_t nf, double* const* fields,
     // its corners; plans with coupled units beyond the former: the tuner
     if (fill_lds_fits(A.P)) return launch_fill_lds(A, p->d_lev_off, p->nlev, st);
     if (p->info.nunits == 0)
-      return launch_fill_flow(A, p->lev_off[1], p->d_lev_off, p->nlev, fill_polls(), st);
+      return launch_fill_flow(A, p->lev_off[1], fill_polls(), st);
   }
   s = plan_weights(p, A.nf, A.kind, A.w, st);
   if (s != GCR_OK) return s;

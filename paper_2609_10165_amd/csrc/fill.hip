@@ -54,11 +54,12 @@ gcr_status launch_fill_lds(const FillArgs& A, const int32_t* d_lev_off, int nlev
 // A ghost reads lower levels only, so workgroups wait for earlier ones
 // (canonical order is by level; fields one after another); the hardware
 // starts workgroups in order, so the one the others wait for runs.  That is
-// not promised, so every wait is bounded (`polls`); one that gives up sets
-// the plan's fault word for good, and k_fill_rest, launched last, then sweeps
-// the plan's levels again in one workgroup, with the same values.
+// not promised, so a wait is bounded (`polls`): a thread that passes it
+// computes the ghosts it waits for itself (fill_help), and the fill ends
+// whichever workgroups run.
 // Bound by the chain of levels.  256^3 sphere, 18,500 ghosts, 11 levels, four
-// fields: 25 us for the three launches against 87 for eleven.
+// fields: 23.5 us for the two launches against 87 for eleven (25 with a third to
+// sweep again after a wait that gave up).
 // --------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) void k_fill_open(FillArgs A, int n1) {
@@ -76,34 +77,17 @@ __global__ __launch_bounds__(256) void k_fill_flow(FillArgs A, int n1, int polls
 }
 
 template <int D>
-__global__ __launch_bounds__(1024) void k_fill_rest(FillArgs A, const int32_t* __restrict__ lev_off,
-                                                    int nlev) {
-  if (A.P.fill_fault[0] == 0) return;   // uniform
-  for (int l = 0; l < nlev; ++l) {
-    const int lo = lev_off[l], n = (lev_off[l + 1] - lo) * A.nf;
-    for (int e = threadIdx.x; e < n; e += blockDim.x) {
-      const int p = lo + e / A.nf, f = e % A.nf;
-      fill_single<D>(A.P, p, A.f[f], A.b[f], A.bt[f], A.kind[f]);
-    }
-    __syncthreads();
-  }
-}
-
-template <int D>
-static void fill_flow(const FillArgs& A, int n1, const int32_t* d_lev_off, int nlev, int polls,
-                      hipStream_t st) {
+static void fill_flow(const FillArgs& A, int n1, int polls, hipStream_t st) {
   const unsigned nf = (unsigned)A.nf;
   k_fill_open<D><<<dim3((unsigned)((A.P.ng + 255) / 256), nf), 256, 0, st>>>(A, n1);
   if (A.P.ng <= n1) return;
   k_fill_flow<D><<<dim3((unsigned)((A.P.ng - n1 + 255) / 256), nf), 256, 0, st>>>(A, n1, polls);
-  k_fill_rest<D><<<1, 1024, 0, st>>>(A, d_lev_off, nlev);
 }
 
-// n1: ghosts of level 1; polls: of a wait before it gives up
-gcr_status launch_fill_flow(const FillArgs& A, int n1, const int32_t* d_lev_off, int nlev,
-                            int polls, hipStream_t st) {
-  if (A.P.g.dim == 2) fill_flow<2>(A, n1, d_lev_off, nlev, polls, st);
-  else fill_flow<3>(A, n1, d_lev_off, nlev, polls, st);
+// n1: ghosts of level 1; polls: of a wait before the thread helps itself
+gcr_status launch_fill_flow(const FillArgs& A, int n1, int polls, hipStream_t st) {
+  if (A.P.g.dim == 2) fill_flow<2>(A, n1, polls, st);
+  else fill_flow<3>(A, n1, polls, st);
   return hipGetLastError() == hipSuccess ? GCR_OK : GCR_E_HIP;
 }
 

@@ -28,7 +28,7 @@ struct PlanD {
   // a fluid corner, -2 for a skipped one (null where the build made none)
   const int32_t* cgi;
   int64_t cgi_stride;
-  int32_t* fill_fault;         // set by a fill whose wait gave up (k_fill_flow)
+  int32_t* fill_fault;         // set by an adjoint whose wait gave up (k_adj_flow)
 };
 
 constexpr unsigned long long kHashEmpty = ~0ull;
@@ -125,8 +125,7 @@ PlanD plan_view(const gcr_plan* p);
 // ghost waiting for its corners (plans without coupled units); see fill.hip.
 bool fill_lds_fits(const PlanD& P);
 gcr_status launch_fill_lds(const FillArgs& A, const int32_t* d_lev_off, int nlev, hipStream_t st);
-gcr_status launch_fill_flow(const FillArgs& A, int n1, const int32_t* d_lev_off, int nlev,
-                            int polls, hipStream_t st);
+gcr_status launch_fill_flow(const FillArgs& A, int n1, int polls, hipStream_t st);
 
 void launch_fill_range(const FillArgs& A, int lo, int hi, hipStream_t st);
 void launch_weights(const PlanD& P, int bc, double* w, uint8_t* kinds, hipStream_t st);

@@ -220,10 +220,55 @@ __device__ __forceinline__ void post_value(double* p, double v) {
                      __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The value of ghost p of a field that others may still be filling, posted,
+// without waiting: as long as one of its corners is open, the thread goes down
+// to that ghost, and from there on, until one has all its corners; it posts
+// that one's value (the same, whoever computes it) and starts again from p.
+// Corners lie in lower levels and each round leaves one ghost fewer open, so
+// this ends whatever other workgroups do.
+template <int D>
+__device__ __forceinline__ void fill_help(const PlanD& P, int p, double* F,
+                                          const double* __restrict__ b,
+                                          const uint8_t* __restrict__ bt, int kind) {
+  for (int cur = p;;) {
+    const int c = P.cell[cur];
+    const uint32_t code = P.code[cur], skip = code_skip(code), ghosts = code_ghosts(code);
+    double val[8];
+    int open = -1;
+#pragma unroll
+    for (int k = 1; k < (1 << D); ++k) {
+      if (k & skip) continue;
+      const int q = c + corner_offset(P.g, code, k);
+      const unsigned long long x = poll_value(F + q);
+      if (((ghosts >> k) & 1u) && x == kFillOpen) open = q;
+      val[k] = __longlong_as_double((long long)x);
+    }
+    if (open >= 0) {
+      cur = ghost_at(P, open);
+      continue;
+    }
+    double dl[3], nn[3], w[8], X[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      dl[a] = a < D ? P.dl[a][cur] : 0.0;
+      nn[a] = a < D ? P.nn[a][cur] : 0.0;
+    }
+    stencil_span(P.g, code, c, X);
+    ghost_weights<D>(dl, nn, X, kind == 2 ? (int)bt[cur] : kind, w);
+    double v = w[0] * b[cur];
+#pragma unroll
+    for (int k = 1; k < (1 << D); ++k)
+      if (!(k & skip)) v += w[k] * val[k];
+    post_value(F + c, v);
+    if (cur == p) return;
+    cur = p;
+  }
+}
+
 // Ghost p of a level above the first, whose wave's lanes each hold such a
 // ghost: its fluid corners and weights are gathered, the slots of its ghost
 // corners (the code's mask) polled until each holds a value, its own stored.
-// A wait that passes `polls` sets the plan's fault word.
+// After `polls` the lanes still waiting compute what they wait for.
 template <int D>
 __device__ __forceinline__ void fill_wait(const PlanD& P, int p, double* F,
                                           const double* __restrict__ b,
@@ -270,7 +315,7 @@ __device__ __forceinline__ void fill_wait(const PlanD& P, int p, double* F,
     }
     if (__ballot(!done) == 0ull) return;
     if (left <= 0) {
-      if (!done) atomicOr(P.fill_fault, 1);
+      if (!done) fill_help<D>(P, p, F, b, bt, kind);
       return;
     }
   }

@@ -27,7 +27,7 @@ struct InstInfo {
   int32_t nfluid;
   int32_t rmax[3];      // largest stencil multiplier per axis
   int32_t layered;      // set when the LDS layering finished the instance
-  int32_t fill_fault;   // set on the device by a fill whose wait gave up
+  int32_t fill_fault;   // set on the device by an adjoint whose wait gave up
   unsigned long long max_alpha_bits[3];
 };
 
@@ -345,7 +345,7 @@ int64_t scan_words(int64_t n);   // of `posted`, zeroed before each scan
 // default), 2 from its first (process-wide).
 void set_batch_tiling(int mode);
 int batch_tiling();
-// Polls of a waiting fill before it gives up (gcr_set_batch_spin).
+// Polls of a waiting fill before it helps itself (gcr_set_batch_spin).
 int fill_polls();
 void set_batch_shape(int threads, int grid);
 void* plan_scratch(gcr_plan* p, int slot, size_t bytes);
