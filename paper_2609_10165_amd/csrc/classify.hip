@@ -30,6 +30,7 @@ namespace gcr {
 // lies within r(w_c) +- lip * D, D the box's angular radius, so a box whose
 // distances from the centre all exceed (or all stay below) that range is
 // fluid (solid) throughout.  Returns 0 / 1, or -1 if the box may straddle.
+template <bool SH>
 __device__ __forceinline__ int star_box(const ShapeD& s, int dim, const double lo[3],
                                         const double hi[3]) {
   double xc[3] = {0.0, 0.0, 0.0}, rc2 = 0.0, hd2 = 0.0;
@@ -46,7 +47,7 @@ __device__ __forceinline__ int star_box(const ShapeD& s, int dim, const double l
   const double inv = 1.0 / rc;
   const double D = hd * inv * 1.0472 * (1.0 + 1e-12) + 1e-15;
   double r;
-  if (s.kind == kStar2D) {
+  if (!SH || s.kind == kStar2D) {
     double r1;
     star_r(s, xc[0] * inv, xc[1] * inv, r, r1);
   } else {
@@ -80,20 +81,22 @@ __device__ __forceinline__ int box_radial(const ShapeD& s, int dim, const double
 }
 
 // The same, then the Lipschitz test for star and SH bodies.
+template <bool SH>
 __device__ __forceinline__ int box_settled(const ShapeD& s, int dim, const double lo[3],
                                            const double hi[3]) {
   const int r = box_radial(s, dim, lo, hi);
   if (r >= 0) return r;
-  if (s.kind == kStar2D || s.kind == kShStar) return star_box(s, dim, lo, hi);
+  if (s.kind == kStar2D || (SH && s.kind == kShStar)) return star_box<SH>(s, dim, lo, hi);
   return -1;
 }
 
 // Solid test of cell (i, j, k); g and s come from registers and LDS (the
 // caller copies them once per workgroup: read through the instance table,
 // every field would be a dependent scalar load).
+template <bool SH>
 __device__ __forceinline__ bool cell_solid(const GridD& g, const ShapeD& s, int i, int j, int k) {
-  double x[3] = {centre(g, 0, i), centre(g, 1, j), g.dim == 3 ? centre(g, 2, k) : 0.0};
-  return inside(s, g.dim, x);
+  double x[3] = {centre(g, 0, i), centre(g, 1, j), SH && g.dim == 3 ? centre(g, 2, k) : 0.0};
+  return inside<SH>(s, SH ? g.dim : 2, x);
 }
 
 // nvalid tags of value v (0 or 1) from cell `dst` on
@@ -173,7 +176,7 @@ __global__ __launch_bounds__(256) void k_spans(const Inst* __restrict__ insts, i
           lo[a] = centre_below(g, a, mn[a]);
           hi[a] = centre_above(g, a, mx[a]);
         }
-        r = (int8_t)box_settled(I.s, g.dim, lo, hi);
+        r = (int8_t)box_settled<true>(I.s, g.dim, lo, hi);
         if (r >= 0 && base + kSpan <= g.ncell) whole = I.cell_off + base;
       }
       span[chunk * kPer + tid % kPer] = r;
@@ -201,8 +204,10 @@ __global__ __launch_bounds__(256) void k_spans(const Inst* __restrict__ insts, i
 // segment within one row is one box; one that crosses a row end (or is cut
 // by the grid end) is the tail of its first row and the head of its second,
 // each boxed with its face neighbours, both of which must agree.
+template <bool SH>
 __device__ __forceinline__ int seg_settled(const GridD& g, const ShapeD& S, int base, int nvalid,
                                            bool full) {
+  const int dim = SH ? g.dim : 2;
   int i0, j, k;
   unlinear(g, base, i0, j, k);
   if (nvalid == kSeg && i0 + kSeg - 1 < g.n[0]) {
@@ -212,11 +217,11 @@ __device__ __forceinline__ int seg_settled(const GridD& g, const ShapeD& S, int 
     lo[1] = centre_below(g, 1, j);
     hi[1] = centre_above(g, 1, j);
     lo[2] = hi[2] = 0.0;
-    if (g.dim == 3) {
+    if (dim == 3) {
       lo[2] = centre_below(g, 2, k);
       hi[2] = centre_above(g, 2, k);
     }
-    return full ? box_settled(S, g.dim, lo, hi) : box_radial(S, g.dim, lo, hi);
+    return full ? box_settled<SH>(S, dim, lo, hi) : box_radial(S, dim, lo, hi);
   }
   // (with rows of 16 cells or more a segment meets at most two rows)
   if (g.n[0] < kSeg) return -1;
@@ -228,20 +233,20 @@ __device__ __forceinline__ int seg_settled(const GridD& g, const ShapeD& S, int 
   // (axes unrolled: a runtime index into g would move it to scratch)
 #pragma unroll
   for (int a = 0; a < 3; ++a)
-    if (a < g.dim) {
+    if (a < dim) {
       lo[a] = centre_below(g, a, seg_a[a]);
       hi[a] = centre_above(g, a, seg_b[a]);
     }
-  int sa = full ? box_settled(S, g.dim, lo, hi) : box_radial(S, g.dim, lo, hi);
+  int sa = full ? box_settled<SH>(S, dim, lo, hi) : box_radial(S, dim, lo, hi);
   if (!one_row && sa >= 0) {
     const int c0[3] = {0, p1[1], p1[2]};
 #pragma unroll
     for (int a = 0; a < 3; ++a)
-      if (a < g.dim) {
+      if (a < dim) {
         lo[a] = centre_below(g, a, c0[a]);
         hi[a] = centre_above(g, a, p1[a]);
       }
-    const int sb = full ? box_settled(S, g.dim, lo, hi) : box_radial(S, g.dim, lo, hi);
+    const int sb = full ? box_settled<SH>(S, dim, lo, hi) : box_radial(S, dim, lo, hi);
     if (sb != sa) sa = -1;
   }
   return sa;
@@ -259,6 +264,7 @@ __device__ __forceinline__ int seg_settled(const GridD& g, const ShapeD& S, int 
 // bit here and their interface mark (a face neighbour of the other class)
 // from k_band_iface; settled segments have none, since their boxes include
 // the face neighbours.  The chunk's band is recorded as a 256-bit mask.
+template <bool SH>
 __device__ __forceinline__ void classify_chunk(int64_t chunk, int ii, const Inst* __restrict__ insts,
                                                const int8_t* __restrict__ span,
                                                int8_t* __restrict__ tags,
@@ -313,7 +319,7 @@ __device__ __forceinline__ void classify_chunk(int64_t chunk, int ii, const Inst
   if (wset >= 0) {
     if (!spans_stored) store_const(tags + cell_off + base64, kSeg, wset);
   } else if (valid) {
-    const int r = seg_settled(g, S, (int)base64, nvalid, false);
+    const int r = seg_settled<SH>(g, S, (int)base64, nvalid, false);
     if (r >= 0) store_const(tags + cell_off + base64, nvalid, r);
     else if (lip) s_la[atomicAdd(&s_na, 1)] = (uint8_t)tid;
     else s_lb[atomicAdd(&s_nb, 1)] = (uint8_t)tid;
@@ -324,7 +330,7 @@ __device__ __forceinline__ void classify_chunk(int64_t chunk, int ii, const Inst
     const int l = s_la[t];
     const int64_t b = cbase + (int64_t)l * kSeg;
     const int nv = (int)min((int64_t)kSeg, g.ncell - b);
-    const int r = seg_settled(g, S, (int)b, nv, true);
+    const int r = seg_settled<SH>(g, S, (int)b, nv, true);
     if (r >= 0) store_const(tags + cell_off + b, nv, r);
     else s_lb[atomicAdd(&s_nb, 1)] = (uint8_t)l;
   }
@@ -338,7 +344,7 @@ __device__ __forceinline__ void classify_chunk(int64_t chunk, int ii, const Inst
     if (c >= g.ncell) continue;
     int i, j, k;
     unlinear(g, (int)c, i, j, k);
-    tags[cell_off + c] = cell_solid(g, S, i, j, k) ? 1 : 0;
+    tags[cell_off + c] = cell_solid<SH>(g, S, i, j, k) ? 1 : 0;
   }
   __syncthreads();
   if (tid < 4) bandmask[chunk * 4 + tid] = s_mask[tid];
@@ -351,8 +357,13 @@ __device__ __forceinline__ void classify_chunk(int64_t chunk, int ii, const Inst
 // launch before it).  The loop of mode 2 costs registers, and so occupancy,
 // that the one-chunk forms do without, so a list is taken by a mode-1 grid
 // and a small mode-2 launch after it for whatever that grid left.
+// Bound by the latency of FP64 chains (square roots, divisions, the star's
+// series) over the waves that fit, so mode 0, which sees 2D grids only, is
+// compiled for them (no body of spherical harmonics, no third axis: 66 registers
+// for 89) and all modes for seven waves: 64 stars, 23,000 chunks, 94 -> 62 us;
+// the list of the 512^3 sphere 18.6 -> 15.5, though mode 1 then spills twelve.
 template <int Mode>
-__global__ __launch_bounds__(256) void k_classify(const Inst* __restrict__ insts,
+__global__ __launch_bounds__(256, 7) void k_classify(const Inst* __restrict__ insts,
                                                   const int32_t* __restrict__ chunk_inst,
                                                   const int8_t* __restrict__ span,
                                                   int8_t* __restrict__ tags,
@@ -362,7 +373,7 @@ __global__ __launch_bounds__(256) void k_classify(const Inst* __restrict__ insts
                                                   const int32_t* __restrict__ nlist,
                                                   bool spans_stored, int first) {
   if (Mode == 0) {
-    classify_chunk(blockIdx.x, chunk_inst[blockIdx.x], insts, span, tags, chunk_cnt, bandmask,
+    classify_chunk<false>(blockIdx.x, chunk_inst[blockIdx.x], insts, span, tags, chunk_cnt, bandmask,
                    false);
     return;
   }
@@ -371,14 +382,14 @@ __global__ __launch_bounds__(256) void k_classify(const Inst* __restrict__ insts
     const int it = first + (int)blockIdx.x;
     if (it < nit) {
       const int64_t chunk = list[it];
-      classify_chunk(chunk, chunk_inst[chunk], insts, span, tags, chunk_cnt, bandmask,
+      classify_chunk<true>(chunk, chunk_inst[chunk], insts, span, tags, chunk_cnt, bandmask,
                      spans_stored);
     }
     return;
   }
   for (int it = first + (int)blockIdx.x; it < nit; it += gridDim.x) {
     const int64_t chunk = list[it];
-    classify_chunk(chunk, chunk_inst[chunk], insts, span, tags, chunk_cnt, bandmask,
+    classify_chunk<true>(chunk, chunk_inst[chunk], insts, span, tags, chunk_cnt, bandmask,
                    spans_stored);
     __syncthreads();   // the LDS lists are reused by the next chunk
   }

@@ -41,7 +41,23 @@ struct GridD {
   double h[3];
   int64_t ncell;
   const double* face[3];   // stretched axis: n + 1 cell faces (device), else null
+  uint32_t div_m[2];       // x / n[a] = x div_m[a] >> div_s[a] for 0 <= x < 2^31 (set_division)
+  int32_t div_s[2];
 };
+
+// Division by the rows' lengths as a product (Granlund and Montgomery, 1994):
+// with 2^(l-1) < n <= 2^l and m = ceil(2^(31+l) / n) < 2^32, m n exceeds
+// 2^(31+l) by less than n <= 2^l, so floor(x m / 2^(31+l)) = floor(x / n) for
+// x < 2^31.  A division by a number that is not known to the compiler takes
+// about 35 instructions, and most passes over cells begin with two.
+inline void set_division(GridD* g) {
+  for (int a = 0; a < 2; ++a) {
+    int l = 0;
+    while ((int64_t(1) << l) < g->n[a]) ++l;
+    g->div_s[a] = 31 + l;
+    g->div_m[a] = (uint32_t)(((uint64_t(1) << (31 + l)) + (uint64_t)g->n[a] - 1) / (uint64_t)g->n[a]);
+  }
+}
 
 struct ShapeD {
   int kind, ncoef, L, pad;
@@ -184,9 +200,9 @@ __device__ __forceinline__ int cell_of(const GridD& g, int ax, double x) {
 }
 
 __device__ __forceinline__ void unlinear(const GridD& g, int c, int& i, int& j, int& k) {
-  const int t = c / g.n[0];
+  const int t = (int)(((uint64_t)(uint32_t)c * g.div_m[0]) >> g.div_s[0]);
   i = c - t * g.n[0];
-  k = g.dim == 2 ? 0 : t / g.n[1];
+  k = g.dim == 2 ? 0 : (int)(((uint64_t)(uint32_t)t * g.div_m[1]) >> g.div_s[1]);
   j = t - k * g.n[1];
 }
 
@@ -475,6 +491,7 @@ __device__ __forceinline__ void sh_r(const ShapeD& s, const double u[3], double&
 }
 
 // Inside test: true for a solid centre (psi >= 0), boundary points solid.
+template <bool SH = true>   // (false: 2D, no body of spherical harmonics)
 __device__ __forceinline__ bool inside(const ShapeD& s, int dim, const double x[3]) {
   if (s.kind == kAirfoil) {
     double dx = (x[0] - s.c[0]) / s.chord, dy = (x[1] - s.c[1]) / s.chord;
@@ -497,7 +514,7 @@ __device__ __forceinline__ bool inside(const ShapeD& s, int dim, const double x[
     r = s.r0;
   } else {
     if (rho == 0.0) return true;
-    if (s.kind == kStar2D) {
+    if (!SH || s.kind == kStar2D) {
       double r1;
       star_r(s, dx / rho, dy / rho, r, r1);
     } else {

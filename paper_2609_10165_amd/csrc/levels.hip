@@ -449,7 +449,7 @@ __device__ __forceinline__ void canonical_order(const LevelsArgs& L, int ii, int
 // against 129 for the push form with its reverse edges (which took another
 // 24 us to build).
 constexpr int kPullMax = 16384;
-constexpr int kPullRounds = 4;
+constexpr int kPullRounds = 8;   // (4: 37 us on the 2731^2 airfoil, 8: 34, the stars alike, 32: worse there)
 constexpr int kPullCand = 256;   // cycle ghosts looked at per stall
 constexpr int kPullWS = 3 * kMaxUnit;   // 2-byte members, 1-byte rows of their reads
 

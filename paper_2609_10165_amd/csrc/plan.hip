@@ -1495,6 +1495,7 @@ static gcr_status make_inst(const gcr_grid& gg, const gcr_shape& gs, int scheme,
     }
   }
   I->g.ncell = ncell;
+  set_division(&I->g);
   I->scheme = base;
   I->layer2 = (scheme & kLayer2) ? 1 : 0;
   if (I->layer2) {
