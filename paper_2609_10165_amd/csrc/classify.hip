@@ -126,6 +126,7 @@ __global__ __launch_bounds__(256) void k_spans(const Inst* __restrict__ insts, i
                                                int32_t* __restrict__ chunk_cnt,
                                                uint64_t* __restrict__ bandmask,
                                                int8_t* __restrict__ tags,
+                                               const int8_t* __restrict__ prev,
                                                int32_t* __restrict__ nband,
                                                unsigned long long* __restrict__ posted,
                                                int64_t nposted) {
@@ -187,7 +188,10 @@ __global__ __launch_bounds__(256) void k_spans(const Inst* __restrict__ insts, i
   __syncthreads();
   if (tid < kSpanChunks && c0 + tid < chunks) {
     bool nd = false;
-    for (int q = 0; q < kPer; ++q) nd = nd || s_base[tid * kPer + q] < 0;
+    for (int q = 0; q < kPer; ++q)
+      nd = nd || (prev ? s_flag[tid * kPer + q] < 0 ||
+                             prev[(c0 + tid) * kPer + q] != s_flag[tid * kPer + q]
+                       : s_base[tid * kPer + q] < 0);
     need[c0 + tid] = nd ? 1 : 0;
   }
   if (!tags) return;
@@ -489,25 +493,12 @@ __global__ __launch_bounds__(256) void k_band_iface(const Inst* __restrict__ ins
 // A chunk keeps its tags across a move when each of its spans was settled
 // before and is settled to the same class after: then every cell of it and
 // every face neighbour lies on that side of both boundaries, so the cell's
-// class is unchanged and it is no interface cell either time.  Those tags
-// are its settled value unless a ghost of the previous plan lies there (a
-// second-layer ghost can sit in a settled solid span), which
-// k_dirty_ghosts catches.  One thread per chunk: dirty[c] = 1 for a chunk
-// to classify again.
-__global__ __launch_bounds__(256) void k_dirty(const int8_t* __restrict__ span0,
-                                               const int8_t* __restrict__ span1, int64_t chunks,
-                                               int32_t* __restrict__ dirty) {
-  constexpr int kPer = kChunk / (64 * kSeg);
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= chunks) return;
-  bool d = false;
-#pragma unroll
-  for (int q = 0; q < kPer; ++q) {
-    const int8_t a = span0[c * kPer + q], b = span1[c * kPer + q];
-    d = d || b < 0 || a != b;
-  }
-  dirty[c] = d ? 1 : 0;
-}
+// class is unchanged and it is no interface cell either time.  The span pass
+// flags the other chunks (prev: the previous plan's spans; a launch of its own
+// took 2.6 us and a gap of each move).  Those tags are
+// its settled value unless a ghost of the previous plan lies there (a
+// second-layer ghost can sit in a settled solid span), which k_dirty_ghosts
+// catches.
 
 // the chunks of the previous plan's ghosts (a single instance from chunk 0)
 __global__ __launch_bounds__(256) void k_dirty_ghosts(const int32_t* __restrict__ cell,
@@ -530,7 +521,7 @@ void launch_classify(const Inst* insts, int ninst, const int64_t* chunk_start, i
   const bool every = !U && W.every_chunk;
   k_spans<<<(unsigned)((chunks + kSpanChunks - 1) / kSpanChunks), 256, 0, st>>>(
       insts, ninst, chunk_start, chunks, span, chunk_inst, W.flag, chunk_cnt, mask,
-      U || every ? nullptr : tags, nband, W.scan_tmp, W.scan_words);
+      U || every ? nullptr : tags, U ? U->span_prev : nullptr, nband, W.scan_tmp, W.scan_words);
   if (ev_prepass) (void)hipEventRecord(ev_prepass, st);
   if (every) {
     k_classify<0><<<(unsigned)chunks, 256, 0, st>>>(insts, chunk_inst, span, tags, chunk_cnt, mask,
@@ -542,8 +533,6 @@ void launch_classify(const Inst* insts, int ninst, const int64_t* chunk_start, i
   }
   if (U) {
     // a re-plan: the chunks the move can change, instead of those left
-    k_dirty<<<(unsigned)((chunks + 255) / 256), 256, 0, st>>>(U->span_prev, span, chunks,
-                                                              W.flag);
     if (U->ng_prev > 0)
       k_dirty_ghosts<<<(unsigned)((U->ng_prev + 255) / 256), 256, 0, st>>>(
           U->ghost_prev, U->ng_prev, W.flag);
