@@ -22,9 +22,11 @@
  *  - `stream` is a hipStream_t (NULL: the null stream).  Every call that
  *    launches work is asynchronous on that stream, except gcr_plan_create
  *    and gcr_batch_create, which synchronise it twice (to size the band
- *    arrays, then to read the level offsets), and the first gcr_fill with
- *    the automatic schedule or gcr_batch_forward for a kind of plan, which
- *    times candidate schedules once and remembers the winner.
+ *    arrays, then to read the level offsets), and, where neither the fill in
+ *    LDS nor the waiting one serves (coupled units beyond LDS; a batch with
+ *    2D instances beyond LDS), the first gcr_fill with the automatic schedule
+ *    or gcr_batch_forward for a kind of plan, which times candidate schedules
+ *    once and remembers the winner.
  *  - Every call returns GCR_OK or an error code; gcr_status_str() names it.
  *    Geometry and graph errors are detected when a plan is built; apply
  *    calls fail only on bad arguments or HIP errors.  On error nothing the
@@ -216,9 +218,12 @@ gcr_status gcr_plan_fresh_cells(const gcr_plan* before, const gcr_plan* after,
                                 int64_t* counts, int32_t* list, int64_t cap,
                                 void* stream);
 
-/* Fill schedule.  0 = automatic (tuned), 1 = one launch per level,
- * 2 = one workgroup sweeping all levels, 3 = per-level launches captured in a
- * HIP graph and replayed.  `param` is reserved (0). */
+/* Fill schedule.  0 = automatic (in LDS where a 2D plan fits, else every
+ * ghost waiting for its corners; for plans with coupled units beyond LDS the
+ * schedules below, timed on the first call for a kind of plan), 1 = one launch
+ * per level, 2 = one workgroup sweeping all levels, 3 = the launches of 1
+ * replayed from a HIP graph.  The values are the same, bit for bit.  param
+ * must be 0. */
 gcr_status gcr_set_schedule(gcr_plan* plan, int32_t schedule, int32_t param);
 
 /* Level-by-level ghost fill (Sec. 3.2 with Eqs. phi_G_Dir_2d, phi_G_Neu_2d,

@@ -1,7 +1,8 @@
 // capi.hip -- the C-ABI of libgcr: argument checks, plan objects, the
-// device memory pool, fill schedules (per-level launches, single-workgroup
-// sweep, per-level launches replayed from a HIP graph) and the tuner that
-// picks among them by timing.
+// device memory pool, the choice of the fill's form, and its schedules beside
+// the LDS and the waiting form (per-level launches, single-workgroup sweep,
+// per-level launches replayed from a HIP graph), among which a tuner picks by
+// timing for plans that those two leave.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -7,13 +7,12 @@
 //                 16-byte constant stores
 //   scan/compact  interface cells in linear-index order
 //   geometry      closest point, analytic normal, psi; ghost tags for CGC,
-//                 CGC_ES and HGC (Eq. HGC_criterion with Eq. delta_n)
-//   ghosts        order-preserving compaction of the ghost cells
+//                 CGC_ES and HGC (Eq. HGC_criterion with Eq. delta_n); the
+//                 ghosts in linear-index order, and their cell table
 //   deps          stencil code (e = sgn n, multipliers r), validation, and
 //                 ghost-to-ghost dependencies (Sec. 3.2)
-//   levels        Kahn layering per instance, emitting the canonical order
-//                 (level, linear index) as it goes; a stall means a cycle:
-//                 its strongly connected groups become coupled units
+//   levels        layering and canonical order (level, linear index); a
+//                 cycle's strongly connected groups become coupled units
 //   finalize      canonical structure-of-arrays for the apply kernels
 #include <hip/hip_runtime.h>
 
