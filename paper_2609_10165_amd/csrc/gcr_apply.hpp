@@ -156,49 +156,11 @@ __device__ __forceinline__ void corner_values(const PlanD& P, int p, const doubl
 
 // Anchor of a point: among ghosts within 2 cells per axis of the point's
 // cell, the one whose foot point is nearest; ties go to the smaller linear
-// index (cells are visited in ascending linear index, strict comparison).
-template <int D>
-__device__ __forceinline__ int find_anchor(const PlanD& P, const double x[3]) {
-  int qi[3] = {0, 0, 0};
-#pragma unroll
-  for (int a = 0; a < D; ++a) qi[a] = cell_of(P.g, a, x[a]);
-  int best = -1;
-  double bd = 1e300;
-  const int z0 = D == 3 ? qi[2] - 2 : 0, z1 = D == 3 ? qi[2] + 2 : 0;
-  for (int kz = z0; kz <= z1; ++kz) {
-    if (D == 3 && (kz < 0 || kz >= P.g.n[2])) continue;
-    for (int jy = qi[1] - 2; jy <= qi[1] + 2; ++jy) {
-      if (jy < 0 || jy >= P.g.n[1]) continue;
-      for (int ix = qi[0] - 2; ix <= qi[0] + 2; ++ix) {
-        if (ix < 0 || ix >= P.g.n[0]) continue;
-        const int c = linear(P.g, ix, jy, kz);
-        const int8_t t = P.tags[c];
-        if (t != 2 && t != -2) continue;
-        const int g = ghost_at(P, c);
-        if (g < 0) continue;
-        const int q[3] = {ix, jy, kz};
-        double d2 = 0.0;
-#pragma unroll
-        for (int a = 0; a < D; ++a) {
-          double s = centre(P.g, a, q[a]) + P.dl[a][g];
-          d2 += (x[a] - s) * (x[a] - s);
-        }
-        if (d2 < bd) {
-          bd = d2;
-          best = g;
-        }
-      }
-    }
-  }
-  return best;
-}
-
-// The same anchor found by NL cooperating lanes (NL a power of two, the
-// lanes sub = 0..NL-1 of one aligned group of a wave, all of them calling):
-// each lane scans every NL-th cell of the 5^D neighbourhood, then the group
-// reduces (d2, linear index) lexicographically, which picks the cell the
-// serial scan picks.  `active` false makes a lane scan nothing (it still
-// takes part in the reduction).
+// index.  Found by NL cooperating lanes (NL a power of two, the lanes sub =
+// 0..NL-1 of one aligned group of a wave, all of them calling): each lane
+// takes every NL-th cell of the 5^D neighbourhood, then the group reduces (d2,
+// linear index) lexicographically.  `active` false makes a lane take nothing
+// (it still takes part in the reduction).
 template <int D>
 constexpr int anchor_lanes() { return D == 3 ? 64 : 32; }
 
