@@ -8,7 +8,7 @@ whole path for all 64 instances:
   plans (classification, tags, geometry, dependency levels, canonical order)
   -> foot points and the caller's boundary data there (kinds and values of
      the three fields, torch)
-  -> one persistent launch: level-by-level fill of the three fields, their
+  -> shared launches: level-by-level fill of the three fields, their
      values and gradients at each instance's 256 surface points and the
      pressure + viscous force on each body.
 Metric: ghost cells per second (ghosts of the 64 plans per step / step
@@ -1102,7 +1102,7 @@ def main():
                                "n ~ U{128..2048} on [-1,1]^2, HGC, 3 FP64 fields with mixed "
                                "Dirichlet/Neumann data per ghost, 256 surface points each; per "
                                "step a batch built and forwarded (fill + surface values + force "
-                               "in one persistent launch); steps pipelined: batches built by "
+                               "by shared launches); steps pipelined: batches built by "
                                "host threads on streams of their own, forwards on another",
                    "ghosts_per_step": m["ghosts"], "cells": W.cells, "instances": W.ninst,
                    "build_threads": m["nbuild"]},
