@@ -17,6 +17,10 @@ namespace gcr {
 constexpr int kStages = 13;   // plan-build stages timed by gcr_last_build_times
 
 
+// InstInfo::layered: 1 by a layering that later ones then pass over, and once
+// k_finalize has mapped the unit members of such an instance
+constexpr int kLayeredMapped = 2;
+
 // Per-instance results of plan building, written by the device.
 struct InstInfo {
   uint32_t err;
@@ -26,7 +30,7 @@ struct InstInfo {
   int32_t maxwidth;
   int32_t nfluid;
   int32_t rmax[3];      // largest stencil multiplier per axis
-  int32_t layered;      // set when the LDS layering finished the instance
+  int32_t layered;      // 0: not, or by k_levels (which comes last)
   int32_t fill_fault;   // set on the device by an adjoint whose wait gave up
   unsigned long long max_alpha_bits[3];
 };

@@ -721,6 +721,7 @@ __global__ __launch_bounds__(1024) void k_levels_fast(LevelsArgs L, int lds_byte
   __shared__ int64_t sh[17];
   __shared__ int s_flag, s_units, s_maxunit, s_maxlev, s_placed, s_bad;
   const int ii = blockIdx.x;
+  if (L.info[ii].layered) return;   // (a second layering: it left this one out)
   const int tid = threadIdx.x;
   const int64_t lo = L.g_off[ii];
   const int n = (int)(L.g_off[ii + 1] - lo);

@@ -1293,8 +1293,11 @@ struct BuildResult {
 };
 
 // Workgroup ii < ninst: the instance's unit members from linear-order to
-// canonical positions, the waves' statistics (k_deps) folded into its info
-// (max, max, sum: the order does not matter), and its results to the host.
+// canonical positions, and its results to the host, the waves' statistics
+// (k_deps) folded into its info there (max, max, sum: the order does not
+// matter).  Run again after a second layering, it leaves an instance that was
+// finished before as it is: the members are mapped once (info.layered), and
+// the device's info stays without the waves' sums.
 __device__ __forceinline__ void finish_instance(int ii, int ninst, const int64_t* __restrict__ g_off,
                                                 const int32_t* __restrict__ perm,
                                                 InstInfo* __restrict__ info,
@@ -1308,8 +1311,10 @@ __device__ __forceinline__ void finish_instance(int ii, int ninst, const int64_t
   const int nu = min(max(info[ii].nunits, 0), kMaxUnits), nl = min(max(info[ii].nlev, 0), kMaxLevels);
   int32_t* um = unit_mem + (int64_t)ii * kMaxUnits * kMaxUnit;
   const int32_t* uc = unit_cnt + (int64_t)ii * kMaxUnits;
-  for (int t = tid; t < nu * kMaxUnit; t += blockDim.x)
-    if (t % kMaxUnit < uc[t / kMaxUnit]) um[t] = perm[um[t]];
+  const int layered = info[ii].layered;
+  if (layered != kLayeredMapped)
+    for (int t = tid; t < nu * kMaxUnit; t += blockDim.x)
+      if (t % kMaxUnit < uc[t / kMaxUnit]) um[t] = perm[um[t]];
   for (int t = tid; t <= nl; t += blockDim.x)
     out.lev_off[(int64_t)ii * (kMaxLevels + 1) + t] = lev_off[(int64_t)ii * (kMaxLevels + 1) + t];
   for (int t = tid; t < nu; t += blockDim.x)
@@ -1356,7 +1361,7 @@ __device__ __forceinline__ void finish_instance(int ii, int ninst, const int64_t
     }
     I.nfluid += s_fl[w];
   }
-  info[ii] = I;
+  if (layered) info[ii].layered = kLayeredMapped;
   out.info[ii] = I;
   out.g_off[ii] = b;
   if (ii == ninst - 1) out.g_off[ninst] = e;
@@ -1424,26 +1429,6 @@ __global__ __launch_bounds__(256) void k_finalize(
 __global__ void k_hash_clear(unsigned long long* __restrict__ t, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) t[i] = ~0ull;
-}
-
-// the tables of a second layering, as k_geometry fills them
-__global__ void k_hash_build(const int64_t* __restrict__ g_off, int ninst,
-                             const int32_t* __restrict__ cell,
-                             const int64_t* __restrict__ hoff,
-                             const uint32_t* __restrict__ hmask,
-                             unsigned long long* __restrict__ htab,
-                             uint32_t* __restrict__ g_slot) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= g_off[ninst]) return;
-  const int ii = find_inst(g_off, ninst, e);
-  g_slot[e] = table_insert(htab + hoff[ii], hmask[ii], cell[e], (uint32_t)e);
-}
-
-// before a second layering of the same ghosts: the statistics that
-// k_finalize adds up, from zero
-__global__ void k_info_reset(InstInfo* __restrict__ info, int ninst) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < ninst) info[i].nfluid = 0;
 }
 
 // --------------------------------------------------------------------------
@@ -1786,23 +1771,20 @@ gcr_status build_update(BatchData& prev, const ShapeD& shape, bool incremental, 
   return build_core(B, st, incremental ? &prev : nullptr, out);
 }
 
-// The ghosts' cell table, dependencies, levels and canonical arrays, from the
-// ghosts in linear order, layered as `how` says: by one workgroup per
-// instance pulling, by the whole GPU, or by the layerings that push along
-// reverse edges, which take every graph the others leave.
+// The levels and canonical arrays, from the ghosts in linear order and their
+// dependencies, layered as `how` says: by one workgroup per instance pulling,
+// by the whole GPU, or by the layerings that push along reverse edges, which
+// take every graph the others leave.  A second call for instances that the
+// first left does no harm to the others: the push layerings pass them by
+// (info.layered), k_finalize stores the same again, and of those left it has
+// stored nothing (their cell tables hold linear-order indices as before).
 enum Layering { kLayerPull, kLayerFlow, kLayerPush };
-static gcr_status build_graph(BatchData& D, hipStream_t st, int ninst, int64_t nif,
-                              int64_t max_if, Layering how, const BuildResult& out,
-                              StageEvents& T) {
+static gcr_status build_levels(BatchData& D, hipStream_t st, int ninst, int64_t nif,
+                               int64_t max_if, Layering how, const FinPart* part,
+                               const BuildResult& out, StageEvents& T) {
   const int64_t cap = D.cap;
   int32_t* hist = nullptr;
   // ghost count unknown on the host: launch over the interface capacity
-  FinPart* const part = own<FinPart>(D, (cap + 63) / 64);
-  if (!part) return GCR_E_NOMEM;
-  k_deps<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, ninst, D.d_g_off, D.d_g_cell, D.d_g_psi,
-                                            D.d_g_n, cap, D.d_g_ext, D.d_tags, D.d_htab, D.d_hoff,
-                                            D.d_hmask, D.d_g_code, D.d_deps, D.d_lev, D.d_info,
-                                            part);
   if (how == kLayerPush) {
     k_zero_words<<<blocks(2 * cap, 256), 256, 0, st>>>(D.d_rcnt, 2 * cap);
     k_rcount<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, D.d_g_off, ninst, cap, D.d_deps,
@@ -2079,6 +2061,7 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
                              reinterpret_cast<int32_t*>(PS.p + o_lo),
                              reinterpret_cast<int32_t*>(PS.p + o_ul)};
   Layering how = kLayerPush;
+  FinPart* part = nullptr;
   if (nif > 0) {
     k_compact_iface<<<(unsigned)nlist, 256, 0, st>>>(D.d_inst, D.d_chunk_inst, D.d_tags,
                                                      D.d_chunk_cnt, D.d_chunk_excl, D.d_chunk_list,
@@ -2101,7 +2084,13 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
     const bool flow = ninst == 1 && max_if >= wide_layering_min() &&
                       (any_3d || wide_layering_forced());
     how = flow ? kLayerFlow : levels_pull(max_if) ? kLayerPull : kLayerPush;
-    const gcr_status s = build_graph(D, st, ninst, nif, max_if, how, out_host, T);
+    part = own<FinPart>(D, (cap + 63) / 64);
+    if (!part) return GCR_E_NOMEM;
+    k_deps<<<blocks(nif, 256), 256, 0, st>>>(D.d_inst, ninst, D.d_g_off, D.d_g_cell, D.d_g_psi,
+                                              D.d_g_n, cap, D.d_g_ext, D.d_tags, D.d_htab,
+                                              D.d_hoff, D.d_hmask, D.d_g_code, D.d_deps, D.d_lev,
+                                              D.d_info, part);
+    const gcr_status s = build_levels(D, st, ninst, nif, max_if, how, part, out_host, T);
     if (s != GCR_OK) return s;
   } else {
     k_hash_clear<<<blocks(D.hoff[ninst], 256), 256, 0, st>>>(D.d_htab, D.hoff[ninst]);
@@ -2123,16 +2112,12 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
     for (int i = 0; i < ninst && how != kLayerPush; ++i)
       again = again || (!D.info[i].layered && !D.info[i].err && D.g_off[i + 1] > D.g_off[i]);
     if (!again) break;
-    // a graph that these layerings leave (deeper than their tables, a unit
-    // beyond the solver's size, a cycle in a large 3D one): once more
+    // graphs that these layerings leave (deeper than their tables, a unit
+    // beyond the solver's size, a cycle in a large 3D one): those once more
     how = kLayerPush;
     int64_t max_if = 0;
     for (int i = 0; i < ninst; ++i) max_if = std::max(max_if, D.if_off[i + 1] - D.if_off[i]);
-    k_info_reset<<<blocks(ninst, 64), 64, 0, st>>>(D.d_info, ninst);
-    k_hash_clear<<<blocks(D.hoff[ninst], 256), 256, 0, st>>>(D.d_htab, D.hoff[ninst]);
-    k_hash_build<<<blocks(nif, 256), 256, 0, st>>>(D.d_g_off, ninst, D.d_g_cell, D.d_hoff,
-                                                    D.d_hmask, D.d_htab, D.d_g_slot);
-    const gcr_status s = build_graph(D, st, ninst, nif, max_if, how, out_host, T);
+    const gcr_status s = build_levels(D, st, ninst, nif, max_if, how, part, out_host, T);
     if (s != GCR_OK) return s;
   }
   PS.pending = false;
