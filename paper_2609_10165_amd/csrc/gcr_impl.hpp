@@ -166,7 +166,7 @@ struct LevelsArgs {
   uint32_t* bits;
   InstInfo* info;
   // whole-GPU layering of a single large instance
-  int32_t* flow;         // [2] workgroups finished, ghosts placed (from zero; 8-byte aligned)
+  int32_t* flow;         // [3] workgroups finished, ghosts placed, stop (from zero; 8-byte aligned)
   int32_t* hist;         // [cap / 256 + 1][kWideLevels] level counts of the tiles of 256 ghosts
   int cur_cap;           // entries of a level list held in LDS (set at launch)
   int wave_res;          // residuals up to this size go to the one-wave solver

@@ -11,8 +11,8 @@
 //                            reverse edges (a CSR list built by grid-wide
 //                            kernels for them alone): batches with larger
 //                            instances, and the graphs the others leave
-//                            (deeper than their tables, a cycle in
-//                            k_levels_flow)
+//                            (deeper than their tables, a cycle in an
+//                            instance too large for k_levels_pull)
 //
 // k_levels, the most general: each ghost (or coupled unit) holds a byte
 // counter of unplaced ghosts it reads, packed four to a word and kept in LDS
@@ -69,11 +69,18 @@ __device__ __forceinline__ uint32_t cnt_get(const uint32_t* c, int i) {
 // grid barrier a level cost 30-40.
 // Reads that have a level are not polled again.  Waves wait only for
 // ghosts of the same launch; its at most kFlowGrid workgroups (half of what
-// the chip holds) are resident together unless other work fills it, and a
-// wave that saw no ghost of its own placed for kFlowPatience polls, nor any
-// workgroup finish meanwhile, gives up, so every wave ends: an instance with a
-// cycle, or one starved that way, is left with info.layered = 0 to the
-// one-workgroup layerings.  The tiles' counts per level follow.
+// the chip holds) are resident together unless other work fills it.  What it
+// does not finish it leaves with info.layered = 0 to the one-workgroup
+// layerings: an instance with a cycle, or one starved of its workgroups.
+//   - Two ghosts that read each other, the most common cycle by far, are
+//     seen as the reads are loaded (the corner is the same for both), and
+//     stop every wave at its next look.  Spheres are spared the search: a
+//     read leads away from the centre along every axis, so |x - c|_1 grows
+//     along a chain, which never closes.
+//   - A wave that placed no ghost of its own for kFlowTicks, nor saw a
+//     workgroup finish, stops every wave too (a chain of kWideLevels levels
+//     takes a third of that), so every wave ends.
+// The tiles' counts per level follow.
 //
 // k_levels_scan: the counts scanned over the tiles of each level, level
 // offsets, results.  k_finalize adds each ghost's rank in its tile: the
@@ -84,7 +91,12 @@ __device__ __forceinline__ uint32_t cnt_get(const uint32_t* c, int i) {
 // rounds with a grid barrier; 256^3 with a second layer (36,000): 26 against
 // 191 for one workgroup in LDS.
 constexpr int kFlowJ = 4, kFlowGrid = 1024;
-constexpr int kFlowPatience = 512;
+// Polls between two looks at the launch's state: often where a pair may have
+// stopped it (64^3 body with cycles: 52 us for both layerings, and 770 more
+// when waves only gave up in their own time), seldom on a sphere, as every
+// look reads one address (640^3: 38 us with the former, 34 with the latter).
+constexpr int kFlowLook = 16, kFlowLookSphere = 256;
+constexpr int64_t kFlowTicks = 20000;   // 200 us of the 100 MHz clock
 
 __device__ __forceinline__ int flow_get(const int32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -93,21 +105,30 @@ __device__ __forceinline__ void flow_put(int32_t* p, int v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Whether a wave that waits may go on: true while ghosts of its own or
-// whole workgroups are being placed.  done: workgroups finished, of the launch.
+// Whether a wave that waits may go on.  state: workgroups finished, ghosts
+// placed, and whether to stop, of the launch.
 struct FlowWait {
+  const int look;
   int polls = 0, seen = -1;
-  __device__ __forceinline__ bool go_on(bool moved, const int32_t* done) {
-    if (__ballot(moved) != 0ull) {
-      polls = 0;
-      return true;
-    }
-    if (++polls < kFlowPatience) return true;
+  bool moved_since = false;
+  int64_t since = 0;
+  __device__ __forceinline__ bool go_on(bool moved, int32_t* state) {
+    moved_since = moved_since || __ballot(moved) != 0ull;
+    if (++polls < look) return true;
     polls = 0;
-    const int d = __builtin_amdgcn_readfirstlane(flow_get(done));   // one answer for the wave
-    const bool alive = d != seen;
-    seen = d;
-    return alive;
+    // (one answer for the wave)
+    const int done = __builtin_amdgcn_readfirstlane(flow_get(state));
+    if (__builtin_amdgcn_readfirstlane(flow_get(state + 2)) != 0) return false;
+    const int64_t now = wall_clock64();
+    if (moved_since || done != seen) {
+      moved_since = false;
+      seen = done;
+      since = now;
+    } else if (now - since > kFlowTicks) {
+      flow_put(state + 2, 1);
+      return false;
+    }
+    return true;
   }
 };
 
@@ -119,6 +140,8 @@ __global__ __launch_bounds__(256) void k_levels_flow(LevelsArgs L) {
   const int n = (int)(L.g_off[1] - lo);
   const int ntiles = (n + 255) >> 8, G = (int)gridDim.x;
   const int np = (1 << L.insts[0].g.dim) - 1;
+  const bool pairs = L.insts[0].s.kind != kSphere;
+  const int look = pairs ? kFlowLook : kFlowLookSphere;
   const int32_t* __restrict__ deps = L.deps + lo;
   int32_t* lev = L.lev + lo;
   if (tid == 0) s_placed = 0;
@@ -146,7 +169,17 @@ __global__ __launch_bounds__(256) void k_levels_flow(LevelsArgs L) {
         L.blk_idx[lo + e] = -1;
       }
     }
-    FlowWait W;
+    if (pairs) {
+      bool met = false;
+#pragma unroll
+      for (int j = 0; j < kFlowJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 7; ++q)
+          if (d[j][q] >= 0)
+            met = met || deps[(int64_t)q * L.cap + d[j][q]] - lo == ((int)blockIdx.x + j * G) * 256 + tid;
+      if (met) flow_put(L.flow + 2, 1);
+    }
+    FlowWait W{look};
     while (__ballot(pend != 0) != 0ull) {
       bool moved = false;
 #pragma unroll
@@ -172,9 +205,16 @@ __global__ __launch_bounds__(256) void k_levels_flow(LevelsArgs L) {
     }
   } else {
     // more ghosts than the registers hold: their reads from memory, every time
-    for (int t = blockIdx.x; t < ntiles; t += G)
-      if (t * 256 + tid < n) L.blk_idx[lo + t * 256 + tid] = -1;
-    FlowWait W;
+    for (int t = blockIdx.x; t < ntiles; t += G) {
+      const int e = t * 256 + tid;
+      if (e >= n) continue;
+      L.blk_idx[lo + e] = -1;
+      for (int q = 0; q < np && pairs; ++q) {
+        const int32_t v = deps[(int64_t)q * L.cap + e];
+        if (v >= 0 && deps[(int64_t)q * L.cap + (v - lo)] - lo == e) flow_put(L.flow + 2, 1);
+      }
+    }
+    FlowWait W{look};
     for (bool open = true; __ballot(open) != 0ull;) {
       bool moved = false;
       open = false;

@@ -1014,7 +1014,7 @@ __global__ __launch_bounds__(BS) void k_geometry(
     for (int i = ii; i >= 0 && if_off[i] == e; --i) g_off[i] = pos;
   if (e == nif - 1)
     for (int i = ninst; i >= 0 && if_off[i] == nif; --i) g_off[i] = pos + (ghost ? 1 : 0);
-  if (e == 0) flow[0] = flow[1] = 0;   // of the whole-GPU layering
+  if (e == 0) flow[0] = flow[1] = flow[2] = 0;   // of the whole-GPU layering
 }
 
 // --------------------------------------------------------------------------
@@ -1825,7 +1825,7 @@ static gcr_status build_levels(BatchData& D, hipStream_t st, int ninst, int64_t 
     L.cur_cap = 0;
     L.wave_res = wave_residual();
     if (how == kLayerFlow) {
-      L.flow = D.d_rcnt;   // two cleared words
+      L.flow = D.d_rcnt;   // (cleared by k_geometry)
       hist = L.hist = own<int32_t>(D, (size_t)kWideLevels * (cap / 256 + 1));
       if (!L.hist) return GCR_E_NOMEM;
     }
@@ -2042,7 +2042,7 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
   D.d_blk = own<int32_t>(D, cap);
   if (any_2d) D.d_cgi = own<int32_t>(D, 3 * cap);
   D.d_listA = own<int32_t>(D, cap);
-  D.d_rcnt = own<int32_t>(D, 2 * cap);   // counts, then fill pointers
+  D.d_rcnt = own<int32_t>(D, 2 * cap + 1);   // counts, then fill pointers; before, LevelsArgs::flow
   D.d_roff = own<int32_t>(D, cap + 1);
   D.d_dcnt = own<uint8_t>(D, cap);
   D.d_radj = own<int32_t>(D, 7 * cap);
@@ -2113,10 +2113,11 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
       again = again || (!D.info[i].layered && !D.info[i].err && D.g_off[i + 1] > D.g_off[i]);
     if (!again) break;
     // graphs that these layerings leave (deeper than their tables, a unit
-    // beyond the solver's size, a cycle in a large 3D one): those once more
-    how = kLayerPush;
+    // beyond the solver's size, a cycle in a large 3D one): those once more,
+    // a cycle by the pull form where it fits
     int64_t max_if = 0;
     for (int i = 0; i < ninst; ++i) max_if = std::max(max_if, D.if_off[i + 1] - D.if_off[i]);
+    how = how == kLayerFlow && levels_pull(max_if) ? kLayerPull : kLayerPush;
     const gcr_status s = build_levels(D, st, ninst, nif, max_if, how, part, out_host, T);
     if (s != GCR_OK) return s;
   }
