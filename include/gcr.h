@@ -471,9 +471,9 @@ gcr_status gcr_set_batch_spin(int32_t polls);
  * or in HBM.  A threshold set here (`min_interface` > 0) sends every plan
  * built alone with at least that many interface cells, 2D ones too, to the
  * whole GPU first (for tests and measurements).  What the first two leave (a
- * cycle or more than 128 levels on the whole GPU, more than 256 levels in the
- * workgroup) is layered by the next that takes its size, so the result never
- * depends on this setting.  0 restores the default.  Process-wide; applies
+ * cycle or more than 128 levels on the whole GPU, more than 1,024 levels in the
+ * workgroup, or 256 up to 1,024 interface cells) is layered by the next that
+ * takes its size, so the result never depends on this setting.  0 restores the default.  Process-wide; applies
  * to plans built afterwards. */
 gcr_status gcr_set_wide_layering(int64_t min_interface);
 

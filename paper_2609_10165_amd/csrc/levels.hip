@@ -382,21 +382,20 @@ __device__ __forceinline__ void wave_push16(bool p, int v, uint16_t* list, int b
 }
 
 // The canonical order (level, linear index) of an instance's n ghosts, and
-// its results: a stable counting sort by one workgroup of BS threads, wave w
-// taking linear positions [w R, (w + 1) R).  tab: (BS / 64) x kFastLevels
-// counts; level_of(g): the level of ghost g.  Every thread calls it, after a
-// barrier behind the last write of a level.
-template <int BS, class F>
+// its results: a stable counting sort by one workgroup of BS threads, wave w <
+// NW taking linear positions [w R, (w + 1) R).  At most BS and 2^BITS levels;
+// tab: NW x nlev counts; level_of(g): the level of ghost g.  Every thread calls
+// it, after a barrier behind the last write of a level.
+template <int BS, int NW, int BITS, class F>
 __device__ __forceinline__ void canonical_order(const LevelsArgs& L, int ii, int64_t lo, int n,
                                                 int nlev, int units, int maxunit, int32_t* tab,
                                                 int* s_off, int* s_tot, int64_t* sh, F level_of) {
-  constexpr int NW = BS / 64;
   const int tid = threadIdx.x;
   const int R = ((((n + NW - 1) / NW) + 63) / 64) * 64;
   const int wv = tid >> 6, lane = tid & 63;
   for (int t = tid; t < NW * nlev; t += BS) tab[t] = 0;
   __syncthreads();
-  const int r0 = wv * R, r1 = min(n, r0 + R);
+  const int r0 = wv * R, r1 = wv < NW ? min(n, r0 + R) : r0;
   for (int g = r0 + lane; g < r1; g += 64) atomicAdd(&tab[wv * nlev + level_of(g) - 1], 1);
   __syncthreads();
   for (int l = tid; l < nlev; l += BS) {
@@ -424,8 +423,6 @@ __device__ __forceinline__ void canonical_order(const LevelsArgs& L, int ii, int
   __syncthreads();
   int32_t* __restrict__ lev = L.lev + lo;
   int32_t* __restrict__ perm = L.perm + lo;
-  static_assert(kFastLevels <= 256 && kFastLevels <= BS,
-                "a level index fits 8 ballots, and a level a thread");
   for (int c = r0; c < r1; c += 64) {
     const int g = c + lane;
     const bool valid = g < r1;
@@ -434,7 +431,7 @@ __device__ __forceinline__ void canonical_order(const LevelsArgs& L, int ii, int
     // of the level index, one ballot a bit
     unsigned long long mk = __ballot(valid);
 #pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
+    for (int bit = 0; bit < BITS; ++bit) {
       const bool on = (l >> bit) & 1;
       const unsigned long long bb = __ballot(valid && on);
       mk &= on ? bb : ~bb;
@@ -488,6 +485,11 @@ __device__ __forceinline__ void canonical_order(const LevelsArgs& L, int ii, int
 // is called by is its smallest ghost.  The 64-star batch: 50 us
 // against 129 for the push form with its reverse edges (which took another
 // 24 us to build).
+//
+// Up to kFastLevels levels are ranked by every wave, more by four, whose rank
+// table has room for kMaxLevels there.  A build of 258 levels and 2,864 ghosts
+// (a circle on 4096 x 64 cells) takes 222 us so; with the push form behind this
+// one 1,065, by the push form alone 930.
 constexpr int kPullMax = 16384;
 constexpr int kPullRounds = 8;   // (4: 37 us on the 2731^2 airfoil, 8: 34, the stars alike, 32: worse there)
 constexpr int kPullCand = 256;   // cycle ghosts looked at per stall
@@ -509,9 +511,10 @@ __host__ __device__ __forceinline__ int64_t pull_lds(int64_t n, int waves) {
          ((2 * n + 15) & ~int64_t(15)) + ((n + 15) & ~int64_t(15));
 }
 
+template <int BS>
 struct PullShared {
-  int off[kFastLevels + 2];
-  int tot[kFastLevels + 1];
+  int off[BS + 2];   // (a level a thread)
+  int tot[BS + 1];
   int64_t sh[17];
   int moved[3];
   int left, cand, units, maxunit, maxlev, ok;
@@ -521,7 +524,7 @@ struct PullShared {
 // thread (strided by BS)
 template <int BS, int NP, int J>
 __device__ __forceinline__ void pull_instance(const LevelsArgs& L, int ii, int64_t lo, int n,
-                                              int np, uint32_t* s_dyn, PullShared& S) {
+                                              int np, uint32_t* s_dyn, PullShared<BS>& S) {
   const int tid = threadIdx.x;
   const int64_t cap = L.cap;
   const int32_t* __restrict__ deps = L.deps;
@@ -734,18 +737,24 @@ __device__ __forceinline__ void pull_instance(const LevelsArgs& L, int ii, int64
   if (top) atomicMax(&S.maxlev, top - 1);
   __syncthreads();
   const int nlev = S.maxlev, nu = S.units;
-  if (nlev > kFastLevels) {   // uniform
+  if (nlev > BS) {   // uniform
     for (int g = tid; g < n; g += BS) L.perm[lo + g] = -1;
     return;
   }
-  canonical_order<BS>(L, ii, lo, n, nlev, nu, S.maxunit, tab, S.off, S.tot, S.sh,
-                      [&](int g) { return (int)lvl[g] - 1; });
+  auto level_of = [&](int g) { return (int)lvl[g] - 1; };
+  static_assert((kTabB > 8192 ? kTabB : 8192) >= 16 * BS, "four waves rank a level a thread");
+  if (BS <= kFastLevels || nlev <= kFastLevels)
+    canonical_order<BS, BS / 64, 8>(L, ii, lo, n, nlev, nu, S.maxunit, tab, S.off, S.tot, S.sh,
+                                    level_of);
+  else
+    canonical_order<BS, 4, 10>(L, ii, lo, n, nlev, nu, S.maxunit, tab, S.off, S.tot, S.sh,
+                               level_of);
 }
 
 template <int BS, int NP, int J>
 __global__ __launch_bounds__(BS) void k_levels_pull(LevelsArgs L, int lds_bytes) {
   extern __shared__ uint32_t s_dyn[];
-  __shared__ PullShared S;
+  __shared__ PullShared<BS> S;
   const int ii = blockIdx.x;
   const int64_t lo = L.g_off[ii];
   const int n = (int)(L.g_off[ii + 1] - lo);
@@ -1273,7 +1282,7 @@ __global__ __launch_bounds__(1024) void k_levels_fast(LevelsArgs L, int lds_byte
   }
   __syncthreads();
   if (s_placed != n || s_maxlev > kFastLevels) return;   // k_levels does it
-  canonical_order<1024>(L, ii, lo, n, s_maxlev, s_units, s_maxunit, tab, s_off, s_tot, sh,
+  canonical_order<1024, kFastWaves, 8>(L, ii, lo, n, s_maxlev, s_units, s_maxunit, tab, s_off, s_tot, sh,
                         [&](int g) { return (int)lvl[g]; });
 }
 

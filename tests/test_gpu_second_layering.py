@@ -30,13 +30,13 @@ def wavy(n, k=40, amp=0.03):
 
 @pytest.mark.parametrize("first", [True, False])
 def test_batch_keeps_what_the_first_layering_finished(gcr, first):  # noqa: F811
-    """A graph of more levels than the first form's table, before and behind
-    instances with many cycles, few, and none."""
+    """The deepest graph, before and behind instances with many cycles, few,
+    and none."""
     b = [(wavy(800), HGC | LAYER2), (circle(200), HGC),
          *[((i.grid, i.shape), HGC) for i in synth.stars64(1) if i.grid.n[0] <= 1200][:4]]
-    b.insert(0 if first else len(b), (thin(4096, 64), CGC))
+    b.insert(0 if first else len(b), (thin(10000, 64), CGC))
     ops = [oracle.OraclePlan(g, s, c) for (g, s), c in b]
-    assert max(o.n_levels for o in ops) > 256 and max(o.n_units_coupled for o in ops) >= 80
+    assert max(o.n_levels for o in ops) == 629 and max(o.n_units_coupled for o in ops) >= 80
     B = gcr.Batch([g for (g, _), _ in b], [s for (_, s), _ in b], [c for _, c in b])
     for p, o, ((g, s), c) in zip(B.plans, ops, b):
         check(p, o)
@@ -70,8 +70,9 @@ def test_plan_with_cycles_3d(gcr, n, amp, scheme):  # noqa: F811
 
 
 # in 2D only when asked for: a cycle, and more levels than the whole GPU's
-# table, pulled (141 levels) and pushed (258)
-@pytest.mark.parametrize("body,scheme", [(wavy(800), HGC | LAYER2), (thin(2048, 64), CGC), (thin(4096, 64), CGC)])
+# table (129 to 629)
+@pytest.mark.parametrize("body,scheme", [(wavy(800), HGC | LAYER2), (thin(2048, 64), CGC), (thin(8192, 64), CGC),
+                                         (thin(10000, 64), CGC)])
 def test_plan_left_by_the_whole_gpu_2d(gcr, body, scheme):  # noqa: F811
     op = oracle.OraclePlan(*body, scheme)
     assert op.n_units_coupled or op.n_levels > 128
@@ -97,3 +98,10 @@ def test_cycles_cost_no_wait(gcr):  # noqa: F811
             times.append(time.perf_counter() - t)
         return min(times)
     assert build(harmonic(128, 0.15)) < 5 * build(harmonic(128, 0.04))
+
+
+# alone: 213 levels, 256 and 257 (the most that every wave ranks), 629
+@pytest.mark.parametrize("nx,ny", [(1300, 8), (4064, 64), (4080, 64), (10000, 64)])
+def test_deep_plan(gcr, nx, ny):  # noqa: F811
+    body = thin(nx, ny)
+    check(gcr.Plan(*body, CGC), oracle.OraclePlan(*body, CGC))
