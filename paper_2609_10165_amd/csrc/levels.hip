@@ -517,7 +517,7 @@ struct PullShared {
   int tot[BS + 1];
   int64_t sh[17];
   int moved[3];
-  int left, cand, units, maxunit, maxlev, ok;
+  int left, cand, units, cyclic, maxunit, maxlev, ok;
 };
 
 // NP dependencies per ghost at most (np in this instance), J ghosts per
@@ -576,6 +576,7 @@ __device__ __forceinline__ void pull_instance(const LevelsArgs& L, int ii, int64
   if (tid == 0) {
     lvl[n] = 1;   // level 0: "no ghost" holds nothing up
     S.units = 0;
+    S.cyclic = 0;
     S.maxunit = 0;
     S.maxlev = 0;
     S.left = 0;
@@ -719,11 +720,13 @@ __device__ __forceinline__ void pull_instance(const LevelsArgs& L, int ii, int64
           unit_lev[slot] = max(ext, 1);   // (levels in LDS are one higher)
         }
         atomicMax(&S.maxunit, k);
+        atomicAdd(&S.cyclic, k);
         S.ok = 1;
       }
     }
     __syncthreads();
-    if (!S.ok || S.units > kMaxUnits) {   // uniform
+    // (more ghosts in cycles than the push form resolves: refused there)
+    if (!S.ok || S.units > kMaxUnits || S.cyclic > kMaxResidual) {   // uniform
       for (int g = tid; g < n; g += BS) L.perm[lo + g] = -1;
       return;
     }
