@@ -212,7 +212,9 @@ gcr_status gcr_plan_foot_points(const gcr_plan* plan, double* S, double* normal,
  *   counts  device int64 [2]: fresh cells, uncovered fresh cells
  *   list    device int32 [cap] or NULL: the fresh cells' linear indices,
  *           ascending, the first cap of them
- * Stream-ordered, no host synchronisation; uses scratch held by `after`.
+ * Stream-ordered, no host synchronisation; uses scratch held by `after`:
+ * calls with the same `after` and different `before` on several streams must
+ * be ordered by the caller, or their counts and lists may mix.
  * GCR_E_ARG if the grids differ. */
 gcr_status gcr_plan_fresh_cells(const gcr_plan* before, const gcr_plan* after,
                                 int64_t* counts, int32_t* list, int64_t cap,

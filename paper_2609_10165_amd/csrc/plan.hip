@@ -479,9 +479,13 @@ void launch_scan(const int32_t* cnt, int64_t n, int64_t* excl, int32_t* list, in
 // (tag 1), so no value was ever reconstructed there.  Tags (their
 // arrays are 256-byte aligned) are not read where both plans settled their
 // span to the same class (each of its cells lies on that side of both
-// boundaries).  The workgroups post their counts to each other, so one pass
-// over the tags counts and lists: 256^3, 12 us; a pass to count, a scan and a
-// pass to list took 20 and their gaps.
+// boundaries).  One launch counts by tile; in the next each workgroup sums the
+// tiles before its own, and lists, reading again only tiles that hold fresh
+// cells.  No workgroup waits for another: the counts lie in scratch of the plan,
+// which calls on two streams may share.  A call at 256^3: 15.5 us, 64^3 12; with
+// a launch between that scans the counts 23 and 15; in one pass of workgroups
+// that post their counts to each other, behind a launch that clears them, 14.9
+// and 15.9.
 __device__ __forceinline__ uint32_t fresh_bits(const int8_t* __restrict__ a,
                                                const int8_t* __restrict__ b, int64_t base,
                                                int64_t n, int& unc) {
@@ -506,64 +510,56 @@ __device__ __forceinline__ uint32_t fresh_bits(const int8_t* __restrict__ a,
   return m;
 }
 
-constexpr int kFreshRuns = 4, kFreshBS = 1024;   // runs of a workgroup's cells; a wave's part is a span
-constexpr int64_t kFreshRun = (int64_t)kFreshBS * kSeg, kFreshTile = kFreshRuns * kFreshRun;
+constexpr int kFreshBS = 1024;   // (a wave's part is a span)
+constexpr int64_t kFreshTile = (int64_t)kFreshBS * kSeg;
+// count [tiles]: a tile's fresh cells, the uncovered ones from bit 31 on (not
+// read for a grid of one tile, which the listing launch alone takes)
+template <bool List>
 __global__ __launch_bounds__(kFreshBS) void k_fresh(const int8_t* __restrict__ a,
-                                               const int8_t* __restrict__ b,
-                                               const int8_t* __restrict__ sa,
-                                               const int8_t* __restrict__ sb, int64_t n,
-                                               unsigned long long* __restrict__ posted,
-                                               int64_t* __restrict__ counts,
-                                               int32_t* __restrict__ list, int64_t cap) {
-  static_assert(kFreshRun < (1 << 16) && kFreshRuns <= 4, "a run's count fits 16 bits");
+                                                    const int8_t* __restrict__ b,
+                                                    const int8_t* __restrict__ sa,
+                                                    const int8_t* __restrict__ sb, int64_t n,
+                                                    int64_t* __restrict__ count,
+                                                    int64_t* __restrict__ counts,
+                                                    int32_t* __restrict__ list, int64_t cap) {
   __shared__ int64_t sh[kFreshBS / 64 + 1];
-  __shared__ int s_b, s_unc;
-  if (threadIdx.x == 0) {
-    s_b = (int)atomicAdd(&posted[gridDim.x], 1ull);
-    s_unc = 0;
-  }
-  __syncthreads();
-  const int t = s_b;
+  const int t = (int)blockIdx.x;
   const int64_t base = (int64_t)t * kFreshTile + (int64_t)threadIdx.x * kSeg;
-  uint32_t m[kFreshRuns];
-  int8_t x[kFreshRuns], y[kFreshRuns];
-#pragma unroll
-  for (int q = 0; q < kFreshRuns; ++q) {
-    const int64_t span = (base + q * kFreshRun) / (64 * kSeg);
-    const bool in = base + q * kFreshRun < n;
-    x[q] = in ? sa[span] : 0;
-    y[q] = in ? sb[span] : 0;
+  const int64_t span = base / (64 * kSeg);
+  int8_t x = 0, y = 0;
+  if (base < n) {
+    x = sa[span];
+    y = sb[span];
   }
-  int64_t sum = 0;   // of each run, 16 bits
-  int uncovered = 0;
-#pragma unroll
-  for (int q = 0; q < kFreshRuns; ++q) {
-    m[q] = 0;
-    int unc = 0;
-    if (x[q] < 0 || x[q] != y[q]) m[q] = fresh_bits(a, b, base + q * kFreshRun, n, unc);
-    sum += (int64_t)__popc(m[q]) << (16 * q);
-    uncovered += unc;
+  int64_t before = 0;
+  if (List && gridDim.x > 1) {
+    const int64_t own = count[t];
+    const bool last = t == (int)gridDim.x - 1;
+    if (own == 0 && !last) return;   // uniform
+    int64_t v = 0;
+    for (int j = threadIdx.x; j < t; j += kFreshBS) v += count[j];
+    (void)block_excl_scan<kFreshBS>(v, &before, sh);
+    if (last && threadIdx.x == 0) {
+      counts[0] = (before + own) & (kScanHi - 1);
+      counts[1] = (before + own) >> 31;
+    }
   }
-  if (uncovered) atomicAdd(&s_unc, uncovered);
-  int64_t packed;
-  const int64_t rank = block_excl_scan<kFreshBS>(sum, &packed, sh);   // (its barriers: s_unc too)
-  int64_t tot = 0;
-#pragma unroll
-  for (int q = 0; q < kFreshRuns; ++q) tot += (packed >> (16 * q)) & 0xffff;
-  tot |= (int64_t)s_unc << 31;
-  const int64_t before = posted_before<kFreshBS>(posted, t, tot);
-  int64_t first = before & ((int64_t(1) << 31) - 1);
-#pragma unroll
-  for (int q = 0; q < kFreshRuns; ++q) {
-    int64_t pos = first + ((rank >> (16 * q)) & 0xffff);
-    for (uint32_t w = m[q]; w; w &= w - 1, ++pos)
-      if (pos < cap) list[pos] = (int32_t)(base + q * kFreshRun + __ffs(w) - 1);
-    first += (packed >> (16 * q)) & 0xffff;
+  int unc = 0;
+  uint32_t m = 0;
+  if (x < 0 || x != y) m = fresh_bits(a, b, base, n, unc);
+  int64_t tot;
+  const int64_t rank = block_excl_scan<kFreshBS>(__popc(m) | (int64_t)unc << 31, &tot, sh);
+  if (!List) {
+    if (threadIdx.x == 0) count[t] = tot;
+    return;
   }
-  if (t == (int)gridDim.x - 1 && threadIdx.x == 0) {
-    counts[0] = (before + tot) & ((int64_t(1) << 31) - 1);
-    counts[1] = (before + tot) >> 31;
+  if (gridDim.x == 1 && threadIdx.x == 0) {
+    counts[0] = tot & (kScanHi - 1);
+    counts[1] = tot >> 31;
   }
+  int64_t pos = (before + rank) & (kScanHi - 1);
+  for (; m; m &= m - 1, ++pos)
+    if (pos < cap) list[pos] = (int32_t)(base + __ffs(m) - 1);
 }
 
 extern "C" gcr_status gcr_plan_fresh_cells(const gcr_plan* a, const gcr_plan* b, int64_t* counts,
@@ -576,14 +572,15 @@ extern "C" gcr_status gcr_plan_fresh_cells(const gcr_plan* a, const gcr_plan* b,
       return GCR_E_ARG;
   hipStream_t st = (hipStream_t)stream;
   const int64_t n = a->ncell, ntiles = (n + kFreshTile - 1) / kFreshTile;
-  unsigned long long* const posted = static_cast<unsigned long long*>(
-      plan_scratch(const_cast<gcr_plan*>(b), 6, sizeof(unsigned long long) * (ntiles + 1)));
-  if (!posted) return GCR_E_NOMEM;
-  const int64_t words = 2 * (ntiles + 1);
-  k_zero_words<<<(unsigned)((words + 255) / 256), 256, 0, st>>>(reinterpret_cast<int32_t*>(posted),
-                                                                words);
-  k_fresh<<<(unsigned)ntiles, kFreshBS, 0, st>>>(a->tags, b->tags, a->span, b->span, n, posted, counts,
-                                            list, list ? cap : 0);
+  int64_t* const count = static_cast<int64_t*>(
+      plan_scratch(const_cast<gcr_plan*>(b), 6, sizeof(int64_t) * ntiles));
+  if (!count) return GCR_E_NOMEM;
+  const int64_t room = list ? cap : 0;
+  if (ntiles > 1)
+    k_fresh<false><<<(unsigned)ntiles, kFreshBS, 0, st>>>(a->tags, b->tags, a->span, b->span, n,
+                                                          count, counts, list, room);
+  k_fresh<true><<<(unsigned)ntiles, kFreshBS, 0, st>>>(a->tags, b->tags, a->span, b->span, n, count,
+                                                       counts, list, room);
   GCR_HIP(hipGetLastError());
   return GCR_OK;
 }

@@ -74,3 +74,35 @@ def test_fresh_cells_refuses_other_grids(gcr):
     b = gcr.Plan(big, a_inst.shape, HGC)
     with pytest.raises(gcr.GcrError):
         a.fresh_cells(b)
+
+
+def test_fresh_cells_on_two_streams_and_captured(gcr):
+    """Calls that share the scratch of `after` overlap on two streams, then are
+    replayed from a graph."""
+    inst = synth.sphere256(seed=1, n=160)
+    h = inst.grid.h[0]
+    shape = moved(inst.shape, (0.6 * h, -0.5 * h, 0.8 * h))
+    want, unc = oracle.OraclePlan(inst.grid, inst.shape, HGC).fresh_cells(
+        oracle.OraclePlan(inst.grid, shape, HGC))
+    a, b = gcr.Plan(inst.grid, inst.shape, HGC), gcr.Plan(inst.grid, shape, HGC)
+    n = len(want)
+    counts = torch.zeros(40, 2, dtype=torch.int64, device="cuda")
+    lst = torch.zeros(40, n, dtype=torch.int32, device="cuda")
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    call = lambda k, st: gcr.lib().gcr_plan_fresh_cells(a._h, b._h, counts[k].data_ptr(), lst[k].data_ptr(),
+                                                        n, st.cuda_stream)
+    def right():
+        torch.cuda.synchronize()
+        assert counts[:, 0].eq(n).all() and counts[:, 1].eq(unc).all()
+        assert np.array_equal(lst.cpu().numpy(), np.broadcast_to(want, lst.shape))
+    torch.cuda.synchronize()
+    assert all(call(k, streams[k % 2]) == 0 for k in range(40))
+    right()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        assert all(call(k, torch.cuda.current_stream()) == 0 for k in range(40))
+    for _ in range(3):
+        counts.zero_()
+        lst.zero_()
+        graph.replay()
+        right()
