@@ -388,14 +388,17 @@ __global__ __launch_bounds__(64) void k_adj_units(AdjArgs A, int level) {
 // and those workgroups lead the grid: they wait for later ones, but fill a
 // corner of the chip at most.  Waits are bounded as the fill's are; a thread
 // that passes the bound computes what it waits for (adj_help), or, in a plan
-// with coupled units, sets the plan's fault word, for k_adj_wg to sweep again.
+// with coupled units, sets the plan's fault word (k_adj_open clears it), for
+// k_adj_wg to sweep this call again.
 // Bound by the chain of levels.  160^3 spherical-harmonic body, four fields,
 // ten levels: 20 us for the two launches against 90 for ten.
 // --------------------------------------------------------------------------
 constexpr int kAdjUnitsPerBlock = 4;
 
-__global__ __launch_bounds__(256) void k_adj_open(double* __restrict__ Lam, int64_t n) {
+__global__ __launch_bounds__(256) void k_adj_open(double* __restrict__ Lam, int64_t n,
+                                                  int32_t* __restrict__ fault) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i == 0) fault[0] = 0;
   if (i < n) Lam[i] = __longlong_as_double((long long)kFillOpen);
 }
 
@@ -499,7 +502,7 @@ template <int D>
 static void adj_flow(const AdjArgs& A, const int32_t* d_lev_off, int nlev, hipStream_t st) {
   const int64_t n = (int64_t)A.nf * A.P.ng;
   const int ub = (A.P.nunits + kAdjUnitsPerBlock - 1) / kAdjUnitsPerBlock;
-  k_adj_open<<<nblk(n, 256), 256, 0, st>>>(A.Lam, n);
+  k_adj_open<<<nblk(n, 256), 256, 0, st>>>(A.Lam, n, A.P.fill_fault);
   k_adj_flow<D><<<dim3((unsigned)ub + nblk(A.P.ng, 256), (unsigned)A.nf), 256, 0, st>>>(
       A, ub, fill_polls());
   if (ub) k_adj_wg<D><<<1, 256, 0, st>>>(A, d_lev_off, nlev, A.P.fill_fault);

@@ -124,3 +124,45 @@ def test_one_array_for_several_fields(gcr):  # noqa: F811
     torch.cuda.synchronize()
     assert not torch.equal(want, start)
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("body", ["star", "harmonic"])
+def test_fill_adjoint_with_units_after_a_wait_that_gave_up(gcr, body):  # noqa: F811
+    """Waits that give up at once in a plan with coupled units: the same
+    values, then and from the next call on, which takes no longer than that of
+    a plan where none gave up (a second sweep by one workgroup, kept up for the
+    plan's life, took five times as long)."""
+    import time
+
+    from test_gpu_second_layering import harmonic
+    if body == "star":
+        inst = next(i for i in synth.stars64(1) if i.grid.n[0] <= 1200 and
+                    gcr.Plan(i.grid, i.shape, HGC).stats()["n_units_coupled"])
+        make = lambda: gcr.Plan(inst.grid, inst.shape, HGC)
+    else:
+        make = lambda: gcr.Plan(*harmonic(128, 0.15), HGC)
+    plan, other = make(), make()
+    kinds = [DIRICHLET, MIXED, NEUMANN, MIXED]
+    gcr.set_batch_spin(1)
+    try:
+        agree(plan, kinds, 9)
+    finally:
+        gcr.set_batch_spin(0)
+    agree(plan, kinds, 9)
+
+    def best(p):
+        lam = [rand(p.n_cells, seed=f) for f in range(4)]
+        bc = [torch.empty(p.n_ghost, dtype=torch.float64, device="cuda") for _ in kinds]
+        t = [torch.zeros(p.n_ghost, dtype=torch.uint8, device="cuda")] * 4
+        p.fill_adjoint(lam, kinds, bc, t)
+        times = []
+        for _ in range(10):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(5):
+                p.fill_adjoint(lam, kinds, bc, t)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t0)
+        return min(times)
+    other.set_schedule(0)
+    assert best(plan) < 2 * best(other)
