@@ -362,7 +362,7 @@ __global__ __launch_bounds__(256) void k_batch_open(BStatic S, BCall C, FlowTab 
   if (p >= P.ng) return;
   double* const F = C.fields[w];
   if (p < S.lev_off[i][1])
-    fill_single<D>(P, p, F, C.bcv[w], C.bct ? C.bct[w] : nullptr, C.kind[f]);
+    fill_single<D, true>(P, p, F, C.bcv[w], C.bct ? C.bct[w] : nullptr, C.kind[f]);
   else
     F[P.cell[p]] = __longlong_as_double((long long)kFillOpen);
 }

@@ -65,7 +65,7 @@ template <int D>
 __global__ __launch_bounds__(256) void k_fill_open(FillArgs A, int n1) {
   const int p = blockIdx.x * 256 + threadIdx.x, f = blockIdx.y;
   if (p >= A.P.ng) return;
-  if (p < n1) fill_single<D>(A.P, p, A.f[f], A.b[f], A.bt[f], A.kind[f]);
+  if (p < n1) fill_single<D, true>(A.P, p, A.f[f], A.b[f], A.bt[f], A.kind[f]);
   else A.f[f][A.P.cell[p]] = __longlong_as_double((long long)kFillOpen);
 }
 

@@ -152,8 +152,19 @@ __device__ __forceinline__ void fill_units_of_level(const FillArgs& A, int level
   }
 }
 
-// One field of one ghost (the batched kernel's inner step).
-template <int D>
+// A value not known yet, in a field's ghost slot (k_fill_flow): a NaN no
+// arithmetic produces; a result that equals it (an input's NaN passed
+// through) is stored as another NaN.
+constexpr unsigned long long kFillOpen = 0x7ff85eed0f11e57aull;
+
+__device__ __forceinline__ double fill_result(double v) {
+  return __double_as_longlong(v) == (long long)kFillOpen ? __longlong_as_double(0x7ff8000000000000LL)
+                                                         : v;
+}
+
+// One field of one ghost (the batched kernel's inner step).  Waited: in a launch
+// whose values others then wait for.
+template <int D, bool Waited = false>
 __device__ __forceinline__ void fill_single(const PlanD& P, int p, double* F, const double* b,
                                             const uint8_t* bt, int kind) {
   const int blk = P.blk[p];
@@ -196,17 +207,7 @@ __device__ __forceinline__ void fill_single(const PlanD& P, int p, double* F, co
 #pragma unroll
   for (int k = 1; k < (1 << D); ++k)
     if (!(k & skip)) v += w[k] * val[k];
-  F[c] = v;
-}
-
-// A value not known yet, in a field's ghost slot (k_fill_flow): a NaN no
-// arithmetic produces; a result that equals it (an input's NaN passed
-// through) is stored as another NaN.
-constexpr unsigned long long kFillOpen = 0x7ff85eed0f11e57aull;
-
-__device__ __forceinline__ double fill_result(double v) {
-  return __double_as_longlong(v) == (long long)kFillOpen ? __longlong_as_double(0x7ff8000000000000LL)
-                                                         : v;
+  F[c] = Waited ? fill_result(v) : v;
 }
 
 // a value that another workgroup may be about to post, and its posting

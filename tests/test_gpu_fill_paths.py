@@ -122,3 +122,35 @@ def test_fill_on_two_streams_and_captured(gcr, name):  # noqa: F811
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(x, y) for x, y in zip(u, want[0]))
+
+
+@pytest.mark.parametrize("kind", [DIRICHLET, NEUMANN])
+@pytest.mark.parametrize("name", ["sphere63", "circle2630"])
+def test_mark_in_a_field_is_not_waited_for(gcr, name, kind):  # noqa: F811
+    """The waiting fill's own mark as an input NaN in every cell: level 1 comes
+    out NaN, and the levels behind it do not take that for a value to come (a
+    wait for one runs to its bound, half a second)."""
+    import time
+    (grid, shape), scheme = CASES[name]
+    plan = gcr.Plan(grid, shape, scheme)
+    u = torch.empty(plan.n_cells, dtype=torch.float64, device="cuda")
+    u.view(torch.int64).fill_(0x7ff85eed0f11e57a)
+    b = torch.ones(plan.n_ghost, dtype=torch.float64, device="cuda")
+    cell = plan.export(("cell",))["cell"].long()
+
+    def timed(f):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        f()
+        torch.cuda.synchronize()
+        return time.perf_counter() - t
+    run = lambda: plan.fill([u], [kind], [b])
+    assert min(timed(run) for _ in range(3)) < 0.05
+    assert u[cell].isnan().all()
+    assert not (u.view(torch.int64)[cell] == 0x7ff85eed0f11e57a).any()
+    if plan.dim == 3:
+        B = gcr.Batch([grid], [shape], [scheme])
+        u.view(torch.int64).fill_(0x7ff85eed0f11e57a)
+        run = lambda: B.forward(1, [u], [kind], [b])
+        assert min(timed(run) for _ in range(3)) < 0.05
+        assert u[cell].isnan().all()
