@@ -607,6 +607,7 @@ struct SurfAdjArgs {
   int32_t* cnt;          // [ng + 1] points per anchor; [ng]: places given out
   int32_t* off;          // [ng] first place of an anchor's points
   int32_t* bucket;       // [nq]
+  int32_t* sorted;       // [nf][nq] the points of anchors with many, ascending
   double* seed;          // [nf][8][ng]
   SupView Sp;
 };
@@ -706,16 +707,49 @@ __device__ __forceinline__ void cotangents(const SurfAdjArgs& S, int f, int64_t 
 
 // per anchor and field, over its points in ascending index: the seeds
 // seed[f][corner][g] = sum_q coef(corner, x_q) . (gval, ggrad).  The next
-// index is searched among the anchor's few points; nothing is moved, so the
-// fields' threads share the bucket.
+// index is searched among an anchor's few points; nothing is moved, so the
+// fields' threads share the bucket.  Beyond kSeedFew the search would take
+// longer than the sum (it grows with the square: 2,048 points at one anchor
+// 280 ms), so there the wave first ranks the points, 64 lanes at a time, into
+// the field's own list: 1.7 ms.
+constexpr int kSeedFew = 32;
+
 template <int D, bool FORCE>
 __global__ __launch_bounds__(256) void k_sadj_seed(SurfAdjArgs S) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x, f = blockIdx.y;
+  const int g = blockIdx.x * blockDim.x + threadIdx.x, f = blockIdx.y, lane = threadIdx.x & 63;
   const PlanD& P = S.P;
-  if (g >= P.ng) return;
-  const int n = S.cnt[g];
+  const int n = g < P.ng ? S.cnt[g] : 0, off = n ? S.off[g] : 0;
+  int32_t* const sorted = S.sorted + (int64_t)f * S.nq;
+  for (unsigned long long many = __ballot(n > kSeedFew); many; many &= many - 1ull) {   // uniform
+    const int src = __ffsll((long long)many) - 1;
+    const int m = __builtin_amdgcn_readlane(n, src), o = __builtin_amdgcn_readlane(off, src);
+    const int32_t* const from = S.bucket + o;
+    constexpr int kOwn = 4;
+    for (int t0 = 0; t0 < m; t0 += 64 * kOwn) {
+      int v[kOwn], rank[kOwn];
+#pragma unroll
+      for (int u = 0; u < kOwn; ++u) {
+        const int t = t0 + 64 * u + lane;
+        v[u] = t < m ? from[t] : 0;
+        rank[u] = 0;
+      }
+      for (int j = 0; j < m; j += 64) {
+        const int e = j + lane < m ? from[j + lane] : 0x7fffffff;   // (below no index)
+#pragma unroll
+        for (int k = 0; k < 64; ++k) {
+          const int x = __builtin_amdgcn_readlane(e, k);
+#pragma unroll
+          for (int u = 0; u < kOwn; ++u) rank[u] += x < v[u] ? 1 : 0;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kOwn; ++u)
+        if (t0 + 64 * u + lane < m) sorted[o + rank[u]] = v[u];
+    }
+  }
+  __threadfence_block();   // the lists, before their anchors' lanes read them
   if (n == 0) return;
-  const int32_t* const bucket = S.bucket + S.off[g];
+  const int32_t* const bucket = (n > kSeedFew ? sorted : S.bucket) + off;
   const uint32_t code = P.code[g];
   int i, j, k;
   unlinear(P.g, P.cell[g], i, j, k);
@@ -728,10 +762,12 @@ __global__ __launch_bounds__(256) void k_sadj_seed(SurfAdjArgs S) {
   int32_t last = -1;
   for (int t = 0; t < n; ++t) {
     int32_t q = 0x7fffffff;
-    for (int u = 0; u < n; ++u) {
-      const int32_t c = bucket[u];
-      if (c > last && c < q) q = c;
-    }
+    if (n > kSeedFew) q = bucket[t];
+    else
+      for (int u = 0; u < n; ++u) {
+        const int32_t c = bucket[u];
+        if (c > last && c < q) q = c;
+      }
     last = q;
     double rel[3] = {0.0, 0.0, 0.0};
 #pragma unroll
@@ -814,7 +850,7 @@ static gcr_status surface_adjoint_impl(gcr_plan* p, SurfAdjArgs S, double* const
     const gcr_status ss = plan_support(p, st, &S.Sp);
     if (ss != GCR_OK) return ss;
   }
-  int32_t* ib = (int32_t*)plan_scratch(p, 1, sizeof(int32_t) * (3 * nq + 2 * (ng + 1)));
+  int32_t* ib = (int32_t*)plan_scratch(p, 1, sizeof(int32_t) * ((3 + S.nf) * nq + 2 * (ng + 1)));
   S.seed = (double*)plan_scratch(p, 2, sizeof(double) * (size_t)S.nf * 8 * ng);
   if (!ib || !S.seed) return GCR_E_NOMEM;
   S.anchor = ib;
@@ -822,6 +858,7 @@ static gcr_status surface_adjoint_impl(gcr_plan* p, SurfAdjArgs S, double* const
   S.bucket = S.rank + nq;
   S.cnt = S.bucket + nq;
   S.off = S.cnt + (ng + 1);
+  S.sorted = S.off + (ng + 1);
   k_zero_i32<<<nblk(ng + 1, 256), 256, 0, st>>>(S.cnt, ng + 1);
   const int D = p->dim;
   const unsigned nba = (unsigned)force_blocks(D, nq);

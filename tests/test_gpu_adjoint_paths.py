@@ -166,3 +166,47 @@ def test_fill_adjoint_with_units_after_a_wait_that_gave_up(gcr, body):  # noqa: 
         return min(times)
     other.set_schedule(0)
     assert best(plan) < 2 * best(other)
+
+
+@pytest.mark.parametrize("name", ["circle128", "sphere24"])
+def test_points_of_one_anchor_in_ascending_order(gcr, name):  # noqa: F811
+    """Points at one anchor, few and many (33 on, ranked first): its seeds are
+    the points' own, summed in ascending order, bit for bit."""
+    (grid, shape), scheme = CASES[name]
+    plan = gcr.Plan(grid, shape, scheme)
+    d = plan.dim
+    sizes = [1, 2, 31, 32, 33, 64, 65, 256, 257, 700]
+    S = plan.foot_points()[0]
+    x = S[:, 5:6] + 1e-6 * rand(d, sizes[-1], seed=1) / grid.n[0]
+    gval, ggrad = rand(2, sizes[-1], seed=2), rand(2, d, sizes[-1], seed=3)
+    cut = lambda a, i, j: a[..., i:j].contiguous()
+    total = torch.zeros(2, plan.n_cells, dtype=torch.float64, device="cuda")
+    for q in range(sizes[-1]):
+        one = torch.zeros_like(total)
+        plan.surface_adjoint(cut(x, q, q + 1), cut(gval, q, q + 1), cut(ggrad, q, q + 1), list(one))
+        total += one
+        if q + 1 in sizes:
+            got = torch.zeros_like(total)
+            plan.surface_adjoint(cut(x, 0, q + 1), cut(gval, 0, q + 1), cut(ggrad, 0, q + 1), list(got))
+            torch.cuda.synchronize()
+            assert got.abs().sum() > 0 and torch.equal(got, total), q + 1
+
+
+def test_many_points_of_one_anchor_cost_their_number(gcr):  # noqa: F811
+    """Eight times the points at an anchor: not sixty-four times the time."""
+    import time
+    (grid, shape), scheme = CASES["sphere24"]
+    plan = gcr.Plan(grid, shape, scheme)
+    lam = [torch.zeros(plan.n_cells, dtype=torch.float64, device="cuda")]
+
+    def best(nq):
+        x = (plan.foot_points()[0][:, 5:6] + 1e-6 * rand(3, nq, seed=1) / 24).contiguous()
+        gval, times = rand(1, nq, seed=2), []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            plan.surface_adjoint(x, gval, None, lam)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t)
+        return min(times[1:])
+    assert best(4096) < 24 * best(512)
