@@ -62,6 +62,7 @@ struct BCall {
   double* const* sgrad;          // [ninst*nf] surface gradients [dim][nq_i] (null: none)
   const int32_t* tile_flag;      // tiled fill ran when set and zero: items skip the levels
   const int32_t* soff;           // [ninst + 1] first chunk of kSurfChunk points of each instance
+  const int32_t* poff;           // [ninst + 1] first anchor workgroup of each (point_anchors)
 };
 
 // Fill by waiting over a whole batch: first workgroup of each instance in the
@@ -367,20 +368,20 @@ __global__ __launch_bounds__(256) void k_batch_open(BStatic S, BCall C, FlowTab 
     F[P.cell[p]] = __longlong_as_double((long long)kFillOpen);
 }
 
-// The anchors of a part of one chunk of points, by workgroup b (of BS threads)
-// behind a launch's fill workgroups.
+// The anchors of kAnchorPoints points of one instance, by workgroup b (of BS
+// threads) behind a launch's fill workgroups.  As many workgroups as an
+// instance's points need: with whole chunks of kSurfChunk points 512 circles
+// of one point each took 102 us a call, so 66.
 template <int D, int BS>
-constexpr int kAnchorParts = kSurfChunk * anchor_lanes<D>() / BS;
+constexpr int kAnchorPoints = BS / anchor_lanes<D>();
 template <int D, int BS>
-__device__ __forceinline__ void chunk_anchors(const BStatic& S, const BCall& C, int b,
+__device__ __forceinline__ void point_anchors(const BStatic& S, const BCall& C, int b,
                                               int32_t* __restrict__ anchor) {
-  constexpr int NL = anchor_lanes<D>(), kParts = kAnchorParts<D, BS>;
-  const int chunk = b / kParts, i = inst_of_block(C.soff, C.ninst, chunk);
+  constexpr int NL = anchor_lanes<D>();
+  const int i = inst_of_block(C.poff, C.ninst, b);
   const int sub = (int)threadIdx.x % NL;
-  const int64_t nq = C.nq[i],
-                q0 = (int64_t)(chunk - C.soff[i]) * kSurfChunk + (b % kParts) * (BS / NL);
-  if (q0 >= nq) return;   // uniform
-  const int64_t q = q0 + (int)threadIdx.x / NL;
+  const int64_t nq = C.nq[i], q = (int64_t)(b - C.poff[i]) * kAnchorPoints<D, BS> +
+                                  (int)threadIdx.x / NL;
   const bool active = q < nq;
   double x[3] = {0.0, 0.0, 0.0};
   if (active)
@@ -395,7 +396,7 @@ template <int D>
 __global__ __launch_bounds__(256) void k_batch_flow(BStatic S, BCall C, FlowTab T, int nfill,
                                                     int32_t* __restrict__ anchor, int polls) {
   if ((int)blockIdx.x >= nfill) {
-    chunk_anchors<D, 256>(S, C, (int)blockIdx.x - nfill, anchor);
+    point_anchors<D, 256>(S, C, (int)blockIdx.x - nfill, anchor);
     return;
   }
   const int f = (int)blockIdx.x / T.nwait, r = (int)blockIdx.x % T.nwait;
@@ -416,7 +417,7 @@ __global__ __launch_bounds__(256) void k_batch_flow(BStatic S, BCall C, FlowTab 
 __global__ __launch_bounds__(1024) void k_batch_lds(BStatic S, BCall C, int32_t* __restrict__ anchor) {
   extern __shared__ double s_lds[];
   if ((int)blockIdx.x >= C.nitems) {
-    chunk_anchors<2, 1024>(S, C, (int)blockIdx.x - C.nitems, anchor);
+    point_anchors<2, 1024>(S, C, (int)blockIdx.x - C.nitems, anchor);
     return;
   }
   const int w = C.order[blockIdx.x], i = w / C.nf, f = w % C.nf, nl = S.nlev[i];
@@ -1324,13 +1325,12 @@ static gcr_status launch_surface(BatchFwdState* S, const BCall& C, int nchunk, d
   return GCR_OK;
 }
 
-// The launches of a batch that fills by waiting.
-static gcr_status launch_flow(BatchFwdState* S, const BCall& C, int nchunk, double* F,
+// The launches of a batch that fills by waiting; na: anchor workgroups.
+static gcr_status launch_flow(BatchFwdState* S, const BCall& C, int nchunk, int na, double* F,
                               hipStream_t st) {
   const BStatic bs{S->d_plans, S->d_levp, S->d_nlev};
   const unsigned nf = (unsigned)C.nf;
   const int nfill = S->ft.nwait * C.nf;
-  const int na = nchunk * kAnchorParts<3, 256>;
   if (S->ft.nopen) k_batch_open<3><<<S->ft.nopen * nf, 256, 0, st>>>(bs, C, S->ft);
   if (nfill + na > 0)
     k_batch_flow<3><<<(unsigned)(nfill + na), 256, 0, st>>>(bs, C, S->ft, nfill, S->d_anchor,
@@ -1338,10 +1338,9 @@ static gcr_status launch_flow(BatchFwdState* S, const BCall& C, int nchunk, doub
   return launch_surface<3>(S, C, nchunk, F, st);
 }
 
-static gcr_status launch_lds(BatchFwdState* S, const BCall& C, int nchunk, double* F,
+static gcr_status launch_lds(BatchFwdState* S, const BCall& C, int nchunk, int na, double* F,
                              hipStream_t st) {
   const BStatic bs{S->d_plans, S->d_levp, S->d_nlev};
-  const int na = nchunk * kAnchorParts<2, 1024>;
   k_batch_lds<<<(unsigned)(C.nitems + na), 1024, S->fill_lds, st>>>(bs, C, S->d_anchor);
   return launch_surface<2>(S, C, nchunk, F, st);
 }
@@ -1469,7 +1468,7 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   // call table: one upload
   const size_t np = (size_t)nitems;
   const size_t bytes = sizeof(void*) * (5 * np + 3 * n) + sizeof(int64_t) * (2 * n + 1) +
-                       sizeof(int32_t) * (np + n + 1) + 64;
+                       sizeof(int32_t) * (np + 2 * (n + 1)) + 64;
   std::vector<char> host(bytes, 0);
   char* h = host.data();
   size_t o = 0;
@@ -1487,9 +1486,9 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   const size_t o_bct = put(bt.data(), sizeof(void*) * np);
   const size_t o_sval = sval ? put(sval, sizeof(void*) * np) : 0;
   const size_t o_sgrad = sgrad ? put(sgrad, sizeof(void*) * np) : 0;
-  size_t o_nq = 0, o_xq = 0, o_nrm = 0, o_wq = 0, o_aoff = 0, o_soff = 0;
+  size_t o_nq = 0, o_xq = 0, o_nrm = 0, o_wq = 0, o_aoff = 0, o_soff = 0, o_poff = 0;
   std::vector<int64_t> aoff(n + 1, 0);
-  std::vector<int32_t> soff(n + 1, 0);
+  std::vector<int32_t> soff(n + 1, 0), poff(n + 1, 0);
   if (nq) {
     for (int i = 0; i < n; ++i) aoff[i + 1] = aoff[i] + nq[i];
     o_nq = put(nq, sizeof(int64_t) * n);
@@ -1501,6 +1500,9 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
     for (int i = 0; i < n; ++i)
       soff[i + 1] = soff[i] + (int32_t)std::max<int64_t>(1, (nq[i] + kSurfChunk - 1) / kSurfChunk);
     o_soff = put(soff.data(), sizeof(int32_t) * (n + 1));
+    const int ppb = dim == 2 ? kAnchorPoints<2, 1024> : kAnchorPoints<3, 256>;
+    for (int i = 0; i < n; ++i) poff[i + 1] = poff[i] + (int32_t)((nq[i] + ppb - 1) / ppb);
+    o_poff = put(poff.data(), sizeof(int32_t) * (n + 1));
   }
   const int64_t npts = aoff[n];
   if (npts > 0 && S->anchor_cap < (size_t)npts) {
@@ -1562,6 +1564,7 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   C.order = reinterpret_cast<const int32_t*>(d + o_order);
   C.aoff = nq ? reinterpret_cast<const int64_t*>(d + o_aoff) : nullptr;
   C.soff = nq ? reinterpret_cast<const int32_t*>(d + o_soff) : nullptr;
+  C.poff = nq ? reinterpret_cast<const int32_t*>(d + o_poff) : nullptr;
   C.anchor = S->d_anchor;
   C.tile_flag = tiles ? S->T.flag : nullptr;
   C.sval = sval ? reinterpret_cast<double* const*>(d + o_sval) : nullptr;
@@ -1581,11 +1584,11 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   };
   if (flow) {
     if (timed) (void)hipEventRecord(ev[1], st);   // (the anchors ride in the fill)
-    return end_call(launch_flow(S, C, soff[n], F, st));
+    return end_call(launch_flow(S, C, soff[n], poff[n], F, st));
   }
   if (lds) {
     if (timed) (void)hipEventRecord(ev[1], st);
-    return end_call(launch_lds(S, C, soff[n], F, st));
+    return end_call(launch_lds(S, C, soff[n], poff[n], F, st));
   }
   if (npts > 0) {
     BStatic bs{S->d_plans, S->d_levp, S->d_nlev};

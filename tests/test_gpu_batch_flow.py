@@ -129,3 +129,14 @@ def test_batch_beyond_lds(gcr):  # noqa: F811
     b = [circle(2630), circle(64)]
     B = agree_on(gcr, [g for g, _ in b], [s for _, s in b], [HGC] * 2, [MIXED, DIRICHLET, NEUMANN], [300, 5])
     assert B.shape() != (0, 0)
+
+
+def test_anchors_at_the_edges_of_their_workgroups(gcr):  # noqa: F811
+    """Points of an instance: none, one, and around the 4 (3D) and 32 (2D) that
+    an anchor workgroup takes, instances without any between."""
+    nqs = [0, 1, 3, 4, 5, 0, 255, 256, 257, 0, 0, 9]
+    agree(gcr, [20 + k for k in range(12)], [HGC] * 12, [DIRICHLET] * 4, nqs)
+    from test_gpu_layering import circle
+    b = [circle(24 + 3 * k) for k in range(12)]
+    nqs = [0, 1, 31, 32, 33, 0, 255, 256, 257, 0, 64, 0]
+    agree_on(gcr, [g for g, _ in b], [s for _, s in b], [HGC] * 12, [DIRICHLET, NEUMANN, MIXED], nqs)
