@@ -253,7 +253,7 @@ __global__ __launch_bounds__(1024) void k_batch_forward(BStatic S, BCall C, doub
       if (P.nunits) {
         if (threadIdx.x < 64)
           for (int s = threadIdx.x; s < P.nunits; s += 64)
-            if (P.unit_lev[s] == l + 1) fill_unit_field<D>(P, s, F, b, bt, kind, ws[threadIdx.x]);
+            if (P.unit_lev[s] == l + 1) fill_unit_field<D, true>(P, s, F, b, bt, kind, ws[threadIdx.x]);
         __syncthreads();
       }
     }
@@ -331,7 +331,7 @@ __global__ __launch_bounds__(1024) void k_batch_split(BStatic S, BCall C, int G,
           if (P.unit_lev[u] == l + 1)
             for (int f = 0; f < nf; ++f) {
               const int w = i * nf + f;
-              fill_unit_field<D>(P, u, C.fields[w], C.bcv[w], C.bct ? C.bct[w] : nullptr,
+              fill_unit_field<D, true>(P, u, C.fields[w], C.bcv[w], C.bct ? C.bct[w] : nullptr,
                                  C.kind[f], ws[threadIdx.x]);
             }
       inst_barrier(cnt, G * ++arrivals, spin, fault, G);

@@ -232,12 +232,16 @@ __device__ __forceinline__ int code_r(uint32_t code, int i) { return (int)((code
 // x_2 - x_1 per axis of the stencil of the ghost in cell c: e_i r_i h_i, or
 // on a stretched axis the difference of the two cell centres (a
 // displacement off the grid, only along an axis the normal does not leave,
-// takes the cell width)
+// takes the cell width).  Apart: the cell's indices are found on that path
+// only, where working them out ahead for every ghost costs registers
+// (k_batch_forward<3>: eight spilled).
+template <bool Apart = false>
 __device__ __forceinline__ void stencil_span(const GridD& g, uint32_t code, int c,
                                              double X[3]) {
 #pragma unroll
   for (int a = 0; a < 3; ++a) X[a] = (double)(code_e(code, a) * code_r(code, a)) * g.h[a];
   if (!g.face[0] && !g.face[1] && !g.face[2]) return;   // uniform: no cell index needed
+  if (Apart) asm volatile("" : "+v"(c));
   int ijk[3];
   unlinear(g, c, ijk[0], ijk[1], ijk[2]);
 #pragma unroll

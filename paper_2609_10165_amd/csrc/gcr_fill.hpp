@@ -9,8 +9,9 @@
 
 namespace gcr {
 
-// One field of coupled unit u: (I - W_int) phi = W_ext phi_ext + ws b.
-template <int D>
+// One field of coupled unit u: (I - W_int) phi = W_ext phi_ext + ws b.  Apart:
+// as stencil_span's.
+template <int D, bool Apart = false>
 __device__ __forceinline__ void fill_unit_field(const PlanD& P, int u, double* F,
                                                 const double* b, const uint8_t* bt, int kind,
                                                 UnitWS& ws) {
@@ -31,7 +32,7 @@ __device__ __forceinline__ void fill_unit_field(const PlanD& P, int u, double* F
     }
     const int bc = kind == 2 ? (int)bt[p] : kind;
     double X[3];
-    stencil_span(P.g, code, ws.cel[i], X);
+    stencil_span<Apart>(P.g, code, ws.cel[i], X);
     ghost_weights<D>(dl, nn, X, bc, w);
     for (int t = 0; t < k; ++t) ws.M[i * k + t] = (t == i) ? 1.0 : 0.0;
     double r = w[0] * b[p];
