@@ -169,23 +169,21 @@ def _ptr_array(ts, dtype=torch.float64):
     return (_PTRS[n] if n < 9 else ctypes.c_void_p * n)(*[_dptr(t, dtype) for t in ts])
 
 
-def _int_array(ks):
-    n = len(ks)
-    return (_INTS[n] if n < 9 else ctypes.c_int32 * n)(*map(int, ks))
-
-
 def _kinds(bc_kind, nf):
-    a = _int_array(bc_kind)
-    if len(a) > nf:
+    """The kinds of nf fields, from any iterable; missing ones 0."""
+    ks = [int(k) for k in bc_kind]
+    if len(ks) > nf:
         raise IndexError("more boundary-condition kinds than fields")
-    return a if len(a) == nf else (ctypes.c_int32 * nf)(*a)
+    return (_INTS[nf] if nf < 9 else ctypes.c_int32 * nf)(*ks)
 
 
 def _opt_array(ts, nf, dtype):
-    """Pointers of nf tensors, None entries and missing ones null."""
-    if len(ts) > nf:
+    """Pointers of nf tensors from any iterable, None entries and missing ones
+    null."""
+    ps = [_dptr(t, dtype) for t in ts]
+    if len(ps) > nf:
         raise IndexError("more entries than fields")
-    return (_PTRS[nf] if nf < 9 else ctypes.c_void_p * nf)(*[_dptr(t, dtype) for t in ts])
+    return (_PTRS[nf] if nf < 9 else ctypes.c_void_p * nf)(*ps)
 
 
 def make_grid(grid) -> _Grid:
