@@ -22,7 +22,8 @@
  *  - `stream` is a hipStream_t (NULL: the null stream).  Every call that
  *    launches work is asynchronous on that stream, except gcr_plan_create
  *    and gcr_batch_create, which synchronise it twice (to size the band
- *    arrays, then to read the level offsets), and, where neither the fill in
+ *    arrays, then to read the level offsets; once more where a graph has to
+ *    be layered again, see gcr_set_wide_layering), and, where neither the fill in
  *    LDS nor the waiting one serves (coupled units beyond LDS; a batch with
  *    2D instances beyond LDS), the first gcr_fill with the automatic schedule
  *    or gcr_batch_forward for a kind of plan, which times candidate schedules
@@ -347,7 +348,7 @@ gcr_status gcr_batch_counts(const gcr_batch* batch, int64_t* n_ghost,
 gcr_status gcr_batch_foot_points(const gcr_batch* batch, double* S, double* normal,
                                  void* stream);
 
-/* Batched forward in one persistent launch: for every instance, fill its nf
+/* Batched forward by shared launches: for every instance, fill its nf
  * fields, then (if nq != NULL) the force on its body from field p_field
  * (pressure) and the dim fields u_first.. (velocity).  Host arrays of device
  * pointers are instance-major, [ninst * nf]:
@@ -381,8 +382,8 @@ gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf,
  * and gcr_batch_create record HIP events on their stream around each stage;
  * gcr_last_build_times copies the device times in milliseconds of the last
  * build on the calling thread into ms[13]: [0] classification, [1] interface
- * scan, [2] interface compaction, [3] geometry and ghost tags, [4] ghost
- * compaction, [5] stencils and dependencies, [6] levels and canonical order,
+ * scan, [2] interface compaction, [3] geometry, ghost tags and the ghosts in
+ * order, [4] 0 (once a pass for that order), [5] stencils and dependencies, [6] levels and canonical order,
  * [7] finalize; [8], [9], [10] split [0] into the span pass, the store pass
  * and the interface marks; [11] the stream's wait for the host between the
  * two halves of the build (the first synchronisation and the sizing of the
@@ -392,11 +393,13 @@ gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf,
 #define GCR_PROFILE_FORWARD 2
 gcr_status gcr_set_profiling(int32_t mask);
 gcr_status gcr_last_build_times(float* ms);
-/* With bit 1 set, each gcr_batch_forward records HIP events around
- * its two kernels (the surface-point anchor search and the persistent fill
- * + force launch; the waiting fill's anchors count with its launches).  This call waits for the recorded work, writes the mean
- * ms of each over the calls since the last query to out[0] and out[1] and
- * their number to out[2] (-1, -1, 0 if none), and clears the record. */
+/* With bit 1 set, each gcr_batch_forward records HIP events around its two
+ * parts: the anchor search of the surface points where it is a launch of its
+ * own (beside the level sweeps and the tiles; else about 0), and the launches
+ * after it (fill, surface values, forces).  This call waits for the recorded
+ * work, writes the mean ms of each over the calls since the last query to
+ * out[0] and out[1] and their number to out[2] (-1, -1, 0 if none), and clears
+ * the record. */
 gcr_status gcr_forward_times(float* out);
 
 /* Tiled batched fill (process-wide).  Tiled, gcr_batch_forward fills the
@@ -418,10 +421,11 @@ gcr_status gcr_forward_times(float* out);
  * of more than about 980,000 ghosts, and any batch whose tile closures would
  * not fit, take the sweep.  Applies to batches not yet set up. */
 gcr_status gcr_set_batch_tiling(int32_t mode);
-/* Which fill a batch's forward calls use: *state = -1 the level-by-level
- * sweep (or, 3D at the default mode, the waiting fill), 0 not decided yet
- * (no forward call so far), 1 the tiled fill,
- * 2 the sweep after the tile closures did not fit.  Synchronises the
+/* Which fill a batch's forward calls use: *state = -1 no tiles (the
+ * level-by-level sweep; at the default mode also the waiting fill of a 3D
+ * batch, and the fill in LDS of a 2D batch with coupled units), 0 not decided
+ * yet (no forward call so far, or one only at the default mode), 1 the tiled
+ * fill, 2 the sweep after the tile closures did not fit.  Synchronises the
  * device (a diagnostic, not for the hot path). */
 gcr_status gcr_batch_tiled(const gcr_batch* batch, int32_t* state);
 
@@ -429,7 +433,8 @@ gcr_status gcr_batch_tiled(const gcr_batch* batch, int32_t* state);
  * *threads per workgroup and *grid, > 0 one workgroup per (instance, field)
  * item times grid (k_batch_forward), < 0 the split sweep with -grid
  * workgroups per instance (k_batch_split); both 0 before the first forward
- * call and for the waiting fill, which has no shape to pick.  Host only, no synchronisation. */
+ * call, and for the waiting fill and the fill in LDS, which have no shape to
+ * pick.  Host only, no synchronisation. */
 gcr_status gcr_batch_shape(const gcr_batch* batch, int32_t* threads, int32_t* grid);
 
 /* Launch shape of the batched forward's level sweep (Sec. 3.2 fill, one

@@ -456,8 +456,9 @@ class Batch:
         _check(lib().gcr_batch_status(self._h), "gcr_batch_status")
 
     def tiled(self) -> int:
-        """gcr_batch_tiled: -1 sweep, 0 undecided, 1 tiled fill, 2 sweep after
-        the closures did not fit (synchronises the device)."""
+        """gcr_batch_tiled: -1 no tiles (sweep, waiting fill, or in LDS with
+        coupled units), 0 undecided, 1 tiled fill, 2 sweep after the closures
+        did not fit (synchronises the device)."""
         st = ctypes.c_int32()
         _check(lib().gcr_batch_tiled(self._h, ctypes.byref(st)), "gcr_batch_tiled")
         return st.value
@@ -465,7 +466,8 @@ class Batch:
     def shape(self):
         """gcr_batch_shape: (threads, grid) of the forward's launches; grid < 0
         the split sweep (k_batch_split), > 0 per-item workgroups
-        (k_batch_forward); (0, 0) before the first forward call."""
+        (k_batch_forward); (0, 0) before the first forward call, and for the
+        fill by waiting or in LDS."""
         t, g = ctypes.c_int32(), ctypes.c_int32()
         _check(lib().gcr_batch_shape(self._h, ctypes.byref(t), ctypes.byref(g)),
                "gcr_batch_shape")
@@ -586,13 +588,15 @@ def set_batch_shape(threads: int = 0, grid: int = 0):
 
 
 def set_batch_spin(polls: int = 0):
-    """Polls of a split sweep's wait before it gives up (0: the default)."""
+    """Polls of a wait between workgroups before it gives up (split sweep) or
+    helps itself (waiting fills and adjoints); 0: the default."""
     _check(lib().gcr_set_batch_spin(int(polls)), "gcr_set_batch_spin")
 
 
 def set_batch_tiling(mode: int):
     """Tiled batched fill: 0 off (level-by-level sweep), 1 from a batch's
-    second forward call (the default), 2 from its first."""
+    second forward call, for batches that fill neither in LDS nor by waiting
+    (the default), 2 from its first."""
     _check(lib().gcr_set_batch_tiling(int(mode)), "gcr_set_batch_tiling")
 
 
@@ -603,8 +607,9 @@ def set_profiling(on):
 
 
 def forward_times() -> dict:
-    """Mean ms of the batched forward's anchor search and fill + force
-    kernels over the calls made with profiling on since the last query."""
+    """Mean ms of the batched forward's anchor search (about 0 where it rides
+    in the fill's launch) and of its other launches over the calls made with
+    profiling on since the last query."""
     buf = (ctypes.c_float * 3)()
     _check(lib().gcr_forward_times(buf), "gcr_forward_times")
     return {"anchor": buf[0], "forward": buf[1], "calls": int(buf[2])}

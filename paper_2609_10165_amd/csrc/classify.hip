@@ -365,7 +365,9 @@ __device__ __forceinline__ void classify_chunk(int64_t chunk, int ii, const Inst
 // series) over the waves that fit, so mode 0, which sees 2D grids only, is
 // compiled for them (no body of spherical harmonics, no third axis: 66 registers
 // for 89) and all modes for seven waves: 64 stars, 23,000 chunks, 94 -> 62 us;
-// the list of the 512^3 sphere 18.6 -> 15.5, though mode 1 then spills twelve.
+// the list of the 512^3 sphere 18.6 -> 15.5, though mode 1 then spills twelve
+// registers and mode 2, seldom reached, 33; of spherical-harmonic bodies, whose
+// test needs most, unchanged at 64^3 to 256^3 (24, 31, 39 us), 73 -> 63 at 384^3.
 template <int Mode>
 __global__ __launch_bounds__(256, 7) void k_classify(const Inst* __restrict__ insts,
                                                   const int32_t* __restrict__ chunk_inst,

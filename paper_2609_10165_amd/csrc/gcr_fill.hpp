@@ -344,9 +344,10 @@ __device__ __forceinline__ void fill_wait(const PlanD& P, int p, double* F,
 // members' records by eight lanes, as fill_unit_field solves them.
 //
 // Bound by that chain along the levels after one gather of every ghost's
-// stencil by one compute unit (4.8 of the 20 us below).  4096^2 airfoil, 2,083
-// ghosts, 66 levels, three fields: 21.4 us against 121 for a level at a time
-// from HBM; 128^2 circle, 106 ghosts: 6 against 11.
+// stencil by one compute unit (4.8 us below).  4096^2 airfoil, 2,083 ghosts,
+// three fields: 21.6 us where its place in the cell gives 67 levels, 29.1 where
+// it gives 111, against 121 and more for a level at a time from HBM; 128^2
+// circle, 106 ghosts: 6 against 11.
 // --------------------------------------------------------------------------
 constexpr int kRecWords = 5;
 constexpr int kRecUnitWS = 8;    // unit workspaces

@@ -330,7 +330,7 @@ void touch_thread_storage();   // see plan.hip; once per thread that calls the l
 int profiling_mask();   // bit 0 build stages, bit 1 batched forward
 // Exclusive scan of n counts into excl[n + 1] (total last); where list is
 // set, the indices with a nonzero count go there in order and their number
-// to nlist[0].  tsum: ceil(n / 8192) + 1 int64 of scratch (plan.hip).
+// to nlist[0].  posted: scan_words(n) words, zeroed before each scan.
 // What a scan of chunk counts also leaves (see instance_offsets); off null:
 // nothing.
 struct ScanOffsets {
@@ -344,7 +344,7 @@ struct ScanOffsets {
 };
 void launch_scan(const int32_t* cnt, int64_t n, int64_t* excl, int32_t* list, int32_t* nlist,
                  unsigned long long* posted, hipStream_t st, const ScanOffsets* O = nullptr);
-int64_t scan_words(int64_t n);   // of `posted`, zeroed before each scan
+int64_t scan_words(int64_t n);
 // Tiled batched fill: 0 off, 1 from a batch's second forward call (the
 // default), 2 from its first (process-wide).
 void set_batch_tiling(int mode);

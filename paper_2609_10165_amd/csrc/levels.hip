@@ -481,6 +481,9 @@ __device__ __forceinline__ void canonical_order(const LevelsArgs& L, int ii, int
 // members read outside it (Sec. 3.2's level with the unit as one node);
 // pulling then goes on behind it.  One such unit always exists; if none of
 // at most kMaxUnit ghosts does, the instance is left to the other layerings.
+// (In 3D beyond 8,192 interface cells a thread holds sixteen ghosts: 128
+// registers, 18 spilled; a 128^3 body of 8,684 with 16 units takes 157 us so,
+// 210 by the push form.)
 // Slots come in no particular order: a unit is solved by itself, and what it
 // is called by is its smallest ghost.  The 64-star batch: 50 us
 // against 129 for the push form with its reverse edges (which took another

@@ -351,7 +351,8 @@ __device__ __forceinline__ void instance_offsets(const ScanOffsets& O, const int
 }
 
 // Elements before workgroup b's own `tot`, for workgroups numbered in the
-// order they started: each posts its count, sums those posted before it, BS at
+// order they started (a single-pass scan with look-back, Merrill and Garland,
+// 2016, the look-back by the whole workgroup): each posts its count, sums those posted before it, BS at
 // a time, back to the nearest that has posted its sum, and posts its own sum.
 // Workgroups wait only for ones that started earlier and post their counts
 // without waiting, so every wait ends.  (Called by all BS threads.)  The
@@ -1668,13 +1669,14 @@ struct StageEvents {
     // the store pass (k_classify) and the interface marks (k_band_iface);
     // 11 is the stream's wait for the host between the two halves (the
     // first synchronisation and the sizing); 12 the call's host time
+    // (stage 4, the ghosts' compaction, is part of stage 3 now)
     constexpr int kEv = kStages - 1;
-    const int a[kEv] = {0, 1, 3, 4, 5, 6, 7, 8, 0, 10, 11, 2};
-    const int b[kEv] = {1, 2, 4, 5, 6, 7, 8, 9, 10, 11, 1, 3};
+    const int a[kEv] = {0, 1, 3, 4, 5, 5, 7, 8, 0, 10, 11, 2};
+    const int b[kEv] = {1, 2, 4, 5, 5, 7, 8, 9, 10, 11, 1, 3};
     g_stage_ms[kEv] = (float)call_ms;
     for (int s = 0; s < kEv; ++s) {
       float ms = 0.f;
-      if (hipEventElapsedTime(&ms, ev[a[s]], ev[b[s]]) != hipSuccess) ms = -1.f;
+      if (a[s] != b[s] && hipEventElapsedTime(&ms, ev[a[s]], ev[b[s]]) != hipSuccess) ms = -1.f;
       g_stage_ms[s] = ms;
     }
   }
@@ -2073,7 +2075,6 @@ static gcr_status build_core(const std::shared_ptr<BatchData>& B, hipStream_t st
     if (nif <= kGeometrySmall) geometry(k_geometry<256>, 256);
     else geometry(k_geometry<1024>, 1024);
     T.mark(5, st);
-    T.mark(6, st);
     int64_t max_if = 0;
     for (int i = 0; i < ninst; ++i) max_if = std::max(max_if, D.if_off[i + 1] - D.if_off[i]);
     // a plan alone: the whole GPU for large 3D bodies (in 2D, where concave
