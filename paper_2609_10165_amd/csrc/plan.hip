@@ -480,13 +480,13 @@ void launch_scan(const int32_t* cnt, int64_t n, int64_t* excl, int32_t* list, in
 // (tag 1), so no value was ever reconstructed there.  Tags (their
 // arrays are 256-byte aligned) are not read where both plans settled their
 // span to the same class (each of its cells lies on that side of both
-// boundaries).  One launch counts by tile; in the next each workgroup sums the
-// tiles before its own, and lists, reading again only tiles that hold fresh
-// cells.  No workgroup waits for another: the counts lie in scratch of the plan,
-// which calls on two streams may share.  A call at 256^3: 15.5 us, 64^3 12; with
-// a launch between that scans the counts 23 and 15; in one pass of workgroups
-// that post their counts to each other, behind a launch that clears them, 14.9
-// and 15.9.
+// boundaries).  One launch counts, a tile or several to a workgroup; in the next
+// each workgroup sums the counts before its own, and lists, reading again only
+// where there are fresh cells.  No workgroup waits for another: the counts lie
+// in scratch of the plan, which calls on two streams may share.  A call at 64^3
+// 12.5 us, 256^3 14.2, 400^3 30, 1024^3 232; with a launch between that scans
+// the counts 15, 23, 50, 660; in one pass of workgroups that post their counts
+// to each other, behind a launch that clears them, 16, 14.7, 33.5, 406.
 __device__ __forceinline__ uint32_t fresh_bits(const int8_t* __restrict__ a,
                                                const int8_t* __restrict__ b, int64_t base,
                                                int64_t n, int& unc) {
@@ -511,56 +511,71 @@ __device__ __forceinline__ uint32_t fresh_bits(const int8_t* __restrict__ a,
   return m;
 }
 
-constexpr int kFreshBS = 1024;   // (a wave's part is a span)
+// A workgroup takes `tiles` tiles in turn, the next one's spans read ahead.
+// count [workgroups]: a workgroup's fresh cells, the uncovered ones from bit 31
+// on (not read for a grid of one, which the listing launch alone takes).
+constexpr int kFreshBS = 1024;   // (a wave's part of a tile is a span)
 constexpr int64_t kFreshTile = (int64_t)kFreshBS * kSeg;
-// count [tiles]: a tile's fresh cells, the uncovered ones from bit 31 on (not
-// read for a grid of one tile, which the listing launch alone takes)
+// Workgroups at most, as each sums the counts before its own and an empty one
+// costs its start too: what the chip holds at once where that leaves no more
+// than two tiles to each (256^3: 14.2 us a call, one tile each 16.6), else four
+// times that (1024^3, us a call with 1024, 2048 and 4096: 296, 232, 344; 400^3:
+// 38, 30, 35).
+constexpr int64_t kFreshGroups = 2048, kFreshRound = 512;
 template <bool List>
 __global__ __launch_bounds__(kFreshBS) void k_fresh(const int8_t* __restrict__ a,
                                                     const int8_t* __restrict__ b,
                                                     const int8_t* __restrict__ sa,
                                                     const int8_t* __restrict__ sb, int64_t n,
-                                                    int64_t* __restrict__ count,
+                                                    int tiles, int64_t* __restrict__ count,
                                                     int64_t* __restrict__ counts,
                                                     int32_t* __restrict__ list, int64_t cap) {
   __shared__ int64_t sh[kFreshBS / 64 + 1];
-  const int t = (int)blockIdx.x;
-  const int64_t base = (int64_t)t * kFreshTile + (int64_t)threadIdx.x * kSeg;
-  const int64_t span = base / (64 * kSeg);
+  const int g = (int)blockIdx.x;
+  int64_t base = (int64_t)g * tiles * kFreshTile + (int64_t)threadIdx.x * kSeg;
   int8_t x = 0, y = 0;
-  if (base < n) {
-    x = sa[span];
-    y = sb[span];
-  }
-  int64_t before = 0;
+  auto spans = [&](int64_t at) {
+    x = at < n ? sa[at / (64 * kSeg)] : 0;
+    y = at < n ? sb[at / (64 * kSeg)] : 0;
+  };
+  spans(base);
+  int64_t first = 0, sum = 0;
   if (List && gridDim.x > 1) {
-    const int64_t own = count[t];
-    const bool last = t == (int)gridDim.x - 1;
+    const int64_t own = count[g];
+    const bool last = g == (int)gridDim.x - 1;
     if (own == 0 && !last) return;   // uniform
     int64_t v = 0;
-    for (int j = threadIdx.x; j < t; j += kFreshBS) v += count[j];
-    (void)block_excl_scan<kFreshBS>(v, &before, sh);
+    for (int j = threadIdx.x; j < g; j += kFreshBS) v += count[j];
+    (void)block_excl_scan<kFreshBS>(v, &first, sh);
     if (last && threadIdx.x == 0) {
-      counts[0] = (before + own) & (kScanHi - 1);
-      counts[1] = (before + own) >> 31;
+      counts[0] = (first + own) & (kScanHi - 1);
+      counts[1] = (first + own) >> 31;
+    }
+    first &= kScanHi - 1;
+  }
+  for (int t = 0; t < tiles; ++t, base += kFreshTile) {
+    const bool read = x < 0 || x != y;
+    if (t + 1 < tiles) spans(base + kFreshTile);
+    int unc = 0;
+    const uint32_t m = read ? fresh_bits(a, b, base, n, unc) : 0u;
+    const int64_t mine = __popc(m) | (int64_t)unc << 31;
+    sum += mine;
+    if (!List || (gridDim.x > 1 && !__syncthreads_or(m != 0))) continue;   // uniform
+    int64_t tot;
+    int64_t pos = first + (block_excl_scan<kFreshBS>(mine, &tot, sh) & (kScanHi - 1));
+    for (uint32_t w = m; w; w &= w - 1, ++pos)
+      if (pos < cap) list[pos] = (int32_t)(base + __ffs(w) - 1);
+    first += tot & (kScanHi - 1);
+    if (gridDim.x == 1 && threadIdx.x == 0) {   // (one tile)
+      counts[0] = tot & (kScanHi - 1);
+      counts[1] = tot >> 31;
     }
   }
-  int unc = 0;
-  uint32_t m = 0;
-  if (x < 0 || x != y) m = fresh_bits(a, b, base, n, unc);
-  int64_t tot;
-  const int64_t rank = block_excl_scan<kFreshBS>(__popc(m) | (int64_t)unc << 31, &tot, sh);
   if (!List) {
-    if (threadIdx.x == 0) count[t] = tot;
-    return;
+    int64_t tot;
+    (void)block_excl_scan<kFreshBS>(sum, &tot, sh);
+    if (threadIdx.x == 0) count[g] = tot;
   }
-  if (gridDim.x == 1 && threadIdx.x == 0) {
-    counts[0] = tot & (kScanHi - 1);
-    counts[1] = tot >> 31;
-  }
-  int64_t pos = (before + rank) & (kScanHi - 1);
-  for (; m; m &= m - 1, ++pos)
-    if (pos < cap) list[pos] = (int32_t)(base + __ffs(m) - 1);
 }
 
 extern "C" gcr_status gcr_plan_fresh_cells(const gcr_plan* a, const gcr_plan* b, int64_t* counts,
@@ -573,15 +588,18 @@ extern "C" gcr_status gcr_plan_fresh_cells(const gcr_plan* a, const gcr_plan* b,
       return GCR_E_ARG;
   hipStream_t st = (hipStream_t)stream;
   const int64_t n = a->ncell, ntiles = (n + kFreshTile - 1) / kFreshTile;
+  const int64_t most = ntiles <= 2 * kFreshRound ? kFreshRound : kFreshGroups;
+  const int tiles = (int)((ntiles + most - 1) / most);
+  const unsigned groups = (unsigned)((ntiles + tiles - 1) / tiles);
   int64_t* const count = static_cast<int64_t*>(
-      plan_scratch(const_cast<gcr_plan*>(b), 6, sizeof(int64_t) * ntiles));
+      plan_scratch(const_cast<gcr_plan*>(b), 6, sizeof(int64_t) * groups));
   if (!count) return GCR_E_NOMEM;
   const int64_t room = list ? cap : 0;
-  if (ntiles > 1)
-    k_fresh<false><<<(unsigned)ntiles, kFreshBS, 0, st>>>(a->tags, b->tags, a->span, b->span, n,
-                                                          count, counts, list, room);
-  k_fresh<true><<<(unsigned)ntiles, kFreshBS, 0, st>>>(a->tags, b->tags, a->span, b->span, n, count,
-                                                       counts, list, room);
+  if (groups > 1)
+    k_fresh<false><<<groups, kFreshBS, 0, st>>>(a->tags, b->tags, a->span, b->span, n, tiles, count,
+                                                counts, list, room);
+  k_fresh<true><<<groups, kFreshBS, 0, st>>>(a->tags, b->tags, a->span, b->span, n, tiles, count,
+                                             counts, list, room);
   GCR_HIP(hipGetLastError());
   return GCR_OK;
 }

@@ -106,3 +106,25 @@ def test_fresh_cells_on_two_streams_and_captured(gcr):
         lst.zero_()
         graph.replay()
         right()
+
+
+# tiles of 16,384 cells: 512 (one to a workgroup), 513 and 1024 (two), 1025 (one
+# again), 2048, 2049 and 4097 (two and three); the last one whole and half
+@pytest.mark.parametrize("tiles", [512, 513, 1024, 1025, 2048, 2049, 4097])
+@pytest.mark.parametrize("whole", [True, False])
+def test_fresh_cells_by_several_tiles(gcr, tiles, whole):
+    h = 2.0 / 8192
+    ny = 2 * tiles - (0 if whole else 1)
+    g = synth.Grid(2, (8192, ny, 1), (-1.0, -1.0, 0.0), (h, h, 1.0))
+    # a body among the first tiles, and one across all of them
+    for y, r in ((60.3 * h, 40.0 * h), (0.5 * ny * h, 0.47 * min(ny * h, 2.0))):
+        c = (0.01, -1.0 + y, 0.0)
+        a = gcr.Plan(g, synth.Shape(synth.SPHERE, c, r), CGC)
+        b = gcr.Plan(g, synth.Shape(synth.SPHERE, (c[0] + 0.7 * h, c[1] - 0.4 * h, 0.0), r), CGC)
+        ta, tb = (p.export(("tags",))["tags"] for p in (a, b))
+        want = ((ta > 0) & ((tb == 0) | (tb == -2))).nonzero()[:, 0]
+        lst, counts = a.fresh_cells(b, cap=len(want) + 3)
+        torch.cuda.synchronize()
+        unc = int(((ta == 1) & ((tb == 0) | (tb == -2))).sum())
+        assert len(want) > 50 and counts.tolist() == [len(want), unc]
+        assert torch.equal(lst[:len(want)].long(), want)
