@@ -93,9 +93,10 @@ __device__ __forceinline__ uint32_t cnt_get(const uint32_t* c, int i) {
 constexpr int kFlowJ = 4, kFlowGrid = 1024;
 // Polls between two looks at the launch's state: often where a pair may have
 // stopped it (64^3 body with cycles: 52 us for both layerings, and 770 more
-// when waves only gave up in their own time), seldom on a sphere, as every
-// look reads one address (640^3: 38 us with the former, 34 with the latter).
-constexpr int kFlowLook = 16, kFlowLookSphere = 256;
+// when waves only gave up in their own time), less so with more than
+// kFlowLookTiles tiles and seldom on a sphere, as every look reads one address
+// (sphere of 640^3: 38 us with the first, 34 with the last).
+constexpr int kFlowLook = 16, kFlowLookMany = 64, kFlowLookSphere = 256, kFlowLookTiles = 128;
 constexpr int64_t kFlowTicks = 20000;   // 200 us of the 100 MHz clock
 
 __device__ __forceinline__ int flow_get(const int32_t* p) {
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(256) void k_levels_flow(LevelsArgs L) {
   const int ntiles = (n + 255) >> 8, G = (int)gridDim.x;
   const int np = (1 << L.insts[0].g.dim) - 1;
   const bool pairs = L.insts[0].s.kind != kSphere;
-  const int look = pairs ? kFlowLook : kFlowLookSphere;
+  const int look = !pairs ? kFlowLookSphere : ntiles <= kFlowLookTiles ? kFlowLook : kFlowLookMany;
   const int32_t* __restrict__ deps = L.deps + lo;
   int32_t* lev = L.lev + lo;
   if (tid == 0) s_placed = 0;
