@@ -1327,10 +1327,9 @@ __device__ __forceinline__ void finish_instance(int ii, int ninst, const int64_t
   const int nu = min(max(info[ii].nunits, 0), kMaxUnits), nl = min(max(info[ii].nlev, 0), kMaxLevels);
   int32_t* um = unit_mem + (int64_t)ii * kMaxUnits * kMaxUnit;
   const int32_t* uc = unit_cnt + (int64_t)ii * kMaxUnits;
-  const int layered = info[ii].layered;
-  if (layered != kLayeredMapped)
-    for (int t = tid; t < nu * kMaxUnit; t += blockDim.x)
-      if (t % kMaxUnit < uc[t / kMaxUnit]) um[t] = perm[um[t]];
+  const int nmap = info[ii].layered == kLayeredMapped ? 0 : nu;
+  for (int t = tid; t < nmap * kMaxUnit; t += blockDim.x)
+    if (t % kMaxUnit < uc[t / kMaxUnit]) um[t] = perm[um[t]];
   for (int t = tid; t <= nl; t += blockDim.x)
     out.lev_off[(int64_t)ii * (kMaxLevels + 1) + t] = lev_off[(int64_t)ii * (kMaxLevels + 1) + t];
   for (int t = tid; t < nu; t += blockDim.x)
@@ -1377,8 +1376,8 @@ __device__ __forceinline__ void finish_instance(int ii, int ninst, const int64_t
     }
     I.nfluid += s_fl[w];
   }
-  if (layered) info[ii].layered = kLayeredMapped;
   out.info[ii] = I;
+  if (I.layered) info[ii].layered = kLayeredMapped;
   out.g_off[ii] = b;
   if (ii == ninst - 1) out.g_off[ninst] = e;
 }
