@@ -1468,7 +1468,7 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
   // call table: one upload
   const size_t np = (size_t)nitems;
   const size_t bytes = sizeof(void*) * (5 * np + 3 * n) + sizeof(int64_t) * (2 * n + 1) +
-                       sizeof(int32_t) * (np + 2 * (n + 1)) + 64;
+                       sizeof(int32_t) * (np + 2 * (n + 1)) + 128;
   std::vector<char> host(bytes, 0);
   char* h = host.data();
   size_t o = 0;
@@ -1497,11 +1497,13 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
     o_wq = put(wq, sizeof(void*) * n);
     o_aoff = put(aoff.data(), sizeof(int64_t) * (n + 1));
     // (an instance without points has one empty chunk: its force is zero)
-    for (int i = 0; i < n; ++i)
+    constexpr int kPoints2 = kAnchorPoints<2, 1024>, kPoints3 = kAnchorPoints<3, 256>;
+    for (int i = 0; i < n; ++i) {
       soff[i + 1] = soff[i] + (int32_t)std::max<int64_t>(1, (nq[i] + kSurfChunk - 1) / kSurfChunk);
+      poff[i + 1] = poff[i] + (int32_t)(dim == 2 ? (nq[i] + kPoints2 - 1) / kPoints2
+                                                 : (nq[i] + kPoints3 - 1) / kPoints3);
+    }
     o_soff = put(soff.data(), sizeof(int32_t) * (n + 1));
-    const int ppb = dim == 2 ? kAnchorPoints<2, 1024> : kAnchorPoints<3, 256>;
-    for (int i = 0; i < n; ++i) poff[i + 1] = poff[i] + (int32_t)((nq[i] + ppb - 1) / ppb);
     o_poff = put(poff.data(), sizeof(int32_t) * (n + 1));
   }
   const int64_t npts = aoff[n];
@@ -1512,6 +1514,7 @@ extern "C" gcr_status gcr_batch_forward(gcr_batch* batch, int32_t nf, double* co
     if (!S->d_anchor) return GCR_E_NOMEM;
   }
   const size_t o_order = put(order.data(), sizeof(int32_t) * np);
+  o = (o + 63) & ~size_t(63);   // (whole 16 bytes: 0.5 us less to copy)
   if (S->call_cap < o) {
     if (!retire(S->d_call)) return GCR_E_HIP;
     S->d_call = static_cast<char*>(pool_alloc(o));
