@@ -970,12 +970,18 @@ gcr_status gcr_fill_adjoint(const gcr_plan* plan, int32_t nf, double* const* lam
     const gcr_status ss = plan_support(p, st, &A.S);
     if (ss != GCR_OK) return ss;
   }
-  // as the fill: by waiting, or a forced schedule's one workgroup or launch
-  // per level
-  if (p->schedule == kSchedAuto) {
+  // As the fill: by waiting, or a forced schedule's one workgroup or launch
+  // per level.  Up to two ghosts' fields to each lane one workgroup costs less
+  // than the launch that opens the waits: 28 to 480 ghosts in at most 12
+  // levels, one field, 10.8 to 24.0 us against 13.7 to 25.6.  It is the slower
+  // one from 600 on (201 ghosts, four fields: 26.6 us against 25.7), in more
+  // levels (267 ghosts in 17: 28.0 us against 25.0) and with a coupled unit,
+  // which holds its lanes up (216 ghosts: 30.4 us against 25.0).
+  const bool small = p->ng * nf <= 512 && p->nlev <= 12 && p->unit_lev_host.empty();
+  if (p->schedule == kSchedAuto && !small) {
     if (p->dim == 2) adj_flow<2>(A, p->d_lev_off, p->nlev, st);
     else adj_flow<3>(A, p->d_lev_off, p->nlev, st);
-  } else if (p->schedule == kSchedWorkgroup) {
+  } else if (p->schedule == kSchedAuto || p->schedule == kSchedWorkgroup) {
     if (p->dim == 2) k_adj_wg<2><<<1, 256, 0, st>>>(A, p->d_lev_off, p->nlev, nullptr);
     else k_adj_wg<3><<<1, 256, 0, st>>>(A, p->d_lev_off, p->nlev, nullptr);
   } else {

@@ -9,7 +9,7 @@ import pytest
 
 import synth
 from synth import HGC
-from test_gpu_fill_paths import CASES, MIXED
+from test_gpu_fill_paths import CASES, MIXED, circle
 from synth import DIRICHLET, NEUMANN
 from test_gpu_parity import gcr  # noqa: F401  (the fixture)
 
@@ -210,3 +210,12 @@ def test_many_points_of_one_anchor_cost_their_number(gcr):  # noqa: F811
             times.append(time.perf_counter() - t)
         return min(times[1:])
     assert best(4096) < 24 * best(512)
+
+
+@pytest.mark.parametrize("n", [24, 128, 300])
+def test_fill_adjoint_of_few_ghosts(gcr, n):  # noqa: F811
+    # the last fields that one workgroup sweeps, the first that wait, and one
+    plan = gcr.Plan(*circle(n), HGC)
+    most = 512 // plan.n_ghost
+    for nf in {1, min(most, 8), min(most + 1, 8)}:
+        agree(plan, ([MIXED, DIRICHLET, NEUMANN] * 3)[:nf], n)
